@@ -24,6 +24,7 @@ struct PrepArgs {
     int *row_slot, *row_pos, *row_bad, *out_row, *seq_bad;
     int4 *seq_info;                // per sequence {first row, end row, cache slot, first row's position}; first row = -1 for an invalid one
     float *seq_scale;
+    int *ctx_top;                  // longest context of the call (at least that of every valid sequence, at most max_ctx), or null
     float *h;
 };
 
@@ -77,6 +78,14 @@ __device__ __forceinline__ void prepare_row(const PrepArgs &a, int r, int *sh) {
             a.out_row[b] = r; a.seq_bad[b] = bad;
             a.seq_scale[b] = s_scale[b];
             a.seq_info[b] = bad ? make_int4(-1, 0, 0, 0) : make_int4(lo, hi, s_slot[b], s_pos[b]);
+        }
+        if (r == 0 && a.ctx_top) {
+            int top = 1;
+            for (int i = 0; i < ns; ++i) {
+                const int len = a.span_off == nullptr ? 1 : s_off[i + 1] - s_off[i];
+                if (len > 0 && s_pos[i] >= 0 && s_pos[i] <= a.max_ctx - len) top = max(top, s_pos[i] + len);
+            }
+            *a.ctx_top = top;
         }
         // a malformed offset table can leave sequences without any row: flag them all
         if (bad && a.span_off != nullptr && r == 0)
@@ -870,8 +879,10 @@ struct AttnArgs {
     float *out;                    // [rows, n_q*hd] fp32
     const int *row_pos, *row_slot, *row_bad;
     int n_q, n_kv, max_ctx, max_seqs, layer, n_slices;
-    int n_rows;                    // token rows in the call (k_attn_partial_rows)
-    int slot_split;                // k_attn_span: workgroups per sequence, slice and KV head
+    int slot_split;                // k_attn_span, k_attn_walk: workgroups per sequence, slice and KV head
+    const int *ctx_top;            // k_attn_walk and the merge after it: longest context of the call, which the slices divide; null: they divide max_ctx
+    int base2;                     // the records' maxima are in units of ln 2 (k_attn_walk)
+    int direct;                    // k_attn_walk: one slice, decode rows: the normalised rows go to `out`, no merge follows
     const int4 *seq_info;          // per sequence {first row, end row, cache slot, first row's position}, first row < 0: invalid (k_attn_span)
 };
 
@@ -895,6 +906,9 @@ __device__ __forceinline__ void split3(const float (&x)[8], bf16x8_t (&pl)[3]) {
     pl[1] = __builtin_bit_cast(bf16x8_t, make_uint4(w1[0], w1[1], w1[2], w1[3]));
     pl[2] = __builtin_bit_cast(bf16x8_t, make_uint4(w2[0], w2[1], w2[2], w2[3]));
 }
+
+// positions per context slice when S slices share n positions: whole 64-position passes
+__device__ __forceinline__ int attn_slice_len(int n, int S) { return ((n + S - 1) / S + ATT_BT - 1) / ATT_BT * ATT_BT; }
 
 template <int HD>
 __host__ __device__ constexpr size_t attn_lds_bytes(int G = ATT_GMAX) { return (size_t)(4 * G * (HD + 4) + 2 * 4 * 16) * 4; }
@@ -1109,174 +1123,19 @@ __global__ void __launch_bounds__(256, ONEPASS ? 3 : 1) k_attn_partial(AttnArgs 
 }
 
 // ------------------------------------------------------------------------------------------------
-// k_attn_partial_rows: the same partial records for a call with several token rows (catch-up spans).
-// grid (n_slices, n_kv_heads, ceil(row slots / W)), block 64 W with W = 1..4 waves, no LDS.  The 16 columns of the
-// matrix-core tiles carry RP = 16 / G token rows at once (G = query heads per KV head): column
-// rr * G + gh is head gh of the rr-th row of the wave's row slot, so one K/V tile serves RP rows.
-// A wave owns one row slot (RP consecutive rows) and one context slice, walks the slice in passes of
-// 64 positions with an online softmax per column, and writes its columns' records itself; the
-// waves of a workgroup hold neighbouring row slots of the SAME slice, so their K/V requests meet in
-// the CU's cache and HBM is read once per slice.  Rows of one slot that belong to different
-// sequences (different cache slots) are taken in separate turns.  Causality is per column: row r
-// attends to positions 0..pos[r].
-// ------------------------------------------------------------------------------------------------
-// MINW: waves per SIMD the register allocation must allow.  1 (243 + 44 registers) schedules best and wins
-// while all workgroups are resident anyway; 2 (243 registers, none spilled) wins on a large cache, where
-// the number of resident workgroups bounds the kernel (eight KV heads, 5000 positions, 2 rows: 12.3 -> 10.4 us).
-template <int HD, int MINW>
-__global__ void __launch_bounds__(256, MINW) k_attn_partial_rows(AttnArgs a) {
-    constexpr int NDS = HD / 32, NDB = HD / 16, PS = HD + 4;
-    const int split = blockIdx.x, S = gridDim.x, kvh = blockIdx.y;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int j = lane & 15, kg = lane >> 4;
-    const int G = a.n_q / a.n_kv, RP = 16 / G;
-    const int rr = j / G, gh = j - rr * G;                    // this lane's column: row rr of the slot, head gh
-    int C = (a.max_ctx + S - 1) / S;
-    C = ((C + 63) / 64) * 64;
-    const int t_begin = split * C;
-    const float scale = 1.0f / sqrtf((float)HD);
-    const int slot_first = (blockIdx.z * (blockDim.x >> 6) + wave) * RP, slot_end = min(slot_first + RP, a.n_rows);
-
-    for (int r0 = slot_first; r0 < slot_end;) {
-        // a turn: the rows r0 .. r1-1 of the slot that share r0's cache slot (and are valid)
-        if (a.row_bad[r0]) { ++r0; continue; }
-        const int kv_slot = min(max(a.row_slot[r0], 0), a.max_seqs - 1);
-        int r1 = r0 + 1;
-        while (r1 < slot_end && !a.row_bad[r1] && a.row_slot[r1] == a.row_slot[r0]) ++r1;
-        const int my_row = r0 + rr;                            // valid column iff rr < RP, my_row < r1
-        const bool col_ok = rr < RP && my_row < r1;
-        const int ctx_col = col_ok ? a.row_pos[my_row] + 1 : 0;
-        const int ctx_max = a.row_pos[r1 - 1] + 1;             // positions grow with the row inside a span
-        const int t_end = min(ctx_max, t_begin + C), t_end_col = min(ctx_col, t_begin + C);
-        if (t_begin < t_end) {
-            const size_t kv_base = (((size_t)a.layer * a.max_seqs + kv_slot) * a.n_kv + kvh) * (size_t)a.max_ctx * HD;
-            const uint16_t *Kp = a.kcache + kv_base, *Vp = a.vcache + kv_base;
-            bf16x8_t qB[NDS][3];
-            {
-                const float4 *qp = reinterpret_cast<const float4 *>(a.qbuf + ((size_t)(col_ok ? my_row : r0) * a.n_q + kvh * G + (col_ok ? gh : 0)) * HD + 8 * kg);
-#pragma unroll
-                for (int ds = 0; ds < NDS; ++ds) {
-                    const float4 x0 = qp[8 * ds], x1 = qp[8 * ds + 1];
-                    float qv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-                    if (!col_ok) {
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) qv[e] = 0.f;
-                    }
-                    split3(qv, qB[ds]);
-                }
-            }
-            float m_run = -INFINITY, l_run = 0.f;
-            f32x4_t acc[NDB];
-#pragma unroll
-            for (int db = 0; db < NDB; ++db) acc[db] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-            for (int t0 = t_begin; t0 < t_end; t0 += 64) {
-                // K rows (A operand of the scores) and V^T rows (A operand of the output); positions clamped into the cache row
-                uint4 kk[4][NDS];
-#pragma unroll
-                for (int tb = 0; tb < 4; ++tb) {
-                    const int tok = min(t0 + 16 * tb + j, a.max_ctx - 1);
-#pragma unroll
-                    for (int ds = 0; ds < NDS; ++ds) kk[tb][ds] = *reinterpret_cast<const uint4 *>(Kp + (size_t)tok * HD + 32 * ds + 8 * kg);
-                }
-                uint2 vv[2][NDB][2];
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-                    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-                        for (int hf = 0; hf < 2; ++hf) {
-                            const int tv = min(t0 + 32 * ks + 16 * hf + 4 * kg, a.max_ctx - 4);
-                            vv[ks][db][hf] = *reinterpret_cast<const uint2 *>(Vp + (size_t)(16 * db + j) * a.max_ctx + tv);
-                        }
-                // scores: lane holds positions t0 + 16 tb + 4 kg + r of its column
-                f32x4_t sc[4];
-                float mx = -INFINITY;
-#pragma unroll
-                for (int tb = 0; tb < 4; ++tb) {
-                    sc[tb] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                    for (int ds = 0; ds < NDS; ++ds) {
-                        const bf16x8_t A = __builtin_bit_cast(bf16x8_t, kk[tb][ds]);
-#pragma unroll
-                        for (int pl = 2; pl >= 0; --pl) sc[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, qB[ds][pl], sc[tb], 0, 0, 0);
-                    }
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const float v = (t0 + 16 * tb + 4 * kg + r) < t_end_col ? sc[tb][r] * scale : -INFINITY;
-                        sc[tb][r] = v;
-                        mx = fmaxf(mx, v);
-                    }
-                }
-                mx = fmaxf(mx, __shfl_xor(mx, 16, RS_WAVE));
-                mx = fmaxf(mx, __shfl_xor(mx, 32, RS_WAVE));
-                const float m_new = fmaxf(m_run, mx);              // may stay -inf for a column without positions here
-                const float alpha = (m_run == -INFINITY) ? 0.f : __expf(m_run - m_new);
-                m_run = m_new;
-                l_run *= alpha;
-#pragma unroll
-                for (int db = 0; db < NDB; ++db) { acc[db][0] *= alpha; acc[db][1] *= alpha; acc[db][2] *= alpha; acc[db][3] *= alpha; }
-#pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    float pv[8];
-#pragma unroll
-                    for (int hf = 0; hf < 2; ++hf)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const float s_ = sc[2 * ks + hf][r];
-                            const float p = (s_ == -INFINITY) ? 0.f : __expf(s_ - m_new);
-                            pv[4 * hf + r] = p;
-                            l_run += p;
-                        }
-                    bf16x8_t pB[3];
-                    split3(pv, pB);
-                    const int tok_lo = t0 + 32 * ks + 4 * kg, tok_hi = tok_lo + 16;
-#pragma unroll
-                    for (int db = 0; db < NDB; ++db) {
-                        // positions at or past the turn's longest context may hold anything: clear their V columns
-                        uint2 lo = vv[ks][db][0], hi = vv[ks][db][1];
-                        if (tok_lo + 3 >= t_end) {
-                            if (tok_lo + 1 >= t_end) lo.x &= 0x0000ffffu;
-                            if (tok_lo + 2 >= t_end) lo.y = 0; else if (tok_lo + 3 >= t_end) lo.y &= 0x0000ffffu;
-                            if (tok_lo >= t_end) lo.x = 0;
-                        }
-                        if (tok_hi + 3 >= t_end) {
-                            if (tok_hi + 1 >= t_end) hi.x &= 0x0000ffffu;
-                            if (tok_hi + 2 >= t_end) hi.y = 0; else if (tok_hi + 3 >= t_end) hi.y &= 0x0000ffffu;
-                            if (tok_hi >= t_end) hi.x = 0;
-                        }
-                        const bf16x8_t A = __builtin_bit_cast(bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
-#pragma unroll
-                        for (int pl = 2; pl >= 0; --pl) acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A, pB[pl], acc[db], 0, 0, 0);
-                    }
-                }
-            }
-            l_run += __shfl_xor(l_run, 16, RS_WAVE);
-            l_run += __shfl_xor(l_run, 32, RS_WAVE);
-            if (col_ok && t_begin < t_end_col) {
-                float *p = a.partials + (((size_t)my_row * a.n_q + kvh * G + gh) * S + split) * PS;
-#pragma unroll
-                for (int db = 0; db < NDB; ++db)
-                    *reinterpret_cast<float4 *>(p + 4 + 16 * db + 4 * kg) = make_float4(acc[db][0], acc[db][1], acc[db][2], acc[db][3]);
-                if (kg == 0) { p[0] = m_run; p[1] = l_run; }
-            }
-        }
-        r0 = r1;
-    }
-}
-
-// ------------------------------------------------------------------------------------------------
-// k_attn_span: the partial records of k_attn_partial_rows for calls whose slices are one 64-position
-// pass, with the K/V tile shared through LDS.  grid (n_slices, n_kv_heads, n_seqs * ZS), block 256
+// k_attn_span: partial records for a call with several token rows per sequence (catch-up spans) whose slices are one
+// 64-position pass.  The 16 columns of the matrix-core tiles carry RP = 16 / G token rows at once (G = query heads per
+// KV head; RP consecutive rows are a row slot): column rr * G + gh is head gh of the rr-th row of the slot, so one K/V
+// tile serves RP rows.  Causality is per column: row r attends to positions 0..pos[r].  grid (n_slices, n_kv_heads,
+// n_seqs * ZS), block 256
 // (ZS = a.slot_split workgroups share a sequence's row slots: workgroup zs takes the slots w + 4 zs, + 4 ZS, ...
 // of wave w; long spans are spread over more CUs that way).
 // A workgroup owns one context slice of one KV head of one SEQUENCE of the call and all of that
 // sequence's rows: the four waves fetch the slice's K rows (64 x HD, contiguous in the cache) and V^T
 // rows (HD pieces of 128 bytes) once, with whole-line 16-byte loads, into LDS; then wave w takes the row
-// slots w, w + 4, ... (a slot = 16 / G consecutive rows in the 16 matrix-core columns, as above) and reads
-// its operands from LDS.  Measured against k_attn_partial_rows, where every wave fetches the tile
-// itself with one 16-byte (K) or 8-byte (V) piece per lane and row, 16 cache lines per instruction:
-// that kernel is bound by the CU's vector-memory request rate (its loads alone take as long as the
-// whole kernel) and re-reads the tile once per four slots.
+// slots w, w + 4, ... and reads its operands from LDS (waves that fetched their operands themselves, one 16-byte (K) or
+// 8-byte (V) piece per lane and row, were bound by the CU's vector-memory request rate: 7B shape, 8 rows 17.5 us
+// against 13.8, 3 rows 11.0 against 6.8).
 // V positions at or past the sequence's last row may hold anything (never written): they are cleared
 // when the tile is written to LDS; K rows there only feed scores that the causal mask discards.
 // ------------------------------------------------------------------------------------------------
@@ -1428,6 +1287,268 @@ __global__ void __launch_bounds__(256) k_attn_span(AttnArgs a) {
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// k_attn_walk: attention of calls with several rows or several sequences where one 64-position pass per
+// workgroup would be many rounds of the machine.  grid (n_slices, n_kv_heads, n_seqs * ZS), block 256.
+// A workgroup walks its slice (S slices divide the longest context of the call) in passes of 64 positions:
+// the four waves fetch the pass's K rows and V^T pieces with whole-line loads one pass ahead into registers and
+// park them in one of two LDS buffers (one bare barrier per pass: the loads of the next pass stay in flight across
+// it).  Online softmax per matrix-core column as in the kernels above.
+//   SHARE = false: wave w owns row slot w (+ 4 zs) of the sequence and takes all 64 positions of a pass
+//   SHARE = true:  the sequence has one row slot (decode steps, very short spans); wave w takes the 16 positions
+//                  16 w .. of every pass and the four states are merged at the end
+// The records' maxima are in units of ln 2 (see q_scale), which the merge is told by a.base2.
+// With one slice a decode step needs no merge kernel: the rows are normalised here (a.direct).
+// What bounds it: long spans the vector work beside the matrix cores (14B, 61 rows at 9000 positions: 53 us a layer against
+// 159 for waves that fetched their own tiles; the matrix cores are busy a third of that), decode steps the one pass a
+// workgroup has in flight (7B, 128 sequences of 520 .. 1000 positions, 195 MB: 47 us = 4.1 TB/s, 77 + 12 us for one pass per
+// workgroup plus the merge; 16 sequences, 42 MB: 15 us against 20.6; 32B, 8 ragged sequences: 58 against 104).
+// ------------------------------------------------------------------------------------------------
+template <int HD>
+__host__ __device__ constexpr size_t attn_walk_lds_bytes() { return 2 * attn_span_lds_bytes<HD>(); }
+
+// workgroup barrier for LDS hand-over that leaves global loads in flight: the LDS accesses issued so far complete
+// (lgkmcnt(0); expcnt and vmcnt are left alone), then the barrier; the compiler moves no memory access across it
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// largest of the four lanes j, j + 16, j + 32, j + 48 (the position groups of one matrix-core column), in all of them
+__device__ __forceinline__ float max_over_kg(float v) {
+    const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+template <int HD, bool SHARE>
+__global__ void __launch_bounds__(256, 2) k_attn_walk(AttnArgs a) {
+    constexpr int NDS = HD / 32, NDB = HD / 16, PS = HD + 4;
+    constexpr int KP = HD * 2 + 16, VP = 64 * 2 + 16;           // LDS row pitches in bytes (padded against bank conflicts)
+    constexpr int KQ = 64 * HD * 2 / 4096, VQ = HD * 128 / 4096; // 16-byte loads per thread for each tile
+    constexpr int NTB = SHARE ? 1 : 4;                           // 16-position score blocks per wave and pass
+    constexpr int SLOTS = SHARE ? 1 : 4;                         // row slots a workgroup takes at a time
+    constexpr size_t BUF = attn_span_lds_bytes<HD>();
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int split = blockIdx.x, S = gridDim.x, kvh = blockIdx.y;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int j = lane & 15, kg = lane >> 4;
+    const int G = a.n_q / a.n_kv, RP = 16 / G;
+    const int rr = j / G, gh = j - rr * G;                      // this lane's column: row rr of the slot, head gh
+    const int ZS = a.slot_split > 1 ? a.slot_split : 1, zs = blockIdx.z % ZS, seq = blockIdx.z / ZS;
+    const int4 info = a.seq_info[seq];                          // {first row, end row, cache slot, position of the first row}, first row < 0: skip
+    if (info.x < 0) {
+        // no merge kernel follows a decode step of one slice: the rejected row's output is cleared here
+        if (SHARE && a.direct)
+            for (int i = tid; i < G * HD; i += 256) a.out[((size_t)seq * a.n_q + kvh * G) * HD + i] = 0.f;
+        return;
+    }
+    const int r_lo = info.x, r_hi = info.y;
+    const int ctx_max = info.w + (r_hi - r_lo);                 // positions the last row attends to
+    const int n_slots = (r_hi - r_lo + RP - 1) / RP;
+    const int C = attn_slice_len(*a.ctx_top, S), t_begin = split * C;
+    if (t_begin >= ctx_max || SLOTS * zs >= n_slots) return;
+    const int kv_slot = min(max(info.z, 0), a.max_seqs - 1);
+    const size_t kv_base = (((size_t)a.layer * a.max_seqs + kv_slot) * a.n_kv + kvh) * (size_t)a.max_ctx * HD;
+    // one head's K or V rows stay below 2^31 bytes (the launch checks), so a piece is a uniform base and a 32-bit offset
+    const unsigned char *Kp = reinterpret_cast<const unsigned char *>(a.kcache + kv_base), *Vp = reinterpret_cast<const unsigned char *>(a.vcache + kv_base);
+    // scores in units of ln 2: the factor goes into q before it is split (one rounding per element of q in the place of
+    // one per score), and a softmax weight is one subtraction and one v_exp_f32
+    const float q_scale = 1.44269504088896341f / sqrtf((float)HD);
+
+    // (vector types, not structs: a struct array that the lambdas capture is left in scratch memory)
+    u32x4_t kq[KQ], vq[VQ];
+    auto fetch = [&](int t0) {                                   // positions clamped into the cache row
+#pragma unroll
+        for (int i = 0; i < KQ; ++i) {
+            const int off = (tid + 256 * i) * 16, row = off / (HD * 2), col = off - row * (HD * 2);
+            kq[i] = *reinterpret_cast<const u32x4_t *>(Kp + (uint32_t)(min(t0 + row, a.max_ctx - 1) * (HD * 2) + col));
+        }
+#pragma unroll
+        for (int i = 0; i < VQ; ++i) {
+            const int off = (tid + 256 * i) * 16, d = off >> 7, c8 = (off & 127) >> 4;
+            vq[i] = *reinterpret_cast<const u32x4_t *>(Vp + (uint32_t)((d * a.max_ctx + min(t0 + 8 * c8, a.max_ctx - 8)) * 2));
+        }
+    };
+    auto park = [&](unsigned char *buf, int t0) {
+        unsigned char *sK = buf, *sV = buf + (size_t)64 * KP;
+#pragma unroll
+        for (int i = 0; i < KQ; ++i) {
+            const int off = (tid + 256 * i) * 16, row = off / (HD * 2), col = off - row * (HD * 2);
+            *reinterpret_cast<u32x4_t *>(sK + (size_t)row * KP + col) = kq[i];
+        }
+        if (t0 + 64 > ctx_max) {
+            // positions past the sequence's last row may hold anything (never written): their V columns are cleared
+            // (n_ok of a piece's 8 positions are inside)
+#pragma unroll
+            for (int i = 0; i < VQ; ++i) {
+                const int n_ok = ctx_max - (t0 + 8 * (((tid + 256 * i) & 7)));
+                auto keep = [&](uint32_t x, int e) { return n_ok >= 2 * e + 2 ? x : (n_ok == 2 * e + 1 ? x & 0x0000ffffu : 0u); };
+                vq[i] = (u32x4_t){keep(vq[i].x, 0), keep(vq[i].y, 1), keep(vq[i].z, 2), keep(vq[i].w, 3)};
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < VQ; ++i) {
+            const int off = (tid + 256 * i) * 16, d = off >> 7, c8 = (off & 127) >> 4;
+            *reinterpret_cast<u32x4_t *>(sV + (size_t)d * VP + c8 * 16) = vq[i];
+        }
+    };
+
+    int parity = 0;
+    for (int slot0 = SLOTS * zs; slot0 < n_slots; slot0 += SLOTS * ZS) {
+        const int last = min(r_lo + (slot0 + SLOTS) * RP, r_hi) - 1;                 // last row of this group of slots
+        const int t_end = min(t_begin + C, info.w + (last - r_lo) + 1);
+        if (t_begin >= t_end) continue;                          // the whole group lies before this slice
+        const int slot = slot0 + (SHARE ? 0 : wave);
+        const int my_row = r_lo + slot * RP + rr;
+        const bool active = slot < n_slots, col_ok = active && rr < RP && my_row < r_hi;
+        // positions this lane's row attends to; a column that belongs to no row (q = 0, never written) takes part in everything
+        const int ctx_col = col_ok ? info.w + (my_row - r_lo) + 1 : ctx_max;
+        const int ctx_lo = info.w + slot * RP + 1;               // ... and the slot's first row
+        const int ctx_hi = min(info.w + (slot + 1) * RP, ctx_max);
+        fetch(t_begin);
+        bf16x8_t qB[NDS][3];
+        {
+            const float4 *qp = reinterpret_cast<const float4 *>(a.qbuf + ((size_t)(col_ok ? my_row : r_lo) * a.n_q + kvh * G + (col_ok ? gh : 0)) * HD + 8 * kg);
+#pragma unroll
+            for (int ds = 0; ds < NDS; ++ds) {
+                const float4 x0 = qp[8 * ds], x1 = qp[8 * ds + 1];
+                float qv[8] = {x0.x * q_scale, x0.y * q_scale, x0.z * q_scale, x0.w * q_scale, x1.x * q_scale, x1.y * q_scale, x1.z * q_scale, x1.w * q_scale};
+                if (!col_ok) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) qv[e] = 0.f;
+                }
+                split3(qv, qB[ds]);
+            }
+        }
+        float m_run = -INFINITY, l_run = 0.f;
+        f32x4_t acc[NDB];
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) acc[db] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+
+        for (int t0 = t_begin; t0 < t_end; t0 += 64) {
+            unsigned char *buf = smem + parity * BUF;
+            parity ^= 1;
+            park(buf, t0);
+            lds_barrier();                                       // the pass is in LDS; everybody is done with the other buffer's last use
+            fetch(min(t0 + 64, t_end - 1));                      // (after the last pass: a duplicate, never used)
+            const int w0 = t0 + (SHARE ? 16 * wave : 0);         // first position this wave looks at
+            if (!active || w0 >= ctx_hi) continue;
+            const unsigned char *sK = buf, *sV = buf + (size_t)64 * KP;
+            // scores: lane holds positions w0 + 16 tb + 4 kg + r of its column.  Consecutive products go to different
+            // accumulators; per accumulator the order is d steps, smallest plane first.
+            f32x4_t sc[NTB];
+#pragma unroll
+            for (int tb = 0; tb < NTB; ++tb) sc[tb] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ds = 0; ds < NDS; ++ds) {
+                bf16x8_t A[NTB];
+#pragma unroll
+                for (int tb = 0; tb < NTB; ++tb)
+                    A[tb] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(sK + (size_t)(w0 - t0 + 16 * tb + j) * KP + 64 * ds + 16 * kg));
+#pragma unroll
+                for (int pl = 2; pl >= 0; --pl)
+#pragma unroll
+                    for (int tb = 0; tb < NTB; ++tb) sc[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[tb], qB[ds][pl], sc[tb], 0, 0, 0);
+            }
+            if (w0 + 16 * NTB > ctx_lo) {                        // the causal edge of some row
+#pragma unroll
+                for (int tb = 0; tb < NTB; ++tb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        if (w0 + 16 * tb + 4 * kg + r >= ctx_col) sc[tb][r] = -INFINITY;
+            }
+            float mx = -INFINITY;
+#pragma unroll
+            for (int tb = 0; tb < NTB; ++tb) mx = fmaxf(mx, fmaxf(fmaxf(sc[tb][0], sc[tb][1]), fmaxf(sc[tb][2], sc[tb][3])));
+            mx = max_over_kg(mx);
+            const float m_new = fmaxf(m_run, mx);                // -inf while the column has no position yet
+            if (__any(m_new > m_run)) {                          // rescale only when some column's maximum moved
+                const float alpha = (m_run == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
+                l_run *= alpha;
+#pragma unroll
+                for (int db = 0; db < NDB; ++db) { acc[db][0] *= alpha; acc[db][1] *= alpha; acc[db][2] *= alpha; acc[db][3] *= alpha; }
+                m_run = m_new;
+            }
+            const float m_sub = m_new == -INFINITY ? 0.f : m_new;                    // 2^-inf = 0 for a column without positions
+#pragma unroll
+            for (int tb = 0; tb < NTB; ++tb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) { sc[tb][r] = __builtin_amdgcn_exp2f(sc[tb][r] - m_sub); l_run += sc[tb][r]; }
+            // P V: k slot (kg, 4 hf + r) is position w0 + 32 ks + 16 hf + 4 kg + r; SHARE fills only hf = 0
+#pragma unroll
+            for (int ks = 0; ks < (SHARE ? 1 : 2); ++ks) {
+                float pv[8];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) { pv[r] = sc[SHARE ? 0 : 2 * ks][r]; pv[4 + r] = SHARE ? 0.f : sc[SHARE ? 0 : 2 * ks + 1][r]; }
+                bf16x8_t pB[3];
+                split3(pv, pB);
+                bf16x8_t A[NDB];
+#pragma unroll
+                for (int db = 0; db < NDB; ++db) {
+                    const unsigned char *vr = sV + (size_t)(16 * db + j) * VP + 2 * (w0 - t0) + 64 * ks + 8 * kg;
+                    const uint2 lo = *reinterpret_cast<const uint2 *>(vr);
+                    uint2 hi = make_uint2(0u, 0u);
+                    if (!SHARE) hi = *reinterpret_cast<const uint2 *>(vr + 32);
+                    A[db] = __builtin_bit_cast(bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
+                }
+#pragma unroll
+                for (int pl = 2; pl >= 0; --pl)
+#pragma unroll
+                    for (int db = 0; db < NDB; ++db) acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[db], pB[pl], acc[db], 0, 0, 0);
+            }
+        }
+        l_run += __shfl_xor(l_run, 16, RS_WAVE);
+        l_run += __shfl_xor(l_run, 32, RS_WAVE);
+        if constexpr (!SHARE) {
+            if (col_ok && t_begin < ctx_col) {
+                float *p = a.partials + (((size_t)my_row * a.n_q + kvh * G + gh) * S + split) * PS;
+#pragma unroll
+                for (int db = 0; db < NDB; ++db)
+                    *reinterpret_cast<float4 *>(p + 4 + 16 * db + 4 * kg) = make_float4(acc[db][0], acc[db][1], acc[db][2], acc[db][3]);
+                if (kg == 0) { p[0] = m_run; p[1] = l_run; }
+            }
+        } else {
+            // merge the four waves' states of the slot's 16 columns; the tiles' LDS is free once everybody is here
+            __syncthreads();
+            float (*m_lds)[16] = reinterpret_cast<float (*)[16]>(smem);
+            float (*l_lds)[16] = m_lds + 4;
+            float *acc_lds = reinterpret_cast<float *>(smem + (size_t)2 * 4 * 16 * 4);                   // [4 waves][16 columns][HD + 4]
+#pragma unroll
+            for (int db = 0; db < NDB; ++db)
+                *reinterpret_cast<float4 *>(&acc_lds[(size_t)(wave * 16 + j) * PS + 16 * db + 4 * kg]) = make_float4(acc[db][0], acc[db][1], acc[db][2], acc[db][3]);
+            if (kg == 0) { m_lds[wave][j] = m_run; l_lds[wave][j] = l_run; }
+            __syncthreads();
+            for (int i = tid; i < RP * G * (HD / 4); i += 256) {
+                const int c = i / (HD / 4), d = 4 * (i - c * (HD / 4)), row = r_lo + slot0 * RP + c / G;
+                if (row >= r_hi || t_begin >= info.w + (row - r_lo) + 1) continue;
+                const float m0 = m_lds[0][c], m1 = m_lds[1][c], m2 = m_lds[2][c], m3 = m_lds[3][c];
+                const float M = fmaxf(fmaxf(m0, m1), fmaxf(m2, m3));                // -inf only if every score is -inf
+                const float w0 = m0 > -INFINITY ? __builtin_amdgcn_exp2f(m0 - M) : 0.f, w1 = m1 > -INFINITY ? __builtin_amdgcn_exp2f(m1 - M) : 0.f;
+                const float w2 = m2 > -INFINITY ? __builtin_amdgcn_exp2f(m2 - M) : 0.f, w3 = m3 > -INFINITY ? __builtin_amdgcn_exp2f(m3 - M) : 0.f;
+                const float L = l_lds[0][c] * w0 + l_lds[1][c] * w1 + l_lds[2][c] * w2 + l_lds[3][c] * w3;
+                const float4 a0 = *reinterpret_cast<const float4 *>(&acc_lds[(size_t)(0 * 16 + c) * PS + d]);
+                const float4 a1 = *reinterpret_cast<const float4 *>(&acc_lds[(size_t)(1 * 16 + c) * PS + d]);
+                const float4 a2 = *reinterpret_cast<const float4 *>(&acc_lds[(size_t)(2 * 16 + c) * PS + d]);
+                const float4 a3 = *reinterpret_cast<const float4 *>(&acc_lds[(size_t)(3 * 16 + c) * PS + d]);
+                float4 O;
+                O.x = a0.x * w0 + a1.x * w1 + a2.x * w2 + a3.x * w3;
+                O.y = a0.y * w0 + a1.y * w1 + a2.y * w2 + a3.y * w3;
+                O.z = a0.z * w0 + a1.z * w1 + a2.z * w2 + a3.z * w3;
+                O.w = a0.w * w0 + a1.w * w1 + a2.w * w2 + a3.w * w3;
+                const size_t head = (size_t)row * a.n_q + kvh * G + c % G;
+                if (a.direct) {
+                    const float inv = L > 0.f ? 1.f / L : 0.f;
+                    *reinterpret_cast<float4 *>(a.out + head * HD + d) = make_float4(O.x * inv, O.y * inv, O.z * inv, O.w * inv);
+                } else {
+                    float *p = a.partials + (head * S + split) * PS;
+                    *reinterpret_cast<float4 *>(p + 4 + d) = O;
+                    if (d == 0) { p[0] = M; p[1] = L; }
+                }
+            }
+            __syncthreads();                                     // (a further slot group would park into this LDS)
+        }
+    }
+}
+
 // merge the context slices of one (row, query head); 256 threads = (float4 columns) x (slice groups).
 // DQ workgroups share a head, each taking HD / DQ output columns: a head's records are S * (HD+4) floats
 // (38 KB for 72 slices), and with one workgroup per head only n_q CUs pull them.
@@ -1447,13 +1568,10 @@ __device__ __forceinline__ void attn_combine_unit(const AttnArgs &a, unsigned ch
     float (*red)[HDB] = reinterpret_cast<float (*)[HDB]>(w_sh + ATT_SMAX);       // [NSG][HDB]: 1024 floats
     const float *pbase = a.partials + ((size_t)row * a.n_q + head) * S * PS;
     const int qd = tid % NQ, sg = tid / NQ;
-    // slices that hold context: same slice length as attn_partial_unit
-    int C = (a.max_ctx + S - 1) / S;
-    C = ((C + ATT_BT - 1) / ATT_BT) * ATT_BT;
     // The records of all S slices are requested together with the row's position (one round trip instead of
     // two dependent ones); a slice past the context holds whatever an earlier call left there and is
     // replaced, never scaled, once the position has arrived.
-    const int bad = a.row_bad[row], pos = a.row_pos[row];
+    const int bad = a.row_bad[row], pos = a.row_pos[row], n_pos = a.ctx_top ? *a.ctx_top : a.max_ctx;
     constexpr int NPL = SMAX / 64;                          // slices per lane (wave 0)
     float4 buf[NLD];
     float2 mlr[NPL];
@@ -1472,7 +1590,8 @@ __device__ __forceinline__ void attn_combine_unit(const AttnArgs &a, unsigned ch
         }
     }
     __builtin_amdgcn_sched_barrier(0);                      // every request is in flight before anything waits
-    const int S_act = bad ? 0 : min(S, pos / C + 1);
+    // slices that hold context: same slice length as the kernel that wrote the records
+    const int S_act = bad ? 0 : min(S, pos / attn_slice_len(n_pos, S) + 1);
 #pragma unroll
     for (int k = 0; k < NLD; ++k)
         if (sg + k * NSG >= S_act) buf[k] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1490,7 +1609,7 @@ __device__ __forceinline__ void attn_combine_unit(const AttnArgs &a, unsigned ch
         float lsum = 0.f;
 #pragma unroll
         for (int k = 0; k < NPL; ++k) {
-            w[k] = ls[k] > 0.f ? __expf(ms[k] - M) : 0.f;
+            w[k] = ls[k] > 0.f ? (a.base2 ? __builtin_amdgcn_exp2f(ms[k] - M) : __expf(ms[k] - M)) : 0.f;
             lsum = fmaf(ls[k], w[k], lsum);
         }
         const float L = wave_sum(lsum);

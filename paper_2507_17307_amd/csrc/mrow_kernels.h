@@ -431,10 +431,6 @@ __host__ __device__ constexpr size_t gemm_tile_lds_bytes() {
     return (size_t)2 * ((MODE == G_GATEUP) ? 2 : 1) * CT * 16 * (128 * tile_sw<TB>() + TILE_PAD);
 }
 
-// workgroup barrier for LDS hand-over that leaves global loads in flight: the LDS accesses issued so far complete
-// (lgkmcnt(0); expcnt and vmcnt are left alone), then the barrier; the compiler moves no memory access across it
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 template <int MODE, int TB, int CT, int NW = 4, int CS = 1>
 __global__ void __launch_bounds__(NW * 64) k_gemm_tile(GemmArgs a) {
     static_assert(MODE == G_GATEUP || MODE == G_PART || MODE == G_LMHEAD, "gate/up, raw partial sums or the LM head");

@@ -69,7 +69,7 @@ const char *check_config(const rs_config *c) {
 }
 
 struct Layout {
-    size_t rope_cos, rope_sin, row_slot, row_pos, row_bad, out_row, seq_bad, seq_scale, seq_info, h, qkv_raw, qbuf,
+    size_t rope_cos, rope_sin, row_slot, row_pos, row_bad, out_row, seq_bad, seq_scale, seq_info, ctx_top, h, qkv_raw, qbuf,
         attn_out, act, attn_part, attn_cnt, lm_parts, sync, layer_ptrs, gemm_part, xn32, lm32, total;
     int attn_rows_x_splits;   // capacity of attn_part in (row, split) pairs
     int lm_parts_cap;         // partial states per sequence
@@ -110,6 +110,7 @@ Layout make_layout(const rs_config &c) {
     L.seq_bad = take(c.max_seqs * 4);
     L.seq_scale = take(c.max_seqs * 4);
     L.seq_info = take((size_t)c.max_seqs * 16);
+    L.ctx_top = take(4);
     L.h = take((size_t)c.max_rows * c.d_model * 4);
     L.qkv_raw = take((size_t)c.max_rows * qkv * 4);
     L.qbuf = take((size_t)c.max_rows * qdim * 4);
@@ -247,43 +248,60 @@ GemvPlan make_plan(const rs_config &c, int n_cu) {
 template <int HD>
 rs_status launch_attn(AttnArgs &a, int n_splits, int n_kv, int n_rows, int n_seqs, int n_cu, hipStream_t st) {
     const bool spans = n_rows > n_seqs;
-    a.n_slices = n_splits;
-    a.n_rows = n_rows;
-    if (spans) {
-        // several rows per sequence: rows share K/V tiles through the columns of the matrix-core tiles
-        // one wave per row slot (rp rows); the kernel needs most of a SIMD's registers, so a workgroup brings
-        // only as many waves as it has slots (up to four): with idle waves in it, a CU held one workgroup at a
-        // time and a two-row call on eight KV heads at 5000 positions took 17.5 us instead of ~7
-        const int rp = 16 / (a.n_q / n_kv);
-        const long base = (long)n_splits * n_kv * n_seqs;
-        if (n_splits * ATT_BT >= a.max_ctx && (n_rows >= 5 || base <= n_cu)) {
-            // every slice is one 64-position pass: one workgroup per (slice, KV head, sequence), K/V tile through LDS
-            // (calls of two to four rows with more workgroups than CUs stay on the kernel below: 7B shape, two rows 7.6 us
-            // against 9.6; per call, three rows: 7B 3.588 -> 3.577 ms, 14B 7.57 -> 7.19; from five rows on it loses).
-            // Measured per call, 7B shape: 5 rows 3.91 -> 3.84 ms, 16 rows 5.03 -> 4.83, 64 rows 10.26 -> 9.61; 1.5B shape: 8 rows
-            // 1.92 -> 1.82, 16 rows 2.43 -> 2.19.
-            // A sequence's row slots are dealt to ZS workgroups where that shortens the busiest CU's queue: cost in slot
-            // turns = workgroups per CU x (slots per wave + 1/2 for the tile), at most (n_rows - n_seqs + 1) rows in a span
-            const int spw = ((n_rows - n_seqs + 1 + rp - 1) / rp + 3) / 4;
-            int zs_best = 1; long cost_best = -1;
-            for (int zs = 1; zs <= 8 && zs <= spw; zs *= 2) {
-                const long cost = ((base * zs + n_cu - 1) / n_cu) * (2 * ((spw + zs - 1) / zs) + 1);
-                if (cost_best < 0 || cost < cost_best) { cost_best = cost; zs_best = zs; }
+    const int *ctx_top = a.ctx_top;
+    a.ctx_top = nullptr; a.base2 = 0; a.direct = 0; a.slot_split = 1;
+    const int rp = 16 / (a.n_q / n_kv), one_pass = (a.max_ctx + ATT_BT - 1) / ATT_BT;
+    const int max_slots = (n_rows - n_seqs + 1 + rp - 1) / rp;   // row slots of the longest span there can be
+    const int walk_zs = (max_slots + 3) / 4;                     // workgroups of four waves that hold them
+    const long walk_base = (long)n_kv * n_seqs * walk_zs;
+    // Walk or one pass per workgroup.  While a launch of one-pass workgroups is about one round of the machine, one pass is
+    // the shorter chain (1.5B shape, 2 rows: 5.5 us against 6.2; 7B, 2 / 5 rows, 288 workgroups: 6.2 / 8.3 against 8.1 / 9.5); beyond that
+    // the walk re-uses its row state, leaves fewer records and needs fewer prologues (7B: 9 rows, 576 workgroups: 10.6 against
+    // 13.6; 16 rows 12.0 against 15.7; 8 sequences at 4400 positions 17.6 against 22.1; 14B, 2 rows at 9000: 11.9 against 14.8).
+    // Caches whose rows do not fit 32-bit offsets stay on the per-row kernel.
+    const bool small_rows = (size_t)a.max_ctx * HD * 2 < ((size_t)1 << 31);
+    const bool walk = n_rows > 1 && small_rows && (n_splits < one_pass || one_pass * walk_base > 3L * n_cu / 2);
+    if (walk) {
+        // Slices: one round of two workgroups per CU, rounded down (a few workgroups in a further round cost a whole one:
+        // 14B, 61 rows, 22 / 21 slices of 48 workgroups: 61 / 53 us).  Several sequences with spans: twice as many, because
+        // their contexts and spans differ and part of the workgroups leaves at once (32B, 8 sequences, 29 rows: 95 -> 58 us).
+        const bool share = max_slots == 1;
+        long S = (share || n_seqs == 1 ? 2L : 4L) * n_cu / walk_base;
+        if (S > one_pass) S = one_pass;
+        if (S > n_splits) S = n_splits;
+        if (S < 1) S = 1;
+        n_splits = (int)S;
+        a.slot_split = walk_zs; a.ctx_top = ctx_top; a.base2 = 1; a.direct = !spans && n_splits == 1;
+        constexpr size_t lds = attn_walk_lds_bytes<HD>();
+        if (lds > 64 * 1024) {
+            static std::atomic<bool> raised{false};       // per instantiation; setting the attribute twice is harmless
+            if (!raised) {
+                hipError_t e = hipFuncSetAttribute((const void *)k_attn_walk<HD, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_attn_walk<HD, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+                if (e != hipSuccess) return fail(RS_EHIP, "raising the LDS limit of attn_walk: %s", hipGetErrorString(e));
+                raised = true;
             }
-            a.slot_split = zs_best;
-            hipLaunchKernelGGL((k_attn_span<HD>), dim3(n_splits, n_kv, n_seqs * zs_best), dim3(256), attn_span_lds_bytes<HD>(), st, a);
-            RS_LAUNCHED("attn_span");
-        } else {
-        const int slots = (n_rows + rp - 1) / rp, wpb = slots < 4 ? slots : 4;
-        const dim3 grid(n_splits, n_kv, (slots + wpb - 1) / wpb);
-        // the one-wave-per-SIMD build schedules best, but only while every wave of the launch is resident at once
-        const bool one = (long)grid.x * grid.y * grid.z * wpb <= 4L * n_cu && (size_t)n_kv * a.max_ctx * HD * 4 <= ((size_t)16 << 20);
-        if (one)
-            hipLaunchKernelGGL((k_attn_partial_rows<HD, 1>), grid, dim3(64 * wpb), 0, st, a);
-        else
-            hipLaunchKernelGGL((k_attn_partial_rows<HD, 2>), grid, dim3(64 * wpb), 0, st, a);
-        RS_LAUNCHED("attn_partial_rows");
         }
+        const dim3 grid(n_splits, n_kv, n_seqs * walk_zs);
+        if (share) hipLaunchKernelGGL((k_attn_walk<HD, true>), grid, dim3(256), lds, st, a);
+        else hipLaunchKernelGGL((k_attn_walk<HD, false>), grid, dim3(256), lds, st, a);
+        RS_LAUNCHED("attn_walk");
+        if (a.direct) return RS_OK;
+    } else if (spans && small_rows) {
+        // several rows per sequence: rows share K/V tiles through the columns of the matrix-core tiles
+        const long base = (long)n_splits * n_kv * n_seqs;
+        // every slice is one 64-position pass: one workgroup per (slice, KV head, sequence), K/V tile through LDS
+        // A sequence's row slots are dealt to ZS workgroups where that shortens the busiest CU's queue: cost in slot
+        // turns = workgroups per CU x (slots per wave + 1/2 for the tile), at most (n_rows - n_seqs + 1) rows in a span
+        const int spw = ((n_rows - n_seqs + 1 + rp - 1) / rp + 3) / 4;
+        int zs_best = 1; long cost_best = -1;
+        for (int zs = 1; zs <= 8 && zs <= spw; zs *= 2) {
+            const long cost = ((base * zs + n_cu - 1) / n_cu) * (2 * ((spw + zs - 1) / zs) + 1);
+            if (cost_best < 0 || cost < cost_best) { cost_best = cost; zs_best = zs; }
+        }
+        a.slot_split = zs_best;
+        hipLaunchKernelGGL((k_attn_span<HD>), dim3(n_splits, n_kv, n_seqs * zs_best), dim3(256), attn_span_lds_bytes<HD>(), st, a);
+        RS_LAUNCHED("attn_span");
     } else {
         // requesting every slice's K and V before the context length is known reads the rows' whole caches up to
         // max_ctx.  That saves a dependent round trip, but on a decode run that walks a 4608-position cache the
@@ -303,6 +321,7 @@ rs_status launch_attn(AttnArgs &a, int n_splits, int n_kv, int n_rows, int n_seq
             hipLaunchKernelGGL((k_attn_partial<HD, false, false>), dim3(n_splits, n_kv, n_rows), dim3(256), attn_lds_bytes<HD>(a.n_q / n_kv), st, a);
         RS_LAUNCHED("attn_partial");
     }
+    a.n_slices = n_splits;
     // the merge is unrolled for 128 slices (contexts up to 8192 positions) or for the most the kernels take
     // HD / 64 workgroups per head, 64 output columns each
     constexpr int DQ = HD / 64 > 0 ? HD / 64 : 1;
@@ -707,7 +726,7 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
     pa.embed = m->embed;
     pa.row_slot = row_slot; pa.row_pos = row_pos; pa.row_bad = row_bad;
     pa.out_row = m->at<int>(L.out_row); pa.seq_bad = m->at<int>(L.seq_bad); pa.seq_scale = m->at<float>(L.seq_scale);
-    pa.seq_info = m->at<int4>(L.seq_info);
+    pa.seq_info = m->at<int4>(L.seq_info); pa.ctx_top = m->at<int>(L.ctx_top);
     pa.h = h;
     hipLaunchKernelGGL(k_prepare, dim3(n_rows), dim3(256), 0, st, pa);
     RS_LAUNCHED("prepare");
@@ -738,7 +757,7 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
         aa.qbuf = m->at<float>(L.qbuf); aa.kcache = m->kv_k; aa.vcache = m->kv_v;
         aa.partials = m->at<float>(L.attn_part);
         aa.out = m->at<float>(L.attn_out);
-        aa.row_pos = row_pos; aa.row_slot = row_slot; aa.row_bad = row_bad; aa.seq_info = m->at<int4>(L.seq_info);
+        aa.row_pos = row_pos; aa.row_slot = row_slot; aa.row_bad = row_bad; aa.seq_info = m->at<int4>(L.seq_info); aa.ctx_top = m->at<int>(L.ctx_top);
         aa.n_q = c.n_q_heads; aa.n_kv = c.n_kv_heads; aa.max_ctx = c.max_ctx; aa.max_seqs = c.max_seqs; aa.layer = l;
 
         if (single) {
