@@ -876,7 +876,8 @@ struct AttnArgs {
     const uint16_t *kcache;        // [layer][slot][kv_head][position][hd] bf16
     const uint16_t *vcache;        // [layer][slot][kv_head][hd][position] bf16
     float *partials;               // [rows, n_q, n_slices, hd+4]
-    float *out;                    // [rows, n_q*hd] fp32
+    float *out;                    // [rows, n_q*hd] fp32, or the same in operand order (out_frag)
+    int out_frag, rsh;             // a matrix-core kernel reads `out`: rows in the order of frag_index with blocks of 1 << rsh
     const int *row_pos, *row_slot, *row_bad;
     int n_q, n_kv, max_ctx, max_seqs, layer, n_slices;
     int slot_split;                // k_attn_span, k_attn_walk: workgroups per sequence, slice and KV head
@@ -885,6 +886,19 @@ struct AttnArgs {
     int direct;                    // k_attn_walk: one slice, decode rows: the normalised rows go to `out`, no merge follows
     const int4 *seq_info;          // per sequence {first row, end row, cache slot, first row's position}, first row < 0: invalid (k_attn_span)
 };
+
+// Place of element k of token row m in an activation buffer of rows of K fp32 values (K a multiple of 32) that a matrix-core
+// kernel reads: [block of R rows][32 k][half of 8][g][row of the block][4], g = (k % 32) / 8, half = (k % 8) / 4, R = 1 << rsh: the
+// 16 bytes that the lanes (row, g) need for one half of their B operand lie in one contiguous piece of 64 R bytes per request.
+// Row by row, a request touches R cache lines that neighbouring lanes take in turn, and the CU's cache looks one up per lane
+// (7B shape: QKV / down of 128 rows 32.6 / 51 -> 23.0 / 41.1 us, gate/up of 16 rows 57.0 -> 54.2; of 5 rows the same).
+// R is 16 for more than 16 rows, else the smallest power of two that holds the rows: one row's worth of requests for the
+// one-row LM head of a long span (1.5B shape: 97 us with blocks of 16, 84 with its own row).
+// Four consecutive k (from a multiple of four) stay contiguous.  Buffers hold whole blocks: rows up to the next multiple of 32.
+__host__ __device__ __forceinline__ size_t frag_index(int m, int k, int K, int rsh) {
+    return ((((size_t)(m >> rsh) * (K >> 5) + (k >> 5)) * 8 + ((k >> 2) & 1) * 4 + ((k >> 3) & 3)) << (rsh + 2)) + ((m & ((1 << rsh) - 1)) << 2) + (k & 3);
+}
+inline int frag_shift(int rows) { int s = 0; while (s < 4 && (1 << s) < rows) ++s; return s; }
 
 constexpr int ATT_GMAX = 8;       // query heads per kv head, at most
 constexpr int ATT_SMAX = 192;     // context slices, at most (a multiple of 64: the merge gives each lane ATT_SMAX / 64 of them)
@@ -1338,7 +1352,8 @@ __global__ void __launch_bounds__(256, 2) k_attn_walk(AttnArgs a) {
     if (info.x < 0) {
         // no merge kernel follows a decode step of one slice: the rejected row's output is cleared here
         if (SHARE && a.direct)
-            for (int i = tid; i < G * HD; i += 256) a.out[((size_t)seq * a.n_q + kvh * G) * HD + i] = 0.f;
+            for (int i = tid; i < G * HD; i += 256)
+                a.out[a.out_frag ? frag_index(seq, kvh * G * HD + i, a.n_q * HD, a.rsh) : ((size_t)seq * a.n_q + kvh * G) * HD + i] = 0.f;
         return;
     }
     const int r_lo = info.x, r_hi = info.y;
@@ -1537,7 +1552,8 @@ __global__ void __launch_bounds__(256, 2) k_attn_walk(AttnArgs a) {
                 const size_t head = (size_t)row * a.n_q + kvh * G + c % G;
                 if (a.direct) {
                     const float inv = L > 0.f ? 1.f / L : 0.f;
-                    *reinterpret_cast<float4 *>(a.out + head * HD + d) = make_float4(O.x * inv, O.y * inv, O.z * inv, O.w * inv);
+                    const size_t oi = a.out_frag ? frag_index(row, (kvh * G + c % G) * HD + d, a.n_q * HD, a.rsh) : head * HD + d;
+                    *reinterpret_cast<float4 *>(a.out + oi) = make_float4(O.x * inv, O.y * inv, O.z * inv, O.w * inv);
                 } else {
                     float *p = a.partials + (head * S + split) * PS;
                     *reinterpret_cast<float4 *>(p + 4 + d) = O;
@@ -1630,7 +1646,8 @@ __device__ __forceinline__ void attn_combine_unit(const AttnArgs &a, unsigned ch
         float o = 0.f;
 #pragma unroll
         for (int g = 0; g < NSG; ++g) o += red[g][tid];
-        const size_t oi = ((size_t)row * a.n_q + head) * HD + dq * HDB + tid;
+        const int k = head * HD + dq * HDB + tid;
+        const size_t oi = a.out_frag ? frag_index(row, k, a.n_q * HD, a.rsh) : (size_t)row * a.n_q * HD + k;
         a.out[oi] = o;
     }
 }

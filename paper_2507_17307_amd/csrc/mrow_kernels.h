@@ -7,7 +7,8 @@
 // bf16(x - p0), p2 = x - p0 - p1, which is exact: 3 x 8 significant bits hold the
 // 24 of an fp32) and multiplies each weight tile with all three, smallest first,
 // so the product is that of the fp32 activation (4 bytes per element through the
-// load path instead of the 6 of stored planes).
+// load path instead of the 6 of stored planes).  They lie in the order in which the
+// matrix-core operands take them (frag_index), not row by row.
 #pragma once
 
 #include "device_utils.h"
@@ -33,13 +34,13 @@ __device__ __forceinline__ float4 sum_splits4(const float *base, size_t i, int k
 
 // RMSNorm of whole rows: grid n_out, block ROWK_THREADS; d a multiple of 4, at most 12 * ROWK_THREADS.
 // src row = gather ? gather[blockIdx.x] : blockIdx.x; the normalised row goes to out32[blockIdx.x] as fp32 (the
-// matrix-core kernels split it into bf16 planes themselves).
+// matrix-core kernels split it into bf16 planes themselves), in operand order (frag_index).
 // part != null: the projection before this norm left its result as `ksplit` partial sums
 // part[ks][row][d] (split over K across workgroups); they are added to the residual row here, in a
 // fixed order, and the row is written back before it is normalised.
 __global__ void __launch_bounds__(ROWK_THREADS)
 k_rmsnorm_rows(float *__restrict__ h, const uint16_t *__restrict__ gain, float eps, int d,
-               const int *__restrict__ gather, float *__restrict__ out32,
+               const int *__restrict__ gather, float *__restrict__ out32, int rsh,
                const float *__restrict__ part, int ksplit, size_t part_stride) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int src = gather ? gather[blockIdx.x] : blockIdx.x;
@@ -77,8 +78,7 @@ k_rmsnorm_rows(float *__restrict__ h, const uint16_t *__restrict__ gain, float e
     for (int k = 0; k < NV; ++k) {
         const int i4 = tid + k * ROWK_THREADS;
         if (i4 >= n4) continue;
-        const size_t o = (size_t)blockIdx.x * d + 4 * i4;
-        *reinterpret_cast<float4 *>(out32 + o) = make_float4(v[k].x * (inv * bf16_lo(gv[k].x)), v[k].y * (inv * bf16_hi(gv[k].x)),
+        *reinterpret_cast<float4 *>(out32 + frag_index(blockIdx.x, 4 * i4, d, rsh)) = make_float4(v[k].x * (inv * bf16_lo(gv[k].x)), v[k].y * (inv * bf16_hi(gv[k].x)),
                                                              v[k].z * (inv * bf16_lo(gv[k].y)), v[k].w * (inv * bf16_hi(gv[k].y)));
     }
 }
@@ -137,8 +137,8 @@ __global__ void __launch_bounds__(ROWK_THREADS) k_rope_kv_rows(RopeArgs a) {
 // A workgroup of GEMM_NW waves owns R consecutive tiles of 16 output columns (for gate/up a tile is 16
 // gate rows plus the 16 matching up rows of W) and ALL of K; wave w takes the k windows w, w+GEMM_NW,
 // ... of 64 elements (more waves where a matrix has few tiles, so that enough requests are in flight).  Per window a wave requests
-//   * its piece of X once: fp32, 16 tokens x 64 k per 16-token block, each lane the values of its
-//     place in the B-operand layout of v_mfma_f32_16x16x32_bf16 (lane (i = lane % 16, g = lane / 16)
+//   * its piece of X once: fp32, 16 tokens x 64 k per 16-token block, four contiguous kilobytes (see frag_index), each lane
+//     the values of its place in the B-operand layout of v_mfma_f32_16x16x32_bf16 (lane (i = lane % 16, g = lane / 16)
 //     supplies the 8 consecutive k at 32 s + 8 g of token i), split into the three planes in
 //     registers; the piece serves all R tiles, so X costs 2/R of the W bytes in L2 traffic (stored
 //     planes cost 3/R: a 7B-shape call of 16 rows 4.84 -> 4.4 ms);
@@ -153,8 +153,9 @@ __global__ void __launch_bounds__(ROWK_THREADS) k_rope_kv_rows(RopeArgs a) {
 // ------------------------------------------------------------------------------------------------
 struct GemmArgs {
     const uint16_t *W; int N, K, M;       // M = valid token rows
-    const float *X32;                     // activations: fp32 rows [.., K] (split into three bf16 planes in registers)
-    float *act32;                         // gate/up: SwiGLU output rows [.., d_ffn] fp32
+    int rsh;                              // rows per block of the activation buffers: 1 << rsh (frag_index); 4 for more than 16 rows
+    const float *X32;                     // activations: fp32 rows of K in operand order (split into three bf16 planes in registers)
+    float *act32;                         // gate/up: SwiGLU output rows of d_ffn, fp32 in operand order
     float *out_f32; int ld_out;           // raw fp32 output [M, ld_out] (QKV)
     int yblocks;                          // > 1: the token rows are cut into yblocks blocks of 16*NB rows, each taken by its own
                                           //      workgroups (same weights; ids arranged so that they meet in one XCD's L2)
@@ -214,15 +215,11 @@ __global__ void __launch_bounds__(GEMM_NW * 64) k_gemm_rows(GemmArgs a) {
     const int part_id = Y == 1 ? (int)blockIdx.x : unit_first;            // LM head: this workgroup's place among its rows' partial states
     const int m_base = yb * 16 * NB;
 
-    // token side: rows past M read row 0 and are cleared after the load
+    // token side: rows past M (inside the padding of the buffer) hold anything; their products fill matrix-core columns
+    // that belong to no row and are never stored
     const float *xp[NB];
-    bool xok[NB];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        const int m = m_base + nb * 16 + i16;
-        xok[nb] = m < a.M;
-        xp[nb] = a.X32 + (size_t)(xok[nb] ? m : 0) * K + g * 8;
-    }
+    for (int nb = 0; nb < NB; ++nb) xp[nb] = a.X32 + (size_t)(m_base + nb * 16) * K + ((g << a.rsh) + min(i16, (1 << a.rsh) - 1)) * 4;
     SoftState st; st.init();
     const int lm_row = m_base + i16;                      // LM head (NB = 1): the output row this lane's state follows
     const float lm_scale = (MODE == G_LMHEAD && lm_row < a.M) ? a.seq_scale[lm_row] : 1.f;
@@ -256,8 +253,8 @@ __global__ void __launch_bounds__(GEMM_NW * 64) k_gemm_rows(GemmArgs a) {
             for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
-                    const float4 *q = reinterpret_cast<const float4 *>(xp[nb] + k0 + 32 * s);
-                    xb[nb][s][0] = q[0]; xb[nb][s][1] = q[1];
+                    const float *q = xp[nb] + ((size_t)(k0 + 32 * s) << a.rsh);
+                    xb[nb][s][0] = *reinterpret_cast<const float4 *>(q); xb[nb][s][1] = *reinterpret_cast<const float4 *>(q + (16 << a.rsh));
                 }
 #pragma unroll
             for (int r = 0; r < R; ++r)
@@ -275,11 +272,7 @@ __global__ void __launch_bounds__(GEMM_NW * 64) k_gemm_rows(GemmArgs a) {
 #pragma unroll
                 for (int s = 0; s < NS; ++s) {
                     const float4 x0 = xb[nb][s][0], x1 = xb[nb][s][1];
-                    float xv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-                    if (!xok[nb]) {
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) xv[e] = 0.f;
-                    }
+                    const float xv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
                     split3(xv, B[nb][s]);
                 }
 #pragma unroll
@@ -359,19 +352,29 @@ __global__ void __launch_bounds__(GEMM_NW * 64) k_gemm_rows(GemmArgs a) {
                 }
             }
             if (tile >= n_tiles || m >= a.M) continue;
-            const float o0[4] = {v[0].x, v[0].y, v[0].z, v[0].w};
-            const float o1[4] = {v[NT - 1].x, v[NT - 1].y, v[NT - 1].z, v[NT - 1].w};
-#pragma unroll
-            for (int rr = 0; rr < 4; ++rr) {
-                const int n = n0 + 4 * g + rr;
-                if (n >= n_out) continue;
-                const float val = o0[rr];
-                if ((MODE == G_QKV || MODE == G_OPROJ || MODE == G_DOWN) && KSP > 1) a.part[ksp * a.part_stride + (size_t)m * n_out + n] = val;
-                else if (MODE == G_QKV) a.out_f32[(size_t)m * a.ld_out + n] = val;
-                else if (MODE == G_OPROJ || MODE == G_DOWN) a.h_out[(size_t)m * a.ld_h + n] += val;
-                else if (MODE == G_GATEUP) a.act32[(size_t)m * a.d_ffn + n] = val / (1.0f + expf(-val)) * o1[rr];
+            if constexpr (MODE != G_LMHEAD) {
+                // (n_out is a multiple of 16: whole tiles, one 16-byte store per lane)
+                const int n = n0 + 4 * g;
+                float *dst;
+                if constexpr (MODE == G_GATEUP) {
+                    dst = a.act32 + frag_index(m, n, a.d_ffn, a.rsh);
+                    v[0].x = v[0].x / (1.0f + expf(-v[0].x)) * v[NT - 1].x; v[0].y = v[0].y / (1.0f + expf(-v[0].y)) * v[NT - 1].y;
+                    v[0].z = v[0].z / (1.0f + expf(-v[0].z)) * v[NT - 1].z; v[0].w = v[0].w / (1.0f + expf(-v[0].w)) * v[NT - 1].w;
+                } else if (KSP > 1) dst = a.part + ksp * a.part_stride + (size_t)m * n_out + n;
+                else if (MODE == G_QKV) dst = a.out_f32 + (size_t)m * a.ld_out + n;
                 else {
-                    const float lg = val * lm_scale;
+                    dst = a.h_out + (size_t)m * a.ld_h + n;
+                    const float4 h = *reinterpret_cast<const float4 *>(dst);
+                    v[0] = make_float4(h.x + v[0].x, h.y + v[0].y, h.z + v[0].z, h.w + v[0].w);
+                }
+                *reinterpret_cast<float4 *>(dst) = v[0];
+            } else {
+                const float o0[4] = {v[0].x, v[0].y, v[0].z, v[0].w};
+#pragma unroll
+                for (int rr = 0; rr < 4; ++rr) {
+                    const int n = n0 + 4 * g + rr;
+                    if (n >= n_out) continue;
+                    const float lg = o0[rr] * lm_scale;
                     st.push(lg, n);
                     if (a.sample_on) st.push_noisy(lg, n, a.sample_key, noise_base);
                     if (a.logits) a.logits[(size_t)m * a.N + n] = lg;
@@ -398,18 +401,20 @@ __global__ void __launch_bounds__(GEMM_NW * 64) k_gemm_rows(GemmArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// k_gemm_tile: the same products for 33 .. 128 token rows, one workgroup per block of output columns.
-// A workgroup of four waves owns CT tiles of 16 output columns (gate/up: CT gate tiles and the CT matching
-// up tiles) and ALL token rows: wave w of NW (four up to 64 rows, eight up to 128) holds the rows 16 TB w ..
-// 16 TB (w + 1) - 1 (TB = 1 block of 16 in every launch; two blocks per wave on four waves measured slower: 7B gate/up at
-// 128 rows 142 us against 110) against every column of the workgroup, so nothing has to be summed across waves and W is read from
-// HBM once per call, whatever the row count.  Per 64-element k window the four waves fetch the window's W
-// rows together (whole 128-byte row pieces, into registers, up to six windows ahead), park them in one of two
-// LDS buffers and every wave reads all of them back in A-operand layout; its X pieces (fp32 rows, split
-// into the three planes in registers, XD - 1 windows ahead) come straight from global memory because no
-// other wave needs them.  One barrier per window, and it is the bare instruction behind a wait for the LDS writes only:
-// __syncthreads() carries a fence that waits for every outstanding load, i.e. for the windows requested
-// ahead, and a window would cost a full memory round trip.
+// k_gemm_tile: the same products for 17 .. 128 token rows, one workgroup per block of output columns.
+// A workgroup owns CT tiles of 16 output columns (gate/up: CT gate tiles and the CT matching up tiles) and ALL token rows:
+// wave w of NW (four up to 64 rows, eight up to 128) holds the rows 16 w .. 16 w + 15 against every column of the workgroup
+// (CS = 2: two waves share a row block and take half of the columns each), so nothing has to be summed across waves and W
+// is read from HBM once per call, whatever the row count.  Per 64-element k window the waves fetch the window's W
+// rows together (whole 128-byte row pieces, into registers, three windows ahead), park them in one of two
+// LDS buffers and every wave reads all of them back in A-operand layout; its X pieces (fp32, split into the three planes in
+// registers) come straight from global memory because no other wave needs them.  One barrier per window, and it is the
+// bare instruction behind a wait for the LDS accesses only: __syncthreads() carries a fence that waits for every
+// outstanding load, i.e. for the windows requested ahead, and a window would cost a full memory round trip.
+// What bounds it (7B gate/up at 128 rows, 272 MB: 112 us; without any of the loads 72, without products 68, W alone 50, matrix
+// cores alone 61): the CU's load path takes W and X one after the other, 20 + 32 KB per window, and its requests
+// stall the waves that also issue the products.  Before the operand-order activations and the pipeline over groups of
+// tiles: gate/up 119, LM head of 128 sequences 548 -> 486, down 51 -> 41, QKV 32.6 -> 23.0.
 // X costs (workgroups) x (rows) x K x 4 bytes of L2 traffic, which is why a workgroup takes as many column
 // tiles as the launch can afford (launch_gemm_tile picks CT and the split of K over workgroups so that the
 // workgroups are close to a whole number of rounds of the machine).
@@ -419,44 +424,40 @@ __global__ void __launch_bounds__(GEMM_NW * 64) k_gemm_rows(GemmArgs a) {
 // ------------------------------------------------------------------------------------------------
 constexpr int G_PART = 5;
 
-// windows per step: a step fetches 128 SW contiguous bytes of every W row.  One everywhere: two windows per step
-// (256-byte row pieces, two register slots each for W and X) measured slower (7B shape, 64 rows, gate/up 108 us
-// against 91)
-template <int TB> constexpr int tile_sw() { return 1; }
-
 constexpr int TILE_PAD = 16;                      // bytes added to a parked row of k_gemm_tile against LDS bank conflicts (48 measured the same)
 
-template <int MODE, int TB, int CT>
+template <int MODE, int CT>
 __host__ __device__ constexpr size_t gemm_tile_lds_bytes() {
-    return (size_t)2 * ((MODE == G_GATEUP) ? 2 : 1) * CT * 16 * (128 * tile_sw<TB>() + TILE_PAD);
+    return (size_t)2 * ((MODE == G_GATEUP) ? 2 : 1) * CT * 16 * (128 + TILE_PAD);
 }
 
-template <int MODE, int TB, int CT, int NW = 4, int CS = 1>
-__global__ void __launch_bounds__(NW * 64) k_gemm_tile(GemmArgs a) {
+template <int MODE, int CT, int NW = 4, int CS = 1>
+__global__ void __launch_bounds__(NW * 64, MODE == G_LMHEAD ? 2 : 1) k_gemm_tile(GemmArgs a) {
     static_assert(MODE == G_GATEUP || MODE == G_PART || MODE == G_LMHEAD, "gate/up, raw partial sums or the LM head");
+    static_assert(NW == 4 || NW == 8, "four or eight waves");
     constexpr int NT = (MODE == G_GATEUP) ? 2 : 1;
     constexpr int NS = GEMM_KW / 32;
-    constexpr int SW = tile_sw<TB>();                         // windows per step
-    constexpr int KSTEP = GEMM_KW * SW;                       // k elements per step: K must be a multiple
-    constexpr int PITCH = 128 * SW + TILE_PAD;                // bytes per parked row (padded against LDS bank conflicts)
-    constexpr int WROWS = NT * CT * 16;                       // W rows of a step
-    constexpr int RPR = 8 * NW / SW;                          // rows per round of 16-byte loads of the whole workgroup
+    constexpr int PITCH = 128 + TILE_PAD;                     // bytes per parked row (padded against LDS bank conflicts)
+    constexpr int WROWS = NT * CT * 16;                       // W rows of a step (one 64-element window of K)
+    constexpr int RPR = 8 * NW;                               // rows per round of 16-byte loads of the whole workgroup
     constexpr int WQ = (WROWS + RPR - 1) / RPR;               // loads per thread and step
     constexpr size_t BUF = (size_t)WROWS * PITCH;
-    constexpr int XD = TB == 1 ? 3 : 2;                       // register slots of X (each holds a step's pieces)
     constexpr int RB = NW / CS;                               // waves that differ in their rows; CS waves share a row block and
     constexpr int CTH = (CT + CS - 1) / CS;                   // split the workgroup's column tiles, CTH each (the last may get fewer)
     static_assert(NW % CS == 0, "whole column splits");
+    constexpr int NTC = NT * CTH;                             // 16-column tiles of a wave
+    constexpr int NCH = (NTC + 4) / 5;                        // a k step's A operands are read in NCH groups of CH tiles
+    constexpr int CH = (NTC + NCH - 1) / NCH, NGR = NS * NCH; // groups per step (even)
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i16 = lane & 15, g = lane >> 4;
-    const int rb = wave % RB, ct0 = (wave / RB) * CTH;          // this wave's row block and first column tile
-    const int lrow = tid / (8 * SW), lchunk = tid % (8 * SW); // W load role: row RPR q + lrow of the step, bytes 16 lchunk ..
+    const int rb = wave % RB, ct0 = (wave / RB) * CTH;        // this wave's row block and first column tile
+    const int lrow = tid / 8, lchunk = tid % 8;               // W load role: row RPR q + lrow of the step, bytes 16 lchunk ..
     const int K = a.K;
     const int n_out = (MODE == G_GATEUP) ? a.d_ffn : a.N;
     const int n_tiles = (n_out + 15) / 16, n_groups = (n_tiles + CT - 1) / CT;
     const int KSP = a.ksplit > 1 ? a.ksplit : 1;
-    const int n_st = K / KSTEP;                               // steps over the whole of K
+    const int n_st = K / GEMM_KW;                             // steps over the whole of K
     const int unit = blockIdx.x;                              // one unit per workgroup
     if (unit >= n_groups * KSP) return;
     const int grp = unit / KSP, ksp = unit - grp * KSP;
@@ -475,42 +476,31 @@ __global__ void __launch_bounds__(NW * 64) k_gemm_tile(GemmArgs a) {
         const int row = min(n0 + col, n_out - 1) + (half ? a.d_ffn : 0);
         wp[q] = a.W + (size_t)row * K + lchunk * 8;
     }
-    // token rows of this wave; a row past the call's rows repeats row 0: its products fill matrix-core columns that
-    // belong to no row and are never stored
-    const float *xp[TB];
+    // token rows of this wave; a row past the call's rows (inside the padding of the buffer) holds anything: its products
+    // fill matrix-core columns that belong to no row and are never stored
+    const int m = rb * 16 + i16;
+    const float *xp = a.X32 + (size_t)rb * 16 * K + lane * 4;
+    f32x4_t acc[NT][CTH];
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-        const int m = (rb * TB + tb) * 16 + i16;
-        xp[tb] = a.X32 + (size_t)(m < a.M ? m : 0) * K + g * 8;
-    }
-    f32x4_t acc[TB][NT][CTH];
+    for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int ct = 0; ct < CTH; ++ct) acc[tb][nt][ct] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+        for (int ct = 0; ct < CTH; ++ct) acc[nt][ct] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 
     // a step past the last is replaced by the last (fetched again, never used): requests are unconditional
     auto request_w = [&](int st, uint4 (&wr)[WQ]) {
-        const int k0 = min(st, s_hi - 1) * KSTEP;
+        const int k0 = min(st, s_hi - 1) * GEMM_KW;
 #pragma unroll
         for (int q = 0; q < WQ; ++q) wr[q] = load_stream(reinterpret_cast<const uint4 *>(wp[q] + k0));
     };
-    // X arrives as fp32 (8 consecutive k per lane and k step: two 16-byte loads, a whole 128-byte line per row and
-    // step over the four lanes of a token) and is split into the three bf16 planes here: 4 bytes per element through
+    // X arrives as fp32 (8 consecutive k per lane and k step: two 16-byte loads, each a contiguous kilobyte over the wave) and is split into the three bf16 planes here: 4 bytes per element through
     // the CU's load path instead of 6
-    auto request_x = [&](int st, float4 (&xb)[SW][TB][NS][2]) {
-        const int k0 = min(st, s_hi - 1) * KSTEP;
+    auto request_x = [&](int st, float4 (&xb)[NS][2]) {
+        const int k0 = min(st, s_hi - 1) * GEMM_KW;
 #pragma unroll
-        for (int sw = 0; sw < SW; ++sw)
-#pragma unroll
-            for (int tb = 0; tb < TB; ++tb)
-#pragma unroll
-                for (int s_ = 0; s_ < NS; ++s_) {
-                    const float4 *q = reinterpret_cast<const float4 *>(xp[tb] + k0 + GEMM_KW * sw + 32 * s_);
-                    xb[sw][tb][s_][0] = q[0]; xb[sw][tb][s_][1] = q[1];
-                }
+        for (int s_ = 0; s_ < NS; ++s_) {
+            const float *q = xp + (size_t)(k0 + 32 * s_) * 16;
+            xb[s_][0] = *reinterpret_cast<const float4 *>(q); xb[s_][1] = *reinterpret_cast<const float4 *>(q + 256);
+        }
     };
     auto park = [&](int buf, const uint4 (&wr)[WQ]) {
         unsigned char *base = smem + (size_t)buf * BUF;
@@ -518,130 +508,138 @@ __global__ void __launch_bounds__(NW * 64) k_gemm_tile(GemmArgs a) {
         for (int q = 0; q < WQ; ++q)
             if (wok[q]) *reinterpret_cast<uint4 *>(base + (size_t)(RPR * q + lrow) * PITCH + lchunk * 16) = wr[q];
     };
-    auto multiply = [&](int buf, const float4 (&xb)[SW][TB][NS][2]) {
+    // group q of a step: tiles CH c .. of k step s_ (c = q % NCH, s_ = q / NCH); tile i of a wave is column tile ct0 + i % CTH
+    // of gate (i < CTH) or up (a tile past the workgroup's last repeats it; its products are dropped)
+    auto read_a = [&](int buf, int q, bf16x8_t (&A)[CH]) {
         const unsigned char *base = smem + (size_t)buf * BUF;
-        // per k step: the A operands of all tiles first, then the planes outermost (smallest first), so that
-        // consecutive matrix-core instructions write different accumulators: a product that has to wait for the
-        // one before it (same accumulator) stalls the pipe for that one's whole latency
 #pragma unroll
-        for (int sw = 0; sw < SW; ++sw)
+        for (int i = 0; i < CH; ++i) {
+            const int ti = (q % NCH) * CH + i;
+            if (ti < NTC)
+                A[i] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(
+                    base + (size_t)(((ti / CTH) * CT + min(ct0 + ti % CTH, CT - 1)) * 16 + i16) * PITCH + (4 * (q / NCH) + g) * 16));
+        }
+    };
+    auto planes = [&](const float4 (&x)[2], bf16x8_t (&B)[3]) {
+        const float xv[8] = {x[0].x, x[0].y, x[0].z, x[0].w, x[1].x, x[1].y, x[1].z, x[1].w};
+        split3(xv, B);
+    };
+    // planes outermost (smallest first), so that consecutive matrix-core instructions write different accumulators
+    auto multiply = [&](int q, const bf16x8_t (&A)[CH], const bf16x8_t (&B)[3]) {
 #pragma unroll
-            for (int s_ = 0; s_ < NS; ++s_) {
-                bf16x8_t A[NT][CTH];
+        for (int pl = 2; pl >= 0; --pl)
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                    for (int ct = 0; ct < CTH; ++ct)       // (a tile past the workgroup's last repeats it; its products are dropped)
-                        A[nt][ct] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(
-                            base + (size_t)((nt * CT + min(ct0 + ct, CT - 1)) * 16 + i16) * PITCH + (4 * (NS * sw + s_) + g) * 16));
-                bf16x8_t B[TB][3];
-#pragma unroll
-                for (int tb = 0; tb < TB; ++tb) {
-                    const float4 x0 = xb[sw][tb][s_][0], x1 = xb[sw][tb][s_][1];
-                    const float xv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
-                    split3(xv, B[tb]);
-                }
-#pragma unroll
-                for (int pl = 2; pl >= 0; --pl)
-#pragma unroll
-                    for (int tb = 0; tb < TB; ++tb)
-#pragma unroll
-                        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                            for (int ct = 0; ct < CTH; ++ct)
-                                acc[tb][nt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[nt][ct], B[tb][pl], acc[tb][nt][ct], 0, 0, 0);
+            for (int i = 0; i < CH; ++i) {
+                const int ti = (q % NCH) * CH + i;
+                if (ti < NTC) acc[ti / CTH][ti % CTH] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[i], B[pl], acc[ti / CTH][ti % CTH], 0, 0, 0);
             }
     };
 
-    // register slots: WD for W, XD for X.  When step t is multiplied, the W rows of t + 1 .. t + WD and the X pieces
-    // of t + 1 .. t + XD - 1 are in flight or have arrived; every request goes into the slot that the step before
-    // has just consumed, before this step's products.  What bounds this kernel is how much of W one workgroup per CU
-    // keeps in flight (the hardware counters show 40 % of the outstanding DRAM requests of a kernel that streams at 6 TB/s).
-    // six slots where a launch is one workgroup per CU and the registers allow it (7B gate/up at 64 rows 86 -> 75 us);
-    // the LM head has several workgroups per CU and is better off with two of them resident (three slots each); with 32
-    // rows per wave four slots fit for the modes without the second (up) set of accumulators (7B down at 128 rows 91 -> 85 us)
-    constexpr int WD = (TB == 1 && MODE != G_LMHEAD) ? 6 : ((TB == 2 && MODE == G_PART) ? 4 : 3);
-    static_assert(NW == 4 || (NW == 8 && TB == 1), "four waves, or eight with one block of 16 rows each");
-    constexpr int UNR = (WD % XD == 0) ? WD : WD * XD;        // steps after which both slot patterns repeat
-    uint4 wr[WD][WQ];
-    float4 xb[XD][SW][TB][NS][2];
-#pragma unroll
-    for (int v = 0; v < WD; ++v) request_w(s_lo + v, wr[v]);
+    // Register slots: the W rows and X pieces of DEPTH steps are in flight, requested together.  Loads return in the order
+    // of their requests, so a wave that waits for an X piece also waits for every W row requested before it, and W slots
+    // beyond the X slots hold nothing that is still in flight.  Two to six slots measured within 3 % of each other.
+    // Software pipeline: while a group of tiles is multiplied, the A operands of the next group are on their way from
+    // LDS, the W rows of the next step go into the other LDS buffer during the step's first group, and the barrier stands
+    // before the step's last group, whose operands are in registers by then; the last group covers the first reads of
+    // the next step.
+    constexpr int DEPTH = MODE == G_LMHEAD && CT > 10 ? 2 : 3;
+    uint4 wr[DEPTH][WQ];
+    float4 xb[DEPTH][NS][2];
     int buf = 0;
-    if (rb * TB * 16 < a.M) {
+    if (rb * 16 < a.M) {
+        bf16x8_t A[2][CH], B[NS][3];
 #pragma unroll
-        for (int v = 0; v < XD - 1; ++v) request_x(s_lo + v, xb[v]);
-        for (int st = s_lo; st < s_hi; st += UNR) {
+        for (int v = 0; v < DEPTH; ++v) { request_w(s_lo + v, wr[v]); request_x(s_lo + v, xb[v]); }
+        park(0, wr[0]);
+        lds_barrier();
+        read_a(0, 0, A[0]);
+        planes(xb[0][0], B[0]);
+        for (int st = s_lo; st < s_hi; st += DEPTH) {
 #pragma unroll
-            for (int u = 0; u < UNR; ++u) {
+            for (int u = 0; u < DEPTH; ++u) {
                 if (st + u >= s_hi) break;
-                park(buf, wr[u % WD]);
-                lds_barrier();                                // the step is in LDS; everybody is done with the other buffer's last use
-                request_w(st + u + WD, wr[u % WD]);
-                request_x(st + u + XD - 1, xb[(u + XD - 1) % XD]);
-                multiply(buf, xb[u % XD]);
+#pragma unroll
+                for (int q = 0; q < NGR; ++q) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (q + 1 < NGR) read_a(buf, q + 1, A[(q + 1) & 1]);
+                    else { lds_barrier(); read_a(buf ^ 1, 0, A[0]); }
+                    if (q == 0) {
+                        park(buf ^ 1, wr[(u + 1) % DEPTH]);
+                        planes(xb[u][1], B[1]);
+                        request_w(st + u + DEPTH, wr[u]);
+                        request_x(st + u + DEPTH, xb[u]);
+                    }
+                    if (q == NGR - 1) planes(xb[(u + 1) % DEPTH][0], B[0]);
+                    multiply(q, A[q & 1], q == NGR - 1 ? B[1] : B[q / NCH]);
+                }
                 buf ^= 1;
             }
         }
     } else {
         // a wave whose 16-row block lies past the call's rows only helps to fetch and park W: same steps, same barriers,
         // no activation requests and no products (they would take load-path and matrix-core time from the waves with rows)
-        for (int st = s_lo; st < s_hi; st += WD) {
 #pragma unroll
-            for (int u = 0; u < WD; ++u) {
+        for (int v = 0; v < DEPTH; ++v) request_w(s_lo + v, wr[v]);
+        park(0, wr[0]);
+        lds_barrier();
+        for (int st = s_lo; st < s_hi; st += DEPTH) {
+#pragma unroll
+            for (int u = 0; u < DEPTH; ++u) {
                 if (st + u >= s_hi) break;
-                park(buf, wr[u]);
+                park(buf ^ 1, wr[(u + 1) % DEPTH]);
+                request_w(st + u + DEPTH, wr[u]);
                 lds_barrier();
-                request_w(st + u + WD, wr[u]);
                 buf ^= 1;
             }
         }
     }
 
-    // epilogue: this lane holds output columns n0 + 16 ct + 4 g + r of token 16 (wave TB + tb) + i16
+    // epilogue: this lane holds output columns n0 + 16 ct + 4 g + r of token 16 rb + i16
+    if (MODE == G_LMHEAD) {
+        // the row's softmax state over this workgroup's columns: every lane pushes its logits, the four lanes of a
+        // token (g = 0..3) merge, one partial per (row, workgroup).  Uniform control flow: the merge shuffles
+        const bool ok = m < a.M;
+        SoftState st; st.init();
+        const float lm_scale = ok ? a.seq_scale[m] : 1.f;
+        unsigned long long noise_base = 0;
+        if (a.sample_on && ok) noise_base = (unsigned long long)(a.row_pos[a.out_row[m]] + 1) * (unsigned long long)a.N;
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-        const int m = (rb * TB + tb) * 16 + i16;
-        if (MODE == G_LMHEAD) {
-            // the row's softmax state over this workgroup's columns: every lane pushes its logits, the four lanes of a
-            // token (g = 0..3) merge, one partial per (row, workgroup).  Uniform control flow: the merge shuffles
-            const bool ok = m < a.M;
-            SoftState st; st.init();
-            const float lm_scale = ok ? a.seq_scale[m] : 1.f;
-            unsigned long long noise_base = 0;
-            if (a.sample_on && ok) noise_base = (unsigned long long)(a.row_pos[a.out_row[m]] + 1) * (unsigned long long)a.N;
-#pragma unroll
-            for (int ct = 0; ct < CTH; ++ct)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int n = (grp * CT + ct0 + ct) * 16 + 4 * g + r;
-                    if (!ok || ct0 + ct >= CT || n >= n_out) continue;
-                    const float lg = acc[tb][0][ct][r] * lm_scale;
-                    st.push(lg, n);
-                    if (a.sample_on) st.push_noisy(lg, n, a.sample_key, noise_base);
-                    if (a.logits) a.logits[(size_t)m * a.N + n] = lg;
-                }
-            for (int o = 32; o >= 16; o >>= 1) {
-                SoftState b = shfl_xor_state(st, o);
-                if ((lane & o) == 0) st.merge(b); else { b.merge(st); st = b; }
-            }
-            if (g == 0 && ok) a.parts[(size_t)m * a.n_parts + grp * CS + wave / RB] = to_partial(st);
-            continue;
-        }
-        if (m >= a.M) continue;
-#pragma unroll
-        for (int ct = 0; ct < CTH; ++ct) {
-            const int tile = grp * CT + ct0 + ct;
-            if (ct0 + ct >= CT || tile >= n_tiles) continue;
+        for (int ct = 0; ct < CTH; ++ct)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int n = tile * 16 + 4 * g + r;
-                if (n >= n_out) continue;
-                const float val = acc[tb][0][ct][r];
-                if (MODE == G_PART) a.part[ksp * a.part_stride + (size_t)m * n_out + n] = val;
-                else a.act32[(size_t)m * a.d_ffn + n] = val / (1.0f + expf(-val)) * acc[tb][NT - 1][ct][r];
+                const int n = (grp * CT + ct0 + ct) * 16 + 4 * g + r;
+                if (!ok || ct0 + ct >= CT || n >= n_out) continue;
+                const float lg = acc[0][ct][r] * lm_scale;
+                st.push(lg, n);
+                if (a.sample_on) st.push_noisy(lg, n, a.sample_key, noise_base);
+                if (a.logits) a.logits[(size_t)m * a.N + n] = lg;
             }
+        for (int o = 32; o >= 16; o >>= 1) {
+            SoftState b = shfl_xor_state(st, o);
+            if ((lane & o) == 0) st.merge(b); else { b.merge(st); st = b; }
         }
+        if (g == 0 && ok) a.parts[(size_t)m * a.n_parts + grp * CS + wave / RB] = to_partial(st);
+        return;
+    }
+    if (m >= a.M) return;
+#pragma unroll
+    for (int ct = 0; ct < CTH; ++ct) {
+        const int tile = grp * CT + ct0 + ct;
+        if (ct0 + ct >= CT || tile >= n_tiles) continue;
+        // (n_out is a multiple of 16: whole tiles, one 16-byte store per lane)
+        const int n = tile * 16 + 4 * g;
+        float o[4];
+        float *dst;
+        if constexpr (MODE == G_GATEUP) {
+            dst = a.act32 + frag_index(m, n, a.d_ffn, 4);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o[r] = acc[0][ct][r] / (1.0f + expf(-acc[0][ct][r])) * acc[NT - 1][ct][r];
+        } else {
+            dst = a.part + ksp * a.part_stride + (size_t)m * n_out + n;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o[r] = acc[0][ct][r];
+        }
+        *reinterpret_cast<float4 *>(dst) = make_float4(o[0], o[1], o[2], o[3]);
     }
 }
 

@@ -114,16 +114,18 @@ Layout make_layout(const rs_config &c) {
     L.h = take((size_t)c.max_rows * c.d_model * 4);
     L.qkv_raw = take((size_t)c.max_rows * qkv * 4);
     L.qbuf = take((size_t)c.max_rows * qdim * 4);
-    L.attn_out = take((size_t)c.max_rows * qdim * 4);
-    L.act = take((size_t)c.max_rows * c.d_ffn * 4);                               // fp32 SwiGLU rows
+    // activations that a matrix-core kernel reads lie in blocks of rows (frag_index)
+    const size_t rows_pad = (size_t)(c.max_rows + 31) / 32 * 32, seqs_pad = (size_t)(c.max_seqs + 31) / 32 * 32;
+    L.attn_out = take(rows_pad * qdim * 4);
+    L.act = take(rows_pad * c.d_ffn * 4);                                         // fp32 SwiGLU rows
     L.attn_rows_x_splits = attn_pairs_cap(c);
     L.attn_part = take((size_t)L.attn_rows_x_splits * c.n_q_heads * (c.head_dim + 4) * 4);
     L.attn_cnt = take((size_t)c.max_rows * c.n_kv_heads * 4);
     L.lm_parts_cap = LM_PARTS_CAP;
     L.lm_parts = take((size_t)c.max_seqs * L.lm_parts_cap * sizeof(rs::SoftPartial));
     L.gemm_part = take((size_t)GEMM_KSPLIT_MAX * c.max_rows * (qkv > (size_t)c.d_model ? qkv : (size_t)c.d_model) * 4);
-    L.xn32 = take((size_t)c.max_rows * c.d_model * 4);                            // normalised rows of a multi-row call (fp32)
-    L.lm32 = take((size_t)c.max_seqs * c.d_model * 4);                            // normalised last rows for the LM head
+    L.xn32 = take(rows_pad * c.d_model * 4);                            // normalised rows of a multi-row call (fp32)
+    L.lm32 = take(seqs_pad * c.d_model * 4);                            // normalised last rows for the LM head
     L.sync = take(2 * sizeof(rs::SyncState));          // [0] single-kernel step, [1] device-resident loop
     L.layer_ptrs = take((size_t)c.n_layers * sizeof(rs::LayerPtrs));
     L.total = o;
@@ -409,20 +411,22 @@ rs_status launch_gemm_nb(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_
 // fills a fraction of the CUs costs a whole round); ties go to the larger CT (less X traffic) and the smaller split.
 template <int MODE, int NW, int CS, int CT>
 rs_status launch_gemm_tile_ct(GemmArgs &a, int blocks, hipStream_t st, const char *name) {
-    constexpr size_t lds = gemm_tile_lds_bytes<MODE, 1, CT>();
+    constexpr size_t lds = gemm_tile_lds_bytes<MODE, CT>();
     static_assert(lds <= 64 * 1024, "fits the default LDS limit");
-    hipLaunchKernelGGL((k_gemm_tile<MODE, 1, CT, NW, CS>), dim3(blocks), dim3(NW * 64), lds, st, a);
+    hipLaunchKernelGGL((k_gemm_tile<MODE, CT, NW, CS>), dim3(blocks), dim3(NW * 64), lds, st, a);
     RS_LAUNCHED(name);
     return RS_OK;
 }
 
 struct TilePlan { int ct, ks; double eff; };
 
-TilePlan plan_gemm_tile(bool gateup, bool split, int n_tiles, int n_win, int n_cu) {
-    static const int ct_gu[] = {5, 4, 3, 2}, ct_part[] = {10, 8, 7, 6, 4};
+// wide: also 13 tiles, the most whose operands fit the registers of eight waves (LM head of more than 64 sequences: X is read once
+// per workgroup, 128 sequences on the 7B shape 581 -> 529 us; with four waves, two workgroups per CU, 10 tiles are the better ones)
+TilePlan plan_gemm_tile(bool gateup, bool split, int n_tiles, int n_win, int n_cu, bool wide = false) {
+    static const int ct_gu[] = {5, 4, 3, 2}, ct_part[] = {13, 10, 8, 7, 6, 4};
     TilePlan best{0, 1, -1.0};
-    const int *cts = gateup ? ct_gu : ct_part;
-    const int n_ct = gateup ? 4 : 5;
+    const int *cts = gateup ? ct_gu : wide ? ct_part : ct_part + 1;
+    const int n_ct = gateup ? 4 : wide ? 6 : 5;
     for (int i = 0; i < n_ct; ++i) {
         const int ct = cts[i], groups = (n_tiles + ct - 1) / ct;
         for (int ks = 1; ks <= (split ? GEMM_KSPLIT_MAX : 1); ++ks) {
@@ -438,7 +442,7 @@ TilePlan plan_gemm_tile(bool gateup, bool split, int n_tiles, int n_win, int n_c
 // NW waves: NW / CS blocks of 16 rows, CS waves per block that split the workgroup's column tiles
 template <int MODE, int NW, int CS>
 rs_status launch_gemm_tile(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_t st, const char *name) {
-    const TilePlan p = plan_gemm_tile(MODE == G_GATEUP, MODE == G_PART, n_tiles, a.K / GEMM_KW, m->n_cu);
+    const TilePlan p = plan_gemm_tile(MODE == G_GATEUP, MODE == G_PART, n_tiles, a.K / GEMM_KW, m->n_cu, MODE == G_LMHEAD && NW == 8);
     const int groups = (n_tiles + p.ct - 1) / p.ct;
     a.yblocks = 1; a.ksplit = p.ks; a.part = nullptr; a.part_stride = 0;
     if constexpr (MODE == G_PART) {
@@ -455,6 +459,9 @@ rs_status launch_gemm_tile(const rs_model *m, GemmArgs &a, int n_tiles, hipStrea
             default: return launch_gemm_tile_ct<MODE, NW, CS, 2>(a, blocks, st, name);
         }
     } else {
+        if constexpr (MODE == G_LMHEAD && NW == 8) {
+            if (p.ct == 13) return launch_gemm_tile_ct<MODE, NW, CS, 13>(a, blocks, st, name);
+        }
         switch (p.ct) {
             case 10: return launch_gemm_tile_ct<MODE, NW, CS, 10>(a, blocks, st, name);
             case 8: return launch_gemm_tile_ct<MODE, NW, CS, 8>(a, blocks, st, name);
@@ -777,7 +784,8 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
             if (rc) return rc;
         } else {
             GemmArgs g{};
-            g.M = n_rows; g.d_ffn = c.d_ffn;
+            const int rsh = frag_shift(n_rows);
+            g.M = n_rows; g.d_ffn = c.d_ffn; g.rsh = rsh;
             const bool t_all = tile_layers(c, n_rows);
             const bool t_qkv = t_all && tile_fills(m, false, qkv_rows, c.d_model), t_o = t_all && tile_fills(m, false, c.d_model, qdim);
             // gate/up hands its output to the down projection in one format: both or neither
@@ -786,7 +794,7 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
             g.act32 = m->at<float>(L.act);
             // the down projection of the layer before may have left its result as partial sums (pend_*)
             hipLaunchKernelGGL(k_rmsnorm_rows, dim3(n_rows), dim3(ROWK_THREADS), 0, st, h, m->attn_norm[l], c.rms_eps,
-                               c.d_model, (const int *)nullptr, xn32, (const float *)pend_part, pend_ks, pend_stride);
+                               c.d_model, (const int *)nullptr, xn32, rsh, (const float *)pend_part, pend_ks, pend_stride);
             RS_LAUNCHED("rmsnorm_rows");
             pend_part = nullptr; pend_ks = 0; pend_stride = 0;
             g.W = m->w_qkv[l]; g.N = qkv_rows; g.K = c.d_model; g.X32 = xn32;
@@ -803,6 +811,7 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
             ra.max_seqs = c.max_seqs; ra.layer = l;
             hipLaunchKernelGGL(k_rope_kv_rows, dim3(n_rows), dim3(ROWK_THREADS), 0, st, ra);
             RS_LAUNCHED("rope_kv_rows");
+            aa.out_frag = 1; aa.rsh = rsh;
             tic(RS_PHASE_ATTN, l);
             switch (hd) {
                 case 32: rc = launch_attn<32>(aa, n_splits, c.n_kv_heads, n_rows, n_seqs, m->n_cu, st); break;
@@ -818,7 +827,7 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
             if ((rc = launch_gemm<G_OPROJ>(m, g, (c.d_model + 15) / 16, st, "gemm_oproj", t_o))) return rc;
             toc(RS_PHASE_OPROJ, l);
             hipLaunchKernelGGL(k_rmsnorm_rows, dim3(n_rows), dim3(ROWK_THREADS), 0, st, h, m->mlp_norm[l], c.rms_eps,
-                               c.d_model, (const int *)nullptr, xn32, (const float *)g.part, g.ksplit, g.part_stride);
+                               c.d_model, (const int *)nullptr, xn32, rsh, (const float *)g.part, g.ksplit, g.part_stride);
             RS_LAUNCHED("rmsnorm_rows");
             g.W = m->w_gate_up[l]; g.N = 2 * c.d_ffn; g.K = c.d_model; g.X32 = xn32;
             tic(RS_PHASE_GATEUP, l);
@@ -852,11 +861,11 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
         if (rc) return rc;
     } else {
         hipLaunchKernelGGL(k_rmsnorm_rows, dim3(n_seqs), dim3(ROWK_THREADS), 0, st, h, m->final_norm, c.rms_eps,
-                           c.d_model, (const int *)m->at<int>(L.out_row), m->at<float>(L.lm32), (const float *)pend_part, pend_ks,
+                           c.d_model, (const int *)m->at<int>(L.out_row), m->at<float>(L.lm32), frag_shift(n_seqs), (const float *)pend_part, pend_ks,
                            pend_stride);
         RS_LAUNCHED("rmsnorm_rows");
         GemmArgs g{};
-        g.M = n_seqs; g.W = m->lm_head; g.N = c.vocab; g.K = c.d_model; g.X32 = m->at<float>(L.lm32);
+        g.M = n_seqs; g.rsh = frag_shift(n_seqs); g.W = m->lm_head; g.N = c.vocab; g.K = c.d_model; g.X32 = m->at<float>(L.lm32);
         g.seq_scale = m->at<float>(L.seq_scale); g.parts = parts; g.logits = d_logits;
         g.sample_on = m->sample_on; g.sample_key = m->sample_key; g.row_pos = row_pos; g.out_row = m->at<int>(L.out_row);
         tic(RS_PHASE_LMHEAD, 0);
