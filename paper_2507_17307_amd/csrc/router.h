@@ -7,55 +7,94 @@
 
 namespace rs {
 
+// One softmax state from the states of all threads of a workgroup of NW waves; valid in thread 0 only.  In place of a tree of
+// pairwise merges (two exponentials and eight shuffles at each of its levels): the workgroup's maximum, one rescale of each
+// thread's sums to it, then plain sums.  The largest logit of a state is its m; the sampled entry takes the same route.
+// sh: NW SoftPartial of LDS, free when the workgroup enters.
+template <int NW>
+__device__ __forceinline__ SoftState block_merge(const SoftState &t, SoftPartial *sh, bool sample) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const float mw = wave_max(t.m);
+    const int iw = wave_min_i32(t.m == mw ? t.idx : 0x7fffffff), bw = __any(t.bad);
+    float gw = -INFINITY; int giw = 0x7fffffff;
+    if (sample) { gw = wave_max(t.gbest); giw = wave_min_i32(t.gbest == gw ? t.gidx : 0x7fffffff); }
+    if (lane == 0) { sh[wave].m = mw; sh[wave].idx = iw; sh[wave].bad = bw; sh[wave].gbest = gw; sh[wave].gidx = giw; }
+    __syncthreads();
+    SoftState o; o.init();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const float m = sh[w].m, gb = sh[w].gbest;
+        if (m > o.m || (m == o.m && sh[w].idx < o.idx)) o.idx = sh[w].idx;
+        o.m = fmaxf(o.m, m);
+        o.bad |= sh[w].bad;
+        if (gb > o.gbest || (gb == o.gbest && sh[w].gidx < o.gidx)) { o.gbest = gb; o.gidx = sh[w].gidx; }
+    }
+    const float d = t.m - o.m, e = t.z > 0.f ? expf(d) : 0.f;
+    // (a factor of zero takes no part: d * z may overflow where all of a thread's logits are masked with a huge negative value)
+    const float z = wave_sum(t.z * e), s = wave_sum(e > 0.f ? e * (t.s + d * t.z) : 0.f);
+    if (lane == 0) { sh[wave].z = z; sh[wave].s = s; }
+    __syncthreads();
+    o.z = sh[0].z; o.s = sh[0].s;
+#pragma unroll
+    for (int w = 1; w < NW; ++w) { o.z += sh[w].z; o.s += sh[w].s; }
+    o.best = o.m;
+    return o;
+}
+
+// State of the logits x[i] * sc of one thread: the values i = first, first + step, ... (vocab % 4 == 0 and x 16-byte aligned:
+// in groups of four).  Four values at a time: one look at the maximum, then four exponentials that do not depend on each other.
+__device__ __forceinline__ SoftState row_state(const float *__restrict__ x, int vocab, float sc, int first, int step) {
+    SoftState st; st.init();
+    auto four = [&](const float (&v)[4], const int (&i)[4], const bool (&ok)[4]) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (!ok[k]) continue;
+            if (!(fabsf(v[k]) <= 3.0e38f)) st.bad = 1;                // NaN or +-Inf: the record says so, whatever the sums hold
+            if (v[k] > st.best) { st.best = v[k]; st.idx = i[k]; }    // (a thread's indices grow)
+        }
+        if (st.best > st.m) {
+            if (st.z > 0.f) { const float d = st.m - st.best, e = expf(d); st.s = e > 0.f ? e * (st.s + d * st.z) : 0.f; st.z *= e; }
+            st.m = st.best;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float d = ok[k] ? v[k] - st.m : 0.f, e = ok[k] ? expf(d) : 0.f;
+            st.z += e; st.s = fmaf(e > 0.f ? d : 0.f, e, st.s);
+        }
+    };
+    if ((vocab & 3) == 0) {
+        const float4 *x4 = reinterpret_cast<const float4 *>(x);
+#pragma unroll 2
+        for (int i = first; i < (vocab >> 2); i += step) {
+            const float4 q = x4[i];
+            four({q.x * sc, q.y * sc, q.z * sc, q.w * sc}, {4 * i, 4 * i + 1, 4 * i + 2, 4 * i + 3}, {true, true, true, true});
+        }
+    } else {
+        for (int i = first; i < vocab; i += 4 * step) {
+            const int j[4] = {i, i + step, i + 2 * step, i + 3 * step};
+            const bool ok[4] = {true, j[1] < vocab, j[2] < vocab, j[3] < vocab};
+            four({x[j[0]] * sc, x[ok[1] ? j[1] : i] * sc, x[ok[2] ? j[2] : i] * sc, x[ok[3] ? j[3] : i] * sc}, j, ok);
+        }
+    }
+    return st;
+}
+
 // Partial states of caller-provided fp32 logits: grid (n_parts, n_rows), block 256.
 // Each workgroup strides over its row; partial p of row r lands in parts[r*n_parts + p].
 __global__ void __launch_bounds__(256)
 k_route_partials(const float *__restrict__ logits, int vocab, const float *__restrict__ scale,
                  SoftPartial *__restrict__ parts) {
-    const int row = blockIdx.y, n_parts = gridDim.x;
-    const float *x = logits + (size_t)row * vocab;
-    const float sc = scale ? scale[row] : 1.f;
-    SoftState st; st.init();
-    const int tid = threadIdx.x, stride = n_parts * 256;
-    if ((vocab & 3) == 0) {
-        const float4 *x4 = reinterpret_cast<const float4 *>(x);
-        for (int i = blockIdx.x * 256 + tid; i < (vocab >> 2); i += stride) {
-            float4 v = x4[i];
-            st.push(v.x * sc, 4 * i); st.push(v.y * sc, 4 * i + 1);
-            st.push(v.z * sc, 4 * i + 2); st.push(v.w * sc, 4 * i + 3);
-        }
-    } else {
-        for (int i = blockIdx.x * 256 + tid; i < vocab; i += stride) st.push(x[i] * sc, i);
-    }
-    wave_merge_state(st);
     __shared__ SoftPartial sh[4];
-    if ((tid & 63) == 0) sh[tid >> 6] = to_partial(st);
-    __syncthreads();
-    if (tid == 0) {
-        SoftState a = from_partial(sh[0]);
-        for (int w = 1; w < 4; ++w) a.merge(from_partial(sh[w]));
-        parts[(size_t)row * n_parts + blockIdx.x] = to_partial(a);
-    }
+    const int row = blockIdx.y, n_parts = gridDim.x;
+    const SoftState st = row_state(logits + (size_t)row * vocab, vocab, scale ? scale[row] : 1.f, blockIdx.x * 256 + threadIdx.x, n_parts * 256);
+    const SoftState a = block_merge<4>(st, sh, false);
+    if (threadIdx.x == 0) parts[(size_t)row * n_parts + blockIdx.x] = to_partial(a);
 }
 
-// Final merge and routing decision for one row by one 256-thread workgroup.
-// row_bad: optional per-row flag (nonzero = the row's inputs were out of range); sh: 4 SoftPartial of LDS.
-// sample: the record's token is the arg max of logit + Gumbel noise (a draw from the distribution) instead of the arg max
-__device__ __forceinline__ void route_merge_row(const SoftPartial *__restrict__ parts, int n_parts, int vocab, float tau,
-                                                int active, const int *__restrict__ row_bad, rs_route_out *__restrict__ out,
-                                                int row, SoftPartial *sh, int sample = 0) {
-    const int tid = threadIdx.x;
-    SoftState st; st.init();
-    for (int p = tid; p < n_parts; p += 256) st.merge(from_partial(parts[(size_t)row * n_parts + p]));
-    wave_merge_state(st);
-    if ((tid & 63) == 0) sh[tid >> 6] = to_partial(st);
-    __syncthreads();
-    if (tid != 0) return;
-    st = from_partial(sh[0]);
-    for (int w = 1; w < 4; ++w) st.merge(from_partial(sh[w]));
+// The record of a row from its merged state (one thread).
+__device__ __forceinline__ rs_route_out route_record(const SoftState &st, int vocab, float tau, int active, bool bad, int sample) {
     rs_route_out r;
     uint32_t flags = 0;
-    const bool bad = row_bad && row_bad[row];
     if (bad || st.bad || !(st.z > 0.f)) {
         const float qnan = __uint_as_float(0x7fc00000u);
         flags = (bad ? RS_FLAG_BADARG : RS_FLAG_NONFINITE) | RS_FLAG_HI | RS_FLAG_NEXT_LLM;
@@ -72,7 +111,44 @@ __device__ __forceinline__ void route_merge_row(const SoftPartial *__restrict__ 
         r.token = sample ? st.gidx : st.idx; r.h_nats = h; r.h_norm = hn; r.max_logit = st.m; r.log_z = st.m + lz;
     }
     r.flags = flags;
-    out[row] = r;
+    return r;
+}
+
+// Final merge and routing decision for one row by one 256-thread workgroup.
+// row_bad: optional per-row flag (nonzero = the row's inputs were out of range); sh: 4 SoftPartial of LDS.
+// sample: the record's token is the arg max of logit + Gumbel noise (a draw from the distribution) instead of the arg max
+__device__ __forceinline__ void route_merge_row(const SoftPartial *__restrict__ parts, int n_parts, int vocab, float tau,
+                                                int active, const int *__restrict__ row_bad, rs_route_out *__restrict__ out,
+                                                int row, SoftPartial *sh, int sample = 0) {
+    const int tid = threadIdx.x;
+    const SoftPartial *pr = parts + (size_t)row * n_parts;
+    const bool bad = row_bad && row_bad[row];
+    // a thread's partials, four requested at a time: their common maximum first, so that the sums wait for one exponential
+    // each instead of a chain of merges
+    SoftState st; st.init();
+    for (int p0 = tid; p0 < n_parts; p0 += 1024) {
+        SoftPartial q[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) q[k] = pr[min(p0 + 256 * k, n_parts - 1)];
+        float m = st.m;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (p0 + 256 * k >= n_parts) q[k].z = 0.f;
+            else {
+                st.bad |= q[k].bad;
+                if (q[k].best > st.best || (q[k].best == st.best && q[k].idx < st.idx)) { st.best = q[k].best; st.idx = q[k].idx; }
+                if (q[k].gbest > st.gbest || (q[k].gbest == st.gbest && q[k].gidx < st.gidx)) { st.gbest = q[k].gbest; st.gidx = q[k].gidx; }
+            }
+            if (q[k].z > 0.f) m = fmaxf(m, q[k].m);
+        }
+        if (st.z > 0.f && m > st.m) { const float d = st.m - m, e = expf(d); st.s = e > 0.f ? e * (st.s + d * st.z) : 0.f; st.z *= e; }
+        st.m = m;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (q[k].z > 0.f) { const float d = q[k].m - m, e = expf(d); st.s += e > 0.f ? e * (q[k].s + d * q[k].z) : 0.f; st.z = fmaf(q[k].z, e, st.z); }
+    }
+    const SoftState o = block_merge<4>(st, sh, sample != 0);
+    if (tid == 0) out[row] = route_record(o, vocab, tau, active, bad, sample);
 }
 
 // grid n_rows, block 256
@@ -81,6 +157,17 @@ k_route_merge(const SoftPartial *__restrict__ parts, int n_parts, int vocab, flo
               const int *__restrict__ row_bad, rs_route_out *__restrict__ out, int sample) {
     __shared__ SoftPartial sh[4];
     route_merge_row(parts, n_parts, vocab, tau, active, row_bad, out, blockIdx.x, sh, sample);
+}
+
+// The whole of rs_route for a short row: grid n_rows, block 1024, no partial states in memory and no second launch.
+__global__ void __launch_bounds__(1024)
+k_route_row(const float *__restrict__ logits, int vocab, const float *__restrict__ scale, float tau, int active,
+            rs_route_out *__restrict__ out) {
+    __shared__ SoftPartial sh[16];
+    const int row = blockIdx.x;
+    const SoftState st = row_state(logits + (size_t)row * vocab, vocab, scale ? scale[row] : 1.f, threadIdx.x, 1024);
+    const SoftState o = block_merge<16>(st, sh, false);
+    if (threadIdx.x == 0) out[row] = route_record(o, vocab, tau, active, false, 0);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -1184,6 +1184,29 @@ static int route_parts(int vocab) {
     return p > 128 ? 128 : p;
 }
 
+// A short row takes one workgroup from its logits to its record (64 rows of 32768: 11.1 us a call against 14.2; one row of
+// 50257: 14.8 against 14.2); longer ones leave partial states, at most route_parts of them per row, that a second kernel merges, and
+// with many rows fewer (ROUTE_WGS workgroups in all: a workgroup's merge costs as much as several groups of logits; 64 / 128 rows of
+// 152064: 45.8 / 79.4 us with 128 workgroups each and pairwise merges, now 15.5 / 22.9; 1024 or 4096 workgroups the same or slower).
+constexpr int ROUTE_ROW_VOCAB = 32768, ROUTE_WGS = 2048;
+static rs_status launch_route(const float *d_logits, int n, int vocab, const float *d_scale, float tau, int active,
+                              rs_route_out *d_out, rs::SoftPartial *scratch, hipStream_t st) {
+    if (vocab <= ROUTE_ROW_VOCAB) {
+        hipLaunchKernelGGL(rs::k_route_row, dim3(n), dim3(1024), 0, st, d_logits, vocab, d_scale, tau, active, d_out);
+        RS_LAUNCHED("route_row");
+        return RS_OK;
+    }
+    int parts = route_parts(vocab);
+    if (parts > (ROUTE_WGS + n - 1) / n) parts = (ROUTE_WGS + n - 1) / n;
+    hipLaunchKernelGGL(rs::k_route_partials, dim3(parts, n), dim3(256), 0, st, d_logits, vocab, d_scale, scratch);
+    RS_LAUNCHED("route_partials");
+    // every partial the merge reads is written by the first kernel of the same call: nothing to clear
+    hipLaunchKernelGGL(rs::k_route_merge, dim3(n), dim3(256), 0, st, (const rs::SoftPartial *)scratch, parts, vocab, tau,
+                       active, (const int *)nullptr, d_out, 0);
+    RS_LAUNCHED("route_merge");
+    return RS_OK;
+}
+
 size_t rs_route_scratch_bytes(int32_t n, int32_t vocab) {
     if (n < 1 || vocab < 2) { fail(RS_EINVAL, "need n >= 1 and vocab >= 2"); return 0; }
     return align_up((size_t)n * route_parts(vocab) * sizeof(rs::SoftPartial));
@@ -1198,15 +1221,7 @@ rs_status rs_route(const float *d_logits, int32_t n, int32_t vocab, const float 
     if ((uintptr_t)d_scratch % 16 || (uintptr_t)d_logits % 16) return fail(RS_EINVAL, "logits and scratch must be 16-byte aligned");
     const size_t need = rs_route_scratch_bytes(n, vocab);
     if (scratch_bytes < need) return fail(RS_EINVAL, "scratch of %zu bytes is smaller than the %zu needed", scratch_bytes, need);
-    const int parts = route_parts(vocab);
-    hipStream_t st = (hipStream_t)stream;
-    hipLaunchKernelGGL(rs::k_route_partials, dim3(parts, n), dim3(256), 0, st, d_logits, vocab, d_logit_scale,
-                       (rs::SoftPartial *)d_scratch);
-    RS_LAUNCHED("route_partials");
-    hipLaunchKernelGGL(rs::k_route_merge, dim3(n), dim3(256), 0, st, (const rs::SoftPartial *)d_scratch, parts, vocab, tau,
-                       active, (const int *)nullptr, d_out, 0);
-    RS_LAUNCHED("route_merge");
-    return RS_OK;
+    return launch_route(d_logits, n, vocab, d_logit_scale, tau, active, d_out, (rs::SoftPartial *)d_scratch, (hipStream_t)stream);
 }
 
 rs_status rs_route_plus(rs_model *m, const float *d_hidden, int32_t n_seqs, const rs_router_weights *w, int32_t active,
@@ -1291,13 +1306,5 @@ extern "C" rs_status rs_route_static(const float *d_logits, int32_t n, int32_t v
         return fail(RS_ECAPACITY, "%d rows of %d partial states exceed the static scratch array", n, parts);
     void *ptr = nullptr;
     if (rs_status rc = route_static_scratch(&ptr)) return rc;
-    hipStream_t st = (hipStream_t)stream;
-    // every partial the merge reads is written by the first kernel of the same call: nothing to clear
-    hipLaunchKernelGGL(rs::k_route_partials, dim3(parts, n), dim3(256), 0, st, d_logits, vocab, d_logit_scale,
-                       (rs::SoftPartial *)ptr);
-    RS_LAUNCHED("route_partials");
-    hipLaunchKernelGGL(rs::k_route_merge, dim3(n), dim3(256), 0, st, (const rs::SoftPartial *)ptr, parts, vocab, tau,
-                       active, (const int *)nullptr, d_out, 0);
-    RS_LAUNCHED("route_merge");
-    return RS_OK;
+    return launch_route(d_logits, n, vocab, d_logit_scale, tau, active, d_out, (rs::SoftPartial *)ptr, (hipStream_t)stream);
 }
