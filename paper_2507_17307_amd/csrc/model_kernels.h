@@ -7,6 +7,8 @@
 #include "device_utils.h"
 #include "router.h"
 
+#include <limits.h>
+
 namespace rs {
 
 // ------------------------------------------------------------------------------------------------
@@ -48,29 +50,37 @@ __device__ __forceinline__ void prepare_row(const PrepArgs &a, int r, int *sh) {
         s_slot[i] = a.seq_slot[i]; s_pos[i] = a.pos0[i]; s_scale[i] = a.scale ? a.scale[i] : 1.f;
     }
     __syncthreads();
+    // Every check is one comparison per thread (one thread walking the table of 128 sequences took 18 us):
+    // first the span table, then the row's own sequence.  sh[0]: this row's sequence; sh[1]: longest context of the call
+    int lo = r, hi = r + 1, bad = 0;
+    if (tid == 0) { sh[0] = a.span_off == nullptr ? r : INT_MAX; sh[1] = 1; }
+    __syncthreads();
+    if (tid < ns) {
+        int len = 1;
+        if (a.span_off != nullptr) {
+            const int o0 = s_off[tid], o1 = s_off[tid + 1];
+            if (o1 <= o0 || o0 < 0 || o1 > a.n_rows) bad = 1;            // empty or malformed span
+            if (r >= o0 && r < o1) atomicMin(&sh[0], tid);
+            len = o1 - o0;
+        }
+        if (r == 0 && len > 0 && len <= a.n_rows && s_pos[tid] >= 0 && s_pos[tid] <= a.max_ctx - len) atomicMax(&sh[1], s_pos[tid] + len);
+    }
+    if (tid == 0 && a.span_off != nullptr && (s_off[0] != 0 || s_off[ns] != a.n_rows)) bad = 1;
+    bad = __syncthreads_or(bad);
+    const bool table_bad = bad;
+    int b = sh[0];
+    const int top = sh[1];
+    if (b == INT_MAX) { b = -1; bad = 1; lo = 0; hi = 0; }
+    else if (a.span_off != nullptr) { lo = s_off[b]; hi = s_off[b + 1]; }
+    int bad2 = 0;
+    if (!bad) {
+        const int slot = s_slot[b], p0 = s_pos[b];
+        if (slot < 0 || slot >= a.max_seqs || p0 < 0 || p0 > a.max_ctx - (hi - lo)) bad2 = 1;
+        if (tid < ns && tid != b && s_slot[tid] == slot) bad2 = 1;       // slots must be distinct
+        if (tid >= lo && tid < hi && (s_tok[tid] < 0 || s_tok[tid] >= a.vocab)) bad2 = 1;
+    }
+    bad |= __syncthreads_or(bad2);
     if (tid == 0) {
-        int b = -1, lo = 0, hi = 0, bad = 0;
-        if (a.span_off == nullptr) { b = r; lo = r; hi = r + 1; }
-        else {
-            if (s_off[0] != 0 || s_off[ns] != a.n_rows) bad = 1;
-            for (int i = 0; i < ns; ++i) {
-                const int o0 = s_off[i], o1 = s_off[i + 1];
-                if (o1 <= o0 || o0 < 0 || o1 > a.n_rows) bad = 1;        // empty or malformed span
-                if (r >= o0 && r < o1 && b < 0) { b = i; lo = o0; hi = o1; }
-            }
-            if (b < 0) bad = 1;
-        }
-        if (!bad) {
-            const int slot = s_slot[b], p0 = s_pos[b];
-            if (slot < 0 || slot >= a.max_seqs || p0 < 0 || p0 > a.max_ctx - (hi - lo)) bad = 1;
-            for (int i = 0; i < ns && !bad; ++i)                         // slots must be distinct
-                if (i != b && s_slot[i] == slot) bad = 1;
-            for (int i = lo; i < hi && !bad; ++i) {
-                const int t = s_tok[i];
-                if (t < 0 || t >= a.vocab) bad = 1;
-            }
-        }
-        sh[0] = b; sh[1] = lo; sh[2] = hi; sh[3] = bad;
         a.row_bad[r] = bad;
         a.row_slot[r] = bad ? 0 : s_slot[b];
         a.row_pos[r] = bad ? 0 : s_pos[b] + (r - lo);
@@ -79,24 +89,20 @@ __device__ __forceinline__ void prepare_row(const PrepArgs &a, int r, int *sh) {
             a.seq_scale[b] = s_scale[b];
             a.seq_info[b] = bad ? make_int4(-1, 0, 0, 0) : make_int4(lo, hi, s_slot[b], s_pos[b]);
         }
-        if (r == 0 && a.ctx_top) {
-            int top = 1;
-            for (int i = 0; i < ns; ++i) {
-                const int len = a.span_off == nullptr ? 1 : s_off[i + 1] - s_off[i];
-                if (len > 0 && s_pos[i] >= 0 && s_pos[i] <= a.max_ctx - len) top = max(top, s_pos[i] + len);
-            }
-            *a.ctx_top = top;
-        }
-        // a malformed offset table can leave sequences without any row: flag them all
-        if (bad && a.span_off != nullptr && r == 0)
+        if (r == 0 && a.ctx_top) *a.ctx_top = top;
+        // a malformed offset table can leave sequences without any row: flag them all (and only then: the rows of the other
+        // sequences write these entries too)
+        if (table_bad && r == 0)
             for (int i = 0; i < ns; ++i) { a.seq_bad[i] = 1; a.out_row[i] = 0; a.seq_scale[i] = 1.f; a.seq_info[i] = make_int4(-1, 0, 0, 0); }
     }
-    __syncthreads();
-    const int bad = sh[3];
-    float *h = a.h + (size_t)r * a.d_model;
-    if (bad) { for (int i = tid; i < a.d_model; i += 256) h[i] = 0.f; return; }
-    const uint16_t *e = a.embed + (size_t)s_tok[r] * a.d_model;
-    for (int i = tid; i < a.d_model; i += 256) h[i] = bf16_to_f32(e[i]);
+    // (d_model is a multiple of 128: four values per thread and round)
+    float4 *h = reinterpret_cast<float4 *>(a.h + (size_t)r * a.d_model);
+    if (bad) { for (int i = tid; i < (a.d_model >> 2); i += 256) h[i] = make_float4(0.f, 0.f, 0.f, 0.f); return; }
+    const uint2 *e = reinterpret_cast<const uint2 *>(a.embed + (size_t)s_tok[r] * a.d_model);
+    for (int i = tid; i < (a.d_model >> 2); i += 256) {
+        const uint2 v = e[i];
+        h[i] = make_float4(bf16_lo(v.x), bf16_hi(v.x), bf16_lo(v.y), bf16_hi(v.y));
+    }
 }
 
 __global__ void __launch_bounds__(256) k_prepare(PrepArgs a) {
