@@ -174,10 +174,13 @@ k_route_row(const float *__restrict__ logits, int vocab, const float *__restrict
 // Router of R-Stitch+ (Section "Architecture and Overhead of Router"; Algorithm 1, R-Stitch+ branch):
 // six residual feed-forward blocks x <- x + W2 gelu(W1 x + b1) + b2 with a bottleneck of r channels,
 // a LayerNorm, a linear layer with two outputs (0 = stay on the small model, 1 = switch to the large
-// one).  One workgroup of 256 threads per sequence; x (fp32, d values) lives in LDS; weights are bf16,
+// one).  One workgroup of ROUTER_THREADS threads per sequence; x (fp32, d values) lives in LDS; weights are bf16,
 // accumulation fp32.  The record of the sequence is updated in place: a small-model step above tau
 // whose router output prefers "stay" keeps its token and stays (RS_FLAG_ROUTER_STAY); every other
 // record is left as the entropy rule made it.
+// What bounds it: twelve dependent phases, each a round trip for its weights.  The weights do not depend on x, so each phase
+// requests those of the next one before it starts on its own (one call, d 1536, r 8: 25.4 -> 10.1 us; 5120, 8: 65 -> 22).
+// With a wide bottleneck it is the megabytes that one CU draws (5120, 64: 562 -> 191 us for 7.9 MB).
 // ------------------------------------------------------------------------------------------------
 constexpr int ROUTER_BLOCKS = 6;
 constexpr int ROUTER_RMAX = 64;
@@ -194,72 +197,116 @@ struct RouterPlusArgs {
     float *logits;                             // [n_seqs, 2] or null
 };
 
-__device__ __forceinline__ float block_sum(float v, float *sh4) {        // 256 threads; sh4: 4 floats of LDS
-    v = wave_sum(v);
-    __syncthreads();                                                      // sh4 may still be read from the last call
-    if ((threadIdx.x & 63) == 0) sh4[threadIdx.x >> 6] = v;
+constexpr int ROUTER_THREADS = 512, ROUTER_WAVES = ROUTER_THREADS / 64;
+
+__device__ __forceinline__ float2 block_sum2(float v, float w, float2 *sh) {        // sh: ROUTER_WAVES float2 of LDS
+    v = wave_sum(v); w = wave_sum(w);
+    __syncthreads();                                                      // sh may still be read from the last call
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = make_float2(v, w);
     __syncthreads();
-    return sh4[0] + sh4[1] + sh4[2] + sh4[3];
+    float2 t = sh[0];
+#pragma unroll
+    for (int i = 1; i < ROUTER_WAVES; ++i) { t.x += sh[i].x; t.y += sh[i].y; }
+    return t;
 }
 
-// dynamic LDS: d floats
-__global__ void __launch_bounds__(256) k_router_plus(RouterPlusArgs a) {
+__device__ __forceinline__ float dot8f(const uint4 &w, const float4 &xa, const float4 &xb, float acc) {
+    acc = fmaf(bf16_lo(w.x), xa.x, acc); acc = fmaf(bf16_hi(w.x), xa.y, acc); acc = fmaf(bf16_lo(w.y), xa.z, acc); acc = fmaf(bf16_hi(w.y), xa.w, acc);
+    acc = fmaf(bf16_lo(w.z), xb.x, acc); acc = fmaf(bf16_hi(w.z), xb.y, acc); acc = fmaf(bf16_lo(w.w), xb.z, acc); return fmaf(bf16_hi(w.w), xb.w, acc);
+}
+
+// NU: pieces of a row of W1 per lane (8 channels each) and output channels per thread, at least d / 512.  dynamic LDS: d floats
+template <int NU>
+__global__ void __launch_bounds__(ROUTER_THREADS) k_router_plus(RouterPlusArgs a) {
+    constexpr bool AHEAD = NU <= 10;
     extern __shared__ __align__(16) unsigned char smem[];
     float *x = reinterpret_cast<float *>(smem);
-    __shared__ float t_sh[ROUTER_RMAX];
-    __shared__ float red[4];
+    __shared__ __align__(16) float t_sh[ROUTER_RMAX];
+    __shared__ float2 red[ROUTER_WAVES];
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int d = a.d, r = a.r;
+    const int d = a.d, r = a.r, n_ch = d >> 3;
     const float *src = a.hidden + (size_t)(a.gather ? a.gather[b] : b) * a.ld_hidden;
-    for (int i = tid; i < d; i += 256) x[i] = src[i];
+    // (vector types: arrays of structs that lambdas capture are left in scratch memory)
+    auto load_w1 = [&](int blk, int row, u32x4_t (&w)[NU]) {
+        const u32x4_t *wp = reinterpret_cast<const u32x4_t *>(a.w1[blk] + (size_t)row * d);
+#pragma unroll
+        for (int u = 0; u < NU; ++u) w[u] = wp[min(lane + 64 * u, n_ch - 1)];
+    };
+    u32x4_t w1[NU];
+    float xin[NU];
+#pragma unroll
+    for (int k = 0; k < NU; ++k) xin[k] = src[min(tid + ROUTER_THREADS * k, d - 1)];
+    load_w1(0, wave, w1);
+#pragma unroll
+    for (int k = 0; k < NU; ++k)
+        if (tid + ROUTER_THREADS * k < d) x[tid + ROUTER_THREADS * k] = xin[k];
     __syncthreads();
     for (int blk = 0; blk < ROUTER_BLOCKS; ++blk) {
-        // t = gelu(W1 x + b1): wave w takes the rows w, w + 4, ...; lanes stride over d in chunks of 8
-        for (int row = wave; row < r; row += 4) {
-            const uint4 *wp = reinterpret_cast<const uint4 *>(a.w1[blk] + (size_t)row * d);
+        // the first 8 of the r values of this thread's rows of W2, and their biases (widths above 5120 have no registers for them)
+        u32x4_t w2[NU];
+        float b2[NU];
+#pragma unroll
+        for (int k = 0; k < NU; ++k) {
+            const int i = min(tid + ROUTER_THREADS * k, d - 1);
+            if (AHEAD) w2[k] = *reinterpret_cast<const u32x4_t *>(a.w2[blk] + (size_t)i * r);
+            if (AHEAD) b2[k] = bf16_to_f32(a.b2[blk][i]);
+        }
+        // t = gelu(W1 x + b1): wave w takes the rows w, w + 8, ... (r is a multiple of 8); lanes stride over d in pieces of 8
+        for (int row = wave; row < r; row += ROUTER_WAVES) {
+            if (row != wave) load_w1(blk, row, w1);
+            const float b1 = bf16_to_f32(a.b1[blk][row]);
             float acc = 0.f;
-            for (int c = lane; c < (d >> 3); c += 64) {
-                const uint4 w = wp[c];
-                const float4 xa = *reinterpret_cast<const float4 *>(x + 8 * c), xb = *reinterpret_cast<const float4 *>(x + 8 * c + 4);
-                acc = fmaf(bf16_lo(w.x), xa.x, acc); acc = fmaf(bf16_hi(w.x), xa.y, acc); acc = fmaf(bf16_lo(w.y), xa.z, acc); acc = fmaf(bf16_hi(w.y), xa.w, acc);
-                acc = fmaf(bf16_lo(w.z), xb.x, acc); acc = fmaf(bf16_hi(w.z), xb.y, acc); acc = fmaf(bf16_lo(w.w), xb.z, acc); acc = fmaf(bf16_hi(w.w), xb.w, acc);
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+                const int c = lane + 64 * u;
+                if (c < n_ch) acc = dot8f(make_uint4(w1[u].x, w1[u].y, w1[u].z, w1[u].w), *reinterpret_cast<const float4 *>(x + 8 * c), *reinterpret_cast<const float4 *>(x + 8 * c + 4), acc);
             }
             acc = wave_sum(acc);
             if (lane == 0) {
-                const float z = acc + bf16_to_f32(a.b1[blk][row]);
+                const float z = acc + b1;
                 t_sh[row] = 0.5f * z * (1.0f + erff(z * 0.70710678118654752f));
             }
         }
+        load_w1(min(blk + 1, ROUTER_BLOCKS - 1), wave, w1);               // the next block's first rows (after the last: unused)
         __syncthreads();
-        // x += W2 t + b2: one output channel per thread and round; a row of W2 is r bf16 values (r a multiple of 8)
-        for (int i = tid; i < d; i += 256) {
+        // x += W2 t + b2: output channels tid, tid + 512, ...; a row of W2 is r bf16 values
+#pragma unroll
+        for (int k = 0; k < NU; ++k) {
+            const int i = tid + ROUTER_THREADS * k;
+            if (i >= d) continue;
+            if (!AHEAD) { w2[k] = *reinterpret_cast<const u32x4_t *>(a.w2[blk] + (size_t)i * r); b2[k] = bf16_to_f32(a.b2[blk][i]); }
+            float acc = dot8f(make_uint4(w2[k].x, w2[k].y, w2[k].z, w2[k].w), *reinterpret_cast<const float4 *>(t_sh), *reinterpret_cast<const float4 *>(t_sh + 4), b2[k]);
             const uint4 *wp = reinterpret_cast<const uint4 *>(a.w2[blk] + (size_t)i * r);
-            float acc = bf16_to_f32(a.b2[blk][i]);
-            for (int c = 0; c < (r >> 3); ++c) {
-                const uint4 w = wp[c];
-                const float *t = t_sh + 8 * c;
-                acc = fmaf(bf16_lo(w.x), t[0], acc); acc = fmaf(bf16_hi(w.x), t[1], acc); acc = fmaf(bf16_lo(w.y), t[2], acc); acc = fmaf(bf16_hi(w.y), t[3], acc);
-                acc = fmaf(bf16_lo(w.z), t[4], acc); acc = fmaf(bf16_hi(w.z), t[5], acc); acc = fmaf(bf16_lo(w.w), t[6], acc); acc = fmaf(bf16_hi(w.w), t[7], acc);
-            }
+            for (int c = 1; c < (r >> 3); ++c) acc = dot8f(wp[c], *reinterpret_cast<const float4 *>(t_sh + 8 * c), *reinterpret_cast<const float4 *>(t_sh + 8 * c + 4), acc);
             x[i] += acc;
         }
         __syncthreads();
     }
-    // LayerNorm (mean, then the mean of squared deviations), then the two outputs
-    float s = 0.f;
-    for (int i = tid; i < d; i += 256) s += x[i];
-    const float mu = block_sum(s, red) / (float)d;
-    float q = 0.f;
-    for (int i = tid; i < d; i += 256) { const float dv = x[i] - mu; q = fmaf(dv, dv, q); }
-    const float inv = 1.0f / sqrtf(block_sum(q, red) / (float)d + a.ln_eps);
-    float o0 = 0.f, o1 = 0.f;
-    for (int i = tid; i < d; i += 256) {
-        const float y = (x[i] - mu) * inv * bf16_to_f32(a.ln_gain[i]) + bf16_to_f32(a.ln_bias[i]);
-        o0 = fmaf(bf16_to_f32(a.w_head[i]), y, o0);
-        o1 = fmaf(bf16_to_f32(a.w_head[d + i]), y, o1);
+    // LayerNorm (mean, then the mean of squared deviations), then the two outputs.  A thread's channels are in registers.
+    float xv[NU], gain[NU], bias[NU], h0[NU], h1[NU], s = 0.f;
+#pragma unroll
+    for (int k = 0; k < NU; ++k) {
+        const int i = tid + ROUTER_THREADS * k, j = min(i, d - 1);
+        gain[k] = bf16_to_f32(a.ln_gain[j]); bias[k] = bf16_to_f32(a.ln_bias[j]);
+        h0[k] = bf16_to_f32(a.w_head[j]); h1[k] = bf16_to_f32(a.w_head[d + j]);
+        xv[k] = i < d ? x[i] : 0.f;
+        s += xv[k];
     }
-    o0 = block_sum(o0, red);
-    o1 = block_sum(o1, red);
+    const float mu = block_sum2(s, 0.f, red).x / (float)d;
+    float q = 0.f;
+#pragma unroll
+    for (int k = 0; k < NU; ++k) { const float dv = tid + ROUTER_THREADS * k < d ? xv[k] - mu : 0.f; q = fmaf(dv, dv, q); }
+    const float inv = 1.0f / sqrtf(block_sum2(q, 0.f, red).x / (float)d + a.ln_eps);
+    float o0 = 0.f, o1 = 0.f;
+#pragma unroll
+    for (int k = 0; k < NU; ++k) {
+        if (tid + ROUTER_THREADS * k >= d) continue;
+        const float y = (xv[k] - mu) * inv * gain[k] + bias[k];
+        o0 = fmaf(h0[k], y, o0);
+        o1 = fmaf(h1[k], y, o1);
+    }
+    const float2 o = block_sum2(o0, o1, red);
+    o0 = o.x; o1 = o.y;
     if (tid != 0) return;
     o0 += bf16_to_f32(a.b_head[0]);
     o1 += bf16_to_f32(a.b_head[1]);
