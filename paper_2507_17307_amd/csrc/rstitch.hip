@@ -392,7 +392,10 @@ rs_status launch_gemm_nb(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_
         }
         return launch_gemm_r<MODE, NB, 2, 4>(a, blocks, st, name);
     } else {
-        const int r = (n_tiles + 1) / 2 >= target ? 2 : 1;
+        int r = (n_tiles + 1) / 2 >= target ? 2 : 1;
+        // the LM head has tiles to spare: four per workgroup, so that each piece of X serves twice the weights, once X is more than a
+        // few rows (7B shape, 3 / 5 / 8 / 12 / 16 sequences: 169 / 180 / 187 / 223 / 231 us with two tiles, 172 / 176 / 179 / 195 / 205 with four)
+        if (MODE == G_LMHEAD && a.M > 4 && (n_tiles + 3) / 4 >= target) r = 4;
         int blocks = (n_tiles + r - 1) / r;
         if (MODE == G_LMHEAD) {
             if (blocks > LM_PARTS_CAP) blocks = LM_PARTS_CAP;             // one partial per workgroup and row block
@@ -400,6 +403,9 @@ rs_status launch_gemm_nb(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_
             a.n_parts = blocks;
         }
         blocks = gemm_grid(blocks, a.yblocks);
+        if constexpr (MODE == G_LMHEAD) {
+            if (r == 4) return launch_gemm_r<MODE, NB, 4, 4>(a, blocks, st, name);
+        }
         if (r == 2) return launch_gemm_r<MODE, NB, 2, 4>(a, blocks, st, name);
         return launch_gemm_r<MODE, NB, 1, 4>(a, blocks, st, name);
     }
