@@ -1658,6 +1658,51 @@ __device__ __forceinline__ void attn_combine_unit(const AttnArgs &a, unsigned ch
     }
 }
 
+// The merge of a few slices (n_slices <= ATT_SFEW) for many rows: one wave per (row, head), no LDS.  Lane s holds slice s's weight,
+// lane d the channels d, d + 64.  grid ceil(n_rows * n_q / 4), block 256.
+constexpr int ATT_SFEW = 32;
+template <int HD>
+__global__ void __launch_bounds__(256) k_attn_merge_few(AttnArgs a, int n_rows) {
+    constexpr int PS = HD + 4, NC = (HD + 63) / 64, BATCH = 8;
+    const int lane = threadIdx.x & 63, item = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (item >= n_rows * a.n_q) return;
+    const int row = item / a.n_q, head = item - row * a.n_q, S = a.n_slices;
+    const float *p = a.partials + (size_t)item * S * PS;
+    const int bad = a.row_bad[row], pos = a.row_pos[row], n_pos = a.ctx_top ? *a.ctx_top : a.max_ctx;
+    // (records of slices past the context hold whatever an earlier call left there and are replaced, never scaled)
+    const float2 ml = *reinterpret_cast<const float2 *>(p + (size_t)min(lane, S - 1) * PS);
+    float v[BATCH][NC];
+    auto load = [&](int s0) {
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) v[k][c] = p[(size_t)min(s0 + k, S - 1) * PS + 4 + min(lane + 64 * c, HD - 1)];
+    };
+    load(0);
+    __builtin_amdgcn_sched_barrier(0);                      // every request is in flight before anything waits
+    const int S_act = bad ? 0 : min(S, pos / attn_slice_len(n_pos, S) + 1);
+    const float l = lane < S_act ? ml.y : 0.f, m = l > 0.f ? ml.x : -INFINITY;
+    const float M = wave_max(m), e = l > 0.f ? (a.base2 ? __builtin_amdgcn_exp2f(m - M) : __expf(m - M)) : 0.f;
+    const float L = wave_sum(l * e), w = L > 0.f ? e / L : 0.f;
+    float o[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) o[c] = 0.f;
+    for (int s0 = 0; s0 < S_act; s0 += BATCH) {
+        if (s0 > 0) load(s0);
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) {
+            const float wk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), min(s0 + k, 63)));
+#pragma unroll
+            for (int c = 0; c < NC; ++c) o[c] = fmaf(s0 + k < S_act ? wk : 0.f, s0 + k < S_act ? v[k][c] : 0.f, o[c]);
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const int d = lane + 64 * c, k = head * HD + d;
+        if (d < HD) a.out[a.out_frag ? frag_index(row, k, a.n_q * HD, a.rsh) : (size_t)row * a.n_q * HD + k] = o[c];
+    }
+}
+
 // grid (n_q_heads, n_rows, DQ)
 template <int HD, int SMAX, int DQ>
 __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {

@@ -327,7 +327,11 @@ rs_status launch_attn(AttnArgs &a, int n_splits, int n_kv, int n_rows, int n_seq
     // the merge is unrolled for 128 slices (contexts up to 8192 positions) or for the most the kernels take
     // HD / 64 workgroups per head, 64 output columns each
     constexpr int DQ = HD / 64 > 0 ? HD / 64 : 1;
-    if (n_splits <= 128)
+    // (a few slices of several rows: one wave per head and row without LDS, 7B shape, 128 rows of 8 slices 15.1 -> 6.7 us, 14B, 61 rows of
+    // 10 slices 10.5 -> 6.0; a single row of 32 slices is better off with a workgroup per half head: 3.5 us against 5.0)
+    if (n_rows > 1 && (n_splits <= 16 || (n_splits <= ATT_SFEW && n_rows * a.n_q >= 512)))
+        hipLaunchKernelGGL((k_attn_merge_few<HD>), dim3((n_rows * a.n_q + 3) / 4), dim3(256), 0, st, a, n_rows);
+    else if (n_splits <= 128)
         hipLaunchKernelGGL((k_attn_combine<HD, 128, DQ>), dim3(a.n_q, n_rows, DQ), dim3(256), attn_combine_lds_bytes<HD>(), st, a);
     else
         hipLaunchKernelGGL((k_attn_combine<HD, ATT_SMAX, DQ>), dim3(a.n_q, n_rows, DQ), dim3(256), attn_combine_lds_bytes<HD>(), st, a);
