@@ -4,6 +4,7 @@
 // rows, and the merge of the slices).  Wave64, 256-thread workgroups.
 #pragma once
 
+#include "attn_plan.h"
 #include "device_utils.h"
 #include "router.h"
 
@@ -909,7 +910,6 @@ inline int frag_shift(int rows) { int s = 0; while (s < 4 && (1 << s) < rows) ++
 constexpr int ATT_GMAX = 8;       // query heads per kv head, at most
 constexpr int ATT_SMAX = 192;     // context slices, at most (a multiple of 64: the merge gives each lane ATT_SMAX / 64 of them)
 constexpr int ATT_WT = 16;        // tokens per wave and pass
-constexpr int ATT_BT = 64;        // tokens per workgroup and pass
 
 // split 8 fp32 values into three bf16x8 planes whose sum is exact
 __device__ __forceinline__ void split3(const float (&x)[8], bf16x8_t (&pl)[3]) {
@@ -1450,7 +1450,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_walk(AttnArgs a) {
             parity ^= 1;
             park(buf, t0);
             lds_barrier();                                       // the pass is in LDS; everybody is done with the other buffer's last use
-            fetch(min(t0 + 64, t_end - 1));                      // (after the last pass: a duplicate, never used)
+            fetch(walk_next_pass(t0, t_end));
             const int w0 = t0 + (SHARE ? 16 * wave : 0);         // first position this wave looks at
             if (!active || w0 >= ctx_hi) continue;
             const unsigned char *sK = buf, *sV = buf + (size_t)64 * KP;
