@@ -27,7 +27,12 @@ struct PrepArgs {
     int *row_slot, *row_pos, *row_bad, *out_row, *seq_bad;
     int4 *seq_info;                // per sequence {first row, end row, cache slot, first row's position}; first row = -1 for an invalid one
     float *seq_scale;
-    int *ctx_top;                  // longest context of the call (at least that of every valid sequence, at most max_ctx), or null
+    // walked attention (attn_plan.h); all null or zero in calls that do not take it
+    int *slice_len;                // [0] positions per context slice of this call, [1] list: slices of the longest context
+    int slices;                    // fixed split: slices that divide the longest context of the call
+    int4 *pieces;                  // list: two entries per piece, {first row, end row, cache slot, first row's position} of its sequence
+                                   // (first row < 0: no piece) and {group of row slots, slice, positions per slice, slices of the longest context}
+    int n_pieces, list_slots, list_slices, slot_rows;      // entries, see WalkPlan; rows per row slot
     float *h;
 };
 
@@ -35,22 +40,32 @@ constexpr int MAX_SEQS = 128;     // sequences one call may carry
 constexpr int MAX_ROWS = 128;     // token rows one call may carry
 constexpr int PREP_LDS_INTS = 8 + 5 * MAX_SEQS;
 
-// sh: PREP_LDS_INTS ints of LDS.  The control values may live in pinned host memory, where every
-// dependent read costs a bus round trip: each one is requested by its own thread, all at once,
+// The call's control values in LDS (sh: PREP_LDS_INTS ints, the first four left free).  They may live in pinned host memory,
+// where every dependent read costs a bus round trip: each one is requested by its own thread, all at once,
 // and the validation then runs out of LDS.
-__device__ __forceinline__ void prepare_row(const PrepArgs &a, int r, int *sh) {
+struct PrepTable { int *off, *slot, *pos, *tok; float *scale; int ns, nr; };       // off: [MAX_SEQS + 1], the others [MAX_SEQS]
+__device__ __forceinline__ PrepTable prepare_table(const PrepArgs &a, int *sh) {
     static_assert(MAX_ROWS <= MAX_SEQS && 2 * MAX_SEQS <= 256, "one thread per control value");
     const int tid = threadIdx.x;
-    int *s_off = sh + 4, *s_slot = sh + 8 + MAX_SEQS, *s_pos = sh + 8 + 2 * MAX_SEQS, *s_tok = sh + 8 + 4 * MAX_SEQS;   // [MAX_SEQS + 1], [MAX_SEQS] ...
-    float *s_scale = reinterpret_cast<float *>(sh + 8 + 3 * MAX_SEQS);
-    const int ns = min(a.n_seqs, MAX_SEQS), nr = min(a.n_rows, MAX_ROWS);            // the host enforces both bounds
-    if (a.span_off != nullptr && tid <= ns) s_off[tid] = a.span_off[tid];
-    if (tid < nr) s_tok[tid] = a.tokens[tid];
-    if (tid >= 128 && tid < 128 + ns) {
+    const PrepTable t{sh + 4, sh + 8 + MAX_SEQS, sh + 8 + 2 * MAX_SEQS, sh + 8 + 4 * MAX_SEQS, reinterpret_cast<float *>(sh + 8 + 3 * MAX_SEQS),
+                      min(a.n_seqs, MAX_SEQS), min(a.n_rows, MAX_ROWS)};            // the host enforces both bounds
+    if (a.span_off != nullptr && tid <= t.ns) t.off[tid] = a.span_off[tid];
+    if (tid < t.nr) t.tok[tid] = a.tokens[tid];
+    if (tid >= 128 && tid < 128 + t.ns) {
         const int i = tid - 128;
-        s_slot[i] = a.seq_slot[i]; s_pos[i] = a.pos0[i]; s_scale[i] = a.scale ? a.scale[i] : 1.f;
+        t.slot[i] = a.seq_slot[i]; t.pos[i] = a.pos0[i]; t.scale[i] = a.scale ? a.scale[i] : 1.f;
     }
     __syncthreads();
+    return t;
+}
+
+// sh: PREP_LDS_INTS ints of LDS
+__device__ __forceinline__ void prepare_row(const PrepArgs &a, int r, int *sh) {
+    const int tid = threadIdx.x;
+    const PrepTable tb = prepare_table(a, sh);
+    int *s_off = tb.off, *s_slot = tb.slot, *s_pos = tb.pos, *s_tok = tb.tok;
+    float *s_scale = tb.scale;
+    const int ns = tb.ns;
     // Every check is one comparison per thread (one thread walking the table of 128 sequences took 18 us):
     // first the span table, then the row's own sequence.  sh[0]: this row's sequence; sh[1]: longest context of the call
     int lo = r, hi = r + 1, bad = 0;
@@ -90,7 +105,7 @@ __device__ __forceinline__ void prepare_row(const PrepArgs &a, int r, int *sh) {
             a.seq_scale[b] = s_scale[b];
             a.seq_info[b] = bad ? make_int4(-1, 0, 0, 0) : make_int4(lo, hi, s_slot[b], s_pos[b]);
         }
-        if (r == 0 && a.ctx_top) *a.ctx_top = top;
+        if (r == 0 && a.slices > 0) *a.slice_len = attn_slice_len(top, a.slices);
         // a malformed offset table can leave sequences without any row: flag them all (and only then: the rows of the other
         // sequences write these entries too)
         if (table_bad && r == 0)
@@ -106,9 +121,84 @@ __device__ __forceinline__ void prepare_row(const PrepArgs &a, int r, int *sh) {
     }
 }
 
+// The pieces of the walked attention of this call (attn_plan.h), by one workgroup beside those of the rows.  Every sequence of
+// a well-formed table whose slot and positions are in range has pieces, also where its rows turn out invalid for another reason
+// (token, slot named twice): what such pieces read is in range, and the merge clears the rows' outputs.
+// It has to end before the rows' workgroups do, which wait for their embedding rows (5 us a call): one thread per row, which is
+// a group's if it is the first row of one, each wave tries slice lengths of its own, no loops over the sequences.
+// sh: PREP_LDS_INTS ints of LDS.
+__device__ __forceinline__ void prepare_pieces(const PrepArgs &a, int *sh) {
+    static_assert(WALK_GROUPS_MAX == MAX_ROWS && MAX_ROWS == 2 * RS_WAVE, "one thread per row, two waves of them");
+    __shared__ int g_seq[MAX_ROWS], g_passes[MAX_ROWS], g_end[MAX_ROWS], tried[WALK_TRIES];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, group_rows = 4 * a.slot_rows;
+    if (tid < MAX_ROWS) g_seq[tid] = -1;
+    const PrepTable tb = prepare_table(a, sh);
+    int lo = tid, hi = tid + 1, bad = 0;
+    if (tid < tb.ns && a.span_off) {
+        lo = tb.off[tid]; hi = tb.off[tid + 1];
+        bad = hi <= lo || lo < 0 || hi > a.n_rows || (tid == 0 && (lo != 0 || tb.off[tb.ns] != a.n_rows));
+    }
+    const bool table_bad = __syncthreads_or(bad);
+    if (tid < tb.ns && !table_bad) {
+        const int slot = tb.slot[tid], p0 = tb.pos[tid];
+        if (slot >= 0 && slot < a.max_seqs && p0 >= 0 && p0 <= a.max_ctx - (hi - lo))
+            for (int r = lo; r < hi; r += group_rows) g_seq[r] = tid;
+    }
+    __syncthreads();
+    // thread r: the passes over the longest context of the group that starts at row r
+    int passes = 0;
+    if (tid < MAX_ROWS) {
+        const int seq = g_seq[tid];
+        if (seq >= 0) {
+            const int first_row = a.span_off ? tb.off[seq] : seq, end_row = a.span_off ? tb.off[seq + 1] : seq + 1;
+            passes = (tb.pos[seq] + min(tid + group_rows, end_row) - first_row + ATT_BT - 1) / ATT_BT;
+        }
+        g_passes[tid] = passes;
+    }
+    __syncthreads();
+    const int p0 = g_passes[lane], p1 = g_passes[64 + lane];
+    // (a row's passes stay below 2^20: its K rows fit 31 bits)
+    const int longest = (int)wave_max((float)max(p0, p1));
+    const int first = walk_first_len(wave_sum_i32(p0 + p1), longest, a.list_slots, a.list_slices);
+    for (int k = wave; k < WALK_TRIES; k += 4) {
+        const int len = walk_try_len(first, k), n = wave_sum_i32((p0 + len - 1) / len + (p1 + len - 1) / len);
+        if (lane == 0) tried[k] = n;
+    }
+    __syncthreads();
+    int len = first;
+    for (int k = WALK_TRIES - 1; k >= 0; --k)
+        if (tried[k] <= a.list_slots) len = walk_try_len(first, k);
+    // place of the group's first piece: the pieces of the groups before it
+    const int n_own = (passes + len - 1) / len;
+    int end = n_own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) { const int u = __shfl_up(end, o, RS_WAVE); if (lane >= o) end += u; }
+    if (tid < MAX_ROWS) g_end[tid] = end;
+    __syncthreads();
+    const int half = g_end[63], n_all = half + g_end[127], most = (longest + len - 1) / len;
+    // the entries: 256 threads over the rows, a power of two each
+    int per = 256 / MAX_ROWS;
+    while (2 * per * tb.nr <= 256) per *= 2;
+    const int r = tid / per;
+    if (r < tb.nr && g_seq[r] >= 0) {
+        const int seq = g_seq[r], n = (g_passes[r] + len - 1) / len, at = g_end[r] + (r >= 64 ? half : 0) - n;
+        const int4 of = a.span_off ? make_int4(tb.off[seq], tb.off[seq + 1], tb.slot[seq], tb.pos[seq]) : make_int4(seq, seq + 1, tb.slot[seq], tb.pos[seq]);
+        for (int s = tid % per; s < n; s += per) {
+            const int i = min(at + s, a.n_pieces - 1);                             // (there are at most slots + groups: see attn_plan.h)
+            a.pieces[2 * i] = of;
+            a.pieces[2 * i + 1] = make_int4((r - of.x) / group_rows, s, len * ATT_BT, most);
+        }
+    }
+    for (int i = n_all + tid; i < a.n_pieces; i += 256) a.pieces[2 * i] = make_int4(-1, 0, 0, 0);
+    if (tid == 0) { a.slice_len[0] = len * ATT_BT; a.slice_len[1] = most; }
+}
+
+// grid n_rows, LIST: and one more workgroup for the list of attention pieces
+template <bool LIST>
 __global__ void __launch_bounds__(256) k_prepare(PrepArgs a) {
     __shared__ int sh[PREP_LDS_INTS];
-    prepare_row(a, blockIdx.x, sh);
+    if (LIST && (int)blockIdx.x == a.n_rows) prepare_pieces(a, sh);
+    else prepare_row(a, blockIdx.x, sh);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -882,15 +972,16 @@ struct AttnArgs {
     const float *qbuf;             // [rows, n_q*hd] fp32, rotated
     const uint16_t *kcache;        // [layer][slot][kv_head][position][hd] bf16
     const uint16_t *vcache;        // [layer][slot][kv_head][hd][position] bf16
-    float *partials;               // [rows, n_q, n_slices, hd+4]
+    float *partials;               // [rows, n_q, n_slices, hd+4]; behind a list of pieces slice_len[1] in the place of n_slices
     float *out;                    // [rows, n_q*hd] fp32, or the same in operand order (out_frag)
     int out_frag, rsh;             // a matrix-core kernel reads `out`: rows in the order of frag_index with blocks of 1 << rsh
     const int *row_pos, *row_slot, *row_bad;
     int n_q, n_kv, max_ctx, max_seqs, layer, n_slices;
-    int slot_split;                // k_attn_span, k_attn_walk: workgroups per sequence, slice and KV head
-    const int *ctx_top;            // k_attn_walk and the merge after it: longest context of the call, which the slices divide; null: they divide max_ctx
-    int base2;                     // the records' maxima are in units of ln 2 (k_attn_walk)
-    int direct;                    // k_attn_walk: one slice, decode rows: the normalised rows go to `out`, no merge follows
+    int slot_split;                // k_attn_span, k_attn_walk with a fixed split: workgroups per sequence, slice and KV head
+    int walked;                    // k_attn_walk and the merge after it: the records' maxima are in units of ln 2, rows of one slice have no record
+    const int *slice_len;          // walked: positions per slice
+    const int4 *pieces;            // walked: list of pieces (PrepArgs), or null for a fixed split
+    int direct;                    // k_attn_walk: one slice for every row, no merge follows
     const int4 *seq_info;          // per sequence {first row, end row, cache slot, first row's position}, first row < 0: invalid (k_attn_span)
 };
 
@@ -908,7 +999,6 @@ __host__ __device__ __forceinline__ size_t frag_index(int m, int k, int K, int r
 inline int frag_shift(int rows) { int s = 0; while (s < 4 && (1 << s) < rows) ++s; return s; }
 
 constexpr int ATT_GMAX = 8;       // query heads per kv head, at most
-constexpr int ATT_SMAX = 192;     // context slices, at most (a multiple of 64: the merge gives each lane ATT_SMAX / 64 of them)
 constexpr int ATT_WT = 16;        // tokens per wave and pass
 
 // split 8 fp32 values into three bf16x8 planes whose sum is exact
@@ -926,9 +1016,6 @@ __device__ __forceinline__ void split3(const float (&x)[8], bf16x8_t (&pl)[3]) {
     pl[1] = __builtin_bit_cast(bf16x8_t, make_uint4(w1[0], w1[1], w1[2], w1[3]));
     pl[2] = __builtin_bit_cast(bf16x8_t, make_uint4(w2[0], w2[1], w2[2], w2[3]));
 }
-
-// positions per context slice when S slices share n positions: whole 64-position passes
-__device__ __forceinline__ int attn_slice_len(int n, int S) { return ((n + S - 1) / S + ATT_BT - 1) / ATT_BT * ATT_BT; }
 
 template <int HD>
 __host__ __device__ constexpr size_t attn_lds_bytes(int G = ATT_GMAX) { return (size_t)(4 * G * (HD + 4) + 2 * 4 * 16) * 4; }
@@ -1309,20 +1396,21 @@ __global__ void __launch_bounds__(256) k_attn_span(AttnArgs a) {
 
 // ------------------------------------------------------------------------------------------------
 // k_attn_walk: attention of calls with several rows or several sequences where one 64-position pass per
-// workgroup would be many rounds of the machine.  grid (n_slices, n_kv_heads, n_seqs * ZS), block 256.
-// A workgroup walks its slice (S slices divide the longest context of the call) in passes of 64 positions:
-// the four waves fetch the pass's K rows and V^T pieces with whole-line loads one pass ahead into registers and
+// workgroup would be many rounds of the machine.  Block 256; grid (n_slices, n_kv_heads, n_seqs * ZS) where the split is fixed,
+// (n_kv_heads, pieces) where the row table lists the pieces (attn_plan.h; heads fastest: with eight KV heads every XCD has
+// one, so that the groups of a long span meet its K/V rows in one L2).
+// A workgroup walks one slice of one group of row slots in passes of 64 positions: the four waves fetch the pass's K rows and V^T pieces with whole-line loads one pass ahead into registers and
 // park them in one of two LDS buffers (one bare barrier per pass: the loads of the next pass stay in flight across
 // it).  Online softmax per matrix-core column as in the kernels above.
-//   SHARE = false: wave w owns row slot w (+ 4 zs) of the sequence and takes all 64 positions of a pass
+//   SHARE = false: wave w owns row slot 4 group + w of the sequence and takes all 64 positions of a pass
 //   SHARE = true:  the sequence has one row slot (decode steps, very short spans); wave w takes the 16 positions
 //                  16 w .. of every pass and the four states are merged at the end
-// The records' maxima are in units of ln 2 (see q_scale), which the merge is told by a.base2.
-// With one slice a decode step needs no merge kernel: the rows are normalised here (a.direct).
+// The records' maxima are in units of ln 2 (see q_scale).  A row whose context is one slice leaves no record: it is
+// normalised here, and the merge passes it by (or is not launched, where that holds for every row: a.direct).
 // What bounds it: long spans the vector work beside the matrix cores (14B, 61 rows at 9000 positions: 53 us a layer against
 // 159 for waves that fetched their own tiles; the matrix cores are busy a third of that), decode steps the one pass a
 // workgroup has in flight (7B, 128 sequences of 520 .. 1000 positions, 195 MB: 47 us = 4.1 TB/s, 77 + 12 us for one pass per
-// workgroup plus the merge; 16 sequences, 42 MB: 15 us against 20.6; 32B, 8 ragged sequences: 58 against 104).
+// workgroup plus the merge; 16 sequences, 42 MB: 11.8 us against 20.6; 32B, 8 ragged sequences: 53 against 104).
 // ------------------------------------------------------------------------------------------------
 template <int HD>
 __host__ __device__ constexpr size_t attn_walk_lds_bytes() { return 2 * attn_span_lds_bytes<HD>(); }
@@ -1345,28 +1433,42 @@ __global__ void __launch_bounds__(256, 2) k_attn_walk(AttnArgs a) {
     constexpr int KP = HD * 2 + 16, VP = 64 * 2 + 16;           // LDS row pitches in bytes (padded against bank conflicts)
     constexpr int KQ = 64 * HD * 2 / 4096, VQ = HD * 128 / 4096; // 16-byte loads per thread for each tile
     constexpr int NTB = SHARE ? 1 : 4;                           // 16-position score blocks per wave and pass
-    constexpr int SLOTS = SHARE ? 1 : 4;                         // row slots a workgroup takes at a time
+    constexpr int SLOTS = SHARE ? 1 : 4;                         // row slots of a group
     constexpr size_t BUF = attn_span_lds_bytes<HD>();
     extern __shared__ __align__(16) unsigned char smem[];
-    const int split = blockIdx.x, S = gridDim.x, kvh = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int j = lane & 15, kg = lane >> 4;
     const int G = a.n_q / a.n_kv, RP = 16 / G;
     const int rr = j / G, gh = j - rr * G;                      // this lane's column: row rr of the slot, head gh
-    const int ZS = a.slot_split > 1 ? a.slot_split : 1, zs = blockIdx.z % ZS, seq = blockIdx.z / ZS;
-    const int4 info = a.seq_info[seq];                          // {first row, end row, cache slot, position of the first row}, first row < 0: skip
-    if (info.x < 0) {
-        // no merge kernel follows a decode step of one slice: the rejected row's output is cleared here
-        if (SHARE && a.direct)
-            for (int i = tid; i < G * HD; i += 256)
-                a.out[a.out_frag ? frag_index(seq, kvh * G * HD + i, a.n_q * HD, a.rsh) : ((size_t)seq * a.n_q + kvh * G) * HD + i] = 0.f;
-        return;
+    int kvh, split, group, C, S = a.n_slices;
+    int4 info;                                                  // {first row, end row, cache slot, position of the first row}, first row < 0: skip
+    if (a.pieces) {
+        kvh = blockIdx.x;
+        info = a.pieces[2 * blockIdx.y];
+        const int4 piece = a.pieces[2 * blockIdx.y + 1];
+        group = piece.x; split = piece.y; C = piece.z; S = piece.w;
+        if (info.x < 0) return;
+    } else {
+        split = blockIdx.x; kvh = blockIdx.y;
+        const int ZS = a.slot_split, seq = blockIdx.z / ZS;
+        group = blockIdx.z % ZS;
+        info = a.seq_info[seq];
+        C = *a.slice_len;
+        if (info.x < 0) {
+            // no merge kernel follows a decode step of one slice: the rejected row's output is cleared here
+            if (SHARE && a.direct)
+                for (int i = tid; i < G * HD; i += 256)
+                    a.out[a.out_frag ? frag_index(seq, kvh * G * HD + i, a.n_q * HD, a.rsh) : ((size_t)seq * a.n_q + kvh * G) * HD + i] = 0.f;
+            return;
+        }
     }
     const int r_lo = info.x, r_hi = info.y;
     const int ctx_max = info.w + (r_hi - r_lo);                 // positions the last row attends to
-    const int n_slots = (r_hi - r_lo + RP - 1) / RP;
-    const int C = attn_slice_len(*a.ctx_top, S), t_begin = split * C;
-    if (t_begin >= ctx_max || SLOTS * zs >= n_slots) return;
+    const int n_slots = (r_hi - r_lo + RP - 1) / RP, slot0 = SLOTS * group;
+    const int t_begin = split * C;
+    const int last = min(r_lo + (slot0 + SLOTS) * RP, r_hi) - 1;                     // last row of the group
+    const int t_end = min(t_begin + C, info.w + (last - r_lo) + 1);
+    if (slot0 >= n_slots || t_begin >= t_end) return;           // no such group, or all of it lies before this slice
     const int kv_slot = min(max(info.z, 0), a.max_seqs - 1);
     const size_t kv_base = (((size_t)a.layer * a.max_seqs + kv_slot) * a.n_kv + kvh) * (size_t)a.max_ctx * HD;
     // one head's K or V rows stay below 2^31 bytes (the launch checks), so a piece is a uniform base and a 32-bit offset
@@ -1414,159 +1516,161 @@ __global__ void __launch_bounds__(256, 2) k_attn_walk(AttnArgs a) {
     };
 
     int parity = 0;
-    for (int slot0 = SLOTS * zs; slot0 < n_slots; slot0 += SLOTS * ZS) {
-        const int last = min(r_lo + (slot0 + SLOTS) * RP, r_hi) - 1;                 // last row of this group of slots
-        const int t_end = min(t_begin + C, info.w + (last - r_lo) + 1);
-        if (t_begin >= t_end) continue;                          // the whole group lies before this slice
-        const int slot = slot0 + (SHARE ? 0 : wave);
-        const int my_row = r_lo + slot * RP + rr;
-        const bool active = slot < n_slots, col_ok = active && rr < RP && my_row < r_hi;
-        // positions this lane's row attends to; a column that belongs to no row (q = 0, never written) takes part in everything
-        const int ctx_col = col_ok ? info.w + (my_row - r_lo) + 1 : ctx_max;
-        const int ctx_lo = info.w + slot * RP + 1;               // ... and the slot's first row
-        const int ctx_hi = min(info.w + (slot + 1) * RP, ctx_max);
-        fetch(t_begin);
-        bf16x8_t qB[NDS][3];
-        {
-            const float4 *qp = reinterpret_cast<const float4 *>(a.qbuf + ((size_t)(col_ok ? my_row : r_lo) * a.n_q + kvh * G + (col_ok ? gh : 0)) * HD + 8 * kg);
+    const int slot = slot0 + (SHARE ? 0 : wave);
+    const int my_row = r_lo + slot * RP + rr;
+    const bool active = slot < n_slots, col_ok = active && rr < RP && my_row < r_hi;
+    // positions this lane's row attends to; a column that belongs to no row (q = 0, never written) takes part in everything
+    const int ctx_col = col_ok ? info.w + (my_row - r_lo) + 1 : ctx_max;
+    const int ctx_lo = info.w + slot * RP + 1;               // ... and the slot's first row
+    const int ctx_hi = min(info.w + (slot + 1) * RP, ctx_max);
+    fetch(t_begin);
+    bf16x8_t qB[NDS][3];
+    {
+        const float4 *qp = reinterpret_cast<const float4 *>(a.qbuf + ((size_t)(col_ok ? my_row : r_lo) * a.n_q + kvh * G + (col_ok ? gh : 0)) * HD + 8 * kg);
 #pragma unroll
-            for (int ds = 0; ds < NDS; ++ds) {
-                const float4 x0 = qp[8 * ds], x1 = qp[8 * ds + 1];
-                float qv[8] = {x0.x * q_scale, x0.y * q_scale, x0.z * q_scale, x0.w * q_scale, x1.x * q_scale, x1.y * q_scale, x1.z * q_scale, x1.w * q_scale};
-                if (!col_ok) {
+        for (int ds = 0; ds < NDS; ++ds) {
+            const float4 x0 = qp[8 * ds], x1 = qp[8 * ds + 1];
+            float qv[8] = {x0.x * q_scale, x0.y * q_scale, x0.z * q_scale, x0.w * q_scale, x1.x * q_scale, x1.y * q_scale, x1.z * q_scale, x1.w * q_scale};
+            if (!col_ok) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) qv[e] = 0.f;
-                }
-                split3(qv, qB[ds]);
+                for (int e = 0; e < 8; ++e) qv[e] = 0.f;
             }
+            split3(qv, qB[ds]);
         }
-        float m_run = -INFINITY, l_run = 0.f;
-        f32x4_t acc[NDB];
+    }
+    float m_run = -INFINITY, l_run = 0.f;
+    f32x4_t acc[NDB];
 #pragma unroll
-        for (int db = 0; db < NDB; ++db) acc[db] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+    for (int db = 0; db < NDB; ++db) acc[db] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 
-        for (int t0 = t_begin; t0 < t_end; t0 += 64) {
-            unsigned char *buf = smem + parity * BUF;
-            parity ^= 1;
-            park(buf, t0);
-            lds_barrier();                                       // the pass is in LDS; everybody is done with the other buffer's last use
-            fetch(walk_next_pass(t0, t_end));
-            const int w0 = t0 + (SHARE ? 16 * wave : 0);         // first position this wave looks at
-            if (!active || w0 >= ctx_hi) continue;
-            const unsigned char *sK = buf, *sV = buf + (size_t)64 * KP;
-            // scores: lane holds positions w0 + 16 tb + 4 kg + r of its column.  Consecutive products go to different
-            // accumulators; per accumulator the order is d steps, smallest plane first.
-            f32x4_t sc[NTB];
+    for (int t0 = t_begin; t0 < t_end; t0 += 64) {
+        unsigned char *buf = smem + parity * BUF;
+        parity ^= 1;
+        park(buf, t0);
+        lds_barrier();                                       // the pass is in LDS; everybody is done with the other buffer's last use
+        fetch(walk_next_pass(t0, t_end));
+        const int w0 = t0 + (SHARE ? 16 * wave : 0);         // first position this wave looks at
+        if (!active || w0 >= ctx_hi) continue;
+        const unsigned char *sK = buf, *sV = buf + (size_t)64 * KP;
+        // scores: lane holds positions w0 + 16 tb + 4 kg + r of its column.  Consecutive products go to different
+        // accumulators; per accumulator the order is d steps, smallest plane first.
+        f32x4_t sc[NTB];
 #pragma unroll
-            for (int tb = 0; tb < NTB; ++tb) sc[tb] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+        for (int tb = 0; tb < NTB; ++tb) sc[tb] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int ds = 0; ds < NDS; ++ds) {
-                bf16x8_t A[NTB];
+        for (int ds = 0; ds < NDS; ++ds) {
+            bf16x8_t A[NTB];
 #pragma unroll
-                for (int tb = 0; tb < NTB; ++tb)
-                    A[tb] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(sK + (size_t)(w0 - t0 + 16 * tb + j) * KP + 64 * ds + 16 * kg));
+            for (int tb = 0; tb < NTB; ++tb)
+                A[tb] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(sK + (size_t)(w0 - t0 + 16 * tb + j) * KP + 64 * ds + 16 * kg));
 #pragma unroll
-                for (int pl = 2; pl >= 0; --pl)
+            for (int pl = 2; pl >= 0; --pl)
 #pragma unroll
-                    for (int tb = 0; tb < NTB; ++tb) sc[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[tb], qB[ds][pl], sc[tb], 0, 0, 0);
-            }
-            if (w0 + 16 * NTB > ctx_lo) {                        // the causal edge of some row
-#pragma unroll
-                for (int tb = 0; tb < NTB; ++tb)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (w0 + 16 * tb + 4 * kg + r >= ctx_col) sc[tb][r] = -INFINITY;
-            }
-            float mx = -INFINITY;
-#pragma unroll
-            for (int tb = 0; tb < NTB; ++tb) mx = fmaxf(mx, fmaxf(fmaxf(sc[tb][0], sc[tb][1]), fmaxf(sc[tb][2], sc[tb][3])));
-            mx = max_over_kg(mx);
-            const float m_new = fmaxf(m_run, mx);                // -inf while the column has no position yet
-            if (__any(m_new > m_run)) {                          // rescale only when some column's maximum moved
-                const float alpha = (m_run == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
-                l_run *= alpha;
-#pragma unroll
-                for (int db = 0; db < NDB; ++db) { acc[db][0] *= alpha; acc[db][1] *= alpha; acc[db][2] *= alpha; acc[db][3] *= alpha; }
-                m_run = m_new;
-            }
-            const float m_sub = m_new == -INFINITY ? 0.f : m_new;                    // 2^-inf = 0 for a column without positions
+                for (int tb = 0; tb < NTB; ++tb) sc[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[tb], qB[ds][pl], sc[tb], 0, 0, 0);
+        }
+        if (w0 + 16 * NTB > ctx_lo) {                        // the causal edge of some row
 #pragma unroll
             for (int tb = 0; tb < NTB; ++tb)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) { sc[tb][r] = __builtin_amdgcn_exp2f(sc[tb][r] - m_sub); l_run += sc[tb][r]; }
-            // P V: k slot (kg, 4 hf + r) is position w0 + 32 ks + 16 hf + 4 kg + r; SHARE fills only hf = 0
-#pragma unroll
-            for (int ks = 0; ks < (SHARE ? 1 : 2); ++ks) {
-                float pv[8];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) { pv[r] = sc[SHARE ? 0 : 2 * ks][r]; pv[4 + r] = SHARE ? 0.f : sc[SHARE ? 0 : 2 * ks + 1][r]; }
-                bf16x8_t pB[3];
-                split3(pv, pB);
-                bf16x8_t A[NDB];
-#pragma unroll
-                for (int db = 0; db < NDB; ++db) {
-                    const unsigned char *vr = sV + (size_t)(16 * db + j) * VP + 2 * (w0 - t0) + 64 * ks + 8 * kg;
-                    const uint2 lo = *reinterpret_cast<const uint2 *>(vr);
-                    uint2 hi = make_uint2(0u, 0u);
-                    if (!SHARE) hi = *reinterpret_cast<const uint2 *>(vr + 32);
-                    A[db] = __builtin_bit_cast(bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
-                }
-#pragma unroll
-                for (int pl = 2; pl >= 0; --pl)
-#pragma unroll
-                    for (int db = 0; db < NDB; ++db) acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[db], pB[pl], acc[db], 0, 0, 0);
-            }
+                for (int r = 0; r < 4; ++r)
+                    if (w0 + 16 * tb + 4 * kg + r >= ctx_col) sc[tb][r] = -INFINITY;
         }
-        l_run += __shfl_xor(l_run, 16, RS_WAVE);
-        l_run += __shfl_xor(l_run, 32, RS_WAVE);
-        if constexpr (!SHARE) {
-            if (col_ok && t_begin < ctx_col) {
-                float *p = a.partials + (((size_t)my_row * a.n_q + kvh * G + gh) * S + split) * PS;
+        float mx = -INFINITY;
 #pragma unroll
-                for (int db = 0; db < NDB; ++db)
-                    *reinterpret_cast<float4 *>(p + 4 + 16 * db + 4 * kg) = make_float4(acc[db][0], acc[db][1], acc[db][2], acc[db][3]);
-                if (kg == 0) { p[0] = m_run; p[1] = l_run; }
+        for (int tb = 0; tb < NTB; ++tb) mx = fmaxf(mx, fmaxf(fmaxf(sc[tb][0], sc[tb][1]), fmaxf(sc[tb][2], sc[tb][3])));
+        mx = max_over_kg(mx);
+        const float m_new = fmaxf(m_run, mx);                // -inf while the column has no position yet
+        if (__any(m_new > m_run)) {                          // rescale only when some column's maximum moved
+            const float alpha = (m_run == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
+            l_run *= alpha;
+#pragma unroll
+            for (int db = 0; db < NDB; ++db) { acc[db][0] *= alpha; acc[db][1] *= alpha; acc[db][2] *= alpha; acc[db][3] *= alpha; }
+            m_run = m_new;
+        }
+        const float m_sub = m_new == -INFINITY ? 0.f : m_new;                    // 2^-inf = 0 for a column without positions
+#pragma unroll
+        for (int tb = 0; tb < NTB; ++tb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) { sc[tb][r] = __builtin_amdgcn_exp2f(sc[tb][r] - m_sub); l_run += sc[tb][r]; }
+        // P V: k slot (kg, 4 hf + r) is position w0 + 32 ks + 16 hf + 4 kg + r; SHARE fills only hf = 0
+#pragma unroll
+        for (int ks = 0; ks < (SHARE ? 1 : 2); ++ks) {
+            float pv[8];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) { pv[r] = sc[SHARE ? 0 : 2 * ks][r]; pv[4 + r] = SHARE ? 0.f : sc[SHARE ? 0 : 2 * ks + 1][r]; }
+            bf16x8_t pB[3];
+            split3(pv, pB);
+            bf16x8_t A[NDB];
+#pragma unroll
+            for (int db = 0; db < NDB; ++db) {
+                const unsigned char *vr = sV + (size_t)(16 * db + j) * VP + 2 * (w0 - t0) + 64 * ks + 8 * kg;
+                const uint2 lo = *reinterpret_cast<const uint2 *>(vr);
+                uint2 hi = make_uint2(0u, 0u);
+                if (!SHARE) hi = *reinterpret_cast<const uint2 *>(vr + 32);
+                A[db] = __builtin_bit_cast(bf16x8_t, make_uint4(lo.x, lo.y, hi.x, hi.y));
             }
-        } else {
-            // merge the four waves' states of the slot's 16 columns; the tiles' LDS is free once everybody is here
-            __syncthreads();
-            float (*m_lds)[16] = reinterpret_cast<float (*)[16]>(smem);
-            float (*l_lds)[16] = m_lds + 4;
-            float *acc_lds = reinterpret_cast<float *>(smem + (size_t)2 * 4 * 16 * 4);                   // [4 waves][16 columns][HD + 4]
+#pragma unroll
+            for (int pl = 2; pl >= 0; --pl)
+#pragma unroll
+                for (int db = 0; db < NDB; ++db) acc[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[db], pB[pl], acc[db], 0, 0, 0);
+        }
+    }
+    l_run += __shfl_xor(l_run, 16, RS_WAVE);
+    l_run += __shfl_xor(l_run, 32, RS_WAVE);
+    if constexpr (!SHARE) {
+        if (col_ok && ctx_col <= C) {
+            const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
+#pragma unroll
+            for (int db = 0; db < NDB; ++db) {
+                const int k = (kvh * G + gh) * HD + 16 * db + 4 * kg;
+                *reinterpret_cast<float4 *>(a.out + (a.out_frag ? frag_index(my_row, k, a.n_q * HD, a.rsh) : (size_t)my_row * a.n_q * HD + k)) =
+                    make_float4(acc[db][0] * inv, acc[db][1] * inv, acc[db][2] * inv, acc[db][3] * inv);
+            }
+        } else if (col_ok && t_begin < ctx_col) {
+            float *p = a.partials + (((size_t)my_row * a.n_q + kvh * G + gh) * S + split) * PS;
 #pragma unroll
             for (int db = 0; db < NDB; ++db)
-                *reinterpret_cast<float4 *>(&acc_lds[(size_t)(wave * 16 + j) * PS + 16 * db + 4 * kg]) = make_float4(acc[db][0], acc[db][1], acc[db][2], acc[db][3]);
-            if (kg == 0) { m_lds[wave][j] = m_run; l_lds[wave][j] = l_run; }
-            __syncthreads();
-            for (int i = tid; i < RP * G * (HD / 4); i += 256) {
-                const int c = i / (HD / 4), d = 4 * (i - c * (HD / 4)), row = r_lo + slot0 * RP + c / G;
-                if (row >= r_hi || t_begin >= info.w + (row - r_lo) + 1) continue;
-                const float m0 = m_lds[0][c], m1 = m_lds[1][c], m2 = m_lds[2][c], m3 = m_lds[3][c];
-                const float M = fmaxf(fmaxf(m0, m1), fmaxf(m2, m3));                // -inf only if every score is -inf
-                const float w0 = m0 > -INFINITY ? __builtin_amdgcn_exp2f(m0 - M) : 0.f, w1 = m1 > -INFINITY ? __builtin_amdgcn_exp2f(m1 - M) : 0.f;
-                const float w2 = m2 > -INFINITY ? __builtin_amdgcn_exp2f(m2 - M) : 0.f, w3 = m3 > -INFINITY ? __builtin_amdgcn_exp2f(m3 - M) : 0.f;
-                const float L = l_lds[0][c] * w0 + l_lds[1][c] * w1 + l_lds[2][c] * w2 + l_lds[3][c] * w3;
-                const float4 a0 = *reinterpret_cast<const float4 *>(&acc_lds[(size_t)(0 * 16 + c) * PS + d]);
-                const float4 a1 = *reinterpret_cast<const float4 *>(&acc_lds[(size_t)(1 * 16 + c) * PS + d]);
-                const float4 a2 = *reinterpret_cast<const float4 *>(&acc_lds[(size_t)(2 * 16 + c) * PS + d]);
-                const float4 a3 = *reinterpret_cast<const float4 *>(&acc_lds[(size_t)(3 * 16 + c) * PS + d]);
-                float4 O;
-                O.x = a0.x * w0 + a1.x * w1 + a2.x * w2 + a3.x * w3;
-                O.y = a0.y * w0 + a1.y * w1 + a2.y * w2 + a3.y * w3;
-                O.z = a0.z * w0 + a1.z * w1 + a2.z * w2 + a3.z * w3;
-                O.w = a0.w * w0 + a1.w * w1 + a2.w * w2 + a3.w * w3;
-                const size_t head = (size_t)row * a.n_q + kvh * G + c % G;
-                if (a.direct) {
-                    const float inv = L > 0.f ? 1.f / L : 0.f;
-                    const size_t oi = a.out_frag ? frag_index(row, (kvh * G + c % G) * HD + d, a.n_q * HD, a.rsh) : head * HD + d;
-                    *reinterpret_cast<float4 *>(a.out + oi) = make_float4(O.x * inv, O.y * inv, O.z * inv, O.w * inv);
-                } else {
-                    float *p = a.partials + (head * S + split) * PS;
-                    *reinterpret_cast<float4 *>(p + 4 + d) = O;
-                    if (d == 0) { p[0] = M; p[1] = L; }
-                }
+                *reinterpret_cast<float4 *>(p + 4 + 16 * db + 4 * kg) = make_float4(acc[db][0], acc[db][1], acc[db][2], acc[db][3]);
+            if (kg == 0) { p[0] = m_run; p[1] = l_run; }
+        }
+    } else {
+        // merge the four waves' states of the slot's 16 columns; the tiles' LDS is free once everybody is here
+        __syncthreads();
+        float (*m_lds)[16] = reinterpret_cast<float (*)[16]>(smem);
+        float (*l_lds)[16] = m_lds + 4;
+        float *acc_lds = reinterpret_cast<float *>(smem + (size_t)2 * 4 * 16 * 4);                   // [4 waves][16 columns][HD + 4]
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+            *reinterpret_cast<float4 *>(&acc_lds[(size_t)(wave * 16 + j) * PS + 16 * db + 4 * kg]) = make_float4(acc[db][0], acc[db][1], acc[db][2], acc[db][3]);
+        if (kg == 0) { m_lds[wave][j] = m_run; l_lds[wave][j] = l_run; }
+        __syncthreads();
+        for (int i = tid; i < RP * G * (HD / 4); i += 256) {
+            const int c = i / (HD / 4), d = 4 * (i - c * (HD / 4)), row = r_lo + slot0 * RP + c / G;
+            if (row >= r_hi || t_begin >= info.w + (row - r_lo) + 1) continue;
+            const float m0 = m_lds[0][c], m1 = m_lds[1][c], m2 = m_lds[2][c], m3 = m_lds[3][c];
+            const float M = fmaxf(fmaxf(m0, m1), fmaxf(m2, m3));                // -inf only if every score is -inf
+            const float w0 = m0 > -INFINITY ? __builtin_amdgcn_exp2f(m0 - M) : 0.f, w1 = m1 > -INFINITY ? __builtin_amdgcn_exp2f(m1 - M) : 0.f;
+            const float w2 = m2 > -INFINITY ? __builtin_amdgcn_exp2f(m2 - M) : 0.f, w3 = m3 > -INFINITY ? __builtin_amdgcn_exp2f(m3 - M) : 0.f;
+            const float L = l_lds[0][c] * w0 + l_lds[1][c] * w1 + l_lds[2][c] * w2 + l_lds[3][c] * w3;
+            const float4 a0 = *reinterpret_cast<const float4 *>(&acc_lds[(size_t)(0 * 16 + c) * PS + d]);
+            const float4 a1 = *reinterpret_cast<const float4 *>(&acc_lds[(size_t)(1 * 16 + c) * PS + d]);
+            const float4 a2 = *reinterpret_cast<const float4 *>(&acc_lds[(size_t)(2 * 16 + c) * PS + d]);
+            const float4 a3 = *reinterpret_cast<const float4 *>(&acc_lds[(size_t)(3 * 16 + c) * PS + d]);
+            float4 O;
+            O.x = a0.x * w0 + a1.x * w1 + a2.x * w2 + a3.x * w3;
+            O.y = a0.y * w0 + a1.y * w1 + a2.y * w2 + a3.y * w3;
+            O.z = a0.z * w0 + a1.z * w1 + a2.z * w2 + a3.z * w3;
+            O.w = a0.w * w0 + a1.w * w1 + a2.w * w2 + a3.w * w3;
+            const size_t head = (size_t)row * a.n_q + kvh * G + c % G;
+            if (info.w + (row - r_lo) + 1 <= C) {
+                const float inv = L > 0.f ? 1.f / L : 0.f;
+                const size_t oi = a.out_frag ? frag_index(row, (kvh * G + c % G) * HD + d, a.n_q * HD, a.rsh) : head * HD + d;
+                *reinterpret_cast<float4 *>(a.out + oi) = make_float4(O.x * inv, O.y * inv, O.z * inv, O.w * inv);
+            } else {
+                float *p = a.partials + (head * S + split) * PS;
+                *reinterpret_cast<float4 *>(p + 4 + d) = O;
+                if (d == 0) { p[0] = M; p[1] = L; }
             }
-            __syncthreads();                                     // (a further slot group would park into this LDS)
         }
     }
 }
@@ -1585,7 +1689,7 @@ __device__ __forceinline__ void attn_combine_unit(const AttnArgs &a, unsigned ch
     static_assert(HD % (4 * DQ) == 0 && 256 % (HD / 4 / DQ) == 0, "whole float4 columns per workgroup");
     constexpr int PS = HD + 4, NQ = HD / 4 / DQ, NSG = 256 / NQ, NLD = (SMAX + NSG - 1) / NSG, HDB = HD / DQ;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int S = a.n_slices;
+    const int S = a.pieces ? a.slice_len[1] : a.n_slices;
     float *w_sh = reinterpret_cast<float *>(smem);                               // [ATT_SMAX]
     float (*red)[HDB] = reinterpret_cast<float (*)[HDB]>(w_sh + ATT_SMAX);       // [NSG][HDB]: 1024 floats
     const float *pbase = a.partials + ((size_t)row * a.n_q + head) * S * PS;
@@ -1593,7 +1697,7 @@ __device__ __forceinline__ void attn_combine_unit(const AttnArgs &a, unsigned ch
     // The records of all S slices are requested together with the row's position (one round trip instead of
     // two dependent ones); a slice past the context holds whatever an earlier call left there and is
     // replaced, never scaled, once the position has arrived.
-    const int bad = a.row_bad[row], pos = a.row_pos[row], n_pos = a.ctx_top ? *a.ctx_top : a.max_ctx;
+    const int bad = a.row_bad[row], pos = a.row_pos[row], len = a.walked ? *a.slice_len : attn_slice_len(a.max_ctx, S);
     constexpr int NPL = SMAX / 64;                          // slices per lane (wave 0)
     float4 buf[NLD];
     float2 mlr[NPL];
@@ -1613,7 +1717,8 @@ __device__ __forceinline__ void attn_combine_unit(const AttnArgs &a, unsigned ch
     }
     __builtin_amdgcn_sched_barrier(0);                      // every request is in flight before anything waits
     // slices that hold context: same slice length as the kernel that wrote the records
-    const int S_act = bad ? 0 : min(S, pos / attn_slice_len(n_pos, S) + 1);
+    const int S_act = bad ? 0 : min(S, pos / len + 1);
+    if (a.walked && S_act == 1) return;                     // k_attn_walk has written this row
 #pragma unroll
     for (int k = 0; k < NLD; ++k)
         if (sg + k * NSG >= S_act) buf[k] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1631,7 +1736,7 @@ __device__ __forceinline__ void attn_combine_unit(const AttnArgs &a, unsigned ch
         float lsum = 0.f;
 #pragma unroll
         for (int k = 0; k < NPL; ++k) {
-            w[k] = ls[k] > 0.f ? (a.base2 ? __builtin_amdgcn_exp2f(ms[k] - M) : __expf(ms[k] - M)) : 0.f;
+            w[k] = ls[k] > 0.f ? (a.walked ? __builtin_amdgcn_exp2f(ms[k] - M) : __expf(ms[k] - M)) : 0.f;
             lsum = fmaf(ls[k], w[k], lsum);
         }
         const float L = wave_sum(lsum);
@@ -1658,17 +1763,18 @@ __device__ __forceinline__ void attn_combine_unit(const AttnArgs &a, unsigned ch
     }
 }
 
-// The merge of a few slices (n_slices <= ATT_SFEW) for many rows: one wave per (row, head), no LDS.  Lane s holds slice s's weight,
-// lane d the channels d, d + 64.  grid ceil(n_rows * n_q / 4), block 256.
-constexpr int ATT_SFEW = 32;
-template <int HD>
+// The merge of a few slices (at most 64) for many rows: one wave per (row, head), no LDS.  Lane s holds slice s's weight, lane d the
+// channels d, d + 64.  grid ceil(n_rows * n_q / 4), block 256.  LIST: behind a list of pieces, where most rows have one slice.
+constexpr int ATT_SFEW = 32;       // slices of a fixed split up to which many rows take it
+template <int HD, bool LIST>
 __global__ void __launch_bounds__(256) k_attn_merge_few(AttnArgs a, int n_rows) {
     constexpr int PS = HD + 4, NC = (HD + 63) / 64, BATCH = 8;
     const int lane = threadIdx.x & 63, item = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (item >= n_rows * a.n_q) return;
-    const int row = item / a.n_q, head = item - row * a.n_q, S = a.n_slices;
+    const int row = item / a.n_q, head = item - row * a.n_q, S = LIST ? a.slice_len[1] : a.n_slices;
     const float *p = a.partials + (size_t)item * S * PS;
-    const int bad = a.row_bad[row], pos = a.row_pos[row], n_pos = a.ctx_top ? *a.ctx_top : a.max_ctx;
+    const int bad = a.row_bad[row], pos = a.row_pos[row], len = a.walked ? *a.slice_len : attn_slice_len(a.max_ctx, S);
+    if (LIST && !bad && pos < len) return;                  // k_attn_walk has written this row: nothing is requested for it
     // (records of slices past the context hold whatever an earlier call left there and are replaced, never scaled)
     const float2 ml = *reinterpret_cast<const float2 *>(p + (size_t)min(lane, S - 1) * PS);
     float v[BATCH][NC];
@@ -1680,9 +1786,10 @@ __global__ void __launch_bounds__(256) k_attn_merge_few(AttnArgs a, int n_rows) 
     };
     load(0);
     __builtin_amdgcn_sched_barrier(0);                      // every request is in flight before anything waits
-    const int S_act = bad ? 0 : min(S, pos / attn_slice_len(n_pos, S) + 1);
+    const int S_act = bad ? 0 : min(S, pos / len + 1);
+    if (a.walked && S_act == 1) return;                     // k_attn_walk has written this row
     const float l = lane < S_act ? ml.y : 0.f, m = l > 0.f ? ml.x : -INFINITY;
-    const float M = wave_max(m), e = l > 0.f ? (a.base2 ? __builtin_amdgcn_exp2f(m - M) : __expf(m - M)) : 0.f;
+    const float M = wave_max(m), e = l > 0.f ? (a.walked ? __builtin_amdgcn_exp2f(m - M) : __expf(m - M)) : 0.f;
     const float L = wave_sum(l * e), w = L > 0.f ? e / L : 0.f;
     float o[NC];
 #pragma unroll

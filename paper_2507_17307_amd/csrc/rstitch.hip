@@ -69,7 +69,7 @@ const char *check_config(const rs_config *c) {
 }
 
 struct Layout {
-    size_t rope_cos, rope_sin, row_slot, row_pos, row_bad, out_row, seq_bad, seq_scale, seq_info, ctx_top, h, qkv_raw, qbuf,
+    size_t rope_cos, rope_sin, row_slot, row_pos, row_bad, out_row, seq_bad, seq_scale, seq_info, slice_len, pieces, h, qkv_raw, qbuf,
         attn_out, act, attn_part, attn_cnt, lm_parts, sync, layer_ptrs, gemm_part, xn32, lm32, total;
     int attn_rows_x_splits;   // capacity of attn_part in (row, split) pairs
     int lm_parts_cap;         // partial states per sequence
@@ -110,7 +110,8 @@ Layout make_layout(const rs_config &c) {
     L.seq_bad = take(c.max_seqs * 4);
     L.seq_scale = take(c.max_seqs * 4);
     L.seq_info = take((size_t)c.max_seqs * 16);
-    L.ctx_top = take(4);
+    L.slice_len = take(8);
+    L.pieces = take((size_t)2 * 16 * (rs::WALK_SLOTS_MAX + rs::WALK_GROUPS_MAX));
     L.h = take((size_t)c.max_rows * c.d_model * 4);
     L.qkv_raw = take((size_t)c.max_rows * qkv * 4);
     L.qbuf = take((size_t)c.max_rows * qdim * 4);
@@ -247,33 +248,17 @@ GemvPlan make_plan(const rs_config &c, int n_cu) {
     return p;
 }
 
+// Caches whose rows do not fit 32-bit offsets stay on the per-row kernel.
+bool walk_rows_fit(int max_ctx, int hd) { return (size_t)max_ctx * hd * 2 < ((size_t)1 << 31); }
+
+// walk: plan_walk() of the call
 template <int HD>
-rs_status launch_attn(AttnArgs &a, int n_splits, int n_kv, int n_rows, int n_seqs, int n_cu, hipStream_t st) {
-    const bool spans = n_rows > n_seqs;
-    const int *ctx_top = a.ctx_top;
-    a.ctx_top = nullptr; a.base2 = 0; a.direct = 0; a.slot_split = 1;
-    const int rp = 16 / (a.n_q / n_kv), one_pass = (a.max_ctx + ATT_BT - 1) / ATT_BT;
-    const int max_slots = (n_rows - n_seqs + 1 + rp - 1) / rp;   // row slots of the longest span there can be
-    const int walk_zs = (max_slots + 3) / 4;                     // workgroups of four waves that hold them
-    const long walk_base = (long)n_kv * n_seqs * walk_zs;
-    // Walk or one pass per workgroup.  While a launch of one-pass workgroups is about one round of the machine, one pass is
-    // the shorter chain (1.5B shape, 2 rows: 5.5 us against 6.2; 7B, 2 / 5 rows, 288 workgroups: 6.2 / 8.3 against 8.1 / 9.5); beyond that
-    // the walk re-uses its row state, leaves fewer records and needs fewer prologues (7B: 9 rows, 576 workgroups: 10.6 against
-    // 13.6; 16 rows 12.0 against 15.7; 8 sequences at 4400 positions 17.6 against 22.1; 14B, 2 rows at 9000: 11.9 against 14.8).
-    // Caches whose rows do not fit 32-bit offsets stay on the per-row kernel.
-    const bool small_rows = (size_t)a.max_ctx * HD * 2 < ((size_t)1 << 31);
-    const bool walk = n_rows > 1 && small_rows && (n_splits < one_pass || one_pass * walk_base > 3L * n_cu / 2);
-    if (walk) {
-        // Slices: one round of two workgroups per CU, rounded down (a few workgroups in a further round cost a whole one:
-        // 14B, 61 rows, 22 / 21 slices of 48 workgroups: 61 / 53 us).  Several sequences with spans: twice as many, because
-        // their contexts and spans differ and part of the workgroups leaves at once (32B, 8 sequences, 29 rows: 95 -> 58 us).
-        const bool share = max_slots == 1;
-        long S = (share || n_seqs == 1 ? 2L : 4L) * n_cu / walk_base;
-        if (S > one_pass) S = one_pass;
-        if (S > n_splits) S = n_splits;
-        if (S < 1) S = 1;
-        n_splits = (int)S;
-        a.slot_split = walk_zs; a.ctx_top = ctx_top; a.base2 = 1; a.direct = !spans && n_splits == 1;
+rs_status launch_attn(AttnArgs &a, const WalkPlan &walk, int n_splits, int n_kv, int n_rows, int n_seqs, int n_cu, hipStream_t st) {
+    const bool spans = n_rows > n_seqs, small_rows = walk_rows_fit(a.max_ctx, HD);
+    const int rp = 16 / (a.n_q / n_kv);
+    a.slot_split = 1; a.n_slices = n_splits;
+    if (walk.walk) {
+        a.walked = 1; a.n_slices = walk.slices; a.direct = walk.direct; a.slot_split = walk.groups;
         constexpr size_t lds = attn_walk_lds_bytes<HD>();
         if (lds > 64 * 1024) {
             static std::atomic<bool> raised{false};       // per instantiation; setting the attribute twice is harmless
@@ -284,8 +269,8 @@ rs_status launch_attn(AttnArgs &a, int n_splits, int n_kv, int n_rows, int n_seq
                 raised = true;
             }
         }
-        const dim3 grid(n_splits, n_kv, n_seqs * walk_zs);
-        if (share) hipLaunchKernelGGL((k_attn_walk<HD, true>), grid, dim3(256), lds, st, a);
+        const dim3 grid = walk.list ? dim3(n_kv, walk.pieces) : dim3(walk.slices, n_kv, n_seqs * walk.groups);
+        if (walk.share) hipLaunchKernelGGL((k_attn_walk<HD, true>), grid, dim3(256), lds, st, a);
         else hipLaunchKernelGGL((k_attn_walk<HD, false>), grid, dim3(256), lds, st, a);
         RS_LAUNCHED("attn_walk");
         if (a.direct) return RS_OK;
@@ -323,15 +308,17 @@ rs_status launch_attn(AttnArgs &a, int n_splits, int n_kv, int n_rows, int n_seq
             hipLaunchKernelGGL((k_attn_partial<HD, false, false>), dim3(n_splits, n_kv, n_rows), dim3(256), attn_lds_bytes<HD>(a.n_q / n_kv), st, a);
         RS_LAUNCHED("attn_partial");
     }
-    a.n_slices = n_splits;
     // the merge is unrolled for 128 slices (contexts up to 8192 positions) or for the most the kernels take
     // HD / 64 workgroups per head, 64 output columns each
     constexpr int DQ = HD / 64 > 0 ? HD / 64 : 1;
     // (a few slices of several rows: one wave per head and row without LDS, 7B shape, 128 rows of 8 slices 15.1 -> 6.7 us, 14B, 61 rows of
     // 10 slices 10.5 -> 6.0; a single row of 32 slices is better off with a workgroup per half head: 3.5 us against 5.0)
-    if (n_rows > 1 && (n_splits <= 16 || (n_splits <= ATT_SFEW && n_rows * a.n_q >= 512)))
-        hipLaunchKernelGGL((k_attn_merge_few<HD>), dim3((n_rows * a.n_q + 3) / 4), dim3(256), 0, st, a, n_rows);
-    else if (n_splits <= 128)
+    const bool few = walk.list ? walk.few : n_rows > 1 && (a.n_slices <= 16 || (a.n_slices <= ATT_SFEW && n_rows * a.n_q >= 512));
+    if (few) {
+        const dim3 grid((n_rows * a.n_q + 3) / 4);
+        if (walk.list) hipLaunchKernelGGL((k_attn_merge_few<HD, true>), grid, dim3(256), 0, st, a, n_rows);
+        else hipLaunchKernelGGL((k_attn_merge_few<HD, false>), grid, dim3(256), 0, st, a, n_rows);
+    } else if (a.n_slices <= 128)
         hipLaunchKernelGGL((k_attn_combine<HD, 128, DQ>), dim3(a.n_q, n_rows, DQ), dim3(256), attn_combine_lds_bytes<HD>(), st, a);
     else
         hipLaunchKernelGGL((k_attn_combine<HD, ATT_SMAX, DQ>), dim3(a.n_q, n_rows, DQ), dim3(256), attn_combine_lds_bytes<HD>(), st, a);
@@ -636,7 +623,7 @@ rs_status forward_persistent(rs_model *m, const int *d_seq_slot, const int *d_to
 // One decoder layer on the FMA kernels for a call of MP (1, 2 or 4) token-row slots: QKV, attention, O-proj,
 // gate/up, down.  Every phase reads the weights once and carries the rows side by side.
 template <int MP, typename Tic, typename Toc>
-rs_status fma_layer(rs_model *m, int l, GemvArgs &g, AttnArgs &aa, int n_rows, int n_splits, int n_seqs, hipStream_t st,
+rs_status fma_layer(rs_model *m, int l, GemvArgs &g, AttnArgs &aa, const WalkPlan &walk, int n_rows, int n_splits, int n_seqs, hipStream_t st,
                     Tic tic, Toc toc) {
     const rs_config &c = m->cfg;
     const Layout &L = m->lay;
@@ -663,9 +650,9 @@ rs_status fma_layer(rs_model *m, int l, GemvArgs &g, AttnArgs &aa, int n_rows, i
     // attention
     tic(RS_PHASE_ATTN, l);
     switch (hd) {
-        case 32: rc = launch_attn<32>(aa, n_splits, c.n_kv_heads, n_rows, n_seqs, m->n_cu, st); break;
-        case 64: rc = launch_attn<64>(aa, n_splits, c.n_kv_heads, n_rows, n_seqs, m->n_cu, st); break;
-        default: rc = launch_attn<128>(aa, n_splits, c.n_kv_heads, n_rows, n_seqs, m->n_cu, st); break;
+        case 32: rc = launch_attn<32>(aa, walk, n_splits, c.n_kv_heads, n_rows, n_seqs, m->n_cu, st); break;
+        case 64: rc = launch_attn<64>(aa, walk, n_splits, c.n_kv_heads, n_rows, n_seqs, m->n_cu, st); break;
+        default: rc = launch_attn<128>(aa, walk, n_splits, c.n_kv_heads, n_rows, n_seqs, m->n_cu, st); break;
     }
     toc(RS_PHASE_ATTN, l);
     if (rc) return rc;
@@ -743,13 +730,20 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
     pa.embed = m->embed;
     pa.row_slot = row_slot; pa.row_pos = row_pos; pa.row_bad = row_bad;
     pa.out_row = m->at<int>(L.out_row); pa.seq_bad = m->at<int>(L.seq_bad); pa.seq_scale = m->at<float>(L.seq_scale);
-    pa.seq_info = m->at<int4>(L.seq_info); pa.ctx_top = m->at<int>(L.ctx_top);
+    pa.seq_info = m->at<int4>(L.seq_info);
     pa.h = h;
-    hipLaunchKernelGGL(k_prepare, dim3(n_rows), dim3(256), 0, st, pa);
-    RS_LAUNCHED("prepare");
-
     // attention launch shape; calls in which some sequence brings several rows share K/V tiles between rows
     const int n_splits = attn_splits(c, L, n_rows);
+    WalkPlan walk{};
+    if (walk_rows_fit(c.max_ctx, hd)) walk = plan_walk(n_rows, n_seqs, c.n_kv_heads, c.n_q_heads / c.n_kv_heads, c.max_ctx, n_splits, m->n_cu);
+    if (walk.walk) pa.slice_len = m->at<int>(L.slice_len);
+    if (walk.list) {
+        pa.pieces = m->at<int4>(L.pieces); pa.n_pieces = walk.pieces; pa.list_slots = walk.slots; pa.list_slices = walk.slices;
+        pa.slot_rows = 16 / (c.n_q_heads / c.n_kv_heads);
+    } else pa.slices = walk.slices;
+    if (walk.list) hipLaunchKernelGGL((k_prepare<true>), dim3(n_rows + 1), dim3(256), 0, st, pa);
+    else hipLaunchKernelGGL((k_prepare<false>), dim3(n_rows), dim3(256), 0, st, pa);
+    RS_LAUNCHED("prepare");
 
     // up to four token rows go through the FMA GEMV kernels (six kernels per layer, rows side by side against one
     // weight stream); more rows go through the matrix-core kernels
@@ -774,7 +768,7 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
         aa.qbuf = m->at<float>(L.qbuf); aa.kcache = m->kv_k; aa.vcache = m->kv_v;
         aa.partials = m->at<float>(L.attn_part);
         aa.out = m->at<float>(L.attn_out);
-        aa.row_pos = row_pos; aa.row_slot = row_slot; aa.row_bad = row_bad; aa.seq_info = m->at<int4>(L.seq_info); aa.ctx_top = m->at<int>(L.ctx_top);
+        aa.row_pos = row_pos; aa.row_slot = row_slot; aa.row_bad = row_bad; aa.seq_info = m->at<int4>(L.seq_info); aa.slice_len = m->at<int>(L.slice_len); aa.pieces = pa.pieces;
         aa.n_q = c.n_q_heads; aa.n_kv = c.n_kv_heads; aa.max_ctx = c.max_ctx; aa.max_seqs = c.max_seqs; aa.layer = l;
 
         if (single) {
@@ -787,9 +781,9 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
             g.qbuf = m->at<float>(L.qbuf); g.kcache = m->kv_k; g.vcache = m->kv_v;
             g.act = m->at<float>(L.act); g.h_out = h;
             switch (mp) {
-                case 1: rc = fma_layer<1>(m, l, g, aa, n_rows, n_splits, n_seqs, st, tic, toc); break;
-                case 2: rc = fma_layer<2>(m, l, g, aa, n_rows, n_splits, n_seqs, st, tic, toc); break;
-                default: rc = fma_layer<4>(m, l, g, aa, n_rows, n_splits, n_seqs, st, tic, toc); break;
+                case 1: rc = fma_layer<1>(m, l, g, aa, walk, n_rows, n_splits, n_seqs, st, tic, toc); break;
+                case 2: rc = fma_layer<2>(m, l, g, aa, walk, n_rows, n_splits, n_seqs, st, tic, toc); break;
+                default: rc = fma_layer<4>(m, l, g, aa, walk, n_rows, n_splits, n_seqs, st, tic, toc); break;
             }
             if (rc) return rc;
         } else {
@@ -824,9 +818,9 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
             aa.out_frag = 1; aa.rsh = rsh;
             tic(RS_PHASE_ATTN, l);
             switch (hd) {
-                case 32: rc = launch_attn<32>(aa, n_splits, c.n_kv_heads, n_rows, n_seqs, m->n_cu, st); break;
-                case 64: rc = launch_attn<64>(aa, n_splits, c.n_kv_heads, n_rows, n_seqs, m->n_cu, st); break;
-                default: rc = launch_attn<128>(aa, n_splits, c.n_kv_heads, n_rows, n_seqs, m->n_cu, st); break;
+                case 32: rc = launch_attn<32>(aa, walk, n_splits, c.n_kv_heads, n_rows, n_seqs, m->n_cu, st); break;
+                case 64: rc = launch_attn<64>(aa, walk, n_splits, c.n_kv_heads, n_rows, n_seqs, m->n_cu, st); break;
+                default: rc = launch_attn<128>(aa, walk, n_splits, c.n_kv_heads, n_rows, n_seqs, m->n_cu, st); break;
             }
             toc(RS_PHASE_ATTN, l);
             if (rc) return rc;

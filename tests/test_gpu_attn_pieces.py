@@ -1,0 +1,88 @@
+"""Walked attention of several sequences, whose pieces the row table lists (attn_plan.h): unlike contexts, balanced spans, spans
+beside decode rows, rows with one slice beside rows with many, rejected sequences; against the oracle."""
+import pytest
+import torch
+
+import test_gpu_attn_walk as walk
+
+pytestmark = pytest.mark.gpu
+
+# name, query heads, KV heads, head_dim, max_ctx, contexts, rows of every sequence (None: one each)
+CASES = [
+    ("one_long_context_g2_hd32", 8, 4, 32, 4608, [70 - i for i in range(39)] + [4500], None),
+    ("decode_17_passes", 8, 4, 32, 1088, [(53 * i) % 1088 for i in range(100)], None),                      # just past the fixed split
+    ("decode_16_passes_one_slice", 8, 4, 32, 1024, [(53 * i) % 1024 for i in range(100)], None),
+    ("more_than_128_slices", 8, 1, 32, 12800, [12000, 9000, 63], None),
+    ("pairs_of_rows_g7_hd128", 14, 2, 128, 2048, [2046, 63, 64, 62, 0, 127, 128, 1000] + [20 * i for i in range(16)], [2] * 24),
+    ("balanced_spans_g7_hd128", 14, 2, 128, 2048, [1900, 1800, 1700, 1600, 1500, 1400], [8] * 6),
+    ("span_beside_decode_rows", 12, 4, 64, 2048, [1024] + [100 * i for i in range(15)], [64] + [1] * 15),
+    ("rows_on_both_sides_of_a_slice_edge", 6, 2, 128, 4608, [60, 120, 190, 250, 4000, 57], [10] * 6),
+]
+
+
+@pytest.mark.parametrize("name,nq,nkv,hd,max_ctx,ctx,rows", CASES, ids=[c[0] for c in CASES])
+def test_listed_pieces_match_the_oracle(name, nq, nkv, hd, max_ctx, ctx, rows):
+    walk.test_walked_attention_matches_the_oracle(name, nq, nkv, hd, max_ctx, ctx, rows)
+
+
+@pytest.mark.parametrize("bad_seq", [0, 3, 5])
+@pytest.mark.parametrize("fault", ["slot", "position", "token", "same slot"])
+def test_a_rejected_sequence_of_a_catch_up_leaves_the_others_alone(bad_seq, fault):
+    """Six spans on a long cache, one of them (the first, one inside, the last) out of range: its record is flagged, its
+    cache rows are not written, and the others are what they are without it."""
+    import paper_2507_17307_amd as P
+    import workloads as W
+    from oracle import decoder, router
+    from parity import check_invocation
+    from workloads.shapes import ModelShape
+    shape = ModelShape("rejected", 1, 256, 14, 2, 128, 256, 512, tied_lm_head=False)
+    w = W.make_weights(shape, 37, 1)
+    spans, ctx, max_ctx = [3, 9, 1, 8, 2, 20], [4000, 63, 128, 2500, 4606, 70], 4608
+    n = len(spans)
+    gpu = P.Model(w.to("cuda"), max_ctx=max_ctx, max_seqs=n + 1, max_rows=64)
+    ref = decoder.OracleModel(w, max_ctx, n_slots=n)
+    g = torch.Generator().manual_seed(11)
+    for i in range(n):
+        for which, cache in (("k", ref.k_cache), ("v", ref.v_cache)):
+            x = torch.randn(1, shape.n_kv_heads, ctx[i], shape.head_dim, generator=g).bfloat16()
+            gpu.kv_view(which)[:, i, :, :ctx[i]] = x.cuda()
+            cache[:, i, :, :ctx[i]] = x.double()
+    toks = [W.rng.randint(37, 60 + i, 0, spans[i], shape.vocab).tolist() for i in range(n)]
+    slots, pos, given = list(range(n)), list(ctx), [list(t) for t in toks]
+    rejected = {bad_seq}
+    if fault == "slot":
+        slots[bad_seq] = n + 1
+    elif fault == "position":
+        pos[bad_seq] = max_ctx - spans[bad_seq] + 1
+    elif fault == "token":
+        given[bad_seq][-1] = shape.vocab
+    else:
+        slots[bad_seq] = slots[(bad_seq + 1) % n]                 # both that name the slot are rejected
+        rejected.add((bad_seq + 1) % n)
+    before = gpu.kv_view("k").clone()
+    got, lg = gpu.catchup_prefill(given, pos, 0.6, P.RS_SLM, [2.0] * n, slots, want_logits=True)
+    torch.cuda.synchronize()
+    for i in range(n):
+        if i in rejected:
+            assert got[i].flags & P.FLAG_BADARG and got[i].token == -1, (i, got[i])
+            assert torch.equal(gpu.kv_view("k")[:, i], before[:, i]), i
+        else:
+            want = ref.forward(toks[i], ctx[i], slot=i, logit_scale=2.0)["logits"]
+            check_invocation(got[i], lg[i], want, 0.6, router.SLM, where=f"sequence {i} beside a rejected one")
+
+
+@pytest.mark.parametrize("table", [[1, 5, 9, 12], [0, 5, 5, 12], [0, 9, 5, 12], [0, 5, 9, 11], [0, 5, 9, 13], [0, -4, 9, 12]])
+def test_a_malformed_offset_table_rejects_every_sequence(table):
+    import paper_2507_17307_amd as P
+    import workloads as W
+    from workloads.shapes import ModelShape
+    shape = ModelShape("malformed", 1, 256, 14, 2, 128, 256, 512, tied_lm_head=False)
+    gpu = P.Model(W.make_weights(shape, 37, 1).to("cuda"), max_ctx=4608, max_seqs=3, max_rows=16)
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device="cuda")  # noqa: E731
+    before = gpu.kv_view("k").clone()
+    out = P.binding.new_route_out(3)
+    P.rs_catchup_prefill(gpu.handle, 3, 12, i32([0, 1, 2]), i32(list(range(12))), i32(table), i32([4000, 70, 0]), None, 0.6, P.RS_SLM, out, None)
+    torch.cuda.synchronize()
+    for r in P.binding.read_route_out(out):
+        assert r.flags & P.FLAG_BADARG and r.token == -1
+    assert torch.equal(gpu.kv_view("k"), before)
