@@ -215,10 +215,25 @@ __device__ __forceinline__ float dot8f(const uint4 &w, const float4 &xa, const f
     acc = fmaf(bf16_lo(w.z), xb.x, acc); acc = fmaf(bf16_hi(w.z), xb.y, acc); acc = fmaf(bf16_lo(w.w), xb.z, acc); return fmaf(bf16_hi(w.w), xb.w, acc);
 }
 
-// NU: pieces of a row of W1 per lane (8 channels each) and output channels per thread, at least d / 512.  dynamic LDS: d floats
+// the two outputs, and the decision in the record (one thread writes)
+__device__ __forceinline__ void router_decide(const RouterPlusArgs &a, float o0, float o1) {
+    const int b = blockIdx.x;
+    if (threadIdx.x != 0) return;
+    o0 += bf16_to_f32(a.b_head[0]);
+    o1 += bf16_to_f32(a.b_head[1]);
+    if (a.logits) { a.logits[2 * b] = o0; a.logits[2 * b + 1] = o1; }
+    rs_route_out rec = a.out[b];
+    const uint32_t untouchable = RS_FLAG_NONFINITE | RS_FLAG_BADARG | RS_FLAG_ABORTED;
+    if (a.active == RS_SLM && (rec.flags & RS_FLAG_HI) && !(rec.flags & untouchable) && !(o1 > o0)) {
+        rec.flags = (rec.flags | RS_FLAG_ACCEPT | RS_FLAG_ROUTER_STAY) & ~RS_FLAG_NEXT_LLM;
+        a.out[b] = rec;
+    }
+}
+
+// NU: pieces of a row of W1 per lane (8 channels each) and output channels per thread, at least d / 512: widths up to 5120.
+// dynamic LDS: d floats
 template <int NU>
 __global__ void __launch_bounds__(ROUTER_THREADS) k_router_plus(RouterPlusArgs a) {
-    constexpr bool AHEAD = NU <= 10;
     extern __shared__ __align__(16) unsigned char smem[];
     float *x = reinterpret_cast<float *>(smem);
     __shared__ __align__(16) float t_sh[ROUTER_RMAX];
@@ -242,14 +257,14 @@ __global__ void __launch_bounds__(ROUTER_THREADS) k_router_plus(RouterPlusArgs a
         if (tid + ROUTER_THREADS * k < d) x[tid + ROUTER_THREADS * k] = xin[k];
     __syncthreads();
     for (int blk = 0; blk < ROUTER_BLOCKS; ++blk) {
-        // the first 8 of the r values of this thread's rows of W2, and their biases (widths above 5120 have no registers for them)
+        // the first 8 of the r values of this thread's rows of W2, and their biases
         u32x4_t w2[NU];
         float b2[NU];
 #pragma unroll
         for (int k = 0; k < NU; ++k) {
             const int i = min(tid + ROUTER_THREADS * k, d - 1);
-            if (AHEAD) w2[k] = *reinterpret_cast<const u32x4_t *>(a.w2[blk] + (size_t)i * r);
-            if (AHEAD) b2[k] = bf16_to_f32(a.b2[blk][i]);
+            w2[k] = *reinterpret_cast<const u32x4_t *>(a.w2[blk] + (size_t)i * r);
+            b2[k] = bf16_to_f32(a.b2[blk][i]);
         }
         // t = gelu(W1 x + b1): wave w takes the rows w, w + 8, ... (r is a multiple of 8); lanes stride over d in pieces of 8
         for (int row = wave; row < r; row += ROUTER_WAVES) {
@@ -274,7 +289,6 @@ __global__ void __launch_bounds__(ROUTER_THREADS) k_router_plus(RouterPlusArgs a
         for (int k = 0; k < NU; ++k) {
             const int i = tid + ROUTER_THREADS * k;
             if (i >= d) continue;
-            if (!AHEAD) { w2[k] = *reinterpret_cast<const u32x4_t *>(a.w2[blk] + (size_t)i * r); b2[k] = bf16_to_f32(a.b2[blk][i]); }
             float acc = dot8f(make_uint4(w2[k].x, w2[k].y, w2[k].z, w2[k].w), *reinterpret_cast<const float4 *>(t_sh), *reinterpret_cast<const float4 *>(t_sh + 4), b2[k]);
             const uint4 *wp = reinterpret_cast<const uint4 *>(a.w2[blk] + (size_t)i * r);
             for (int c = 1; c < (r >> 3); ++c) acc = dot8f(wp[c], *reinterpret_cast<const float4 *>(t_sh + 8 * c), *reinterpret_cast<const float4 *>(t_sh + 8 * c + 4), acc);
@@ -306,17 +320,95 @@ __global__ void __launch_bounds__(ROUTER_THREADS) k_router_plus(RouterPlusArgs a
         o1 = fmaf(h1[k], y, o1);
     }
     const float2 o = block_sum2(o0, o1, red);
-    o0 = o.x; o1 = o.y;
-    if (tid != 0) return;
-    o0 += bf16_to_f32(a.b_head[0]);
-    o1 += bf16_to_f32(a.b_head[1]);
-    if (a.logits) { a.logits[2 * b] = o0; a.logits[2 * b + 1] = o1; }
-    rs_route_out rec = a.out[b];
-    const uint32_t untouchable = RS_FLAG_NONFINITE | RS_FLAG_BADARG | RS_FLAG_ABORTED;
-    if (a.active == RS_SLM && (rec.flags & RS_FLAG_HI) && !(rec.flags & untouchable) && !(o1 > o0)) {
-        rec.flags = (rec.flags | RS_FLAG_ACCEPT | RS_FLAG_ROUTER_STAY) & ~RS_FLAG_NEXT_LLM;
-        a.out[b] = rec;
+    router_decide(a, o.x, o.y);
+}
+
+// Wider ones: the same phases over parts of ROUTER_PART pieces of 512 channels, of which only the first part's weights are requested a
+// phase ahead.  (With one part of 24 pieces for every width the kernel above spilled 123 registers: d 5128, r 8, 1 / 128 sequences
+// 53 / 74 us a call, now 30 / 32; 8192, 16: 86 / 118 -> 59 / 62; 12288, 64: 491 / 506 -> 445 / 478.)  dynamic LDS: d floats
+constexpr int ROUTER_PART = 8;
+__global__ void __launch_bounds__(ROUTER_THREADS) k_router_plus_wide(RouterPlusArgs a) {
+    constexpr int NU = ROUTER_PART;
+    extern __shared__ __align__(16) unsigned char smem[];
+    float *x = reinterpret_cast<float *>(smem);
+    __shared__ __align__(16) float t_sh[ROUTER_RMAX];
+    __shared__ float2 red[ROUTER_WAVES];
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int d = a.d, r = a.r, n_ch = d >> 3, parts = (d + ROUTER_THREADS * NU - 1) / (ROUTER_THREADS * NU);
+    const float *src = a.hidden + (size_t)(a.gather ? a.gather[b] : b) * a.ld_hidden;
+    auto channel = [&](int part, int k) { return tid + ROUTER_THREADS * (k + NU * part); };       // output channel k of this thread
+    auto load_w1 = [&](int blk, int row, int part, u32x4_t (&w)[NU]) {
+        const u32x4_t *wp = reinterpret_cast<const u32x4_t *>(a.w1[blk] + (size_t)row * d);
+#pragma unroll
+        for (int u = 0; u < NU; ++u) w[u] = wp[min(lane + 64 * (u + NU * part), n_ch - 1)];
+    };
+    auto load_w2 = [&](int blk, int part, u32x4_t (&w)[NU], float (&bias)[NU]) {
+#pragma unroll
+        for (int k = 0; k < NU; ++k) {
+            const int i = min(channel(part, k), d - 1);
+            w[k] = *reinterpret_cast<const u32x4_t *>(a.w2[blk] + (size_t)i * r);
+            bias[k] = bf16_to_f32(a.b2[blk][i]);
+        }
+    };
+    auto dot_w1 = [&](int part, const u32x4_t (&w)[NU], float acc) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            const int c = lane + 64 * (u + NU * part);
+            if (c < n_ch) acc = dot8f(make_uint4(w[u].x, w[u].y, w[u].z, w[u].w), *reinterpret_cast<const float4 *>(x + 8 * c), *reinterpret_cast<const float4 *>(x + 8 * c + 4), acc);
+        }
+        return acc;
+    };
+    auto add_w2 = [&](int blk, int part, const u32x4_t (&w)[NU], const float (&bias)[NU]) {
+#pragma unroll
+        for (int k = 0; k < NU; ++k) {
+            const int i = channel(part, k);
+            if (i >= d) continue;
+            float acc = dot8f(make_uint4(w[k].x, w[k].y, w[k].z, w[k].w), *reinterpret_cast<const float4 *>(t_sh), *reinterpret_cast<const float4 *>(t_sh + 4), bias[k]);
+            const uint4 *wp = reinterpret_cast<const uint4 *>(a.w2[blk] + (size_t)i * r);
+            for (int c = 1; c < (r >> 3); ++c) acc = dot8f(wp[c], *reinterpret_cast<const float4 *>(t_sh + 8 * c), *reinterpret_cast<const float4 *>(t_sh + 8 * c + 4), acc);
+            x[i] += acc;
+        }
+    };
+    u32x4_t w1[NU];
+    load_w1(0, wave, 0, w1);
+    for (int i = tid; i < d; i += ROUTER_THREADS) x[i] = src[i];
+    __syncthreads();
+    for (int blk = 0; blk < ROUTER_BLOCKS; ++blk) {
+        u32x4_t w2[NU];
+        float b2[NU];
+        load_w2(blk, 0, w2, b2);
+        for (int row = wave; row < r; row += ROUTER_WAVES) {
+            const float b1 = bf16_to_f32(a.b1[blk][row]);
+            if (row != wave) load_w1(blk, row, 0, w1);
+            float acc = dot_w1(0, w1, 0.f);
+#pragma unroll 1
+            for (int part = 1; part < parts; ++part) { load_w1(blk, row, part, w1); acc = dot_w1(part, w1, acc); }
+            acc = wave_sum(acc);
+            if (lane == 0) {
+                const float z = acc + b1;
+                t_sh[row] = 0.5f * z * (1.0f + erff(z * 0.70710678118654752f));
+            }
+        }
+        load_w1(min(blk + 1, ROUTER_BLOCKS - 1), wave, 0, w1);
+        __syncthreads();
+        add_w2(blk, 0, w2, b2);
+#pragma unroll 1
+        for (int part = 1; part < parts; ++part) { load_w2(blk, part, w2, b2); add_w2(blk, part, w2, b2); }
+        __syncthreads();
     }
+    float s = 0.f, q = 0.f, o0 = 0.f, o1 = 0.f;
+    for (int i = tid; i < d; i += ROUTER_THREADS) s += x[i];
+    const float mu = block_sum2(s, 0.f, red).x / (float)d;
+    for (int i = tid; i < d; i += ROUTER_THREADS) { const float dv = x[i] - mu; q = fmaf(dv, dv, q); }
+    const float inv = 1.0f / sqrtf(block_sum2(q, 0.f, red).x / (float)d + a.ln_eps);
+#pragma unroll 4
+    for (int i = tid; i < d; i += ROUTER_THREADS) {
+        const float y = (x[i] - mu) * inv * bf16_to_f32(a.ln_gain[i]) + bf16_to_f32(a.ln_bias[i]);
+        o0 = fmaf(bf16_to_f32(a.w_head[i]), y, o0);
+        o1 = fmaf(bf16_to_f32(a.w_head[d + i]), y, o1);
+    }
+    const float2 o = block_sum2(o0, o1, red);
+    router_decide(a, o.x, o.y);
 }
 
 }  // namespace rs

@@ -1260,7 +1260,7 @@ rs_status rs_route_plus(rs_model *m, const float *d_hidden, int32_t n_seqs, cons
     if (m) { a.hidden = m->at<float>(m->lay.h); a.ld_hidden = m->cfg.d_model; a.gather = m->at<int>(m->lay.out_row); }
     else { a.hidden = d_hidden; a.ld_hidden = w->d; a.gather = nullptr; }
     a.active = active; a.out = d_out; a.logits = d_router_logits;
-    // instantiated for the pieces of 512 channels of the widths in use (1536, 2048, 3584, 5120) and of the widest
+    // instantiated for the pieces of 512 channels of the widths in use (1536, 2048, 3584, 5120); wider ones take several parts
     const int nu = (w->d + 511) / 512;
     const dim3 grid(n_seqs), block(rs::ROUTER_THREADS);
     const size_t lds = (size_t)w->d * 4;
@@ -1269,7 +1269,7 @@ rs_status rs_route_plus(rs_model *m, const float *d_hidden, int32_t n_seqs, cons
     else if (nu <= 4) hipLaunchKernelGGL((rs::k_router_plus<4>), grid, block, lds, st, a);
     else if (nu <= 7) hipLaunchKernelGGL((rs::k_router_plus<7>), grid, block, lds, st, a);
     else if (nu <= 10) hipLaunchKernelGGL((rs::k_router_plus<10>), grid, block, lds, st, a);
-    else hipLaunchKernelGGL((rs::k_router_plus<24>), grid, block, lds, st, a);
+    else hipLaunchKernelGGL(rs::k_router_plus_wide, grid, block, lds, st, a);
     RS_LAUNCHED("router_plus");
     return RS_OK;
 }
