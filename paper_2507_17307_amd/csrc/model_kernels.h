@@ -1771,7 +1771,7 @@ __global__ void __launch_bounds__(256, 2) k_attn_walk(AttnArgs a) {
     l_run += __shfl_xor(l_run, 16, RS_WAVE);
     l_run += __shfl_xor(l_run, 32, RS_WAVE);
     if constexpr (!SHARE) {
-        if (col_ok && ctx_col <= C) {
+        if (col_ok && ctx_col <= C && t_begin == 0) {             // (a later slice of the group holds nothing of this row)
             const float inv = l_run > 0.f ? 1.f / l_run : 0.f;
 #pragma unroll
             for (int db = 0; db < NDB; ++db) {

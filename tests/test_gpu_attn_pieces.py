@@ -25,6 +25,44 @@ def test_listed_pieces_match_the_oracle(name, nq, nkv, hd, max_ctx, ctx, rows):
     walk.test_walked_attention_matches_the_oracle(name, nq, nkv, hd, max_ctx, ctx, rows)
 
 
+@pytest.mark.parametrize("name,nq,nkv,hd,max_ctx,ctx,rows", [
+    ("slice_edges_g7_hd128", 14, 2, 128, 4608, [60, 120, 190, 250, 4000, 57], [10] * 6),
+    ("slice_edges_two_passes_g6_hd128", 12, 2, 128, 1024, [127, 125, 120, 255, 63] + [(71 * i) % 1000 for i in range(35)], [5, 4, 3, 5, 2] + [2] * 35),
+    ("slice_edges_g8_hd64", 8, 1, 64, 9216, [9000, 60, 3000], [60, 10, 56]),
+    ("one_sequence_g7_hd128", 14, 2, 128, 4608, [50], [128]),
+], ids=lambda v: v if isinstance(v, str) else "")
+def test_every_row_of_a_span_is_right_at_slice_edges(name, nq, nkv, hd, max_ctx, ctx, rows):
+    """Spans whose first rows have one slice and whose last ones more: the outputs of all rows, through the K/V rows that the
+    second layer makes of them (logits come from the last row only)."""
+    import paper_2507_17307_amd as P
+    import workloads as W
+    from oracle import decoder, router
+    from parity import check_invocation
+    from workloads.shapes import ModelShape
+    shape = ModelShape(name, 2, 256, nq, nkv, hd, 256, 512, tied_lm_head=False)
+    w = W.make_weights(shape, 31, 1)
+    n = len(ctx)
+    gpu = P.Model(w.to("cuda"), max_ctx=max_ctx, max_seqs=n, max_rows=128)
+    ref = decoder.OracleModel(w, max_ctx, n_slots=n)
+    g = torch.Generator().manual_seed(7)
+    for i in range(n):
+        for which, cache in (("k", ref.k_cache), ("v", ref.v_cache)):
+            x = torch.randn(2, nkv, ctx[i], hd, generator=g).bfloat16()
+            gpu.kv_view(which)[:, i, :, :ctx[i]] = x.cuda()
+            cache[:, i, :, :ctx[i]] = x.double()
+    toks = [W.rng.randint(31, 50 + i, 0, rows[i], shape.vocab).tolist() for i in range(n)]
+    got, lg = gpu.catchup_prefill(toks, ctx, 0.6, P.RS_SLM, [2.0] * n, list(range(n)), want_logits=True)
+    torch.cuda.synchronize()
+    for i in range(n):
+        want = ref.forward(toks[i], ctx[i], slot=i, logit_scale=2.0)["logits"]
+        check_invocation(got[i], lg[i], want, 0.6, router.SLM, where=f"{name} sequence {i}")
+        for which, cache in (("k", ref.k_cache), ("v", ref.v_cache)):
+            a = gpu.kv_view(which)[1, i, :, ctx[i]:ctx[i] + rows[i]].cpu().double()
+            b = cache[1, i, :, ctx[i]:ctx[i] + rows[i]].double()
+            # bf16 values of nearly equal fp32 sums: one rounding step (2^-8 of the value) apart at most, and a little for values near 0
+            assert float(((a - b).abs() - b.abs() * 2.0 ** -7).max()) <= 1e-3, (name, which, i)
+
+
 @pytest.mark.parametrize("bad_seq", [0, 3, 5])
 @pytest.mark.parametrize("fault", ["slot", "position", "token", "same slot"])
 def test_a_rejected_sequence_of_a_catch_up_leaves_the_others_alone(bad_seq, fault):
