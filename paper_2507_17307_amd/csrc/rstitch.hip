@@ -4,7 +4,6 @@
 // cos/sin table, which is input-independent and built once per model.
 #include <hip/hip_runtime.h>
 
-#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -16,6 +15,7 @@
 
 #include "../../include/rstitch.h"
 #include "../../include/rstitch_aids.h"
+#include "device_once.h"
 #include "device_utils.h"
 #include "router.h"
 #include "model_kernels.h"
@@ -181,19 +181,26 @@ int clamp_blocks(int want, int n_tiles_per_wg_unit) {
     return want < 1 ? 1 : want;
 }
 
+// Dynamic LDS above the default 64 KB has to be allowed per kernel and per device (a process may hold models on several).
+template <auto KERNEL>
+rs_status allow_lds(size_t bytes, const char *name) {
+    static DeviceOnce raised;
+    if (bytes <= 64 * 1024) return RS_OK;
+    int dev = -1;
+    RS_HIP(hipGetDevice(&dev));
+    if (raised.done(dev)) return RS_OK;
+    const hipError_t e = hipFuncSetAttribute((const void *)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e != hipSuccess) return fail(RS_EHIP, "raising the LDS limit of %s: %s", name, hipGetErrorString(e));
+    raised.mark(dev);
+    return RS_OK;
+}
+
 // `blocks` workgroups share the phase; every workgroup takes a contiguous range of tiles
 template <int MODE, int RT, int KS, int UNR, int MP, int PRE = 0>
 rs_status launch_gemv_mp(GemvArgs &a, int blocks, hipStream_t st, const char *name) {
     const size_t lds = gemv_lds_bytes<MP>(a.K);
-    if (lds > 64 * 1024) {
-        static std::atomic<bool> raised{false};           // per instantiation; setting the attribute twice is harmless
-        if (!raised) {
-            hipError_t e = hipFuncSetAttribute((const void *)k_gemv<MODE, RT, KS, UNR, MP, PRE>,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024 - 4096);
-            if (e != hipSuccess) return fail(RS_EHIP, "raising the LDS limit of %s: %s", name, hipGetErrorString(e));
-            raised = true;
-        }
-    }
+    // (the most a K of this kernel needs, once for all of them)
+    if (rs_status rc = allow_lds<k_gemv<MODE, RT, KS, UNR, MP, PRE>>(lds > 64 * 1024 ? 160 * 1024 - 4096 : lds, name)) return rc;
     if (gemv_seg<MP>(a.K) != a.K && KS != 4) return fail(RS_EINVAL, "internal: segmented K needs the split-K launch");
     hipLaunchKernelGGL((k_gemv<MODE, RT, KS, UNR, MP, PRE>), dim3(blocks), dim3(256), lds, st, a);
     RS_LAUNCHED(name);
@@ -260,15 +267,7 @@ rs_status launch_attn(AttnArgs &a, const WalkPlan &walk, int n_splits, int n_kv,
     if (walk.walk) {
         a.walked = 1; a.n_slices = walk.slices; a.direct = walk.direct; a.slot_split = walk.groups;
         constexpr size_t lds = attn_walk_lds_bytes<HD>();
-        if (lds > 64 * 1024) {
-            static std::atomic<bool> raised{false};       // per instantiation; setting the attribute twice is harmless
-            if (!raised) {
-                hipError_t e = hipFuncSetAttribute((const void *)k_attn_walk<HD, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k_attn_walk<HD, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                if (e != hipSuccess) return fail(RS_EHIP, "raising the LDS limit of attn_walk: %s", hipGetErrorString(e));
-                raised = true;
-            }
-        }
+        if (rs_status rc = walk.share ? allow_lds<k_attn_walk<HD, true>>(lds, "attn_walk") : allow_lds<k_attn_walk<HD, false>>(lds, "attn_walk")) return rc;
         const dim3 grid = walk.list ? dim3(n_kv, walk.pieces) : dim3(walk.slices, n_kv, n_seqs * walk.groups);
         if (walk.share) hipLaunchKernelGGL((k_attn_walk<HD, true>), grid, dim3(256), lds, st, a);
         else hipLaunchKernelGGL((k_attn_walk<HD, false>), grid, dim3(256), lds, st, a);
@@ -335,15 +334,7 @@ template <int MODE, int NB, int R, int NW>
 rs_status launch_gemm_r(GemmArgs &a, int blocks, hipStream_t st, const char *name) {
     constexpr size_t lds = gemm_lds_bytes<MODE, NB, R, NW>();
     static_assert(lds <= 76 * 1024, "two workgroups per CU must fit");
-    if (lds > 64 * 1024) {
-        static std::atomic<bool> raised{false};           // per instantiation; setting the attribute twice is harmless
-        if (!raised) {
-            hipError_t e = hipFuncSetAttribute((const void *)k_gemm_rows<MODE, NB, R, NW>,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return fail(RS_EHIP, "raising the LDS limit of %s: %s", name, hipGetErrorString(e));
-            raised = true;
-        }
-    }
+    if (rs_status rc = allow_lds<k_gemm_rows<MODE, NB, R, NW>>(lds, name)) return rc;
     hipLaunchKernelGGL((k_gemm_rows<MODE, NB, R, NW>), dim3(blocks), dim3(NW * 64), lds, st, a);
     RS_LAUNCHED(name);
     return RS_OK;
