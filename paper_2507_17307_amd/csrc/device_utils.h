@@ -166,17 +166,6 @@ __device__ __forceinline__ SoftState shfl_xor_state(const SoftState &a, int o) {
     return b;
 }
 
-// all lanes end up with the merged state of the lanes that share the bits of
-// the lane id NOT covered by `span` (span = 64: whole wave; span = 16: groups of 16)
-__device__ __forceinline__ void wave_merge_state(SoftState &a, int span = RS_WAVE) {
-    for (int o = span >> 1; o > 0; o >>= 1) {
-        SoftState b = shfl_xor_state(a, o);
-        // merge in a fixed order (lower lane first) so that both partners compute the same bits
-        if ((threadIdx.x & o) == 0) { a.merge(b); }
-        else { b.merge(a); a = b; }
-    }
-}
-
 // What a workgroup (or wave) leaves in global memory for the final merge: 32 bytes.
 struct __align__(16) SoftPartial {
     float m, z, s, best;

@@ -1,5 +1,7 @@
-"""Calls of 3 .. 33 rows on the matrix-core kernels: the activation buffers between them hold blocks of 1, 2, 4, 8 or 16 rows in
-operand order (frag_index), so every row count around those block sizes, as a span and as decode rows, against the oracle."""
+"""Calls of 3 .. 128 rows on the matrix-core kernels: the activation buffers between them hold blocks of 1, 2, 4, 8 or 16 rows in
+operand order (frag_index), so every row count around those block sizes, as a span and as decode rows, against the oracle.
+The first shape's projections have too few column tiles for k_gemm_tile (tile_fills) and stay on k_gemm_rows, whatever the row
+count; those of the second take it from 17 rows on, with two waves per row block up to 32 rows, four waves up to 64, eight above."""
 import pytest
 import torch
 
@@ -51,3 +53,30 @@ def test_lm_head_of_many_sequences_with_thirteen_column_tiles(n):
     for i in range(n):
         want = ref.forward([toks[i]], 0, slot=i, logit_scale=scales[i])["logits"]
         check_invocation(got[i], lg[i], want, 0.6, router.SLM, where=f"sequence {i} of {n}")
+
+
+TILE_SHAPE = ModelShape("tile_kernel", 1, 3072, 24, 8, 128, 10240, 1000, tied_lm_head=False)
+
+
+@pytest.fixture(scope="module")
+def tile_weights():
+    return W.make_weights(TILE_SHAPE, 47, 1)
+
+
+@pytest.mark.parametrize("rows", [16, 17, 32, 33, 64, 65, 128])
+def test_row_counts_around_the_wave_arrangements_of_the_tile_kernel(rows, tile_weights):
+    import paper_2507_17307_amd as P
+    w = tile_weights
+    gpu = P.Model(w.to("cuda"), max_ctx=136, max_seqs=rows, max_rows=rows)
+    ref = decoder.OracleModel(w, 136, n_slots=rows)
+    toks = W.rng.randint(47, rows, 0, 2 * rows, TILE_SHAPE.vocab).tolist()
+    got, lg = gpu.catchup_prefill([toks[:rows]], [0], 0.6, P.RS_SLM, [2.0], [rows - 1], want_logits=True)
+    torch.cuda.synchronize()
+    check_invocation(got[0], lg[0], ref.forward(toks[:rows], 0, slot=rows - 1, logit_scale=2.0)["logits"], 0.6, router.SLM, where=f"span of {rows}")
+    pos = [0] * (rows - 1) + [rows]
+    scales = [1.0 + i % 5 for i in range(rows)]
+    got, lg = gpu.decode_step(toks[rows:], pos, 0.6, P.RS_SLM, scales, want_logits=True)
+    torch.cuda.synchronize()
+    for i in sorted({0, 15, min(16, rows - 1), rows // 2, rows - 1}):          # rows at the edges of 16-row blocks
+        want = ref.forward([toks[rows + i]], pos[i], slot=i, logit_scale=scales[i])["logits"]
+        check_invocation(got[i], lg[i], want, 0.6, router.SLM, where=f"{rows} sequences, {i}")
