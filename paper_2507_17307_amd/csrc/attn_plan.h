@@ -90,15 +90,6 @@ inline WalkPlan plan_walk(int n_rows, int n_seqs, int n_kv, int heads_per_kv, in
     return p;
 }
 
-// Calls of spans that do not walk, one 64-position pass per workgroup: k_attn_partial_rows, whose waves fetch their own tiles, or
-// k_attn_span, whose workgroups share one through LDS.  The former only for up to four rows that fit one row slot per sequence and
-// only past one workgroup per CU, where the shared tile costs a second turn on some CUs (per layer, per-wave / shared: 7B, 2 rows
-// on a 4608-position cache 13.2 / 15.2 us, 1.5B, 2 x 2 rows 12.9 / 15.1, 14B, 3 rows on 3072 14.1 / 15.8; below that and with more rows the
-// shared tile: 7B, 3 rows on 4608 17.3 / 16.5).
-inline bool rows_kernel(int n_rows, int n_seqs, int n_kv, int heads_per_kv, int n_splits, int n_cu) {
-    return n_rows <= 4 && n_rows <= 16 / heads_per_kv * n_seqs && (long)n_splits * n_kv * n_seqs > n_cu;
-}
-
 // Passes per slice of a list, from the passes of all groups and of the longest one.  The first length gives every workgroup of a
 // round its average share; sum of ceil(p / length) is then at most slots + groups.  Up to twice that length is tried
 // for one that fits one round (a workgroup that starts when others end would add its whole slice).

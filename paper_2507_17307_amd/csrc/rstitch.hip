@@ -273,11 +273,6 @@ rs_status launch_attn(AttnArgs &a, const WalkPlan &walk, int n_splits, int n_kv,
         else hipLaunchKernelGGL((k_attn_walk<HD, false>), grid, dim3(256), lds, st, a);
         RS_LAUNCHED("attn_walk");
         if (a.direct) return RS_OK;
-    } else if (spans && small_rows && rows_kernel(n_rows, n_seqs, n_kv, a.n_q / n_kv, n_splits, n_cu)) {
-        a.n_rows = n_rows;
-        const int slots = (n_rows + rp - 1) / rp;                // one wave each, two at most
-        hipLaunchKernelGGL((k_attn_partial_rows<HD>), dim3(n_splits, n_kv, 1), dim3(64 * slots), 0, st, a);
-        RS_LAUNCHED("attn_partial_rows");
     } else if (spans && small_rows) {
         // several rows per sequence: rows share K/V tiles through the columns of the matrix-core tiles
         const long base = (long)n_splits * n_kv * n_seqs;
