@@ -90,6 +90,16 @@ inline WalkPlan plan_walk(int n_rows, int n_seqs, int n_kv, int heads_per_kv, in
     return p;
 }
 
+// Calls of spans that do not walk take k_attn_span, one 64-position pass per workgroup.  As it schedules best, its registers fill a
+// SIMD and a CU holds one workgroup, so that a launch with more workgroups than CUs has a second turn.  Few rows that fit one
+// row slot per sequence are short enough for that turn to show; they take a build of which a CU holds two (six layers, contexts of
+// 0.2 / 0.8 / 1.0 of the cache, one / two workgroups per CU, us: 7B, 2 rows, 288 workgroups 656 / 666 / 686 and 660 / 671 / 672; 1.5B,
+// 2 x 2 rows 336 / 342 / 361 and 338 / 348 / 347; workgroups past the context leave at once).  From five rows on the shared
+// CU costs more than the turn (7B, 5 rows at 0.8: 773 and 783).
+inline bool span_pairs(int n_rows, int n_seqs, int n_kv, int heads_per_kv, int n_splits, int n_cu) {
+    return n_rows <= 4 && n_rows <= 16 / heads_per_kv * n_seqs && (long)n_splits * n_kv * n_seqs > n_cu;
+}
+
 // Passes per slice of a list, from the passes of all groups and of the longest one.  The first length gives every workgroup of a
 // round its average share; sum of ceil(p / length) is then at most slots + groups.  Up to twice that length is tried
 // for one that fits one round (a workgroup that starts when others end would add its whole slice).

@@ -1249,8 +1249,9 @@ __global__ void __launch_bounds__(256, ONEPASS ? 3 : 1) k_attn_partial(AttnArgs 
 template <int HD>
 __host__ __device__ constexpr size_t attn_span_lds_bytes() { return (size_t)64 * (HD * 2 + 16) + (size_t)HD * (64 * 2 + 16); }
 
-template <int HD>
-__global__ void __launch_bounds__(256) k_attn_span(AttnArgs a) {
+// MINW: workgroups per CU that the registers must allow, see span_pairs (attn_plan.h)
+template <int HD, int MINW>
+__global__ void __launch_bounds__(256, MINW) k_attn_span(AttnArgs a) {
     constexpr int NDS = HD / 32, NDB = HD / 16, PS = HD + 4;
     constexpr int KP = HD * 2 + 16, VP = 64 * 2 + 16;           // LDS row pitches in bytes (padded against bank conflicts)
     constexpr int KQ = 64 * HD * 2 / 4096, VQ = HD * 128 / 4096; // 16-byte loads per thread for each tile
@@ -1683,13 +1684,14 @@ template <int HD>
 __host__ __device__ constexpr size_t attn_combine_lds_bytes() { return (size_t)(ATT_SMAX + 1024) * 4; }
 
 // SMAX: the slice count this instantiation is unrolled for (n_slices <= SMAX <= ATT_SMAX, a multiple of 64)
-template <int HD, int SMAX = ATT_SMAX, int DQ = 1>
+// LIST: behind a list of pieces.
+template <int HD, int SMAX = ATT_SMAX, int DQ = 1, bool LIST = false>
 __device__ __forceinline__ void attn_combine_unit(const AttnArgs &a, unsigned char *smem, int head, int row, int dq = 0) {
     static_assert(SMAX % 64 == 0 && SMAX <= ATT_SMAX, "whole slices per lane, inside the LDS weights array");
     static_assert(HD % (4 * DQ) == 0 && 256 % (HD / 4 / DQ) == 0, "whole float4 columns per workgroup");
     constexpr int PS = HD + 4, NQ = HD / 4 / DQ, NSG = 256 / NQ, NLD = (SMAX + NSG - 1) / NSG, HDB = HD / DQ;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int S = a.pieces ? a.slice_len[1] : a.n_slices;
+    const int S = LIST ? a.slice_len[1] : a.n_slices;
     float *w_sh = reinterpret_cast<float *>(smem);                               // [ATT_SMAX]
     float (*red)[HDB] = reinterpret_cast<float (*)[HDB]>(w_sh + ATT_SMAX);       // [NSG][HDB]: 1024 floats
     const float *pbase = a.partials + ((size_t)row * a.n_q + head) * S * PS;
@@ -1811,10 +1813,10 @@ __global__ void __launch_bounds__(256) k_attn_merge_few(AttnArgs a, int n_rows) 
 }
 
 // grid (n_q_heads, n_rows, DQ)
-template <int HD, int SMAX, int DQ>
+template <int HD, int SMAX, int DQ, bool LIST>
 __global__ void __launch_bounds__(256) k_attn_combine(AttnArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
-    attn_combine_unit<HD, SMAX, DQ>(a, smem, blockIdx.x, blockIdx.y, blockIdx.z);
+    attn_combine_unit<HD, SMAX, DQ, LIST>(a, smem, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 }  // namespace rs

@@ -111,7 +111,6 @@ Layout make_layout(const rs_config &c) {
     L.seq_scale = take(c.max_seqs * 4);
     L.seq_info = take((size_t)c.max_seqs * 16);
     L.slice_len = take(8);
-    L.pieces = take((size_t)2 * 16 * (rs::WALK_SLOTS_MAX + rs::WALK_GROUPS_MAX));
     L.h = take((size_t)c.max_rows * c.d_model * 4);
     L.qkv_raw = take((size_t)c.max_rows * qkv * 4);
     L.qbuf = take((size_t)c.max_rows * qdim * 4);
@@ -129,6 +128,7 @@ Layout make_layout(const rs_config &c) {
     L.lm32 = take(seqs_pad * c.d_model * 4);                            // normalised last rows for the LM head
     L.sync = take(2 * sizeof(rs::SyncState));          // [0] single-kernel step, [1] device-resident loop
     L.layer_ptrs = take((size_t)c.n_layers * sizeof(rs::LayerPtrs));
+    L.pieces = take((size_t)2 * 16 * (rs::WALK_SLOTS_MAX + rs::WALK_GROUPS_MAX));
     L.total = o;
     return L;
 }
@@ -286,7 +286,10 @@ rs_status launch_attn(AttnArgs &a, const WalkPlan &walk, int n_splits, int n_kv,
             if (cost_best < 0 || cost < cost_best) { cost_best = cost; zs_best = zs; }
         }
         a.slot_split = zs_best;
-        hipLaunchKernelGGL((k_attn_span<HD>), dim3(n_splits, n_kv, n_seqs * zs_best), dim3(256), attn_span_lds_bytes<HD>(), st, a);
+        const dim3 grid(n_splits, n_kv, n_seqs * zs_best);
+        constexpr int PAIR = HD == 128 ? 2 : 1;                  // (smaller heads leave room for two by themselves)
+        if (span_pairs(n_rows, n_seqs, n_kv, a.n_q / n_kv, n_splits, n_cu)) hipLaunchKernelGGL((k_attn_span<HD, PAIR>), grid, dim3(256), attn_span_lds_bytes<HD>(), st, a);
+        else hipLaunchKernelGGL((k_attn_span<HD, 1>), grid, dim3(256), attn_span_lds_bytes<HD>(), st, a);
         RS_LAUNCHED("attn_span");
     } else {
         // requesting every slice's K and V before the context length is known reads the rows' whole caches up to
@@ -317,10 +320,15 @@ rs_status launch_attn(AttnArgs &a, const WalkPlan &walk, int n_splits, int n_kv,
         const dim3 grid((n_rows * a.n_q + 3) / 4);
         if (walk.list) hipLaunchKernelGGL((k_attn_merge_few<HD, true>), grid, dim3(256), 0, st, a, n_rows);
         else hipLaunchKernelGGL((k_attn_merge_few<HD, false>), grid, dim3(256), 0, st, a, n_rows);
-    } else if (a.n_slices <= 128)
-        hipLaunchKernelGGL((k_attn_combine<HD, 128, DQ>), dim3(a.n_q, n_rows, DQ), dim3(256), attn_combine_lds_bytes<HD>(), st, a);
-    else
-        hipLaunchKernelGGL((k_attn_combine<HD, ATT_SMAX, DQ>), dim3(a.n_q, n_rows, DQ), dim3(256), attn_combine_lds_bytes<HD>(), st, a);
+    } else {
+        const dim3 grid(a.n_q, n_rows, DQ);
+        constexpr size_t lds = attn_combine_lds_bytes<HD>();
+        if (walk.list) {
+            if (a.n_slices <= 128) hipLaunchKernelGGL((k_attn_combine<HD, 128, DQ, true>), grid, dim3(256), lds, st, a);
+            else hipLaunchKernelGGL((k_attn_combine<HD, ATT_SMAX, DQ, true>), grid, dim3(256), lds, st, a);
+        } else if (a.n_slices <= 128) hipLaunchKernelGGL((k_attn_combine<HD, 128, DQ, false>), grid, dim3(256), lds, st, a);
+        else hipLaunchKernelGGL((k_attn_combine<HD, ATT_SMAX, DQ, false>), grid, dim3(256), lds, st, a);
+    }
     RS_LAUNCHED("attn_combine");
     return RS_OK;
 }

@@ -15,6 +15,9 @@ extern "C" void plan(int n_rows, int n_seqs, int n_kv, int heads, int max_ctx, i
 }
 extern "C" int first_len(int total, int longest, int slots, int slices) { return rs::walk_first_len(total, longest, slots, slices); }
 extern "C" int try_len(int first, int k) { return rs::walk_try_len(first, k); }
+extern "C" int pairs(int n_rows, int n_seqs, int n_kv, int heads, int n_splits, int n_cu) {
+    return rs::span_pairs(n_rows, n_seqs, n_kv, heads, n_splits, n_cu);
+}
 extern "C" int tries() { return rs::WALK_TRIES; }
 extern "C" int slots_max() { return rs::WALK_SLOTS_MAX; }
 extern "C" int groups_max() { return rs::WALK_GROUPS_MAX; }
@@ -127,3 +130,14 @@ def test_every_pass_is_in_one_piece_and_the_pieces_fit_their_list(lib):
             assert len(parts) <= p.slices
         assert len(per_group) == sum(-(-s // (4 * (16 // heads))) for s in spans)
     assert listed > 500
+
+
+@pytest.mark.parametrize("rows,seqs,n_kv,heads,max_ctx,pairs", [
+    (2, 1, 4, 7, 4608, True), (2, 1, 4, 7, 4096, False), (3, 1, 4, 7, 4608, False), (5, 1, 4, 7, 4608, False), (3, 1, 8, 5, 3072, True),
+    (4, 1, 8, 5, 3072, False), (3, 2, 2, 6, 4608, True), (4, 2, 2, 6, 4608, True), (2, 1, 2, 6, 4608, False), (2, 1, 2, 6, 9216, True)])
+def test_few_rows_past_one_workgroup_per_cu_share_cus(lib, rows, seqs, n_kv, heads, max_ctx, pairs):
+    """Calls of two to four rows in one row slot per sequence that are between one and one and a half workgroups per CU."""
+    p = Plan()
+    lib.plan(rows, seqs, n_kv, heads, max_ctx, max_ctx // 64, 256, ctypes.byref(p))
+    assert not p.walk
+    assert bool(lib.pairs(rows, seqs, n_kv, heads, max_ctx // 64, 256)) == pairs

@@ -124,3 +124,14 @@ def test_a_malformed_offset_table_rejects_every_sequence(table):
     for r in P.binding.read_route_out(out):
         assert r.flags & P.FLAG_BADARG and r.token == -1
     assert torch.equal(gpu.kv_view("k"), before)
+
+
+@pytest.mark.parametrize("name,nq,nkv,hd,max_ctx,ctx,rows", [
+    ("two_pairs_g7_hd128", 14, 2, 128, 4608, [4400, 70], [2, 2]),
+    ("one_and_two_rows_g7_hd128", 14, 2, 128, 4608, [100, 4606], [1, 2]),
+    ("three_rows_g5_hd64", 10, 2, 64, 8448, [8383], [3]),
+    ("four_rows_g4_hd32", 16, 4, 32, 5120, [62], [4]),
+], ids=lambda v: v if isinstance(v, str) else "")
+def test_few_rows_past_one_workgroup_per_cu_match_the_oracle(name, nq, nkv, hd, max_ctx, ctx, rows):
+    """k_attn_span built for two workgroups per CU: two to four rows, more workgroups than CUs but too few to walk."""
+    walk.test_walked_attention_matches_the_oracle(name, nq, nkv, hd, max_ctx, ctx, rows)
