@@ -411,10 +411,12 @@ __global__ void __launch_bounds__(GEMM_NW * 64) k_gemm_rows(GemmArgs a) {
 // registers) come straight from global memory because no other wave needs them.  One barrier per window, and it is the
 // bare instruction behind a wait for the LDS accesses only: __syncthreads() carries a fence that waits for every
 // outstanding load, i.e. for the windows requested ahead, and a window would cost a full memory round trip.
-// What bounds it (7B gate/up at 128 rows, 272 MB: 112 us; without any of the loads 72, without products 68, W alone 50, matrix
-// cores alone 61): the CU's load path takes W and X one after the other, 20 + 32 KB per window, and its requests
-// stall the waves that also issue the products.  Before the operand-order activations and the pipeline over groups of
-// tiles: gate/up 119, LM head of 128 sequences 548 -> 486, down 51 -> 41, QKV 32.6 -> 23.0.
+// What bounds it (7B gate/up at 128 rows, 272 MB; in a series of ablations at 114 us: matrix cores alone 61, with LDS reads and
+// splits 72, W alone 50, X alone 37, W and X without products 68 .. 81): the CU's load path takes W and X one after the other, 20
+// + 32 KB per window, and its requests stall the waves that also issue the products.
+// Measured (7B shape, 128 rows, kernel trace, the last 20 of 30 passes; the first passes after an idle GPU take up to 15 % longer),
+// before the operand-order activations and the pipeline over groups of tiles -> with them: gate/up 108 -> 100 us, LM head of
+// 128 sequences 503 -> 437 with ten column tiles per workgroup and 423 with thirteen, down 51 -> 41, QKV 32.6 -> 23.0.
 // X costs (workgroups) x (rows) x K x 4 bytes of L2 traffic, which is why a workgroup takes as many column
 // tiles as the launch can afford (launch_gemm_tile picks CT and the split of K over workgroups so that the
 // workgroups are close to a whole number of rounds of the machine).
@@ -542,6 +544,8 @@ __global__ void __launch_bounds__(NW * 64, MODE == G_LMHEAD ? 2 : 1) k_gemm_tile
     // LDS, the W rows of the next step go into the other LDS buffer during the step's first group, and the barrier stands
     // before the step's last group, whose operands are in registers by then; the last group covers the first reads of
     // the next step.
+    // (LM head, ten tiles on four waves, two workgroups per CU: three windows spill three registers, two spill none, and calls of
+    // 17 .. 48 sequences on the 7B shape are 4 - 7 us slower with two.)
     constexpr int DEPTH = MODE == G_LMHEAD && CT > 10 ? 2 : 3;
     uint4 wr[DEPTH][WQ];
     float4 xb[DEPTH][NS][2];

@@ -401,7 +401,7 @@ rs_status launch_gemm_nb(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_
     }
 }
 
-// Launch of k_gemm_tile (33 .. 128 token rows).  CT (column tiles per workgroup) and, for the modes that leave partial
+// Launch of k_gemm_tile (17 .. 128 token rows).  CT (column tiles per workgroup) and, for the modes that leave partial
 // sums, the split of K are picked so that the workgroups come as close as possible to a whole number of rounds of the
 // machine with one workgroup per CU (each workgroup streams its share of W at the rate a CU can draw, so a round that
 // fills a fraction of the CUs costs a whole round); ties go to the larger CT (less X traffic) and the smaller split.
@@ -417,7 +417,7 @@ rs_status launch_gemm_tile_ct(GemmArgs &a, int blocks, hipStream_t st, const cha
 struct TilePlan { int ct, ks; double eff; };
 
 // wide: also 13 tiles, the most whose operands fit the registers of eight waves (LM head of more than 64 sequences: X is read once
-// per workgroup, 128 sequences on the 7B shape 581 -> 529 us; with four waves, two workgroups per CU, 10 tiles are the better ones)
+// per workgroup, 128 sequences on the 7B shape 437 -> 423 us a kernel; with four waves, two workgroups per CU, 10 tiles are the better ones)
 TilePlan plan_gemm_tile(bool gateup, bool split, int n_tiles, int n_win, int n_cu, bool wide = false) {
     static const int ct_gu[] = {5, 4, 3, 2}, ct_part[] = {13, 10, 8, 7, 6, 4};
     TilePlan best{0, 1, -1.0};
