@@ -135,3 +135,39 @@ def test_a_malformed_offset_table_rejects_every_sequence(table):
 def test_few_rows_past_one_workgroup_per_cu_match_the_oracle(name, nq, nkv, hd, max_ctx, ctx, rows):
     """k_attn_span built for two workgroups per CU: two to four rows, more workgroups than CUs but too few to walk."""
     walk.test_walked_attention_matches_the_oracle(name, nq, nkv, hd, max_ctx, ctx, rows)
+
+
+def test_replayed_calls_list_the_pieces_of_their_own_contexts():
+    """A call whose buffers repeat is replayed from a graph: the pieces have to follow the positions that the buffers hold at that
+    time.  Contexts of two kinds in turn, with eager work in between, against plain launches (the legacy stream)."""
+    import paper_2507_17307_amd as P
+    import workloads as W
+    from workloads.shapes import ModelShape
+    shape = ModelShape("replays", 2, 256, 14, 2, 128, 256, 512, tied_lm_head=False)
+    n, max_ctx = 24, 4608
+    gpu = P.Model(W.make_weights(shape, 39, 1).to("cuda"), max_ctx=max_ctx, max_seqs=n, max_rows=n)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    gpu.kv_k.normal_(generator=g)
+    gpu.kv_v.normal_(generator=g)
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device="cuda")  # noqa: E731
+    contexts = [i32([4500] + [70] * (n - 1)), i32([64 * i + 1000 for i in range(n)])]
+    slot, tok, pos = i32(list(range(n))), i32([7 * i % 512 for i in range(n)]), i32([0] * n)
+    out, logits = P.binding.new_route_out(n), torch.zeros(n, shape.vocab, device="cuda")
+    side = torch.cuda.Stream()
+
+    def call(ctx, stream):
+        pos.copy_(ctx)
+        logits.zero_()
+        torch.cuda.synchronize()
+        P.rs_decode_step(gpu.handle, n, slot, tok, pos, None, 0.6, P.RS_SLM, out, logits, stream)
+        torch.cuda.synchronize()
+        return logits.clone()
+
+    # a call of one kind writes K/V rows inside the other kind's contexts: after two passes over them the caches no longer change
+    for _ in range(2):
+        for c in contexts:
+            call(c, 0)
+    want = [call(c, 0) for c in contexts]
+    assert not torch.equal(want[0], want[1])
+    for k in range(8):                                        # plain, captured, replays
+        assert torch.equal(call(contexts[k % 2], side), want[k % 2]), k
