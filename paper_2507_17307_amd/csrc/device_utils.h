@@ -138,6 +138,25 @@ struct SoftState {
             z += e; s = fmaf(d, e, s);
         }
     }
+    // the values v[k] with indices i[k], larger than all before; ok[k] false: none.  One look at the maximum, then four
+    // exponentials that do not depend on each other.
+    __device__ __forceinline__ void push4(const float (&v)[4], const int (&i)[4], const bool (&ok)[4]) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (!ok[k]) continue;
+            if (!(fabsf(v[k]) <= 3.0e38f)) bad = 1;                // NaN or +-Inf: the record says so, whatever the sums hold
+            if (v[k] > best) { best = v[k]; idx = i[k]; }
+        }
+        if (best > m) {
+            if (z > 0.f) { const float d = m - best, e = expf(d); s = e > 0.f ? e * (s + d * z) : 0.f; z *= e; }
+            m = best;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const float d = ok[k] ? v[k] - m : 0.f, e = ok[k] ? expf(d) : 0.f;
+            z += e; s = fmaf(e > 0.f ? d : 0.f, e, s);
+        }
+    }
     __device__ __forceinline__ void merge(const SoftState &o) {
         bad |= o.bad;
         if (o.best > best || (o.best == best && o.idx < idx)) { best = o.best; idx = o.idx; }

@@ -161,6 +161,7 @@ struct GemmArgs {
                                           //      workgroups (same weights; ids arranged so that they meet in one XCD's L2)
     int ksplit; size_t part_stride;       // > 1: K is split over workgroups too; split ks writes its partial sums to
     float *part;                          //      part[ks * part_stride + m * N + n] (QKV, O-proj, down) and the consumer adds them up
+    int win_per_split, win_extra;         // k_gemm_ring: k windows of a split, the first win_extra splits take one more
     float *h_out; int ld_h;               // residual accumulate
     int d_ffn;
     const float *seq_scale; SoftPartial *parts; float *logits; int n_parts;   // LM head
@@ -397,253 +398,6 @@ __global__ void __launch_bounds__(GEMM_NW * 64) k_gemm_rows(GemmArgs a) {
             for (int w = 1; w < GEMM_NW; ++w) s0.merge(from_partial(sp[w * 16 + i16]));
             a.parts[(size_t)lm_row * a.n_parts + part_id] = to_partial(s0);
         }
-    }
-}
-
-// ------------------------------------------------------------------------------------------------
-// k_gemm_tile: the same products for 17 .. 128 token rows, one workgroup per block of output columns.
-// A workgroup owns CT tiles of 16 output columns (gate/up: CT gate tiles and the CT matching up tiles) and ALL token rows:
-// wave w of NW (four up to 64 rows, eight up to 128) holds the rows 16 w .. 16 w + 15 against every column of the workgroup
-// (CS = 2: two waves share a row block and take half of the columns each), so nothing has to be summed across waves and W
-// is read from HBM once per call, whatever the row count.  Per 64-element k window the waves fetch the window's W
-// rows together (whole 128-byte row pieces, into registers, three windows ahead), park them in one of two
-// LDS buffers and every wave reads all of them back in A-operand layout; its X pieces (fp32, split into the three planes in
-// registers) come straight from global memory because no other wave needs them.  One barrier per window, and it is the
-// bare instruction behind a wait for the LDS accesses only: __syncthreads() carries a fence that waits for every
-// outstanding load, i.e. for the windows requested ahead, and a window would cost a full memory round trip.
-// What bounds it (7B gate/up at 128 rows, 272 MB; in a series of ablations at 114 us: matrix cores alone 61, with LDS reads and
-// splits 72, W alone 50, X alone 37, W and X without products 68 .. 81): the CU's load path takes W and X one after the other, 20
-// + 32 KB per window, and its requests stall the waves that also issue the products.
-// Measured (7B shape, 128 rows, kernel trace, the last 20 of 30 passes; the first passes after an idle GPU take up to 15 % longer),
-// before the operand-order activations and the pipeline over groups of tiles -> with them: gate/up 108 -> 100 us, LM head of
-// 128 sequences 503 -> 437 with ten column tiles per workgroup and 423 with thirteen, down 51 -> 41, QKV 32.6 -> 23.0.
-// X costs (workgroups) x (rows) x K x 4 bytes of L2 traffic, which is why a workgroup takes as many column
-// tiles as the launch can afford (launch_gemm_tile picks CT and the split of K over workgroups so that the
-// workgroups are close to a whole number of rounds of the machine).
-// Modes: G_GATEUP (whole K, SwiGLU epilogue into the activation planes), G_PART (K split ksplit >= 1
-// ways over workgroups, raw partial sums part[ks][row][n] for the next kernel to add up in a fixed order) and
-// G_LMHEAD (whole K; scaled logits feed each row's single-pass softmax state, one partial per row and workgroup).
-// ------------------------------------------------------------------------------------------------
-constexpr int G_PART = 5;
-
-constexpr int TILE_PAD = 16;                      // bytes added to a parked row of k_gemm_tile against LDS bank conflicts (48 measured the same)
-
-template <int MODE, int CT>
-__host__ __device__ constexpr size_t gemm_tile_lds_bytes() {
-    return (size_t)2 * ((MODE == G_GATEUP) ? 2 : 1) * CT * 16 * (128 + TILE_PAD);
-}
-
-template <int MODE, int CT, int NW = 4, int CS = 1>
-__global__ void __launch_bounds__(NW * 64, MODE == G_LMHEAD ? 2 : 1) k_gemm_tile(GemmArgs a) {
-    static_assert(MODE == G_GATEUP || MODE == G_PART || MODE == G_LMHEAD, "gate/up, raw partial sums or the LM head");
-    static_assert(NW == 4 || NW == 8, "four or eight waves");
-    constexpr int NT = (MODE == G_GATEUP) ? 2 : 1;
-    constexpr int NS = GEMM_KW / 32;
-    constexpr int PITCH = 128 + TILE_PAD;                     // bytes per parked row (padded against LDS bank conflicts)
-    constexpr int WROWS = NT * CT * 16;                       // W rows of a step (one 64-element window of K)
-    constexpr int RPR = 8 * NW;                               // rows per round of 16-byte loads of the whole workgroup
-    constexpr int WQ = (WROWS + RPR - 1) / RPR;               // loads per thread and step
-    constexpr size_t BUF = (size_t)WROWS * PITCH;
-    constexpr int RB = NW / CS;                               // waves that differ in their rows; CS waves share a row block and
-    constexpr int CTH = (CT + CS - 1) / CS;                   // split the workgroup's column tiles, CTH each (the last may get fewer)
-    static_assert(NW % CS == 0, "whole column splits");
-    constexpr int NTC = NT * CTH;                             // 16-column tiles of a wave
-    constexpr int NCH = (NTC + 4) / 5;                        // a k step's A operands are read in NCH groups of CH tiles
-    constexpr int CH = (NTC + NCH - 1) / NCH, NGR = NS * NCH; // groups per step (even)
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int i16 = lane & 15, g = lane >> 4;
-    const int rb = wave % RB, ct0 = (wave / RB) * CTH;        // this wave's row block and first column tile
-    const int lrow = tid / 8, lchunk = tid % 8;               // W load role: row RPR q + lrow of the step, bytes 16 lchunk ..
-    const int K = a.K;
-    const int n_out = (MODE == G_GATEUP) ? a.d_ffn : a.N;
-    const int n_tiles = (n_out + 15) / 16, n_groups = (n_tiles + CT - 1) / CT;
-    const int KSP = a.ksplit > 1 ? a.ksplit : 1;
-    const int n_st = K / GEMM_KW;                             // steps over the whole of K
-    const int unit = blockIdx.x;                              // one unit per workgroup
-    if (unit >= n_groups * KSP) return;
-    const int grp = unit / KSP, ksp = unit - grp * KSP;
-    const int s_lo = (int)(((long long)n_st * ksp) / KSP), s_hi = (int)(((long long)n_st * (ksp + 1)) / KSP);
-    const int n0 = grp * CT * 16;
-    if (s_hi <= s_lo) return;                                 // (the launch never splits K finer than its steps)
-
-    // W rows this thread fetches: step row j < CT * 16 is output column n0 + j (gate), the others the matching up rows
-    const uint16_t *wp[WQ];
-    bool wok[WQ];
-#pragma unroll
-    for (int q = 0; q < WQ; ++q) {
-        const int j = RPR * q + lrow;
-        wok[q] = j < WROWS;
-        const int jj = wok[q] ? j : 0, half = jj / (CT * 16), col = jj - half * (CT * 16);
-        const int row = min(n0 + col, n_out - 1) + (half ? a.d_ffn : 0);
-        wp[q] = a.W + (size_t)row * K + lchunk * 8;
-    }
-    // token rows of this wave; a row past the call's rows (inside the padding of the buffer) holds anything: its products
-    // fill matrix-core columns that belong to no row and are never stored
-    const int m = rb * 16 + i16;
-    const float *xp = a.X32 + (size_t)rb * 16 * K + lane * 4;
-    f32x4_t acc[NT][CTH];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-        for (int ct = 0; ct < CTH; ++ct) acc[nt][ct] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-
-    // a step past the last is replaced by the last (fetched again, never used): requests are unconditional
-    auto request_w = [&](int st, uint4 (&wr)[WQ]) {
-        const int k0 = min(st, s_hi - 1) * GEMM_KW;
-#pragma unroll
-        for (int q = 0; q < WQ; ++q) wr[q] = load_stream(reinterpret_cast<const uint4 *>(wp[q] + k0));
-    };
-    // X arrives as fp32 (8 consecutive k per lane and k step: two 16-byte loads, each a contiguous kilobyte over the wave) and is split into the three bf16 planes here: 4 bytes per element through
-    // the CU's load path instead of 6
-    auto request_x = [&](int st, float4 (&xb)[NS][2]) {
-        const int k0 = min(st, s_hi - 1) * GEMM_KW;
-#pragma unroll
-        for (int s_ = 0; s_ < NS; ++s_) {
-            const float *q = xp + (size_t)(k0 + 32 * s_) * 16;
-            xb[s_][0] = *reinterpret_cast<const float4 *>(q); xb[s_][1] = *reinterpret_cast<const float4 *>(q + 256);
-        }
-    };
-    auto park = [&](int buf, const uint4 (&wr)[WQ]) {
-        unsigned char *base = smem + (size_t)buf * BUF;
-#pragma unroll
-        for (int q = 0; q < WQ; ++q)
-            if (wok[q]) *reinterpret_cast<uint4 *>(base + (size_t)(RPR * q + lrow) * PITCH + lchunk * 16) = wr[q];
-    };
-    // group q of a step: tiles CH c .. of k step s_ (c = q % NCH, s_ = q / NCH); tile i of a wave is column tile ct0 + i % CTH
-    // of gate (i < CTH) or up (a tile past the workgroup's last repeats it; its products are dropped)
-    auto read_a = [&](int buf, int q, bf16x8_t (&A)[CH]) {
-        const unsigned char *base = smem + (size_t)buf * BUF;
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            const int ti = (q % NCH) * CH + i;
-            if (ti < NTC)
-                A[i] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(
-                    base + (size_t)(((ti / CTH) * CT + min(ct0 + ti % CTH, CT - 1)) * 16 + i16) * PITCH + (4 * (q / NCH) + g) * 16));
-        }
-    };
-    auto planes = [&](const float4 (&x)[2], bf16x8_t (&B)[3]) {
-        const float xv[8] = {x[0].x, x[0].y, x[0].z, x[0].w, x[1].x, x[1].y, x[1].z, x[1].w};
-        split3(xv, B);
-    };
-    // planes outermost (smallest first), so that consecutive matrix-core instructions write different accumulators
-    auto multiply = [&](int q, const bf16x8_t (&A)[CH], const bf16x8_t (&B)[3]) {
-#pragma unroll
-        for (int pl = 2; pl >= 0; --pl)
-#pragma unroll
-            for (int i = 0; i < CH; ++i) {
-                const int ti = (q % NCH) * CH + i;
-                if (ti < NTC) acc[ti / CTH][ti % CTH] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[i], B[pl], acc[ti / CTH][ti % CTH], 0, 0, 0);
-            }
-    };
-
-    // Register slots: the W rows and X pieces of DEPTH steps are in flight, requested together.  Loads return in the order
-    // of their requests, so a wave that waits for an X piece also waits for every W row requested before it, and W slots
-    // beyond the X slots hold nothing that is still in flight.  Two to six slots measured within 3 % of each other.
-    // Software pipeline: while a group of tiles is multiplied, the A operands of the next group are on their way from
-    // LDS, the W rows of the next step go into the other LDS buffer during the step's first group, and the barrier stands
-    // before the step's last group, whose operands are in registers by then; the last group covers the first reads of
-    // the next step.
-    // (LM head, ten tiles on four waves, two workgroups per CU: three windows spill three registers, two spill none, and calls of
-    // 17 .. 48 sequences on the 7B shape are 4 - 7 us slower with two.)
-    constexpr int DEPTH = MODE == G_LMHEAD && CT > 10 ? 2 : 3;
-    uint4 wr[DEPTH][WQ];
-    float4 xb[DEPTH][NS][2];
-    int buf = 0;
-    if (rb * 16 < a.M) {
-        bf16x8_t A[2][CH], B[NS][3];
-#pragma unroll
-        for (int v = 0; v < DEPTH; ++v) { request_w(s_lo + v, wr[v]); request_x(s_lo + v, xb[v]); }
-        park(0, wr[0]);
-        lds_barrier();
-        read_a(0, 0, A[0]);
-        planes(xb[0][0], B[0]);
-        for (int st = s_lo; st < s_hi; st += DEPTH) {
-#pragma unroll
-            for (int u = 0; u < DEPTH; ++u) {
-                if (st + u >= s_hi) break;
-#pragma unroll
-                for (int q = 0; q < NGR; ++q) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (q + 1 < NGR) read_a(buf, q + 1, A[(q + 1) & 1]);
-                    else { lds_barrier(); read_a(buf ^ 1, 0, A[0]); }
-                    if (q == 0) {
-                        park(buf ^ 1, wr[(u + 1) % DEPTH]);
-                        planes(xb[u][1], B[1]);
-                        request_w(st + u + DEPTH, wr[u]);
-                        request_x(st + u + DEPTH, xb[u]);
-                    }
-                    if (q == NGR - 1) planes(xb[(u + 1) % DEPTH][0], B[0]);
-                    multiply(q, A[q & 1], q == NGR - 1 ? B[1] : B[q / NCH]);
-                }
-                buf ^= 1;
-            }
-        }
-    } else {
-        // a wave whose 16-row block lies past the call's rows only helps to fetch and park W: same steps, same barriers,
-        // no activation requests and no products (they would take load-path and matrix-core time from the waves with rows)
-#pragma unroll
-        for (int v = 0; v < DEPTH; ++v) request_w(s_lo + v, wr[v]);
-        park(0, wr[0]);
-        lds_barrier();
-        for (int st = s_lo; st < s_hi; st += DEPTH) {
-#pragma unroll
-            for (int u = 0; u < DEPTH; ++u) {
-                if (st + u >= s_hi) break;
-                park(buf ^ 1, wr[(u + 1) % DEPTH]);
-                request_w(st + u + DEPTH, wr[u]);
-                lds_barrier();
-                buf ^= 1;
-            }
-        }
-    }
-
-    // epilogue: this lane holds output columns n0 + 16 ct + 4 g + r of token 16 rb + i16
-    if (MODE == G_LMHEAD) {
-        // the row's softmax state over this workgroup's columns: every lane pushes its logits, the four lanes of a
-        // token (g = 0..3) merge, one partial per (row, workgroup).  Uniform control flow: the merge shuffles
-        const bool ok = m < a.M;
-        SoftState st; st.init();
-        const float lm_scale = ok ? a.seq_scale[m] : 1.f;
-        unsigned long long noise_base = 0;
-        if (a.sample_on && ok) noise_base = (unsigned long long)(a.row_pos[a.out_row[m]] + 1) * (unsigned long long)a.N;
-#pragma unroll
-        for (int ct = 0; ct < CTH; ++ct)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int n = (grp * CT + ct0 + ct) * 16 + 4 * g + r;
-                if (!ok || ct0 + ct >= CT || n >= n_out) continue;
-                const float lg = acc[0][ct][r] * lm_scale;
-                st.push(lg, n);
-                if (a.sample_on) st.push_noisy(lg, n, a.sample_key, noise_base);
-                if (a.logits) a.logits[(size_t)m * a.N + n] = lg;
-            }
-        for (int o = 32; o >= 16; o >>= 1) {
-            SoftState b = shfl_xor_state(st, o);
-            if ((lane & o) == 0) st.merge(b); else { b.merge(st); st = b; }
-        }
-        if (g == 0 && ok) a.parts[(size_t)m * a.n_parts + grp * CS + wave / RB] = to_partial(st);
-        return;
-    }
-    if (m >= a.M) return;
-#pragma unroll
-    for (int ct = 0; ct < CTH; ++ct) {
-        const int tile = grp * CT + ct0 + ct;
-        if (ct0 + ct >= CT || tile >= n_tiles) continue;
-        // (n_out is a multiple of 16: whole tiles, one 16-byte store per lane)
-        const int n = tile * 16 + 4 * g;
-        float o[4];
-        float *dst;
-        if constexpr (MODE == G_GATEUP) {
-            dst = a.act32 + frag_index(m, n, a.d_ffn, 4);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) o[r] = acc[0][ct][r] / (1.0f + expf(-acc[0][ct][r])) * acc[NT - 1][ct][r];
-        } else {
-            dst = a.part + ksp * a.part_stride + (size_t)m * n_out + n;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) o[r] = acc[0][ct][r];
-        }
-        *reinterpret_cast<float4 *>(dst) = make_float4(o[0], o[1], o[2], o[3]);
     }
 }
 

@@ -42,38 +42,21 @@ __device__ __forceinline__ SoftState block_merge(const SoftState &t, SoftPartial
 }
 
 // State of the logits x[i] * sc of one thread: the values i = first, first + step, ... (vocab % 4 == 0 and x 16-byte aligned:
-// in groups of four).  Four values at a time: one look at the maximum, then four exponentials that do not depend on each other.
+// in groups of four).
 __device__ __forceinline__ SoftState row_state(const float *__restrict__ x, int vocab, float sc, int first, int step) {
     SoftState st; st.init();
-    auto four = [&](const float (&v)[4], const int (&i)[4], const bool (&ok)[4]) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            if (!ok[k]) continue;
-            if (!(fabsf(v[k]) <= 3.0e38f)) st.bad = 1;                // NaN or +-Inf: the record says so, whatever the sums hold
-            if (v[k] > st.best) { st.best = v[k]; st.idx = i[k]; }    // (a thread's indices grow)
-        }
-        if (st.best > st.m) {
-            if (st.z > 0.f) { const float d = st.m - st.best, e = expf(d); st.s = e > 0.f ? e * (st.s + d * st.z) : 0.f; st.z *= e; }
-            st.m = st.best;
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float d = ok[k] ? v[k] - st.m : 0.f, e = ok[k] ? expf(d) : 0.f;
-            st.z += e; st.s = fmaf(e > 0.f ? d : 0.f, e, st.s);
-        }
-    };
     if ((vocab & 3) == 0) {
         const float4 *x4 = reinterpret_cast<const float4 *>(x);
 #pragma unroll 2
         for (int i = first; i < (vocab >> 2); i += step) {
             const float4 q = x4[i];
-            four({q.x * sc, q.y * sc, q.z * sc, q.w * sc}, {4 * i, 4 * i + 1, 4 * i + 2, 4 * i + 3}, {true, true, true, true});
+            st.push4({q.x * sc, q.y * sc, q.z * sc, q.w * sc}, {4 * i, 4 * i + 1, 4 * i + 2, 4 * i + 3}, {true, true, true, true});
         }
     } else {
         for (int i = first; i < vocab; i += 4 * step) {
             const int j[4] = {i, i + step, i + 2 * step, i + 3 * step};
             const bool ok[4] = {true, j[1] < vocab, j[2] < vocab, j[3] < vocab};
-            four({x[j[0]] * sc, x[ok[1] ? j[1] : i] * sc, x[ok[2] ? j[2] : i] * sc, x[ok[3] ? j[3] : i] * sc}, j, ok);
+            st.push4({x[j[0]] * sc, x[ok[1] ? j[1] : i] * sc, x[ok[2] ? j[2] : i] * sc, x[ok[3] ? j[3] : i] * sc}, j, ok);
         }
     }
     return st;

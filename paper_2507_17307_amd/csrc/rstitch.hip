@@ -20,6 +20,7 @@
 #include "router.h"
 #include "model_kernels.h"
 #include "mrow_kernels.h"
+#include "gemm_ring.h"
 #include "persistent.h"
 
 namespace {
@@ -382,149 +383,115 @@ rs_status launch_gemm_nb(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_
         }
         return launch_gemm_r<MODE, NB, 2, 4>(a, blocks, st, name);
     } else {
-        int r = (n_tiles + 1) / 2 >= target ? 2 : 1;
-        // the LM head has tiles to spare: four per workgroup, so that each piece of X serves twice the weights, once X is more than a
-        // few rows (7B shape, 3 / 5 / 8 / 12 / 16 sequences: 169 / 180 / 187 / 223 / 231 us with two tiles, 172 / 176 / 179 / 195 / 205 with four)
-        if (MODE == G_LMHEAD && a.M > 4 && (n_tiles + 3) / 4 >= target) r = 4;
-        int blocks = (n_tiles + r - 1) / r;
-        if (MODE == G_LMHEAD) {
-            if (blocks > LM_PARTS_CAP) blocks = LM_PARTS_CAP;             // one partial per workgroup and row block
-            if (a.yblocks > 1) blocks = ((blocks + 7) / 8) * 8;           // LM_PARTS_CAP is a multiple of 8
-            a.n_parts = blocks;
-        }
-        blocks = gemm_grid(blocks, a.yblocks);
-        if constexpr (MODE == G_LMHEAD) {
-            if (r == 4) return launch_gemm_r<MODE, NB, 4, 4>(a, blocks, st, name);
-        }
+        // (LM head: vocabularies too small for k_gemm_ring, up to 16 sequences)
+        const int r = (n_tiles + 1) / 2 >= target ? 2 : 1;
+        const int blocks = gemm_grid((n_tiles + r - 1) / r, a.yblocks);
+        if (MODE == G_LMHEAD) a.n_parts = blocks;                         // one partial per workgroup
         if (r == 2) return launch_gemm_r<MODE, NB, 2, 4>(a, blocks, st, name);
         return launch_gemm_r<MODE, NB, 1, 4>(a, blocks, st, name);
     }
 }
 
-// Launch of k_gemm_tile (17 .. 128 token rows).  CT (column tiles per workgroup) and, for the modes that leave partial
-// sums, the split of K are picked so that the workgroups come as close as possible to a whole number of rounds of the
-// machine with one workgroup per CU (each workgroup streams its share of W at the rate a CU can draw, so a round that
-// fills a fraction of the CUs costs a whole round); ties go to the larger CT (less X traffic) and the smaller split.
-template <int MODE, int NW, int CS, int CT>
-rs_status launch_gemm_tile_ct(GemmArgs &a, int blocks, hipStream_t st, const char *name) {
-    constexpr size_t lds = gemm_tile_lds_bytes<MODE, CT>();
-    static_assert(lds <= 64 * 1024, "fits the default LDS limit");
-    hipLaunchKernelGGL((k_gemm_tile<MODE, CT, NW, CS>), dim3(blocks), dim3(NW * 64), lds, st, a);
+template <int MODE, int RBW, int CS, int CT>
+rs_status launch_gemm_ring_ct(GemmArgs &a, dim3 blocks, hipStream_t st, const char *name) {
+    constexpr size_t lds = ring_lds_bytes<CT, 4 / CS * RBW>();
+    if (rs_status rc = allow_lds<k_gemm_ring<MODE, CT, RBW, CS>>(lds, name)) return rc;
+    hipLaunchKernelGGL((k_gemm_ring<MODE, CT, RBW, CS>), blocks, dim3(512), lds, st, a);
     RS_LAUNCHED(name);
     return RS_OK;
 }
 
-struct TilePlan { int ct, ks; double eff; };
+struct RingPlan { int ct, ks, units; };
 
-// wide: also 13 tiles, the most whose operands fit the registers of eight waves (LM head of more than 64 sequences: X is read once
-// per workgroup, 128 sequences on the 7B shape 437 -> 423 us a kernel; with four waves, two workgroups per CU, 10 tiles are the better ones)
-TilePlan plan_gemm_tile(bool gateup, bool split, int n_tiles, int n_win, int n_cu, bool wide = false) {
-    static const int ct_gu[] = {5, 4, 3, 2}, ct_part[] = {13, 10, 8, 7, 6, 4};
-    TilePlan best{0, 1, -1.0};
-    const int *cts = gateup ? ct_gu : wide ? ct_part : ct_part + 1;
-    const int n_ct = gateup ? 4 : wide ? 6 : 5;
-    for (int i = 0; i < n_ct; ++i) {
-        const int ct = cts[i], groups = (n_tiles + ct - 1) / ct;
-        for (int ks = 1; ks <= (split ? GEMM_KSPLIT_MAX : 1); ++ks) {
-            if (ks > 1 && n_win / ks < 6) break;
+// Column tiles per workgroup and split of K of a product of M rows with n_tiles tiles (gate/up 8 + 8 columns each, else 16) over n_win
+// windows: the least estimated time.  A window of a workgroup takes the longest of
+//   its matrix instructions   60.5 ns for each 16 x 16 tile of a wave (96 of them at 128 rows: 1.16 us at the 1.8 GHz that this load leaves)
+//   its loads                 45 bytes/ns into one CU, W at 24.5 of them (6.3 TB/s over 256 CUs)
+//   its dependent steps       0.45 us; 1.0 us above 64 rows, where X is requested only one window ahead
+// and partial sums cost their way through memory, written and read again at about 3 TB/s.
+RingPlan plan_ring(int mode, int M, int n_tiles, int n_win, int n_cu) {
+    static const int ct_layer[] = {14, 13, 10, 9, 8, 7, 6, 5, 4, 0}, ct_lm[] = {13, 10, 8, 6, 4, 2, 1, 0};
+    const int rbw = M > 64 ? 2 : 1, cs = M > 32 ? 1 : M > 16 ? 2 : 4, blocks = (M + 15) / 16;
+    const double row_tiles = M > 64 && blocks <= 4 ? 1 : rbw;
+    RingPlan best{0, 1, 0};
+    double least = 1e30;
+    for (const int *c = mode == G_LMHEAD ? ct_lm : ct_layer; *c; ++c) {
+        const int ct = *c, groups = (n_tiles + ct - 1) / ct;
+        if (mode == G_LMHEAD && rbw == 2 && ct > 10) continue;                     // (its accumulators would spill)
+        for (int ks = 1; ks <= (mode == G_PART ? GEMM_KSPLIT_MAX : 1); ++ks) {
+            if (ks > 1 && n_win / ks < 3) break;
             const int units = groups * ks, rounds = (units + n_cu - 1) / n_cu;
-            const double eff = (double)units / ((double)rounds * n_cu) * ((double)n_tiles / ((double)groups * ct));
-            if (eff > best.eff + 1e-9) best = TilePlan{ct, ks, eff};
+            const double kb = 2.048 * ct, mfma = 0.0605 * ((ct + cs - 1) / cs) * row_tiles, load = (kb + 4.096 * blocks) / 45, w = kb / 24.5;
+            double win = rbw == 2 ? (ct > 10 ? 1.0 : 0.6) : 0.45;
+            for (double t : {mfma, load, w}) win = t > win ? t : win;
+            const double us = rounds * ((n_win + ks - 1) / ks) * win + (mode == G_PART ? 16.0 * M * n_tiles * 4 * ks / 3e6 : 0.0);
+            if (us < least + 1e-9) { least = us; best = RingPlan{ct, ks, units}; }         // (equal: the smaller groups)
         }
     }
     return best;
 }
 
-// NW waves: NW / CS blocks of 16 rows, CS waves per block that split the workgroup's column tiles
-template <int MODE, int NW, int CS>
-rs_status launch_gemm_tile(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_t st, const char *name) {
-    const TilePlan p = plan_gemm_tile(MODE == G_GATEUP, MODE == G_PART, n_tiles, a.K / GEMM_KW, m->n_cu, MODE == G_LMHEAD && NW == 8);
+template <int MODE, int RBW, int CS>
+rs_status launch_gemm_ring(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_t st, const char *name) {
+    const RingPlan p = plan_ring(MODE, a.M, n_tiles, a.K / GEMM_KW, m->n_cu);
     const int groups = (n_tiles + p.ct - 1) / p.ct;
     a.yblocks = 1; a.ksplit = p.ks; a.part = nullptr; a.part_stride = 0;
     if constexpr (MODE == G_PART) {
         a.part = m->at<float>(m->lay.gemm_part);
         a.part_stride = (size_t)m->cfg.max_rows * (size_t)a.N;
     }
-    const int blocks = groups * p.ks;
-    if constexpr (MODE == G_LMHEAD) a.n_parts = groups * CS;        // one partial per row, workgroup and column split
-    if constexpr (MODE == G_GATEUP) {
-        switch (p.ct) {
-            case 5: return launch_gemm_tile_ct<MODE, NW, CS, 5>(a, blocks, st, name);
-            case 4: return launch_gemm_tile_ct<MODE, NW, CS, 4>(a, blocks, st, name);
-            case 3: return launch_gemm_tile_ct<MODE, NW, CS, 3>(a, blocks, st, name);
-            default: return launch_gemm_tile_ct<MODE, NW, CS, 2>(a, blocks, st, name);
-        }
-    } else {
-        if constexpr (MODE == G_LMHEAD && NW == 8) {
-            if (p.ct == 13) return launch_gemm_tile_ct<MODE, NW, CS, 13>(a, blocks, st, name);
-        }
-        switch (p.ct) {
-            case 10: return launch_gemm_tile_ct<MODE, NW, CS, 10>(a, blocks, st, name);
-            case 8: return launch_gemm_tile_ct<MODE, NW, CS, 8>(a, blocks, st, name);
-            case 7: return launch_gemm_tile_ct<MODE, NW, CS, 7>(a, blocks, st, name);
-            case 6: return launch_gemm_tile_ct<MODE, NW, CS, 6>(a, blocks, st, name);
-            default: return launch_gemm_tile_ct<MODE, NW, CS, 4>(a, blocks, st, name);
-        }
+    a.win_per_split = a.K / GEMM_KW / p.ks; a.win_extra = a.K / GEMM_KW % p.ks;
+    const dim3 blocks(p.ks, MODE == G_PART || groups < m->n_cu ? groups : m->n_cu);
+    if constexpr (MODE == G_LMHEAD) a.n_parts = blocks.y * CS;      // one partial per row, workgroup and column split
+    switch (p.ct) {
+#define RS_CT(ct) case ct: return launch_gemm_ring_ct<MODE, RBW, CS, ct>(a, blocks, st, name);
+        RS_CT(10) RS_CT(8) RS_CT(6) RS_CT(4)
     }
+    if constexpr (MODE != G_LMHEAD || RBW == 1) { switch (p.ct) { RS_CT(13) } }
+    if constexpr (MODE == G_LMHEAD) { switch (p.ct) { RS_CT(2) default: RS_CT(1) } }
+    else { switch (p.ct) { RS_CT(14) RS_CT(9) RS_CT(7) default: RS_CT(5) } }
+#undef RS_CT
 }
 
-// wave arrangement by row count: four waves of 16 rows up to 64 rows, eight up to 128.  Up to 32 rows two of the four
-// waves would hold no rows: there two waves share each row block and split the workgroup's column tiles (k_gemm_tile's
-// CS = 2; per call at 17 / 24 / 32 rows: 7B shape 5.41 / 5.53 / 5.76 -> 4.98 / 5.15 / 5.46 ms, 14B 12.2 / 12.8 / 13.8 ->
-// 11.0 / 11.8 / 13.0, 1.5B 2.65 / 2.71 / 2.85 -> 2.56 / 2.65 / 2.82); not the LM head, whose partial states are counted
-// per workgroup.  The same split with eight waves measured slower at 64 rows (7B shape: 7.8 ms per call against 7.0;
-// every wave of a row block fetches that block's X pieces again), and four waves on one row block lose against
-// k_gemm_rows (7B shape, 16 rows: 4.83 against 4.26 ms)
+// wave arrangement by row count, see k_gemm_ring
 template <int MODE>
-rs_status launch_gemm_tile_rows(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_t st, const char *name) {
-    if (a.M > 64) return launch_gemm_tile<MODE, 8, 1>(m, a, n_tiles, st, name);
-    if constexpr (MODE != G_LMHEAD) {
-        if (a.M <= 32) return launch_gemm_tile<MODE, 4, 2>(m, a, n_tiles, st, name);
-    }
-    return launch_gemm_tile<MODE, 4, 1>(m, a, n_tiles, st, name);
+rs_status launch_gemm_ring_rows(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_t st, const char *name) {
+    if (a.M > 64) return launch_gemm_ring<MODE, 2, 1>(m, a, n_tiles, st, name);
+    if (a.M <= 16) return launch_gemm_ring<MODE, 1, 4>(m, a, n_tiles, st, name);
+    if (a.M <= 32) return launch_gemm_ring<MODE, 1, 2>(m, a, n_tiles, st, name);
+    return launch_gemm_ring<MODE, 1, 1>(m, a, n_tiles, st, name);
 }
 
-// Which calls take k_gemm_tile.  Layers: every call of more than 16 rows.
-// Measured per call against 16- / 32-row blocks with workgroups of their own (k_gemm_rows): 7B shape 24 rows 5.81 -> 5.54
-// ms, 32 rows 6.35 -> 5.75, 64 rows 9.57 -> 6.9, 128 rows 14.9 -> 10.1; 14B 32 rows 14.5 -> 13.8, 64 rows 24.0 -> 18.0, 128
-// rows 44.7 -> 31.3; 32B 128 rows 78.6 -> 55.3; 1.5B shape 33 rows 3.50 -> 2.95, 64 rows 3.68 -> 3.32, 128 rows 5.44 -> 4.82
-// From 17 rows on: the 32-row blocks of k_gemm_rows split two blocks' activations per window in every wave and lose
-// against the tile kernel even where two of its four waves hold no rows (7B shape, 17 / 23 rows: 6.16 / 6.27 ms against
-// 5.35 / 5.50; 32B 22.1 / 23.0 against 21.4 / 22.2; 1.5B 2.69 / 2.79 against 2.64 / 2.75; only the 14B shape is 2 %
-// better off there).
-// LM head: more than 16 sequences (16-row blocks with workgroups of their own cost 230 us per block on the 7B shape:
-// 1.85 ms at 128 sequences against 0.47 ms; 1.5B shape 0.86 -> 0.24 ms); one partial per workgroup must fit the buffer
-// even with four column tiles per workgroup.
-bool tile_layers(const rs_config &, int rows) { return rows > 16; }
-// ... and only the matrices whose workgroups fill at least 70 % of their rounds of the machine (the 1.5B shape's QKV and
-// O projection have 128 and 96 of them at best: 15.6 and 14.7 us per layer at 128 rows against 12.7 and 11.0 on k_gemm_rows)
-bool tile_fills(const rs_model *m, bool gateup, int n_out, int K) {
-    return plan_gemm_tile(gateup, !gateup, (n_out + 15) / 16, K / GEMM_KW, m->n_cu).eff >= 0.7;
+// Which products take k_gemm_ring: those of more than 16 rows unless their workgroups would leave two thirds of the CUs without one;
+// up to 16 rows those of matrices from 64 MB on, because a workgroup that fills a CU starts and ends more slowly than the
+// small ones of k_gemm_rows (5 / 16 rows, us, k_gemm_rows / k_gemm_ring: 26 MB 8.3 / 9.2 and 9.5 / 10.2, 33 MB 9.7 / 11.1 and 10.9 / 11.7,
+// 52 MB 13.3 / 13.4 and 15.2 / 14.2, 55 MB 14.2 / 15.4 and 16.6 / 16.2, 73 MB 16.3 / 15.0 and 18.6 / 16.0, 136 MB 25.8 / 26.6 and 27.1 / 27.0,
+// 141 MB 27.4 / 26.5 and 28.9 / 27.1, 272 MB 50.8 / 45.2 and 53.3 / 45.1, 566 MB 101 / 88 and 108 / 90).
+bool ring_layer(const rs_model *m, int rows, bool gateup, int w_rows, int K) {
+    if (rows <= 16 && (size_t)w_rows * K * 2 < ((size_t)64 << 20)) return false;
+    return plan_ring(gateup ? G_GATEUP : G_PART, rows, (w_rows + 15) / 16, K / GEMM_KW, m->n_cu).units >= m->n_cu / 3;
 }
-bool tile_lm_head(const rs_config &c, int n_seqs) { return n_seqs > 16 && ((c.vocab + 15) / 16 + 3) / 4 <= LM_PARTS_CAP; }
+// LM head: from five column tiles per CU on (a window of fewer costs its dependent steps: vocabulary 8192, one row of the 1.5B shape 12.7 us
+// on k_gemm_rows, 16.0 here; 32 000 entries 22.6 and 21.7, 152 064 81.6 and 77.5) and for more than 16 sequences.
+bool ring_lm_head(const rs_model *m, int n_seqs) { return n_seqs > 16 || (m->cfg.vocab + 15) / 16 >= 5 * m->n_cu; }
 
 // n_tiles = number of 16-column output tiles; 16 * NB token rows compiled in (NB = 1, 2 or 4)
-// tile: the caller's choice of k_gemm_tile for this matrix (it has prepared the activations in that kernel's format)
+// ring: this matrix takes k_gemm_ring (ring_layer)
 template <int MODE>
-rs_status launch_gemm(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_t st, const char *name, bool tile = false) {
+rs_status launch_gemm(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_t st, const char *name, bool ring = false) {
     if (a.K % GEMM_KW) return fail(RS_EINVAL, "internal: K = %d is not a multiple of %d", a.K, GEMM_KW);
     a.yblocks = 1;
     if constexpr (MODE == G_LMHEAD) {
-        // more than 16 sequences: one workgroup per block of vocabulary columns holds all rows, so the matrix is read once
-        if (tile_lm_head(m->cfg, a.M))
-            return launch_gemm_tile_rows<G_LMHEAD>(m, a, n_tiles, st, name);
-        a.yblocks = (a.M + 15) / 16;
-        return launch_gemm_nb<MODE, 1>(m, a, n_tiles, st, name);
+        if (!ring_lm_head(m, a.M)) return launch_gemm_nb<MODE, 1>(m, a, n_tiles, st, name);
+        return launch_gemm_ring_rows<G_LMHEAD>(m, a, n_tiles, st, name);
     } else {
-        // up to 16 rows: one 16-row block; more: blocks of 32 rows (two 16-row blocks per workgroup), each
-        // block with workgroups of its own.  Measured on the 7B shape: 32 rows 6.0 ms, 64 rows 9.1 ms this
-        // way; 64-row blocks are no faster (9.7 ms) and 16-row blocks slower.
-        if (a.M <= 16) return launch_gemm_nb<MODE, 1>(m, a, n_tiles, st, name);
-        if (tile) {
+        if (ring) {
             // partial sums are always left for the next kernel (a split of one is a plain copy of the result)
-            if constexpr (MODE == G_GATEUP) return launch_gemm_tile_rows<G_GATEUP>(m, a, n_tiles, st, name);
-            else return launch_gemm_tile_rows<G_PART>(m, a, n_tiles, st, name);
+            if constexpr (MODE == G_GATEUP) return launch_gemm_ring_rows<G_GATEUP>(m, a, (a.d_ffn + 7) / 8, st, name);
+            else return launch_gemm_ring_rows<G_PART>(m, a, n_tiles, st, name);
         }
+        // up to 16 rows: one 16-row block; more (matrices with few columns): blocks of 32 rows with workgroups of their own
+        if (a.M <= 16) return launch_gemm_nb<MODE, 1>(m, a, n_tiles, st, name);
         a.yblocks = (a.M + 31) / 32;
         return launch_gemm_nb<MODE, 2>(m, a, n_tiles, st, name);
     }
@@ -789,10 +756,8 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
             GemmArgs g{};
             const int rsh = frag_shift(n_rows);
             g.M = n_rows; g.d_ffn = c.d_ffn; g.rsh = rsh;
-            const bool t_all = tile_layers(c, n_rows);
-            const bool t_qkv = t_all && tile_fills(m, false, qkv_rows, c.d_model), t_o = t_all && tile_fills(m, false, c.d_model, qdim);
-            // gate/up hands its output to the down projection in one format: both or neither
-            const bool t_mlp = t_all && tile_fills(m, true, c.d_ffn, c.d_model) && tile_fills(m, false, c.d_model, c.d_ffn);
+            const bool t_qkv = ring_layer(m, n_rows, false, qkv_rows, c.d_model), t_o = ring_layer(m, n_rows, false, c.d_model, qdim);
+            const bool t_gu = ring_layer(m, n_rows, true, 2 * c.d_ffn, c.d_model), t_down = ring_layer(m, n_rows, false, c.d_model, c.d_ffn);
             float *xn32 = m->at<float>(L.xn32);
             g.act32 = m->at<float>(L.act);
             // the down projection of the layer before may have left its result as partial sums (pend_*)
@@ -834,12 +799,12 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
             RS_LAUNCHED("rmsnorm_rows");
             g.W = m->w_gate_up[l]; g.N = 2 * c.d_ffn; g.K = c.d_model; g.X32 = xn32;
             tic(RS_PHASE_GATEUP, l);
-            if ((rc = launch_gemm<G_GATEUP>(m, g, (c.d_ffn + 15) / 16, st, "gemm_gateup", t_mlp))) return rc;
+            if ((rc = launch_gemm<G_GATEUP>(m, g, (c.d_ffn + 15) / 16, st, "gemm_gateup", t_gu))) return rc;
             toc(RS_PHASE_GATEUP, l);
             g.W = m->w_down[l]; g.N = c.d_model; g.K = c.d_ffn;
             g.X32 = m->at<float>(L.act);
             tic(RS_PHASE_DOWN, l);
-            if ((rc = launch_gemm<G_DOWN>(m, g, (c.d_model + 15) / 16, st, "gemm_down", t_mlp))) return rc;
+            if ((rc = launch_gemm<G_DOWN>(m, g, (c.d_model + 15) / 16, st, "gemm_down", t_down))) return rc;
             toc(RS_PHASE_DOWN, l);
             if (g.part) { pend_part = g.part; pend_ks = g.ksplit; pend_stride = g.part_stride; }
         }
@@ -863,12 +828,13 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
         toc(RS_PHASE_LMHEAD, 0);
         if (rc) return rc;
     } else {
+        const int lm_rsh = ring_lm_head(m, n_seqs) && n_seqs < 4 ? 2 : frag_shift(n_seqs);         // (k_gemm_ring: blocks of four rows at least)
         hipLaunchKernelGGL(k_rmsnorm_rows, dim3(n_seqs), dim3(ROWK_THREADS), 0, st, h, m->final_norm, c.rms_eps,
-                           c.d_model, (const int *)m->at<int>(L.out_row), m->at<float>(L.lm32), frag_shift(n_seqs), (const float *)pend_part, pend_ks,
+                           c.d_model, (const int *)m->at<int>(L.out_row), m->at<float>(L.lm32), lm_rsh, (const float *)pend_part, pend_ks,
                            pend_stride);
         RS_LAUNCHED("rmsnorm_rows");
         GemmArgs g{};
-        g.M = n_seqs; g.rsh = frag_shift(n_seqs); g.W = m->lm_head; g.N = c.vocab; g.K = c.d_model; g.X32 = m->at<float>(L.lm32);
+        g.M = n_seqs; g.rsh = lm_rsh; g.W = m->lm_head; g.N = c.vocab; g.K = c.d_model; g.X32 = m->at<float>(L.lm32);
         g.seq_scale = m->at<float>(L.seq_scale); g.parts = parts; g.logits = d_logits;
         g.sample_on = m->sample_on; g.sample_key = m->sample_key; g.row_pos = row_pos; g.out_row = m->at<int>(L.out_row);
         tic(RS_PHASE_LMHEAD, 0);

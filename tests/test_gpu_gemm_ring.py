@@ -1,0 +1,47 @@
+"""k_gemm_ring where it can go wrong: blocks of 4, 8 and 16 rows on matrices that take it from three rows on, an LM head of up to
+three sequences in blocks of four rows, waves with one and with two row blocks, vocabularies whose last tile is ragged, a matrix
+of two windows of K (fewer than the rings hold), and a head of fewer groups than CUs."""
+import pytest
+import torch
+
+import workloads as W
+from oracle import decoder, router
+from parity import check_invocation
+from workloads.shapes import ModelShape
+
+pytestmark = pytest.mark.gpu
+
+BIG = ModelShape("ring_big", 1, 3072, 24, 8, 128, 11264, 20503, tied_lm_head=True)      # gate/up, down and LM head: 64 MB and more
+
+
+@pytest.fixture(scope="module")
+def big():
+    return W.make_weights(BIG, 53, 1)
+
+
+def run(w, shape, spans, slots, max_ctx, where):
+    """One call of spans[i] rows per sequence, the first token at position 0, checked against the oracle."""
+    import paper_2507_17307_amd as P
+    n, rows = len(spans), sum(spans)
+    gpu = P.Model(w.to("cuda"), max_ctx=max_ctx, max_seqs=max(slots) + 1, max_rows=rows)
+    ref = decoder.OracleModel(w, max_ctx, n_slots=max(slots) + 1)
+    toks = W.rng.randint(53, rows, 0, rows, shape.vocab).tolist()
+    cut = [toks[sum(spans[:i]):sum(spans[:i + 1])] for i in range(n)]
+    scales = [1.0 + i % 5 for i in range(n)]
+    got, lg = gpu.catchup_prefill(cut, [0] * n, 0.6, P.RS_SLM, scales, slots, want_logits=True)
+    torch.cuda.synchronize()
+    for i in sorted({0, n // 2, n - 1}):
+        want = ref.forward(cut[i], 0, slot=slots[i], logit_scale=scales[i])["logits"]
+        check_invocation(got[i], lg[i], want, 0.6, router.SLM, where=f"{where}, sequence {i}")
+
+
+@pytest.mark.parametrize("spans", [[3], [2, 2], [2, 1, 2], [8], [9], [1, 2, 3, 4, 6], [70], [30, 51]])
+def test_rows_of_a_large_matrix(spans, big):
+    run(big, BIG, spans, list(range(len(spans))), 96, f"spans {spans}")
+
+
+@pytest.mark.parametrize("vocab", [65, 8197])
+@pytest.mark.parametrize("n", [17, 66, 97])
+def test_lm_head_of_few_tiles(vocab, n):
+    shape = ModelShape("ring_head", 1, 128, 4, 2, 32, 128, vocab, tied_lm_head=False)
+    run(W.make_weights(shape, 59, 1), shape, [1] * (n - 1) + [2], list(range(n)), 16, f"{n} sequences")

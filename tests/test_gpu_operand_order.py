@@ -1,7 +1,8 @@
 """Calls of 3 .. 128 rows on the matrix-core kernels: the activation buffers between them hold blocks of 1, 2, 4, 8 or 16 rows in
 operand order (frag_index), so every row count around those block sizes, as a span and as decode rows, against the oracle.
-The first shape's projections have too few column tiles for k_gemm_tile (tile_fills) and stay on k_gemm_rows, whatever the row
-count; those of the second take it from 17 rows on, with two waves per row block up to 32 rows, four waves up to 64, eight above."""
+The first shape's projections have too few columns for k_gemm_ring (ring_layer) and stay on k_gemm_rows, whatever the row count;
+those of the second take it from 17 rows on (gate/up from 3), with two waves per row block up to 32 rows, one up to 64, and two
+row blocks per wave above."""
 import pytest
 import torch
 
