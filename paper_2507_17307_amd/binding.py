@@ -103,8 +103,14 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# torch.cuda.current_stream() builds a stream object (2.7 us, of a call of rs_route on 1024 logits 6.8); its raw handle alone takes 0.2
+_raw_stream, _raw_device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
+        if _raw_stream is not None and _raw_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_raw_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
