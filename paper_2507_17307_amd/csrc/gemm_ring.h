@@ -162,15 +162,14 @@ __global__ void __launch_bounds__(512, 1) k_gemm_ring(GemmArgs a) {
     constexpr int NA = CS == 4 ? 4 : 1;
     f32x4_t acc[RBW][CTH], part[NA][RBW][CTH];
     SoftState state[MODE == G_LMHEAD ? RBW : 1];
-    float inv[RBW], lm_scale[RBW];                            // factors of the lane's rows
+    float lm_scale[RBW];
     unsigned long long noise_base[RBW];                       // sampling: (position of the token being predicted) * V
 #pragma unroll
     for (int r = 0; r < RBW; ++r) {
-        inv[r] = lm_scale[r] = 1.f; noise_base[r] = 0;
-        const int m = (rb0 + r * RBK) * 16 + i16;
-        if (MODE != G_PART && m < a.M) inv[r] = row_factor(a.ss, m, K, a.eps);
+        lm_scale[r] = 1.f; noise_base[r] = 0;
         if (MODE == G_LMHEAD) {
             state[r].init();
+            const int m = (rb0 + r * RBK) * 16 + i16;
             if (m < a.M) {
                 lm_scale[r] = a.seq_scale[m];
                 if (a.sample_on) noise_base[r] = (unsigned long long)(a.row_pos[a.out_row[m]] + 1) * (unsigned long long)a.N;
@@ -285,7 +284,7 @@ __global__ void __launch_bounds__(512, 1) k_gemm_ring(GemmArgs a) {
                     if (ct0 + c >= CT || n0 >= n_out) continue;
                     float v[4];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = acc[r][c][e] * inv[r] * lm_scale[r];
+                    for (int e = 0; e < 4; ++e) v[e] = acc[r][c][e] * lm_scale[r];
                     const int idx[4] = {n, n + 1, n + 2, n + 3};
                     if (n0 + 16 <= n_out) state[r].push4(v, idx, {true, true, true, true});
                     else state[r].push4(v, idx, {n < n_out, n + 1 < n_out, n + 2 < n_out, n + 3 < n_out});
@@ -313,7 +312,6 @@ __global__ void __launch_bounds__(512, 1) k_gemm_ring(GemmArgs a) {
                     const int ct = c + (g >> 1), tile = grp * CT + ct0 + ct;
                     if (m >= a.M || ct >= CTH || ct0 + ct >= CT || tile >= n_tiles) continue;
                     float o[4];
-                    gate *= inv[r]; up *= inv[r];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) o[e] = gate[e] / (1.0f + expf(-gate[e])) * up[e];
                     *reinterpret_cast<float4 *>(a.act32 + frag_index(m, tile * 8 + 4 * (g & 1), a.d_ffn, RB == 1 ? a.rsh : 4)) = make_float4(o[0], o[1], o[2], o[3]);

@@ -16,7 +16,7 @@
 
 namespace rs {
 
-constexpr int ROWK_THREADS = 256;      // the two row kernels below: several workgroups per token row
+constexpr int ROWK_THREADS = 1024;     // one workgroup per token row in the two row kernels below
 constexpr int KSPLIT_MAX = 8;
 
 // x[i] (+ the other split-K partial sums of it): all requests are issued together, unconditionally
@@ -32,101 +32,103 @@ __device__ __forceinline__ float4 sum_splits4(const float *base, size_t i, int k
     return first;
 }
 
-// RMSNorm of rows, all but the row's factor: grid (n_out, norm_chunks(d)), block ROWK_THREADS, one float4 a thread.
-// src row = gather ? gather[blockIdx.x] : blockIdx.x; h * gain goes to out32[blockIdx.x] as fp32 (the matrix-core kernels
-// split it into bf16 planes themselves), in operand order (frag_index), and the chunk's sum of squares to ss[blockIdx.x][chunk].  Who
-// uses the products multiplies them with row_factor(): no workgroup has to see the whole row, so a row is spread over several CUs
-// (with one workgroup per row, 14B shape, 61 rows: norms 6.8 / 6.4 us, now 5.9 / 5.6; together with the rotary kernel
-// below, which was one workgroup per row as well, calls of the 7B shape of 5 rows and of 16 sequences 912 / 728 -> 890 / 712 us).
+// RMSNorm of whole rows: grid n_out, block ROWK_THREADS; d a multiple of 4, at most 12 * ROWK_THREADS.
+// src row = gather ? gather[blockIdx.x] : blockIdx.x; the normalised row goes to out32[blockIdx.x] as fp32 (the
+// matrix-core kernels split it into bf16 planes themselves), in operand order (frag_index).
 // part != null: the projection before this norm left its result as `ksplit` partial sums
 // part[ks][row][d] (split over K across workgroups); they are added to the residual row here, in a
-// fixed order, and the row is written back.
-constexpr int NORM_CHUNK = 4 * ROWK_THREADS;
-__host__ __device__ constexpr int norm_chunks(int d) { return (d + NORM_CHUNK - 1) / NORM_CHUNK; }
-__device__ __forceinline__ float row_factor(const float *ss, int row, int d, float eps) {
-    const int n = norm_chunks(d);
-    float tot = 0.f;
-    for (int c = 0; c < n; ++c) tot += ss[(size_t)row * n + c];
-    return 1.0f / sqrtf(tot / (float)d + eps);
-}
-
+// fixed order, and the row is written back before it is normalised.
 __global__ void __launch_bounds__(ROWK_THREADS)
-k_rmsnorm_rows(float *__restrict__ h, const uint16_t *__restrict__ gain, int d,
-               const int *__restrict__ gather, float *__restrict__ out32, int rsh, float *__restrict__ ss,
+k_rmsnorm_rows(float *__restrict__ h, const uint16_t *__restrict__ gain, float eps, int d,
+               const int *__restrict__ gather, float *__restrict__ out32, int rsh,
                const float *__restrict__ part, int ksplit, size_t part_stride) {
-    const int tid = threadIdx.x, i = (blockIdx.y * ROWK_THREADS + tid) * 4;                     // (d is a multiple of 4)
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int src = gather ? gather[blockIdx.x] : blockIdx.x;
-    __shared__ float red[ROWK_THREADS / 64];
-    float sq = 0.f;
-    if (i < d) {
-        float *hr = h + (size_t)src * d + i;
-        float4 v = *reinterpret_cast<const float4 *>(hr);
-        const uint2 g = *reinterpret_cast<const uint2 *>(gain + i);
-        if (part) {
-            const float *p = part + (size_t)src * d + i;
-            const float4 t = sum_splits4(p, 0, ksplit, part_stride, *reinterpret_cast<const float4 *>(p));
-            v.x += t.x; v.y += t.y; v.z += t.z; v.w += t.w;
-            *reinterpret_cast<float4 *>(hr) = v;
+    float *hr = h + (size_t)src * d;
+    __shared__ float red_ss[ROWK_THREADS / 64];
+    const int n4 = d >> 2;
+    constexpr int NV = 3;
+    float4 v[NV];
+    uint2 gv[NV];
+    float ss = 0.f;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const int i4 = tid + k * ROWK_THREADS;
+        v[k] = make_float4(0.f, 0.f, 0.f, 0.f); gv[k] = make_uint2(0, 0);
+        if (i4 < n4) {
+            v[k] = *reinterpret_cast<const float4 *>(hr + 4 * i4);
+            gv[k] = *reinterpret_cast<const uint2 *>(gain + 4 * i4);
+            if (part) {
+                const float4 p0 = *reinterpret_cast<const float4 *>(part + (size_t)src * d + 4 * i4);
+                float4 t = sum_splits4(part, (size_t)src * d + 4 * i4, ksplit, part_stride, p0);
+                v[k].x += t.x; v[k].y += t.y; v[k].z += t.z; v[k].w += t.w;
+                *reinterpret_cast<float4 *>(hr + 4 * i4) = v[k];
+            }
         }
-        sq = fmaf(v.w, v.w, fmaf(v.z, v.z, fmaf(v.y, v.y, v.x * v.x)));
-        *reinterpret_cast<float4 *>(out32 + frag_index(blockIdx.x, i, d, rsh)) = make_float4(v.x * bf16_lo(g.x), v.y * bf16_hi(g.x), v.z * bf16_lo(g.y), v.w * bf16_hi(g.y));
+        ss = fmaf(v[k].x, v[k].x, ss); ss = fmaf(v[k].y, v[k].y, ss); ss = fmaf(v[k].z, v[k].z, ss); ss = fmaf(v[k].w, v[k].w, ss);
     }
-    sq = wave_sum(sq);
-    if ((tid & 63) == 0) red[tid >> 6] = sq;
+    ss = wave_sum(ss);
+    if (lane == 0) red_ss[wave] = ss;
     __syncthreads();
-    if (tid == 0) ss[(size_t)blockIdx.x * gridDim.y + blockIdx.y] = (red[0] + red[1]) + (red[2] + red[3]);
+    float tot = 0.f;
+#pragma unroll
+    for (int w = 0; w < ROWK_THREADS / 64; ++w) tot += red_ss[w];
+    const float inv = 1.0f / sqrtf(tot / (float)d + eps);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const int i4 = tid + k * ROWK_THREADS;
+        if (i4 >= n4) continue;
+        *reinterpret_cast<float4 *>(out32 + frag_index(blockIdx.x, 4 * i4, d, rsh)) = make_float4(v[k].x * (inv * bf16_lo(gv[k].x)), v[k].y * (inv * bf16_hi(gv[k].x)),
+                                                             v[k].z * (inv * bf16_lo(gv[k].y)), v[k].w * (inv * bf16_hi(gv[k].y)));
+    }
 }
 
-// Factor of the row's norm, rotary embedding of q and k, KV-cache write: grid (n_rows, rope_blocks), block ROWK_THREADS; a thread
-// has four consecutive rotary pairs or four values of V (head_dim / 2 is a multiple of 4).  (One workgroup of 1024 threads per row
-// pulled the partial sums of the whole row into one CU: 7B shape, 128 rows 6.4 -> 5.7 us, 14B, 61 rows 6.2 -> 5.3.)
+// Rotary embedding of q and k, KV-cache write, for every row: grid n_rows, block ROWK_THREADS.
 struct RopeArgs {
     const float *qkv;              // [rows, (n_q+2 n_kv) hd] fp32, or `ksplit` partial sums of it, part_stride elements apart
     int ksplit; size_t part_stride;
-    const float *ss; int d; float eps;                    // row_factor of the norm before the projection
     float *qbuf; uint16_t *kcache, *vcache;
     const float *rope_cos, *rope_sin;
     const int *row_pos, *row_slot, *row_bad;
     int n_q, n_kv, head_dim, max_ctx, max_seqs, layer;
 };
-inline int rope_blocks(int n_q, int n_kv, int hd) { return ((n_q + n_kv) * (hd / 8) + n_kv * (hd / 4) + ROWK_THREADS - 1) / ROWK_THREADS; }
 
 __global__ void __launch_bounds__(ROWK_THREADS) k_rope_kv_rows(RopeArgs a) {
-    const int r = blockIdx.x, hd = a.head_dim, half = hd >> 1, quads = half >> 2;
-    const int n_rot = (a.n_q + a.n_kv) * quads, p4 = blockIdx.y * ROWK_THREADS + threadIdx.x;
-    const int bad = a.row_bad[r], pos = a.row_pos[r], slot = a.row_slot[r];
-    const size_t xo = (size_t)r * (a.n_q + 2 * a.n_kv) * hd;
+    const int r = blockIdx.x, tid = threadIdx.x;
+    if (a.row_bad[r]) {
+        for (int i = tid; i < a.n_q * a.head_dim; i += ROWK_THREADS) a.qbuf[(size_t)r * a.n_q * a.head_dim + i] = 0.f;
+        return;
+    }
+    const int hd = a.head_dim, half = hd >> 1, pos = a.row_pos[r], slot = a.row_slot[r];
+    const int n_qkv = (a.n_q + 2 * a.n_kv) * hd;
+    const size_t xo = (size_t)r * n_qkv;
     const int ks_n = a.ksplit > 1 ? a.ksplit : 1;
-    if (p4 < n_rot) {
-        const int head = p4 / quads, i = (p4 - head * quads) * 4;
-        float *q = a.qbuf + ((size_t)r * a.n_q + head) * hd;
-        if (bad) {
-            if (head < a.n_q) { const float4 z = make_float4(0.f, 0.f, 0.f, 0.f); *reinterpret_cast<float4 *>(q + i) = z; *reinterpret_cast<float4 *>(q + i + half) = z; }
-            return;
-        }
-        const float inv = row_factor(a.ss, r, a.d, a.eps);
-        const float4 c = *reinterpret_cast<const float4 *>(a.rope_cos + (size_t)pos * half + i), s = *reinterpret_cast<const float4 *>(a.rope_sin + (size_t)pos * half + i);
+    const float *cs = a.rope_cos + (size_t)pos * half, *sn = a.rope_sin + (size_t)pos * half;
+    // four consecutive rotary pairs per thread (head_dim / 2 is a multiple of 4)
+    for (int p4 = tid; p4 < (a.n_q + a.n_kv) * (half >> 2); p4 += ROWK_THREADS) {
+        const int head = p4 / (half >> 2), i = (p4 - head * (half >> 2)) * 4;
         const size_t e0 = xo + head * hd + i;
-        float4 x0 = sum_splits4(a.qkv, e0, ks_n, a.part_stride, *reinterpret_cast<const float4 *>(a.qkv + e0));
-        float4 x1 = sum_splits4(a.qkv, e0 + half, ks_n, a.part_stride, *reinterpret_cast<const float4 *>(a.qkv + e0 + half));
-        x0.x *= inv; x0.y *= inv; x0.z *= inv; x0.w *= inv; x1.x *= inv; x1.y *= inv; x1.z *= inv; x1.w *= inv;
+        const float4 x0 = sum_splits4(a.qkv, e0, ks_n, a.part_stride, *reinterpret_cast<const float4 *>(a.qkv + e0));
+        const float4 x1 = sum_splits4(a.qkv, e0 + half, ks_n, a.part_stride, *reinterpret_cast<const float4 *>(a.qkv + e0 + half));
+        const float4 c = *reinterpret_cast<const float4 *>(cs + i), s = *reinterpret_cast<const float4 *>(sn + i);
         const float4 y0 = make_float4(x0.x * c.x - x1.x * s.x, x0.y * c.y - x1.y * s.y, x0.z * c.z - x1.z * s.z, x0.w * c.w - x1.w * s.w);
         const float4 y1 = make_float4(x1.x * c.x + x0.x * s.x, x1.y * c.y + x0.y * s.y, x1.z * c.z + x0.z * s.z, x1.w * c.w + x0.w * s.w);
         if (head < a.n_q) {
+            float *q = a.qbuf + ((size_t)r * a.n_q + head) * hd;
             *reinterpret_cast<float4 *>(q + i) = y0; *reinterpret_cast<float4 *>(q + i + half) = y1;
         } else {
             const size_t base = ((((size_t)a.layer * a.max_seqs + slot) * a.n_kv + (head - a.n_q)) * a.max_ctx + pos) * hd;
             *reinterpret_cast<uint2 *>(a.kcache + base + i) = make_uint2(pack_bf16x2(y0.x, y0.y), pack_bf16x2(y0.z, y0.w));
             *reinterpret_cast<uint2 *>(a.kcache + base + i + half) = make_uint2(pack_bf16x2(y1.x, y1.y), pack_bf16x2(y1.z, y1.w));
         }
-    } else if (p4 - n_rot < (a.n_kv * hd) >> 2 && !bad) {
-        const int p = (p4 - n_rot) * 4, vh = p / hd, e = p - vh * hd;
+    }
+    for (int p4 = tid; p4 < (a.n_kv * hd) >> 2; p4 += ROWK_THREADS) {
+        const int p = p4 * 4, vh = p / hd, e = p - vh * hd;
         const size_t e0 = xo + (a.n_q + a.n_kv) * hd + p;
-        const float inv = row_factor(a.ss, r, a.d, a.eps);
         const float4 x = sum_splits4(a.qkv, e0, ks_n, a.part_stride, *reinterpret_cast<const float4 *>(a.qkv + e0));
         const size_t base = (((size_t)a.layer * a.max_seqs + slot) * a.n_kv + vh) * (size_t)a.max_ctx * hd;
         uint16_t *vp = a.vcache + base + (size_t)e * a.max_ctx + pos;          // V is stored [hd][position]
-        vp[0] = f32_to_bf16(x.x * inv); vp[a.max_ctx] = f32_to_bf16(x.y * inv); vp[2 * (size_t)a.max_ctx] = f32_to_bf16(x.z * inv); vp[3 * (size_t)a.max_ctx] = f32_to_bf16(x.w * inv);
+        vp[0] = f32_to_bf16(x.x); vp[a.max_ctx] = f32_to_bf16(x.y); vp[2 * (size_t)a.max_ctx] = f32_to_bf16(x.z); vp[3 * (size_t)a.max_ctx] = f32_to_bf16(x.w);
     }
 }
 
@@ -164,7 +166,6 @@ struct GemmArgs {
     int d_ffn;
     const float *seq_scale; SoftPartial *parts; float *logits; int n_parts;   // LM head
     int sample_on; unsigned long long sample_key;         // LM head: also track the arg max of logit + Gumbel noise
-    const float *ss; float eps;                           // gate/up, LM head: row_factor of the norm before it, over K channels
     const int *row_pos, *out_row;                         // sampling: position of the row that feeds output row m is row_pos[out_row[m]]
 };
 
@@ -225,10 +226,6 @@ __global__ void __launch_bounds__(GEMM_NW * 64) k_gemm_rows(GemmArgs a) {
     const float lm_scale = (MODE == G_LMHEAD && lm_row < a.M) ? a.seq_scale[lm_row] : 1.f;
     unsigned long long noise_base = 0;                    // sampling: (position of the token being predicted) * V
     if (MODE == G_LMHEAD && a.sample_on && lm_row < a.M) noise_base = (unsigned long long)(a.row_pos[a.out_row[lm_row]] + 1) * (unsigned long long)a.N;
-
-    float inv[NB];                                        // row factors of this lane's tokens
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) inv[nb] = (MODE == G_GATEUP || MODE == G_LMHEAD) && m_base + nb * 16 + i16 < a.M ? row_factor(a.ss, m_base + nb * 16 + i16, K, a.eps) : 1.f;
 
     for (int unit = unit_first; unit < n_units; unit += unit_step) {
         const int grp = unit / KSP, ksp = unit - grp * KSP;
@@ -356,11 +353,6 @@ __global__ void __launch_bounds__(GEMM_NW * 64) k_gemm_rows(GemmArgs a) {
                 }
             }
             if (tile >= n_tiles || m >= a.M) continue;
-            if constexpr (MODE == G_GATEUP || MODE == G_LMHEAD) {
-                const float f = NB > 1 && nb == 1 ? inv[NB - 1] : inv[0];
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) { v[nt].x *= f; v[nt].y *= f; v[nt].z *= f; v[nt].w *= f; }
-            }
             if constexpr (MODE != G_LMHEAD) {
                 // (n_out is a multiple of 16: whole tiles, one 16-byte store per lane)
                 const int n = n0 + 4 * g;

@@ -70,7 +70,7 @@ const char *check_config(const rs_config *c) {
 }
 
 struct Layout {
-    size_t rope_cos, rope_sin, row_slot, row_pos, row_bad, out_row, seq_bad, seq_scale, seq_info, slice_len, pieces, h, row_ss, qkv_raw, qbuf,
+    size_t rope_cos, rope_sin, row_slot, row_pos, row_bad, out_row, seq_bad, seq_scale, seq_info, slice_len, pieces, h, qkv_raw, qbuf,
         attn_out, act, attn_part, attn_cnt, lm_parts, sync, layer_ptrs, gemm_part, xn32, lm32, total;
     int attn_rows_x_splits;   // capacity of attn_part in (row, split) pairs
     int lm_parts_cap;         // partial states per sequence
@@ -113,7 +113,6 @@ Layout make_layout(const rs_config &c) {
     L.seq_info = take((size_t)c.max_seqs * 16);
     L.slice_len = take(8);
     L.h = take((size_t)c.max_rows * c.d_model * 4);
-    L.row_ss = take((size_t)(c.max_rows > c.max_seqs ? c.max_rows : c.max_seqs) * rs::norm_chunks(c.d_model) * 4);      // sums of squares of the row norms
     L.qkv_raw = take((size_t)c.max_rows * qkv * 4);
     L.qbuf = take((size_t)c.max_rows * qdim * 4);
     // activations that a matrix-core kernel reads lie in blocks of rows (frag_index)
@@ -688,7 +687,7 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
     const Layout &L = m->lay;
     const int hd = c.head_dim, qdim = c.n_q_heads * hd, qkv_rows = (c.n_q_heads + 2 * c.n_kv_heads) * hd;
     int *row_slot = m->at<int>(L.row_slot), *row_pos = m->at<int>(L.row_pos), *row_bad = m->at<int>(L.row_bad);
-    float *h = m->at<float>(L.h), *row_ss = m->at<float>(L.row_ss);
+    float *h = m->at<float>(L.h);
 
     PrepArgs pa{};
     pa.n_seqs = n_seqs; pa.n_rows = n_rows; pa.d_model = c.d_model; pa.vocab = c.vocab;
@@ -756,14 +755,14 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
         } else {
             GemmArgs g{};
             const int rsh = frag_shift(n_rows);
-            g.M = n_rows; g.d_ffn = c.d_ffn; g.rsh = rsh; g.ss = row_ss; g.eps = c.rms_eps;
+            g.M = n_rows; g.d_ffn = c.d_ffn; g.rsh = rsh;
             const bool t_qkv = ring_layer(m, n_rows, false, qkv_rows, c.d_model), t_o = ring_layer(m, n_rows, false, c.d_model, qdim);
             const bool t_gu = ring_layer(m, n_rows, true, 2 * c.d_ffn, c.d_model), t_down = ring_layer(m, n_rows, false, c.d_model, c.d_ffn);
             float *xn32 = m->at<float>(L.xn32);
             g.act32 = m->at<float>(L.act);
             // the down projection of the layer before may have left its result as partial sums (pend_*)
-            hipLaunchKernelGGL(k_rmsnorm_rows, dim3(n_rows, norm_chunks(c.d_model)), dim3(ROWK_THREADS), 0, st, h, m->attn_norm[l],
-                               c.d_model, (const int *)nullptr, xn32, rsh, row_ss, (const float *)pend_part, pend_ks, pend_stride);
+            hipLaunchKernelGGL(k_rmsnorm_rows, dim3(n_rows), dim3(ROWK_THREADS), 0, st, h, m->attn_norm[l], c.rms_eps,
+                               c.d_model, (const int *)nullptr, xn32, rsh, (const float *)pend_part, pend_ks, pend_stride);
             RS_LAUNCHED("rmsnorm_rows");
             pend_part = nullptr; pend_ks = 0; pend_stride = 0;
             g.W = m->w_qkv[l]; g.N = qkv_rows; g.K = c.d_model; g.X32 = xn32;
@@ -773,13 +772,12 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
             toc(RS_PHASE_QKV, l);
             RopeArgs ra{};
             ra.qkv = g.part ? g.part : m->at<float>(L.qkv_raw); ra.ksplit = g.ksplit; ra.part_stride = g.part_stride;
-            ra.ss = row_ss; ra.d = c.d_model; ra.eps = c.rms_eps;
             ra.qbuf = m->at<float>(L.qbuf); ra.kcache = m->kv_k; ra.vcache = m->kv_v;
             ra.rope_cos = m->at<float>(L.rope_cos); ra.rope_sin = m->at<float>(L.rope_sin);
             ra.row_pos = row_pos; ra.row_slot = row_slot; ra.row_bad = row_bad;
             ra.n_q = c.n_q_heads; ra.n_kv = c.n_kv_heads; ra.head_dim = hd; ra.max_ctx = c.max_ctx;
             ra.max_seqs = c.max_seqs; ra.layer = l;
-            hipLaunchKernelGGL(k_rope_kv_rows, dim3(n_rows, rope_blocks(c.n_q_heads, c.n_kv_heads, hd)), dim3(ROWK_THREADS), 0, st, ra);
+            hipLaunchKernelGGL(k_rope_kv_rows, dim3(n_rows), dim3(ROWK_THREADS), 0, st, ra);
             RS_LAUNCHED("rope_kv_rows");
             aa.out_frag = 1; aa.rsh = rsh;
             tic(RS_PHASE_ATTN, l);
@@ -796,8 +794,8 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
             tic(RS_PHASE_OPROJ, l);
             if ((rc = launch_gemm<G_OPROJ>(m, g, (c.d_model + 15) / 16, st, "gemm_oproj", t_o))) return rc;
             toc(RS_PHASE_OPROJ, l);
-            hipLaunchKernelGGL(k_rmsnorm_rows, dim3(n_rows, norm_chunks(c.d_model)), dim3(ROWK_THREADS), 0, st, h, m->mlp_norm[l],
-                               c.d_model, (const int *)nullptr, xn32, rsh, row_ss, (const float *)g.part, g.ksplit, g.part_stride);
+            hipLaunchKernelGGL(k_rmsnorm_rows, dim3(n_rows), dim3(ROWK_THREADS), 0, st, h, m->mlp_norm[l], c.rms_eps,
+                               c.d_model, (const int *)nullptr, xn32, rsh, (const float *)g.part, g.ksplit, g.part_stride);
             RS_LAUNCHED("rmsnorm_rows");
             g.W = m->w_gate_up[l]; g.N = 2 * c.d_ffn; g.K = c.d_model; g.X32 = xn32;
             tic(RS_PHASE_GATEUP, l);
@@ -831,12 +829,12 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
         if (rc) return rc;
     } else {
         const int lm_rsh = ring_lm_head(m, n_seqs) && n_seqs < 4 ? 2 : frag_shift(n_seqs);         // (k_gemm_ring: blocks of four rows at least)
-        hipLaunchKernelGGL(k_rmsnorm_rows, dim3(n_seqs, norm_chunks(c.d_model)), dim3(ROWK_THREADS), 0, st, h, m->final_norm,
-                           c.d_model, (const int *)m->at<int>(L.out_row), m->at<float>(L.lm32), lm_rsh, row_ss, (const float *)pend_part, pend_ks,
+        hipLaunchKernelGGL(k_rmsnorm_rows, dim3(n_seqs), dim3(ROWK_THREADS), 0, st, h, m->final_norm, c.rms_eps,
+                           c.d_model, (const int *)m->at<int>(L.out_row), m->at<float>(L.lm32), lm_rsh, (const float *)pend_part, pend_ks,
                            pend_stride);
         RS_LAUNCHED("rmsnorm_rows");
         GemmArgs g{};
-        g.M = n_seqs; g.rsh = lm_rsh; g.ss = row_ss; g.eps = c.rms_eps; g.W = m->lm_head; g.N = c.vocab; g.K = c.d_model; g.X32 = m->at<float>(L.lm32);
+        g.M = n_seqs; g.rsh = lm_rsh; g.W = m->lm_head; g.N = c.vocab; g.K = c.d_model; g.X32 = m->at<float>(L.lm32);
         g.seq_scale = m->at<float>(L.seq_scale); g.parts = parts; g.logits = d_logits;
         g.sample_on = m->sample_on; g.sample_key = m->sample_key; g.row_pos = row_pos; g.out_row = m->at<int>(L.out_row);
         tic(RS_PHASE_LMHEAD, 0);
