@@ -777,7 +777,7 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
             ra.row_pos = row_pos; ra.row_slot = row_slot; ra.row_bad = row_bad;
             ra.n_q = c.n_q_heads; ra.n_kv = c.n_kv_heads; ra.head_dim = hd; ra.max_ctx = c.max_ctx;
             ra.max_seqs = c.max_seqs; ra.layer = l;
-            hipLaunchKernelGGL(k_rope_kv_rows, dim3(n_rows), dim3(ROWK_THREADS), 0, st, ra);
+            hipLaunchKernelGGL(k_rope_kv_rows, dim3(n_rows, rope_blocks(c.n_q_heads, c.n_kv_heads, hd)), dim3(ROPE_THREADS), 0, st, ra);
             RS_LAUNCHED("rope_kv_rows");
             aa.out_frag = 1; aa.rsh = rsh;
             tic(RS_PHASE_ATTN, l);

@@ -45,3 +45,25 @@ def test_rows_of_a_large_matrix(spans, big):
 def test_lm_head_of_few_tiles(vocab, n):
     shape = ModelShape("ring_head", 1, 128, 4, 2, 32, 128, vocab, tied_lm_head=False)
     run(W.make_weights(shape, 59, 1), shape, [1] * (n - 1) + [2], list(range(n)), 16, f"{n} sequences")
+
+
+@pytest.mark.parametrize("d, heads, hd", [(128, 4, 32), (1152, 4, 32), (2176, 8, 128)])
+def test_rotary_of_ragged_workgroups(d, heads, hd):
+    """Rotary items around the 256 of a workgroup, a rejected sequence among the rows."""
+    import paper_2507_17307_amd as P
+    shape = ModelShape("chunks", 2, d, heads, 2, hd, 256, 1000, tied_lm_head=False)
+    w = W.make_weights(shape, 61, 1)
+    n = 5
+    gpu = P.Model(w.to("cuda"), max_ctx=16, max_seqs=n, max_rows=n)
+    ref = decoder.OracleModel(w, 16, n_slots=n)
+    toks = W.rng.randint(61, n, 0, n, shape.vocab).tolist()
+    toks[2] = shape.vocab                                                  # out of range: this sequence alone is flagged
+    scales = [1.0 + i % 5 for i in range(n)]
+    got, lg = gpu.decode_step(toks, [0] * n, 0.6, P.RS_SLM, scales, want_logits=True)
+    torch.cuda.synchronize()
+    for i in range(n):
+        if i == 2:
+            assert got[i].flags & P.FLAG_BADARG, got[i]
+            continue
+        want = ref.forward([toks[i]], 0, slot=i, logit_scale=scales[i])["logits"]
+        check_invocation(got[i], lg[i], want, 0.6, router.SLM, where=f"width {d}, sequence {i}")
