@@ -88,8 +88,8 @@ __global__ void __launch_bounds__(512, 1) k_gemm_ring(GemmArgs a) {
     // G_PART: grid (splits of K, groups of tiles), so that with eight splits every XCD reads one piece of X; else whole K and
     // a workgroup takes the groups blockIdx.y, + gridDim.y ..
     const int n_win = K / GEMM_KW, ksp = MODE == G_PART ? blockIdx.x : 0;
-    const int w_first = MODE == G_PART ? ksp * a.win_per_split + min(ksp, a.win_extra) : 0;
-    const int w_count = MODE == G_PART ? a.win_per_split + (ksp < a.win_extra ? 1 : 0) : n_win;
+    const int w_first = MODE == G_PART ? n_win * ksp / a.ksplit : 0;
+    const int w_count = MODE == G_PART ? n_win * (ksp + 1) / a.ksplit - w_first : n_win;
     const int nrb = min((a.M + 15) >> 4, RB);
 
     if (wave >= NCW) {
@@ -157,8 +157,8 @@ __global__ void __launch_bounds__(512, 1) k_gemm_ring(GemmArgs a) {
     const int rb0 = wave % RBK, ct0 = (wave / RBK) * CTH;     // row blocks rb0, rb0 + RBK ..; first column tile
     const bool rows = rb0 < nrb;
     const int a_off[NS] = {i16 * 128 + ((g ^ (i16 & 7)) << 4), i16 * 128 + (((4 + g) ^ (i16 & 7)) << 4)};
-    // Up to 16 rows there is room for four sums in the place of one: the first plane and the two small ones, of even and of odd k steps.
-    // Sums of a sixth of the length at full magnitude: as close to 64 bits as the four waves of k_gemm_rows, each with a quarter of K.
+    // Up to 16 rows there is room for four sums in the place of one, of every fourth window each: the sums of k_gemm_rows' four waves,
+    // in their order, so that it does not matter to a result which of the two kernels a matrix takes.
     constexpr int NA = CS == 4 ? 4 : 1;
     f32x4_t acc[RBW][CTH], part[NA][RBW][CTH];
     SoftState state[MODE == G_LMHEAD ? RBW : 1];
@@ -199,51 +199,58 @@ __global__ void __launch_bounds__(512, 1) k_gemm_ring(GemmArgs a) {
     bf16x8_t A[2][CH], B[NS][RBW][3];
     float4 x0[RBW][2], x1[RBW][2];
     int xb = 0, wb = 0;
-    // the windows of a group of tiles, for a wave with R row blocks
-    auto walk = [&](auto blocks) {
-        constexpr int R = decltype(blocks)::value;
-        for (int st = 0; st < w_count; ++st) {
-            const unsigned char *w = smem + XS * XB + wb * WB;
-            wb = wb + 1 == WS ? 0 : wb + 1; xb = xb + 1 == XS ? 0 : xb + 1;
-            const unsigned char *w_next = smem + XS * XB + wb * WB, *x_next = smem + xb * XB;
+    // a window of a group of tiles, added to sums `which`, for a wave with R row blocks
+    auto window = [&](auto blocks, auto which) {
+        constexpr int R = decltype(blocks)::value, WHICH = decltype(which)::value;
+        const unsigned char *w = smem + XS * XB + wb * WB;
+        wb = wb + 1 == WS ? 0 : wb + 1; xb = xb + 1 == XS ? 0 : xb + 1;
+        const unsigned char *w_next = smem + XS * XB + wb * WB, *x_next = smem + xb * XB;
 #pragma unroll
-            for (int q = 0; q < NGR; ++q) {
-                __builtin_amdgcn_sched_barrier(0);
-                if (q + 1 < NGR) read_a(w, q + 1, A[(q + 1) & 1]);
-                else {
-                    if (NCH == 1) read_x(x_next, 1, x1);
-                    lds_barrier();
-                    read_a(w_next, 0, A[0]);
-                }
-                if (q == NCH - 1) read_x(x_next, 0, x0);
-                if (NCH > 1 && q == NGR - 2) read_x(x_next, 1, x1);
+        for (int q = 0; q < NGR; ++q) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (q + 1 < NGR) read_a(w, q + 1, A[(q + 1) & 1]);
+            else {
+                if (NCH == 1) read_x(x_next, 1, x1);
+                lds_barrier();
+                read_a(w_next, 0, A[0]);
+            }
+            if (q == NCH - 1) read_x(x_next, 0, x0);
+            if (NCH > 1 && q == NGR - 2) read_x(x_next, 1, x1);
 #pragma unroll
-                for (int pl = 2; pl >= 0; --pl)
-#pragma unroll
-                    for (int r = 0; r < R; ++r)
-#pragma unroll
-                        for (int i = 0; i < CH; ++i) {
-                            const int t = (q % NCH) * CH + i;
-                            if (t < CTH) {
-                                f32x4_t &sum = part[NA == 4 ? 2 * (q / NCH) + (pl == 0 ? 0 : 1) : 0][r][t];
-                                sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[q & 1][i], B[q / NCH][r][pl], sum, 0, 0, 0);
-                            }
-                        }
-                // the planes of the next k step, spread over the groups of this one
-                bool split = false;
+            for (int pl = 2; pl >= 0; --pl)
 #pragma unroll
                 for (int r = 0; r < R; ++r)
-                    if (r * NCH / R == q % NCH) {
-                        if (q < NCH) planes(x1[r], B[1][r]); else planes(x0[r], B[0][r]);
-                        split = true;
-                    }
-                if (split) {
 #pragma unroll
-                    for (int i = 0; i < 3 * R * CH; ++i) {
-                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+                    for (int i = 0; i < CH; ++i) {
+                        const int t = (q % NCH) * CH + i;
+                        if (t < CTH) part[WHICH][r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[q & 1][i], B[q / NCH][r][pl], part[WHICH][r][t], 0, 0, 0);
                     }
+            // the planes of the next k step, spread over the groups of this one
+            bool split = false;
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (r * NCH / R == q % NCH) {
+                    if (q < NCH) planes(x1[r], B[1][r]); else planes(x0[r], B[0][r]);
+                    split = true;
                 }
+            if (split) {
+#pragma unroll
+                for (int i = 0; i < 3 * R * CH; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+                }
+            }
+        }
+    };
+    auto walk = [&](auto blocks) {
+        if constexpr (NA == 1) {
+            for (int st = 0; st < w_count; ++st) window(blocks, std::integral_constant<int, 0>{});
+        } else {
+            for (int st = 0; st < w_count; st += 4) {
+                window(blocks, std::integral_constant<int, 0>{});
+                if (st + 1 < w_count) window(blocks, std::integral_constant<int, 1>{});
+                if (st + 2 < w_count) window(blocks, std::integral_constant<int, 2>{});
+                if (st + 3 < w_count) window(blocks, std::integral_constant<int, 3>{});
             }
         }
     };
@@ -271,7 +278,7 @@ __global__ void __launch_bounds__(512, 1) k_gemm_ring(GemmArgs a) {
 #pragma unroll
         for (int r = 0; r < RBW; ++r)
 #pragma unroll
-            for (int t = 0; t < CTH; ++t) acc[r][t] = NA == 4 ? (part[NA - 1][r][t] + part[NA / 4][r][t]) + (part[0][r][t] + part[NA / 2][r][t]) : part[0][r][t];
+            for (int t = 0; t < CTH; ++t) acc[r][t] = NA == 4 ? ((part[0][r][t] + part[NA / 4][r][t]) + part[NA / 2][r][t]) + part[NA - 1][r][t] : part[0][r][t];
         // ---- epilogue: this lane holds output columns 16 tile + 4 g + e of token 16 rb + i16
 #pragma unroll
         for (int r = 0; r < RBW; ++r) {

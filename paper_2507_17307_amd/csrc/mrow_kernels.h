@@ -163,7 +163,6 @@ struct GemmArgs {
                                           //      workgroups (same weights; ids arranged so that they meet in one XCD's L2)
     int ksplit; size_t part_stride;       // > 1: K is split over workgroups too; split ks writes its partial sums to
     float *part;                          //      part[ks * part_stride + m * N + n] (QKV, O-proj, down) and the consumer adds them up
-    int win_per_split, win_extra;         // k_gemm_ring: k windows of a split, the first win_extra splits take one more
     float *h_out; int ld_h;               // residual accumulate
     int d_ffn;
     const float *seq_scale; SoftPartial *parts; float *logits; int n_parts;   // LM head
