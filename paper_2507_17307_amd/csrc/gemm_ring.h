@@ -156,6 +156,8 @@ __global__ void __launch_bounds__(512, 1) k_gemm_ring(GemmArgs a) {
     // ---------------- multiplying waves
     const int rb0 = wave % RBK, ct0 = (wave / RBK) * CTH;     // row blocks rb0, rb0 + RBK ..; first column tile
     const bool rows = rb0 < nrb;
+    // logits of a whole quad of columns in one store (64 bytes of a row in the place of four times 16 dwords)
+    const bool wide = MODE == G_LMHEAD && a.logits && (a.N & 3) == 0 && (reinterpret_cast<size_t>(a.logits) & 15) == 0;
     const int a_off[NS] = {i16 * 128 + ((g ^ (i16 & 7)) << 4), i16 * 128 + (((4 + g) ^ (i16 & 7)) << 4)};
     // Up to 16 rows there is room for four sums in the place of one, of every fourth window each: the sums of k_gemm_rows' four waves,
     // in their order, so that it does not matter to a result which of the two kernels a matrix takes.
@@ -296,11 +298,13 @@ __global__ void __launch_bounds__(512, 1) k_gemm_ring(GemmArgs a) {
                     if (n0 + 16 <= n_out) state[r].push4(v, idx, {true, true, true, true});
                     else state[r].push4(v, idx, {n < n_out, n + 1 < n_out, n + 2 < n_out, n + 3 < n_out});
                     if (m >= a.M || (!a.sample_on && !a.logits)) continue;
+                    if (wide && n < n_out) *reinterpret_cast<float4 *>(a.logits + (size_t)m * a.N + n) = make_float4(v[0], v[1], v[2], v[3]);
+                    if (!a.sample_on && wide) continue;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         if (n + e >= n_out) continue;
                         if (a.sample_on) state[r].push_noisy(v[e], n + e, a.sample_key, noise_base[r]);
-                        if (a.logits) a.logits[(size_t)m * a.N + n + e] = v[e];
+                        if (a.logits && !wide) a.logits[(size_t)m * a.N + n + e] = v[e];
                     }
                 }
                 continue;
