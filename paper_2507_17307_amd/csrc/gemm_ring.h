@@ -20,8 +20,8 @@
 // load (2330 cycles a window of 120 instructions, 2230 of them matrix-core time).  Kernel times before -> now, us:
 //   7B gate/up (272 MB)   5 / 16 / 24 / 48 / 72 / 128 rows   51 / 53 / 63 / 72 / 86 / 108 -> 45 / 45 / 46 / 53 / 75 / 90
 //   14B gate/up (283 MB)  8 / 61 / 128 rows  55 / 90 / 112 -> 48 / 69 / 101;   32B gate/up (566 MB)  16 / 29 rows  108 / 128 -> 90 / 94
-//   14B down + O (194 MB) 61 rows 65 -> 53;  7B QKV (33 MB) 48 / 128 rows 15.4 / 22.0 -> 13.3 / 21.5;  1.5B QKV (6 MB) 29 rows 7.3 -> 5.4
-//   LM head of the 7B shape (1090 MB)  5 / 16 / 24 / 72 / 128 sequences  175 / 203 / 219 / 385 / 452 -> 168 / 183 / 198 / 338 / 403
+//   14B down + O (194 MB) 61 rows 65 -> 53;  7B QKV (33 MB) 48 / 128 rows 15.4 / 22.0 -> 13.3 / 21.5
+//   LM head of the 7B shape (1090 MB)  5 / 16 / 24 / 72 / 128 sequences  175 / 203 / 219 / 385 / 452 -> 168 / 180 / 195 / 336 / 390
 //
 // Modes: G_GATEUP (SwiGLU epilogue into operand order), G_PART (K split over workgroups, raw partial sums part[ks][row][n] that the next
 // kernel adds up in a fixed order), G_LMHEAD (scaled logits feed each row's softmax state, one partial per row and wave column).

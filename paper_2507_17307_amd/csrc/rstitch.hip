@@ -431,7 +431,7 @@ rs_status launch_gemm_ring_ct(GemmArgs &a, dim3 blocks, hipStream_t st, const ch
 // ks ways: the least estimated time.  A window of a workgroup takes the longest of
 //   its matrix instructions   60.5 ns for each 16 x 16 tile of a wave (96 of them at 128 rows: 1.16 us at the 1.8 GHz that this load leaves)
 //   its loads                 45 bytes/ns into one CU, W at 24.5 of them (6.3 TB/s over 256 CUs)
-//   its dependent steps       0.45 us; 1.0 us above 64 rows, where X is requested only one window ahead
+//   its dependent steps       0.45 us; above 64 rows 0.6, or 1.0 where X is requested only one window ahead
 int plan_ring(int mode, int M, int n_tiles, int n_win, int ks, int n_cu) {
     static const int ct_layer[] = {14, 13, 10, 9, 8, 7, 6, 5, 4, 0}, ct_lm[] = {13, 10, 8, 6, 4, 2, 1, 0};
     const int rbw = M > 64 ? 2 : 1, cs = M > 32 ? 1 : M > 16 ? 2 : 4, blocks = (M + 15) / 16;
@@ -483,8 +483,8 @@ rs_status launch_gemm_ring_rows(const rs_model *m, GemmArgs &a, int n_tiles, hip
 }
 
 // Which products take k_gemm_ring: of more than 16 rows those whose workgroups fill at least 70 % of their rounds of the machine (1.5B
-// shape, 29 rows, QKV of 6 MB would take 5.4 us in place of 7.3, but with a sum in the place of four); up to 16 rows those of matrices from 64 MB on, because a workgroup that fills a CU starts and ends more slowly than the
-// small ones of k_gemm_rows (5 / 16 rows, us, k_gemm_rows / k_gemm_ring: 26 MB 8.3 / 9.2 and 9.5 / 10.2, 33 MB 9.7 / 11.1 and 10.9 / 11.7,
+// shape, 29 rows, QKV of 6 MB would take 5.4 us in place of 7.3, but with one sum in the place of four); up to 16 rows those of
+// matrices from 64 MB on, because a workgroup that fills a CU starts and ends more slowly than the small ones of k_gemm_rows (5 / 16 rows, us, k_gemm_rows / k_gemm_ring: 26 MB 8.3 / 9.2 and 9.5 / 10.2, 33 MB 9.7 / 11.1 and 10.9 / 11.7,
 // 52 MB 13.3 / 13.4 and 15.2 / 14.2, 55 MB 14.2 / 15.4 and 16.6 / 16.2, 73 MB 16.3 / 15.0 and 18.6 / 16.0, 136 MB 25.8 / 26.6 and 27.1 / 27.0,
 // 141 MB 27.4 / 26.5 and 28.9 / 27.1, 272 MB 50.8 / 45.2 and 53.3 / 45.1, 566 MB 101 / 88 and 108 / 90).
 bool ring_layer(const rs_model *m, int rows, bool gateup, int n_out, int K) {
