@@ -40,7 +40,7 @@ def test_rows_of_a_large_matrix(spans, big):
     run(big, BIG, spans, list(range(len(spans))), 96, f"spans {spans}")
 
 
-@pytest.mark.parametrize("vocab", [65, 8197])
+@pytest.mark.parametrize("vocab", [65, 8196, 8197])
 @pytest.mark.parametrize("n", [17, 66, 97])
 def test_lm_head_of_few_tiles(vocab, n):
     shape = ModelShape("ring_head", 1, 128, 4, 2, 32, 128, vocab, tied_lm_head=False)
@@ -67,3 +67,24 @@ def test_rotary_of_ragged_workgroups(d, heads, hd):
             continue
         want = ref.forward([toks[i]], 0, slot=i, logit_scale=scales[i])["logits"]
         check_invocation(got[i], lg[i], want, 0.6, router.SLM, where=f"width {d}, sequence {i}")
+
+
+@pytest.mark.parametrize("vocab", [1004, 1005])
+def test_logits_of_a_buffer_at_any_address(vocab):
+    """Quads of logits leave in one store where vocabulary and address allow it: the same values wherever the buffer starts, nothing outside."""
+    import paper_2507_17307_amd as P
+    n = 18
+    shape = ModelShape("ring_logits", 1, 128, 4, 2, 32, 128, vocab, tied_lm_head=False)
+    gpu = P.Model(W.make_weights(shape, 67, 1).to("cuda"), max_ctx=16, max_seqs=n, max_rows=n)
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device="cuda")  # noqa: E731
+    slot, pos, tok = i32(list(range(n))), i32([0] * n), i32(W.rng.randint(67, n, 0, n, vocab).tolist())
+    scale, out = torch.ones(n, device="cuda"), P.binding.new_route_out(n)
+    got = []
+    for first in (4, 5, 7):
+        buf = torch.full((n * vocab + 16,), 7.0, device="cuda")
+        lg = buf[first:first + n * vocab].view(n, vocab)
+        P.rs_decode_step(gpu.handle, n, slot, tok, pos, scale, 0.6, P.RS_SLM, out, lg)
+        torch.cuda.synchronize()
+        assert (buf[:first] == 7.0).all() and (buf[first + n * vocab:] == 7.0).all()
+        got.append(lg.clone())
+    assert torch.equal(got[0], got[1]) and torch.equal(got[0], got[2])
