@@ -1,0 +1,82 @@
+// Arithmetic of the launches of the matrix-core products (k_gemm_rows, k_gemm_ring): which kernel takes a matrix, how K is split and how many
+// column tiles a workgroup gets.  Plain C++ without HIP types, so that it can also be compiled and checked on a CPU.
+#pragma once
+
+#include <cstddef>
+#include <initializer_list>
+
+namespace rs {
+
+constexpr int GEMM_KW = 64;                       // k elements per window: K must be a multiple
+constexpr int KSPLIT_MAX = 8;                     // workgroup-level splits of K, at most
+
+// ---- In which order a product's terms are added: a matter of its shape, kept apart from the kernels and their launch shapes.
+// K and V are rounded to bf16, and a sum in another order now and then rounds the other way; with a context of a few hundred positions one
+// such step moves a row's logits by up to 1e-4 of their size, fifty times what the order itself does.  So the splits of K below stay as
+// they are whichever kernel takes a matrix.
+// k_gemm_rows: tiles of a workgroup, and its split of K: further while the launch has fewer than 1.75 workgroups per CU (A/B of the
+// whole stitched run: with a threshold of 2 the 7B O-proj went from 448 to 896 workgroups of 7 windows each and its calls
+// were 0.04 ms slower)
+inline int rows_tiles(bool one_block, int n_win) { return one_block && n_win < 128 ? 2 : 4; }      // short rows: smaller groups rather than thin K slices
+inline int split_few(bool one_block, int n_tiles, int n_win, int n_cu) {
+    const int r = rows_tiles(one_block, n_win), groups = (n_tiles + r - 1) / r;
+    int ks = 1;
+    while (ks < KSPLIT_MAX && groups * ks < 7 * n_cu / 4 && n_win / (2 * ks) >= 4) ks *= 2;
+    return ks;
+}
+// More than 16 rows: the split with which groups of ten tiles or fewer (gate/up, which cannot be split: pairs of five or fewer) come
+// closest to whole rounds of the machine, and how close that is.
+struct SplitPlan { int ks; double eff; };
+inline SplitPlan split_many(bool gateup, int n_tiles, int n_win, int n_cu) {
+    static const int ct_gu[] = {5, 4, 3, 2, 0}, ct_part[] = {10, 8, 7, 6, 4, 0};
+    SplitPlan best{1, -1.0};
+    for (const int *c = gateup ? ct_gu : ct_part; *c; ++c) {
+        const int groups = (n_tiles + *c - 1) / *c;
+        for (int ks = 1; ks <= (gateup ? 1 : KSPLIT_MAX); ++ks) {
+            if (ks > 1 && n_win / ks < 6) break;
+            const int units = groups * ks, rounds = (units + n_cu - 1) / n_cu;
+            const double eff = (double)units / ((double)rounds * n_cu) * ((double)n_tiles / ((double)groups * *c));
+            if (eff > best.eff + 1e-9) best = SplitPlan{ks, eff};
+        }
+    }
+    return best;
+}
+
+// Column tiles per workgroup of a product of M rows with n_tiles tiles (gate/up 8 + 8 columns each, else 16) over n_win windows, K split
+// ks ways: the least estimated time.  A window of a workgroup takes the longest of
+//   its matrix instructions   60.5 ns for each 16 x 16 tile of a wave (96 of them at 128 rows: 1.16 us at the 1.8 GHz that this load leaves)
+//   its loads                 45 bytes/ns into one CU, W at 24.5 of them (6.3 TB/s over 256 CUs)
+//   its dependent steps       0.45 us; above 64 rows 0.6, or 1.0 where X is requested only one window ahead
+inline int plan_ring(bool lm_head, int M, int n_tiles, int n_win, int ks, int n_cu) {
+    static const int ct_layer[] = {14, 13, 10, 9, 8, 7, 6, 5, 4, 0}, ct_lm[] = {13, 10, 8, 6, 4, 2, 1, 0};
+    const int rbw = M > 64 ? 2 : 1, cs = M > 32 ? 1 : M > 16 ? 2 : 4, blocks = (M + 15) / 16;
+    const double row_tiles = M > 64 && blocks <= 4 ? 1 : rbw;
+    int best = 0;
+    double least = 1e30;
+    for (const int *c = lm_head ? ct_lm : ct_layer; *c; ++c) {
+        const int ct = *c, groups = (n_tiles + ct - 1) / ct;
+        if (lm_head && rbw == 2 && ct > 10) continue;                     // (its accumulators would spill)
+        const int units = groups * ks, rounds = (units + n_cu - 1) / n_cu;
+        const double kb = 2.048 * ct, mfma = 0.0605 * ((ct + cs - 1) / cs) * row_tiles, load = (kb + 4.096 * blocks) / 45, w = kb / 24.5;
+        double win = rbw == 2 ? (ct > 10 ? 1.0 : 0.6) : 0.45;
+        for (double t : {mfma, load, w}) win = t > win ? t : win;
+        const double us = rounds * ((n_win + ks - 1) / ks) * win;
+        if (us < least + 1e-9) { least = us; best = ct; }                               // (equal: the smaller groups)
+    }
+    return best;
+}
+
+// Which products take k_gemm_ring: of more than 16 rows those whose workgroups fill at least 70 % of their rounds of the machine (1.5B
+// shape, 29 rows, QKV of 6 MB would take 5.4 us in place of 7.3, but with one sum in the place of four); up to 16 rows those of
+// matrices from 64 MB on, because a workgroup that fills a CU starts and ends more slowly than the small ones of k_gemm_rows (5 / 16 rows, us, k_gemm_rows / k_gemm_ring: 26 MB 8.3 / 9.2 and 9.5 / 10.2, 33 MB 9.7 / 11.1 and 10.9 / 11.7,
+// 52 MB 13.3 / 13.4 and 15.2 / 14.2, 55 MB 14.2 / 15.4 and 16.6 / 16.2, 73 MB 16.3 / 15.0 and 18.6 / 16.0, 136 MB 25.8 / 26.6 and 27.1 / 27.0,
+// 141 MB 27.4 / 26.5 and 28.9 / 27.1, 272 MB 50.8 / 45.2 and 53.3 / 45.1, 566 MB 101 / 88 and 108 / 90).
+inline bool ring_layer(int n_cu, int rows, bool gateup, int n_out, int K) {
+    if (rows <= 16) return (size_t)n_out * (gateup ? 2 : 1) * K * 2 >= ((size_t)64 << 20);
+    return split_many(gateup, (n_out + 15) / 16, K / GEMM_KW, n_cu).eff >= 0.7;
+}
+// LM head: from five column tiles per CU on (a window of fewer costs its dependent steps: vocabulary 8192, one row of the 1.5B shape 12.7 us
+// on k_gemm_rows, 16.0 here; 32 000 entries 22.6 and 21.7, 152 064 81.6 and 77.5) and for more than 16 sequences.
+inline bool ring_lm_head(int n_cu, int n_seqs, int vocab) { return n_seqs > 16 || (vocab + 15) / 16 >= 5 * n_cu; }
+
+}  // namespace rs

@@ -12,13 +12,13 @@
 #pragma once
 
 #include "device_utils.h"
+#include "gemm_plan.h"
 #include "model_kernels.h"
 
 namespace rs {
 
 constexpr int ROWK_THREADS = 1024;     // row norm: one workgroup per token row
 constexpr int ROPE_THREADS = 256;      // rotary kernel: several
-constexpr int KSPLIT_MAX = 8;
 
 // x[i] (+ the other split-K partial sums of it): all requests are issued together, unconditionally
 // (the split index is clamped, a duplicate is dropped by a select), so a row costs one round trip.
@@ -170,7 +170,6 @@ struct GemmArgs {
     const int *row_pos, *out_row;                         // sampling: position of the row that feeds output row m is row_pos[out_row[m]]
 };
 
-constexpr int GEMM_KW = 64;                       // k elements per window: K must be a multiple
 constexpr int GEMM_PITCH = GEMM_KW * 2 + 16;      // bytes per parked row (padded against LDS bank conflicts)
 
 template <int MODE, int NB, int R, int GEMM_NW>

@@ -1,0 +1,51 @@
+"""The launch arithmetic of the matrix-core products (csrc/gemm_plan.h), compiled for the CPU."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2507_17307_amd", "csrc")
+WRAP = """
+#include "gemm_plan.h"
+extern "C" int few(int one_block, int n_tiles, int n_win, int n_cu) { return rs::split_few(one_block, n_tiles, n_win, n_cu); }
+extern "C" int many(int n_tiles, int n_win, int n_cu) { return rs::split_many(false, n_tiles, n_win, n_cu).ks; }
+extern "C" int ring_layer(int n_cu, int rows, int gateup, int n_out, int K) { return rs::ring_layer(n_cu, rows, gateup, n_out, K); }
+"""
+CU = 256
+# outputs and width of the products whose K is split
+SHAPES = {"s15": (1536, 12, 2, 8960), "m7": (3584, 28, 4, 18944), "m14": (5120, 40, 8, 13824), "m32": (5120, 40, 8, 27648)}
+
+
+def products(shape):
+    d, nq, nkv, ffn = SHAPES[shape]
+    return {"qkv": ((nq + 2 * nkv) * 128, d), "o": (d, nq * 128), "down": (d, ffn)}
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("gemm_plan")
+    src, so = d / "wrap.cpp", d / "libgemm_plan.so"
+    src.write_text(WRAP)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC, str(src), "-o", str(so)], check=True)
+    return ctypes.CDLL(str(so))
+
+
+# workgroup-level splits of K on 256 CUs: up to 16 rows; more rows on k_gemm_rows; more rows on k_gemm_ring (0: does not take it)
+SPLITS = {
+    ("s15", "qkv"): (4, 4, 0), ("s15", "o"): (4, 4, 0), ("s15", "down"): (8, 8, 8),
+    ("m7", "qkv"): (4, 8, 7), ("m7", "o"): (4, 8, 8), ("m7", "down"): (8, 8, 8),
+    ("m14", "qkv"): (2, 4, 4), ("m14", "o"): (4, 8, 8), ("m14", "down"): (8, 8, 8),
+    ("m32", "qkv"): (2, 4, 4), ("m32", "o"): (4, 8, 8), ("m32", "down"): (8, 8, 8),
+}
+
+
+@pytest.mark.parametrize("shape,name", SPLITS)
+def test_the_order_of_sums_of_a_product(lib, shape, name):
+    """K and V are rounded to bf16, so the split of a sum can be seen in later logits: what a split is follows from the matrix and the number
+    of CUs alone, and which of the two kernels takes up to 16 rows does not matter to it."""
+    n, k = products(shape)[name]
+    tiles, wins = n // 16, k // 64
+    many = [lib.many(tiles, wins, CU) if lib.ring_layer(CU, rows, 0, n, k) else 0 for rows in (17, 64, 65, 128)]
+    assert len(set(many)) == 1
+    assert (lib.few(1, tiles, wins, CU), lib.few(0, tiles, wins, CU), many[0]) == SPLITS[shape, name]
