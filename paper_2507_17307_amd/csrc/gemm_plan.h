@@ -42,6 +42,9 @@ inline SplitPlan split_many(bool gateup, int n_tiles, int n_win, int n_cu) {
     return best;
 }
 
+// k_gemm_ring: multiplying waves that share a block of 16 rows and split the workgroup's columns
+inline int ring_column_splits(int M) { return M <= 16 ? 4 : M <= 32 ? 2 : 1; }
+
 // Column tiles per workgroup of a product of M rows with n_tiles tiles (gate/up 8 + 8 columns each, else 16) over n_win windows, K split
 // ks ways: the least estimated time.  A window of a workgroup takes the longest of
 //   its matrix instructions   60.5 ns for each 16 x 16 tile of a wave (96 of them at 128 rows: 1.16 us at the 1.8 GHz that this load leaves)
@@ -49,13 +52,12 @@ inline SplitPlan split_many(bool gateup, int n_tiles, int n_win, int n_cu) {
 //   its dependent steps       0.45 us; above 64 rows 0.6, or 1.0 where X is requested only one window ahead
 inline int plan_ring(bool lm_head, int M, int n_tiles, int n_win, int ks, int n_cu) {
     static const int ct_layer[] = {14, 13, 10, 9, 8, 7, 6, 5, 4, 0}, ct_lm[] = {13, 10, 8, 6, 4, 2, 1, 0};
-    const int rbw = M > 64 ? 2 : 1, cs = M > 32 ? 1 : M > 16 ? 2 : 4, blocks = (M + 15) / 16;
+    const int rbw = M > 64 ? 2 : 1, cs = ring_column_splits(M), blocks = (M + 15) / 16;
     const double row_tiles = M > 64 && blocks <= 4 ? 1 : rbw;
     int best = 0;
     double least = 1e30;
     for (const int *c = lm_head ? ct_lm : ct_layer; *c; ++c) {
         const int ct = *c, groups = (n_tiles + ct - 1) / ct;
-        if (lm_head && rbw == 2 && ct > 10) continue;                     // (its accumulators would spill)
         const int units = groups * ks, rounds = (units + n_cu - 1) / n_cu;
         const double kb = 2.048 * ct, mfma = 0.0605 * ((ct + cs - 1) / cs) * row_tiles, load = (kb + 4.096 * blocks) / 45, w = kb / 24.5;
         double win = rbw == 2 ? (ct > 10 ? 1.0 : 0.6) : 0.45;

@@ -1,7 +1,7 @@
 // k_gemm_ring: out[m, n] = sum_k X[m, k] W[n, k] for 3 .. 128 token rows, one workgroup per block of output columns and all rows, so
 // that W is read from HBM once per call.  The products are those of k_gemm_rows (three exact bf16 planes of X, smallest first).
 //
-// A workgroup fills a CU: four waves multiply, two waves fetch X and two fetch W, window by window (64 elements of K), with
+// A workgroup fills a CU: NCW waves multiply (four, or eight), two waves fetch X and two fetch W, window by window (64 elements of K), with
 // loads that go straight to LDS.  Before, every wave fetched its share of W and its own X into registers, parked W in LDS and
 // multiplied: its requests held up its products, and because loads return in order the wait for a piece of X (L2) was a wait
 // for all the W (HBM) requested before it.  Now X and W have rings of their own (XS and WS windows), each filled as far ahead as the
@@ -13,7 +13,9 @@
 //   matrix instructions to hide behind, two vector instructions between two of them (a third would cost issue slots).
 // Rows: a multiplying wave takes RBW blocks of 16 rows (two above 64 rows, so that a tile of W read from LDS serves 32 rows), or
 // up to 32 / 16 rows two / four waves share a block and split the columns (CS).  A wave whose second block lies past the
-// call's rows leaves its products out.  Columns: CT tiles of 16; for gate/up a tile is 8 gate and the 8 matching up columns, which come
+// call's rows leaves its products out.  The LM head of more than 64 sequences has eight waves of one block: beside the softmax state the sums
+// of two blocks and 13 tiles do not fit the registers (57 spilled), and twice the waves share the softmax of a group.  With two blocks
+// and ten tiles at most a vocabulary of 50257 took two rounds of 8 tiles in place of one of 13.  Columns: CT tiles of 16; for gate/up a tile is 8 gate and the 8 matching up columns, which come
 // closer to equal shares of the CUs than 16 + 16 (14B: 247 workgroups of 7 instead of 216 of 4; 32B one round of 247 instead of 432).
 //
 // What bounds it: up to 64 rows W, streamed at 5.3 .. 6.1 TB/s; at 128 rows the matrix cores, which run at 1.7 .. 1.8 GHz under this
@@ -21,7 +23,9 @@
 //   7B gate/up (272 MB)   5 / 16 / 24 / 48 / 72 / 128 rows   51 / 53 / 63 / 72 / 86 / 108 -> 45 / 45 / 46 / 53 / 75 / 90
 //   14B gate/up (283 MB)  8 / 61 / 128 rows  55 / 90 / 112 -> 48 / 69 / 101;   32B gate/up (566 MB)  16 / 29 rows  108 / 128 -> 90 / 94
 //   14B down + O (194 MB) 61 rows 65 -> 53;  7B QKV (33 MB) 48 / 128 rows 15.4 / 22.0 -> 13.3 / 21.5
-//   LM head of the 7B shape (1090 MB)  5 / 16 / 24 / 72 / 128 sequences  175 / 203 / 219 / 385 / 452 -> 168 / 180 / 195 / 336 / 390
+//   LM head of the 7B shape (1090 MB)  5 / 16 / 24 / 65 / 128 sequences  179 / 202 / 213 / 378 / 428 -> 170 / 175 / 193 / 304 / 348
+//   LM head of more than 64 sequences, before / two blocks a wave / eight waves: 50257 entries, 65 / 128 sequences, 1.5B width 71 / 80 / 55 and
+//   76 / 89 / 65, 7B 127 / 146 / 105 and 147 / 165 / 130, 14B 178 / 196 / 148 and 203 / 222 / 177; 8192 entries, 7B 47 / 43 / 39 and 55 / 52 / 50
 //
 // Modes: G_GATEUP (SwiGLU epilogue into operand order), G_PART (K split over workgroups, raw partial sums part[ks][row][n] that the next
 // kernel adds up in a fixed order), G_LMHEAD (scaled logits feed each row's softmax state, one partial per row and wave column).
@@ -69,9 +73,10 @@ __device__ __forceinline__ void wait_loads(int n) {
 typedef __attribute__((address_space(3))) unsigned char lds_byte;
 typedef __attribute__((address_space(1))) const unsigned char global_byte;
 
-template <int MODE, int CT, int RBW, int CS>
-__global__ void __launch_bounds__(512, 1) k_gemm_ring(GemmArgs a) {
-    constexpr int NS = GEMM_KW / 32, NCW = 4;                 // four waves multiply, two fetch X, two fetch W
+template <int MODE, int CT, int RBW, int CS, int NCW>
+__global__ void __launch_bounds__(NCW * 64 + 256, 1) k_gemm_ring(GemmArgs a) {
+    constexpr int NS = GEMM_KW / 32;                          // NCW waves multiply, two fetch X, two fetch W
+    static_assert(MODE != G_LMHEAD || RBW == 1, "the router state of a lane follows one token");
     constexpr int RBK = NCW / CS, RB = RBK * RBW;             // multiplying waves that differ in their rows; row blocks
     constexpr int XS = ring_x_stages<CT, RB>(), WS = ring_w_stages<CT, RB>(), XB = RB * RING_X, WB = CT * RING_W;
     static_assert(WS >= 3, "W of two windows in flight at least");
@@ -163,20 +168,12 @@ __global__ void __launch_bounds__(512, 1) k_gemm_ring(GemmArgs a) {
     // in their order, so that it does not matter to a result which of the two kernels a matrix takes.
     constexpr int NA = CS == 4 ? 4 : 1;
     f32x4_t acc[RBW][CTH], part[NA][RBW][CTH];
-    SoftState state[MODE == G_LMHEAD ? RBW : 1];
-    float lm_scale[RBW];
-    unsigned long long noise_base[RBW];                       // sampling: (position of the token being predicted) * V
-#pragma unroll
-    for (int r = 0; r < RBW; ++r) {
-        lm_scale[r] = 1.f; noise_base[r] = 0;
-        if (MODE == G_LMHEAD) {
-            state[r].init();
-            const int m = (rb0 + r * RBK) * 16 + i16;
-            if (m < a.M) {
-                lm_scale[r] = a.seq_scale[m];
-                if (a.sample_on) noise_base[r] = (unsigned long long)(a.row_pos[a.out_row[m]] + 1) * (unsigned long long)a.N;
-            }
-        }
+    SoftState state; state.init();
+    float lm_scale = 1.f;
+    unsigned long long noise_base = 0;                        // sampling: (position of the token being predicted) * V
+    if (MODE == G_LMHEAD && rb0 * 16 + i16 < a.M) {
+        lm_scale = a.seq_scale[rb0 * 16 + i16];
+        if (a.sample_on) noise_base = (unsigned long long)(a.row_pos[a.out_row[rb0 * 16 + i16]] + 1) * (unsigned long long)a.N;
     }
     // group q of a window: tiles CH (q % NCH) .. of k step q / NCH (a tile past the workgroup's last repeats it; its products are dropped)
     auto read_a = [&](const unsigned char *w, int q, bf16x8_t (&A)[CH]) {
@@ -293,17 +290,17 @@ __global__ void __launch_bounds__(512, 1) k_gemm_ring(GemmArgs a) {
                     if (ct0 + c >= CT || n0 >= n_out) continue;
                     float v[4];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = acc[r][c][e] * lm_scale[r];
+                    for (int e = 0; e < 4; ++e) v[e] = acc[r][c][e] * lm_scale;
                     const int idx[4] = {n, n + 1, n + 2, n + 3};
-                    if (n0 + 16 <= n_out) state[r].push4(v, idx, {true, true, true, true});
-                    else state[r].push4(v, idx, {n < n_out, n + 1 < n_out, n + 2 < n_out, n + 3 < n_out});
+                    if (n0 + 16 <= n_out) state.push4(v, idx, {true, true, true, true});
+                    else state.push4(v, idx, {n < n_out, n + 1 < n_out, n + 2 < n_out, n + 3 < n_out});
                     if (m >= a.M || (!a.sample_on && !a.logits)) continue;
                     if (wide && n < n_out) *reinterpret_cast<float4 *>(a.logits + (size_t)m * a.N + n) = make_float4(v[0], v[1], v[2], v[3]);
                     if (!a.sample_on && wide) continue;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         if (n + e >= n_out) continue;
-                        if (a.sample_on) state[r].push_noisy(v[e], n + e, a.sample_key, noise_base[r]);
+                        if (a.sample_on) state.push_noisy(v[e], n + e, a.sample_key, noise_base);
                         if (a.logits && !wide) a.logits[(size_t)m * a.N + n + e] = v[e];
                     }
                 }
@@ -340,16 +337,12 @@ __global__ void __launch_bounds__(512, 1) k_gemm_ring(GemmArgs a) {
         }
     }
     if (MODE == G_LMHEAD && rows) {
-#pragma unroll
-        for (int r = 0; r < RBW; ++r) {
-            const int m = (rb0 + r * RBK) * 16 + i16;
-            SoftState st = state[r];
-            for (int o = 32; o >= 16; o >>= 1) {
-                SoftState b = shfl_xor_state(st, o);
-                if ((lane & o) == 0) st.merge(b); else { b.merge(st); st = b; }
-            }
-            if (g == 0 && m < a.M) a.parts[(size_t)m * a.n_parts + blockIdx.y * CS + wave / RBK] = to_partial(st);
+        const int m = rb0 * 16 + i16;
+        for (int o = 32; o >= 16; o >>= 1) {
+            SoftState b = shfl_xor_state(state, o);
+            if ((lane & o) == 0) state.merge(b); else { b.merge(state); state = b; }
         }
+        if (g == 0 && m < a.M) a.parts[(size_t)m * a.n_parts + blockIdx.y * CS + wave / RBK] = to_partial(state);
     }
 }
 

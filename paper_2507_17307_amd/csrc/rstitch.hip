@@ -386,16 +386,28 @@ rs_status launch_gemm_nb(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_
     }
 }
 
-template <int MODE, int RBW, int CS, int CT>
-rs_status launch_gemm_ring_ct(GemmArgs &a, dim3 blocks, hipStream_t st, const char *name) {
-    constexpr size_t lds = ring_lds_bytes<CT, 4 / CS * RBW>();
-    if (rs_status rc = allow_lds<k_gemm_ring<MODE, CT, RBW, CS>>(lds, name)) return rc;
-    hipLaunchKernelGGL((k_gemm_ring<MODE, CT, RBW, CS>), blocks, dim3(512), lds, st, a);
+template <int MODE, int CT, int RBW, int CS, int NCW>
+rs_status launch_gemm_ring_ct(const GemmArgs &a, dim3 blocks, hipStream_t st, const char *name) {
+    constexpr size_t lds = ring_lds_bytes<CT, NCW / CS * RBW>();
+    if (rs_status rc = allow_lds<k_gemm_ring<MODE, CT, RBW, CS, NCW>>(lds, name)) return rc;
+    hipLaunchKernelGGL((k_gemm_ring<MODE, CT, RBW, CS, NCW>), blocks, dim3(NCW * 64 + 256), lds, st, a);
     RS_LAUNCHED(name);
     return RS_OK;
 }
 
-template <int MODE, int RBW, int CS>
+// the column tiles that plan_ring chooses from
+template <int MODE, int RBW, int CS, int NCW>
+rs_status launch_gemm_ring_waves(int ct, const GemmArgs &a, dim3 blocks, hipStream_t st, const char *name) {
+#define RS_CT(ct) case ct: return launch_gemm_ring_ct<MODE, ct, RBW, CS, NCW>(a, blocks, st, name);
+    switch (ct) { RS_CT(13) RS_CT(10) RS_CT(8) RS_CT(6) RS_CT(4) }
+    if constexpr (MODE == G_LMHEAD) { switch (ct) { RS_CT(2) RS_CT(1) } }
+    else { switch (ct) { RS_CT(14) RS_CT(9) RS_CT(7) RS_CT(5) } }
+#undef RS_CT
+    return fail(RS_EINVAL, "internal: no kernel of %d column tiles for %s", ct, name);
+}
+
+// wave arrangement by row count, see k_gemm_ring
+template <int MODE>
 rs_status launch_gemm_ring(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_t st, const char *name) {
     const int n_win = a.K / GEMM_KW;
     const int ks = MODE != G_PART ? 1 : a.M <= 16 ? split_few(true, n_tiles, n_win, m->n_cu) : split_many(false, n_tiles, n_win, m->n_cu).ks;
@@ -406,24 +418,12 @@ rs_status launch_gemm_ring(const rs_model *m, GemmArgs &a, int n_tiles, hipStrea
         a.part_stride = (size_t)m->cfg.max_rows * (size_t)a.N;
     }
     const dim3 blocks(ks, MODE == G_PART || groups < m->n_cu ? groups : m->n_cu);
-    if constexpr (MODE == G_LMHEAD) a.n_parts = blocks.y * CS;      // one partial per row, workgroup and column split
-    switch (ct) {
-#define RS_CT(ct) case ct: return launch_gemm_ring_ct<MODE, RBW, CS, ct>(a, blocks, st, name);
-        RS_CT(10) RS_CT(8) RS_CT(6) RS_CT(4)
-    }
-    if constexpr (MODE != G_LMHEAD || RBW == 1) { switch (ct) { RS_CT(13) } }
-    if constexpr (MODE == G_LMHEAD) { switch (ct) { RS_CT(2) default: RS_CT(1) } }
-    else { switch (ct) { RS_CT(14) RS_CT(9) RS_CT(7) default: RS_CT(5) } }
-#undef RS_CT
-}
-
-// wave arrangement by row count, see k_gemm_ring
-template <int MODE>
-rs_status launch_gemm_ring_rows(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_t st, const char *name) {
-    if (a.M > 64) return launch_gemm_ring<MODE, 2, 1>(m, a, n_tiles, st, name);
-    if (a.M <= 16) return launch_gemm_ring<MODE, 1, 4>(m, a, n_tiles, st, name);
-    if (a.M <= 32) return launch_gemm_ring<MODE, 1, 2>(m, a, n_tiles, st, name);
-    return launch_gemm_ring<MODE, 1, 1>(m, a, n_tiles, st, name);
+    if constexpr (MODE == G_LMHEAD) a.n_parts = blocks.y * ring_column_splits(a.M);      // one partial per row, workgroup and column split
+    if (a.M <= 16) return launch_gemm_ring_waves<MODE, 1, 4, 4>(ct, a, blocks, st, name);
+    if (a.M <= 32) return launch_gemm_ring_waves<MODE, 1, 2, 4>(ct, a, blocks, st, name);
+    if (a.M <= 64) return launch_gemm_ring_waves<MODE, 1, 1, 4>(ct, a, blocks, st, name);
+    if constexpr (MODE == G_LMHEAD) return launch_gemm_ring_waves<MODE, 1, 1, 8>(ct, a, blocks, st, name);
+    else return launch_gemm_ring_waves<MODE, 2, 1, 4>(ct, a, blocks, st, name);
 }
 
 // n_tiles = number of 16-column output tiles; 16 * NB token rows compiled in (NB = 1, 2 or 4)
@@ -434,12 +434,12 @@ rs_status launch_gemm(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_t s
     a.yblocks = 1;
     if constexpr (MODE == G_LMHEAD) {
         if (!ring_lm_head(m->n_cu, a.M, a.N)) return launch_gemm_nb<MODE, 1>(m, a, n_tiles, st, name);
-        return launch_gemm_ring_rows<G_LMHEAD>(m, a, n_tiles, st, name);
+        return launch_gemm_ring<G_LMHEAD>(m, a, n_tiles, st, name);
     } else {
         if (ring) {
             // partial sums are always left for the next kernel (a split of one is a plain copy of the result)
-            if constexpr (MODE == G_GATEUP) return launch_gemm_ring_rows<G_GATEUP>(m, a, (a.d_ffn + 7) / 8, st, name);
-            else return launch_gemm_ring_rows<G_PART>(m, a, n_tiles, st, name);
+            if constexpr (MODE == G_GATEUP) return launch_gemm_ring<G_GATEUP>(m, a, (a.d_ffn + 7) / 8, st, name);
+            else return launch_gemm_ring<G_PART>(m, a, n_tiles, st, name);
         }
         // up to 16 rows: one 16-row block; more (matrices with few columns): blocks of 32 rows with workgroups of their own
         if (a.M <= 16) return launch_gemm_nb<MODE, 1>(m, a, n_tiles, st, name);

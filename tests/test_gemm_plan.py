@@ -11,6 +11,7 @@ WRAP = """
 extern "C" int few(int one_block, int n_tiles, int n_win, int n_cu) { return rs::split_few(one_block, n_tiles, n_win, n_cu); }
 extern "C" int many(int n_tiles, int n_win, int n_cu) { return rs::split_many(false, n_tiles, n_win, n_cu).ks; }
 extern "C" int ring_layer(int n_cu, int rows, int gateup, int n_out, int K) { return rs::ring_layer(n_cu, rows, gateup, n_out, K); }
+extern "C" int tiles(int lm_head, int rows, int n_tiles, int n_win, int ks, int n_cu) { return rs::plan_ring(lm_head, rows, n_tiles, n_win, ks, n_cu); }
 """
 CU = 256
 # outputs and width of the products whose K is split
@@ -49,3 +50,10 @@ def test_the_order_of_sums_of_a_product(lib, shape, name):
     many = [lib.many(tiles, wins, CU) if lib.ring_layer(CU, rows, 0, n, k) else 0 for rows in (17, 64, 65, 128)]
     assert len(set(many)) == 1
     assert (lib.few(1, tiles, wins, CU), lib.few(0, tiles, wins, CU), many[0]) == SPLITS[shape, name]
+
+
+@pytest.mark.parametrize("rows", [65, 96, 128])
+@pytest.mark.parametrize("vocab", [50257, 53248])
+def test_lm_head_of_many_sequences_in_one_round(lib, rows, vocab):
+    """A vocabulary that 13 tiles a workgroup hold in one round of the machine does not take two."""
+    assert lib.tiles(1, rows, (vocab + 15) // 16, 24, 1, CU) == 13
