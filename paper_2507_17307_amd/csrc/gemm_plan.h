@@ -44,6 +44,12 @@ inline SplitPlan split_many(bool gateup, int n_tiles, int n_win, int n_cu) {
 
 // k_gemm_ring: multiplying waves that share a block of 16 rows and split the workgroup's columns
 inline int ring_column_splits(int M) { return M <= 16 ? 4 : M <= 32 ? 2 : 1; }
+// More than 64 rows: whether eight waves of one block multiply and not four of two.  A wave splits its X into planes by itself, some 110
+// vector instructions a block and window, which the matrix instructions of a few tiles do not hide; two waves of a SIMD hide each other's.
+// 1.5B down (24 groups of 4 tiles, K split 8 ways), 65 / 128 rows: four waves 19.4 / 22.5 us, eight 18.1 / 20.3, with three tiles and X fetched
+// four windows ahead 17.8 / 20.4 (k_gemm_tile 17.2 / 20.5).  Wider groups are better off with every W tile read once for 32 rows: 7B gate/up,
+// ten tiles, 77.6 / 84.6 and 81.1 / 87.5.
+inline bool ring_eight_waves(bool lm_head, int M, int ct) { return M > 64 && (lm_head || ct <= 5); }
 
 // Column tiles per workgroup of a product of M rows with n_tiles tiles (gate/up 8 + 8 columns each, else 16) over n_win windows, K split
 // ks ways: the least estimated time.  A window of a workgroup takes the longest of
@@ -51,13 +57,14 @@ inline int ring_column_splits(int M) { return M <= 16 ? 4 : M <= 32 ? 2 : 1; }
 //   its loads                 45 bytes/ns into one CU, W at 24.5 of them (6.3 TB/s over 256 CUs)
 //   its dependent steps       0.45 us; above 64 rows 0.6, or 1.0 where X is requested only one window ahead
 inline int plan_ring(bool lm_head, int M, int n_tiles, int n_win, int ks, int n_cu) {
-    static const int ct_layer[] = {14, 13, 10, 9, 8, 7, 6, 5, 4, 0}, ct_lm[] = {13, 10, 8, 6, 4, 2, 1, 0};
+    static const int ct_layer[] = {14, 13, 10, 9, 8, 7, 6, 5, 4, 3, 0}, ct_lm[] = {13, 10, 8, 6, 4, 2, 1, 0};
     const int rbw = M > 64 ? 2 : 1, cs = ring_column_splits(M), blocks = (M + 15) / 16;
     const double row_tiles = M > 64 && blocks <= 4 ? 1 : rbw;
     int best = 0;
     double least = 1e30;
     for (const int *c = lm_head ? ct_lm : ct_layer; *c; ++c) {
         const int ct = *c, groups = (n_tiles + ct - 1) / ct;
+        if (ct == 3 && M <= 64) continue;
         const int units = groups * ks, rounds = (units + n_cu - 1) / n_cu;
         const double kb = 2.048 * ct, mfma = 0.0605 * ((ct + cs - 1) / cs) * row_tiles, load = (kb + 4.096 * blocks) / 45, w = kb / 24.5;
         double win = rbw == 2 ? (ct > 10 ? 1.0 : 0.6) : 0.45;

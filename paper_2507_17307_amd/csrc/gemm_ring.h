@@ -13,7 +13,7 @@
 //   matrix instructions to hide behind, two vector instructions between two of them (a third would cost issue slots).
 // Rows: a multiplying wave takes RBW blocks of 16 rows (two above 64 rows, so that a tile of W read from LDS serves 32 rows), or
 // up to 32 / 16 rows two / four waves share a block and split the columns (CS).  A wave whose second block lies past the
-// call's rows leaves its products out.  The LM head of more than 64 sequences has eight waves of one block: beside the softmax state the sums
+// call's rows leaves its products out.  Above 64 rows narrow groups (ring_eight_waves) and the LM head have eight waves of one block: beside the softmax state the sums
 // of two blocks and 13 tiles do not fit the registers (57 spilled), and twice the waves share the softmax of a group.  With two blocks
 // and ten tiles at most a vocabulary of 50257 took two rounds of 8 tiles in place of one of 13.  Columns: CT tiles of 16; for gate/up a tile is 8 gate and the 8 matching up columns, which come
 // closer to equal shares of the CUs than 16 + 16 (14B: 247 workgroups of 7 instead of 216 of 4; 32B one round of 247 instead of 432).
@@ -44,9 +44,10 @@ constexpr int RING_LDS = 160 * 1024;                           // of a CU
 
 // LDS of a workgroup with CT column tiles and RB row blocks: XS buffers of X windows, then WS buffers of W windows
 constexpr int RING_X = 4096, RING_W = 2048;                   // bytes of a window of one row block / one column tile
-// (X two windows ahead where that leaves W three buffers: 100 rows, LM head of 8192 entries 59 -> 50 us, 7B down 55 -> 49)
+// (X two windows ahead where that leaves W three buffers: 100 rows, LM head of 8192 entries 59 -> 50 us, 7B down 55 -> 49; three where it leaves
+// that of five tiles three: 1.5B down 65 rows 19.2 -> 18.6, gate/up 128 rows 30.2 -> 29.7)
 template <int CT, int RB>
-__host__ __device__ constexpr int ring_x_stages() { return RB > 4 && CT > 10 ? 2 : 3; }
+__host__ __device__ constexpr int ring_x_stages() { return RB <= 4 ? 3 : CT > 10 ? 2 : CT > 5 ? 3 : 4; }
 template <int CT, int RB>
 __host__ __device__ constexpr int ring_w_stages() {
     const int n = (RING_LDS - ring_x_stages<CT, RB>() * RB * RING_X) / (CT * RING_W);

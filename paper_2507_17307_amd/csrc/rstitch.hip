@@ -399,9 +399,13 @@ rs_status launch_gemm_ring_ct(const GemmArgs &a, dim3 blocks, hipStream_t st, co
 template <int MODE, int RBW, int CS, int NCW>
 rs_status launch_gemm_ring_waves(int ct, const GemmArgs &a, dim3 blocks, hipStream_t st, const char *name) {
 #define RS_CT(ct) case ct: return launch_gemm_ring_ct<MODE, ct, RBW, CS, NCW>(a, blocks, st, name);
-    switch (ct) { RS_CT(13) RS_CT(10) RS_CT(8) RS_CT(6) RS_CT(4) }
-    if constexpr (MODE == G_LMHEAD) { switch (ct) { RS_CT(2) RS_CT(1) } }
-    else { switch (ct) { RS_CT(14) RS_CT(9) RS_CT(7) RS_CT(5) } }
+    if constexpr (MODE == G_LMHEAD) {
+        switch (ct) { RS_CT(13) RS_CT(10) RS_CT(8) RS_CT(6) RS_CT(4) RS_CT(2) RS_CT(1) }
+    } else {
+        if constexpr (NCW == 4) { switch (ct) { RS_CT(14) RS_CT(13) RS_CT(10) RS_CT(9) RS_CT(8) RS_CT(7) RS_CT(6) } }
+        if constexpr (RBW == 1) { switch (ct) { RS_CT(5) RS_CT(4) } }
+        if constexpr (NCW == 8) { switch (ct) { RS_CT(3) } }
+    }
 #undef RS_CT
     return fail(RS_EINVAL, "internal: no kernel of %d column tiles for %s", ct, name);
 }
@@ -422,7 +426,8 @@ rs_status launch_gemm_ring(const rs_model *m, GemmArgs &a, int n_tiles, hipStrea
     if (a.M <= 16) return launch_gemm_ring_waves<MODE, 1, 4, 4>(ct, a, blocks, st, name);
     if (a.M <= 32) return launch_gemm_ring_waves<MODE, 1, 2, 4>(ct, a, blocks, st, name);
     if (a.M <= 64) return launch_gemm_ring_waves<MODE, 1, 1, 4>(ct, a, blocks, st, name);
-    if constexpr (MODE == G_LMHEAD) return launch_gemm_ring_waves<MODE, 1, 1, 8>(ct, a, blocks, st, name);
+    if (ring_eight_waves(MODE == G_LMHEAD, a.M, ct)) return launch_gemm_ring_waves<MODE, 1, 1, 8>(ct, a, blocks, st, name);
+    if constexpr (MODE == G_LMHEAD) return fail(RS_EINVAL, "internal: %d sequences", a.M);
     else return launch_gemm_ring_waves<MODE, 2, 1, 4>(ct, a, blocks, st, name);
 }
 

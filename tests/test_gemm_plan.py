@@ -12,6 +12,7 @@ extern "C" int few(int one_block, int n_tiles, int n_win, int n_cu) { return rs:
 extern "C" int many(int n_tiles, int n_win, int n_cu) { return rs::split_many(false, n_tiles, n_win, n_cu).ks; }
 extern "C" int ring_layer(int n_cu, int rows, int gateup, int n_out, int K) { return rs::ring_layer(n_cu, rows, gateup, n_out, K); }
 extern "C" int tiles(int lm_head, int rows, int n_tiles, int n_win, int ks, int n_cu) { return rs::plan_ring(lm_head, rows, n_tiles, n_win, ks, n_cu); }
+extern "C" int eight(int lm_head, int rows, int ct) { return rs::ring_eight_waves(lm_head, rows, ct); }
 """
 CU = 256
 # outputs and width of the products whose K is split
@@ -57,3 +58,10 @@ def test_the_order_of_sums_of_a_product(lib, shape, name):
 def test_lm_head_of_many_sequences_in_one_round(lib, rows, vocab):
     """A vocabulary that 13 tiles a workgroup hold in one round of the machine does not take two."""
     assert lib.tiles(1, rows, (vocab + 15) // 16, 24, 1, CU) == 13
+
+
+@pytest.mark.parametrize("rows", [65, 128])
+def test_narrow_groups_of_many_rows_fill_the_machine(lib, rows):
+    """The 1.5B shape's down projection above 64 rows: 96 tiles, K split 8 ways, take every CU, and two waves a SIMD."""
+    ct = lib.tiles(0, rows, 96, 140, 8, CU)
+    assert -(-96 // ct) * 8 == CU and lib.eight(0, rows, ct)

@@ -12,6 +12,7 @@ from workloads.shapes import ModelShape
 pytestmark = pytest.mark.gpu
 
 BIG = ModelShape("ring_big", 1, 3072, 24, 8, 128, 11264, 20503, tied_lm_head=True)      # gate/up, down and LM head: 64 MB and more
+NARROW = ModelShape("ring_narrow", 1, 1536, 12, 2, 128, 8960, 1000, tied_lm_head=False)
 
 
 @pytest.fixture(scope="module")
@@ -38,6 +39,17 @@ def run(w, shape, spans, slots, max_ctx, where):
 @pytest.mark.parametrize("spans", [[3], [2, 2], [2, 1, 2], [8], [9], [1, 2, 3, 4, 6], [70], [30, 51]])
 def test_rows_of_a_large_matrix(spans, big):
     run(big, BIG, spans, list(range(len(spans))), 96, f"spans {spans}")
+
+
+@pytest.fixture(scope="module")
+def narrow():
+    return W.make_weights(NARROW, 57, 1)
+
+
+@pytest.mark.parametrize("spans", [[65], [40, 41], [128]])
+def test_narrow_groups_of_many_rows(spans, narrow):
+    """Eight multiplying waves of one row block, some without rows: groups of three tiles (down) and of five (gate/up)."""
+    run(narrow, NARROW, spans, list(range(len(spans))), 136, f"spans {spans}")
 
 
 @pytest.mark.parametrize("vocab", [65, 8196, 8197])
