@@ -24,6 +24,8 @@ inline int split_few(bool one_block, int n_tiles, int n_win, int n_cu) {
     while (ks < KSPLIT_MAX && groups * ks < 7 * n_cu / 4 && n_win / (2 * ks) >= 4) ks *= 2;
     return ks;
 }
+// k_gemm_rows, products over whole K (gate/up and LM head of up to 16 rows): tiles of a workgroup
+inline int rows_tiles_whole(int n_tiles, int n_cu) { return (n_tiles + 1) / 2 >= 7 * n_cu / 4 ? 2 : 1; }
 // More than 16 rows: the split with which groups of ten tiles or fewer (gate/up, which cannot be split: pairs of five or fewer) come
 // closest to whole rounds of the machine, and how close that is.
 struct SplitPlan { int ks; double eff; };
@@ -75,14 +77,27 @@ inline int plan_ring(bool lm_head, int M, int n_tiles, int n_win, int ks, int n_
     return best;
 }
 
-// Which products take k_gemm_ring: of more than 16 rows those whose workgroups fill at least 70 % of their rounds of the machine (1.5B
-// shape, 29 rows, QKV of 6 MB would take 5.4 us in place of 7.3, but with one sum in the place of four); up to 16 rows those of
-// matrices from 64 MB on, because a workgroup that fills a CU starts and ends more slowly than the small ones of k_gemm_rows (5 / 16 rows, us, k_gemm_rows / k_gemm_ring: 26 MB 8.3 / 9.2 and 9.5 / 10.2, 33 MB 9.7 / 11.1 and 10.9 / 11.7,
-// 52 MB 13.3 / 13.4 and 15.2 / 14.2, 55 MB 14.2 / 15.4 and 16.6 / 16.2, 73 MB 16.3 / 15.0 and 18.6 / 16.0, 136 MB 25.8 / 26.6 and 27.1 / 27.0,
-// 141 MB 27.4 / 26.5 and 28.9 / 27.1, 272 MB 50.8 / 45.2 and 53.3 / 45.1, 566 MB 101 / 88 and 108 / 90).
+// Which products take k_gemm_ring.  More than 16 rows: those whose workgroups fill at least 70 % of their rounds of the machine (1.5B
+// shape, 29 rows, QKV of 6 MB would take 5.4 us in place of 7.3, but with one sum in the place of four).
+// Up to 16 rows: matrices from 64 MB on, because a workgroup that fills a CU starts and ends more slowly than the small ones of k_gemm_rows, and of
+// these the ones that k_gemm_rows does not spread evenly.  It has all of two or three workgroups a CU resident at once, so where every CU gets nearly
+// as many it streams as well as the ring and starts sooner; where some get one more than others they are what the rest waits for.
+// Above 8 rows its workgroups pull twice the X, and K split over ring workgroups of six tiles and 33 windows or more wins all the same.
+// Measured, us at 3 / 8 / 16 rows, k_gemm_rows (workgroups a CU) and k_gemm_ring:
+//   even    14B QKV  73 MB (1.75)  15.8 17.0 19.6 and 19.8 19.9 20.6;  7B down 136 MB (1.75)  25.5 26.4 26.9 and 26.0 26.3 26.1;
+//           width 3072 gate/up 101 MB (2)  19.2 19.6 21.6 and 22.6 22.7 23.2;  width 8192 O 134 MB (2)  31.9 32.0 32.8 and 36.3 36.0 37.0;
+//           width 4096 gate/up 235 MB (1.75)  45.5 46.2 47.9 and 50.2 50.7 50.9;  width 6144 down 201 MB (3)  46.5 45.7 46.7 and 45.6 46.5 48.1
+//   uneven  7B gate/up 272 MB (2.3)  52.0 52.4 52.6 and 45.4 45.4 43.4;  14B gate/up 283 MB (3.4)  54.0 56.2 64.1 and 47.6 47.5 47.8;
+//           14B down 142 MB (2.5)  27.9 28.6 30.4 and 26.1 26.6 26.8;  width 2560 down 71 MB (1.25)  16.6 17.5 19.3 and 16.1 16.7 17.0
+//   below   14B O 52 MB (2.5)  12.3 13.5 15.3 and 13.4 13.8 14.2;  1.5B gate/up 55 MB (2.2), 5 / 8 / 16 rows  14.2 14.3 16.3 and 14.6 14.6 14.1
 inline bool ring_layer(int n_cu, int rows, bool gateup, int n_out, int K) {
-    if (rows <= 16) return (size_t)n_out * (gateup ? 2 : 1) * K * 2 >= ((size_t)64 << 20);
-    return split_many(gateup, (n_out + 15) / 16, K / GEMM_KW, n_cu).eff >= 0.7;
+    const int n_tiles = (n_out + 15) / 16, n_win = K / GEMM_KW;
+    if (rows > 16) return split_many(gateup, n_tiles, n_win, n_cu).eff >= 0.7;
+    if ((size_t)n_out * (gateup ? 2 : 1) * K * 2 < ((size_t)64 << 20)) return false;
+    const int r = gateup ? rows_tiles_whole(n_tiles, n_cu) : rows_tiles(true, n_win), ks = gateup ? 1 : split_few(true, n_tiles, n_win, n_cu);
+    const int units = (n_tiles + r - 1) / r * ks, most = (units + n_cu - 1) / n_cu;
+    const bool even = (most == 2 || most == 3) && 8 * units >= 7 * n_cu * most;
+    return !even || (rows > 8 && !gateup && n_win / ks > 32 && n_tiles * ks >= 6 * n_cu);
 }
 // LM head: from five column tiles per CU on (a window of fewer costs its dependent steps: vocabulary 8192, one row of the 1.5B shape 12.7 us
 // on k_gemm_rows, 16.0 here; 32 000 entries 22.6 and 21.7, 152 064 81.6 and 77.5) and for more than 16 sequences.

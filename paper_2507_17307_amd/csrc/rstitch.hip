@@ -358,7 +358,7 @@ int gemm_grid(int units, int yblocks) { return yblocks > 1 ? ((units + 7) / 8) *
 template <int MODE, int NB>
 rs_status launch_gemm_nb(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_t st, const char *name) {
     constexpr bool SPLITS = MODE == G_QKV || MODE == G_OPROJ || MODE == G_DOWN;
-    const int target = 7 * m->n_cu / 4, n_win = a.K / GEMM_KW;
+    const int n_win = a.K / GEMM_KW;
     a.ksplit = 1; a.part = nullptr; a.part_stride = 0;
     if constexpr (SPLITS) {
         const int r = rows_tiles(NB == 1, n_win), groups = (n_tiles + r - 1) / r, ks = split_few(NB == 1, n_tiles, n_win, m->n_cu);
@@ -378,7 +378,7 @@ rs_status launch_gemm_nb(const rs_model *m, GemmArgs &a, int n_tiles, hipStream_
         return launch_gemm_r<MODE, NB, 2, 4>(a, blocks, st, name);
     } else {
         // (LM head: vocabularies too small for k_gemm_ring, up to 16 sequences)
-        const int r = (n_tiles + 1) / 2 >= target ? 2 : 1;
+        const int r = rows_tiles_whole(n_tiles, m->n_cu);
         const int blocks = gemm_grid((n_tiles + r - 1) / r, a.yblocks);
         if (MODE == G_LMHEAD) a.n_parts = blocks;                         // one partial per workgroup
         if (r == 2) return launch_gemm_r<MODE, NB, 2, 4>(a, blocks, st, name);

@@ -65,3 +65,15 @@ def test_narrow_groups_of_many_rows_fill_the_machine(lib, rows):
     """The 1.5B shape's down projection above 64 rows: 96 tiles, K split 8 ways, take every CU, and two waves a SIMD."""
     ct = lib.tiles(0, rows, 96, 140, 8, CU)
     assert -(-96 // ct) * 8 == CU and lib.eight(0, rows, ct)
+
+
+@pytest.mark.parametrize("shape,name,gateup,takes", [
+    # rows at which the matrix takes k_gemm_ring, of 3, 8, 9 and 16 (the measurements beside ring_layer)
+    ("s15", "gu", 1, ()), ("s15", "down", 0, ()), ("m7", "qkv", 0, ()), ("m7", "o", 0, ()), ("m7", "gu", 1, (3, 8, 9, 16)),
+    ("m7", "down", 0, (9, 16)), ("m14", "qkv", 0, ()), ("m14", "o", 0, ()), ("m14", "gu", 1, (3, 8, 9, 16)), ("m14", "down", 0, (3, 8, 9, 16)),
+    ("m32", "qkv", 0, ()), ("m32", "gu", 1, (3, 8, 9, 16)), ("m32", "down", 0, (3, 8, 9, 16))])
+def test_which_products_of_few_rows_take_the_ring(lib, shape, name, gateup, takes):
+    """Not those that k_gemm_rows spreads evenly over the CUs."""
+    d, _, _, ffn = SHAPES[shape]
+    n, k = (ffn, d) if gateup else products(shape)[name]
+    assert tuple(r for r in (3, 8, 9, 16) if lib.ring_layer(CU, r, gateup, n, k)) == takes
