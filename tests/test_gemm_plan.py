@@ -12,6 +12,7 @@ extern "C" int few(int one_block, int n_tiles, int n_win, int n_cu) { return rs:
 extern "C" int many(int n_tiles, int n_win, int n_cu) { return rs::split_many(false, n_tiles, n_win, n_cu).ks; }
 extern "C" int ring_layer(int n_cu, int rows, int gateup, int n_out, int K) { return rs::ring_layer(n_cu, rows, gateup, n_out, K); }
 extern "C" int tiles(int lm_head, int rows, int n_tiles, int n_win, int ks, int n_cu) { return rs::plan_ring(lm_head, rows, n_tiles, n_win, ks, n_cu); }
+extern "C" int ring_lm_head(int n_cu, int n_seqs, int vocab) { return rs::ring_lm_head(n_cu, n_seqs, vocab); }
 extern "C" int eight(int lm_head, int rows, int ct) { return rs::ring_eight_waves(lm_head, rows, ct); }
 """
 CU = 256
@@ -60,6 +61,19 @@ def test_lm_head_of_many_sequences_in_one_round(lib, rows, vocab):
     assert lib.tiles(1, rows, (vocab + 15) // 16, 24, 1, CU) == 13
 
 
+@pytest.mark.parametrize("rows", [18, 40, 65, 128])
+def test_the_lm_head_tests_of_thirteen_tiles_take_thirteen(lib, rows):
+    """The shape of test_gpu_operand_order.py: 53233 entries, two windows of K."""
+    assert lib.tiles(1, rows, (53233 + 15) // 16, 2, 1, CU) == 13
+
+
+@pytest.mark.parametrize("rows", [81, 97, 128])
+def test_the_widest_groups_of_many_rows_are_tested(lib, rows):
+    """The shape of test_gpu_gemm_ring.py whose gate/up takes 14 tiles on four waves of two row blocks: X two windows in LDS, W three."""
+    assert lib.tiles(0, rows, 27648 // 8, 1536 // 64, 1, CU) == 14 and not lib.eight(0, rows, 14)
+    assert lib.ring_layer(CU, rows, 1, 27648, 1536) and lib.ring_layer(CU, rows, 0, 1536, 27648)      # (gate/up and down go together)
+
+
 @pytest.mark.parametrize("rows", [65, 128])
 def test_narrow_groups_of_many_rows_fill_the_machine(lib, rows):
     """The 1.5B shape's down projection above 64 rows: 96 tiles, K split 8 ways, take every CU, and two waves a SIMD."""
@@ -77,3 +91,9 @@ def test_which_products_of_few_rows_take_the_ring(lib, shape, name, gateup, take
     d, _, _, ffn = SHAPES[shape]
     n, k = (ffn, d) if gateup else products(shape)[name]
     assert tuple(r for r in (3, 8, 9, 16) if lib.ring_layer(CU, r, gateup, n, k)) == takes
+
+
+def test_the_layer_that_changes_kernels_between_8_and_9_rows(lib):
+    """The shape of test_gpu_gemm_ring.py that compares the two kernels' sums, and its LM head on either side of the rule."""
+    assert not lib.ring_layer(CU, 8, 0, 3584, 16896) and lib.ring_layer(CU, 9, 0, 3584, 16896)
+    assert not lib.ring_lm_head(CU, 3, 20464) and lib.ring_lm_head(CU, 3, 20480)

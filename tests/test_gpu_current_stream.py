@@ -22,4 +22,5 @@ def test_default_stream_of_a_call_is_the_current_one():
         t.start()
         t.join()
     note()
+    assert len(seen) == 4                                    # (an exception in the thread leaves three)
     assert all(a == b for a, b in seen) and seen[1][0] == side.cuda_stream != seen[2][0], seen

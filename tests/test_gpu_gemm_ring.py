@@ -1,6 +1,8 @@
 """k_gemm_ring where it can go wrong: blocks of 4, 8 and 16 rows on matrices that take it from three rows on, an LM head of up to
-three sequences in blocks of four rows, waves with one and with two row blocks, vocabularies whose last tile is ragged, a matrix
-of two windows of K (fewer than the rings hold), and a head of fewer groups than CUs."""
+three sequences in blocks of four rows, waves with one and with two row blocks, four and eight of them, vocabularies whose last tile is ragged, a
+matrix of two windows of K (fewer than the rings hold), a head of fewer groups than CUs, the widest groups, and the order of its sums."""
+import dataclasses
+
 import pytest
 import torch
 
@@ -12,6 +14,7 @@ from workloads.shapes import ModelShape
 pytestmark = pytest.mark.gpu
 
 BIG = ModelShape("ring_big", 1, 3072, 24, 8, 128, 11264, 20503, tied_lm_head=True)      # gate/up, down and LM head: 64 MB and more
+WIDE = ModelShape("ring_wide", 1, 1536, 12, 2, 128, 27648, 1000, tied_lm_head=False)
 NARROW = ModelShape("ring_narrow", 1, 1536, 12, 2, 128, 8960, 1000, tied_lm_head=False)
 
 
@@ -50,6 +53,45 @@ def narrow():
 def test_narrow_groups_of_many_rows(spans, narrow):
     """Eight multiplying waves of one row block, some without rows: groups of three tiles (down) and of five (gate/up)."""
     run(narrow, NARROW, spans, list(range(len(spans))), 136, f"spans {spans}")
+
+
+@pytest.fixture(scope="module")
+def wide():
+    return W.make_weights(WIDE, 71, 1)
+
+
+@pytest.mark.parametrize("rows", [81, 97, 128])
+def test_widest_groups_of_many_rows(rows, wide):
+    """Gate/up in groups of 14 tiles above 64 rows (as on the 32B width): X one window ahead, W two; waves with one row block and with two."""
+    run(wide, WIDE, [rows], [0], 136, f"{rows} rows")
+
+
+def call(weights, n, max_ctx=16):
+    """A decode step of n sequences at position 0 (attention to one position is the value row itself): logits, K and V of every layer."""
+    import paper_2507_17307_amd as P
+    m = P.Model(weights, max_ctx=max_ctx, max_seqs=16, max_rows=16)
+    toks = W.rng.randint(73, 1, 0, 16, 1000).tolist()[:n]
+    _, lg = m.decode_step(toks, [0] * n, 0.6, P.RS_SLM, [1.0 + i % 5 for i in range(n)], want_logits=True)
+    torch.cuda.synchronize()
+    return lg.clone(), m.kv_view("k")[:, :n, :, 0].clone(), m.kv_view("v")[:, :n, :, 0].clone()
+
+
+@pytest.mark.parametrize("n", [3, 5, 8, 16])
+def test_the_order_of_sums_of_an_lm_head_is_the_same_on_both_kernels(n):
+    """1279 column tiles stay on k_gemm_rows, 1280 take the ring: the logits that both have are the same bits."""
+    shape = ModelShape("order_head", 1, 2176, 8, 2, 64, 384, 20480, tied_lm_head=False)
+    w = W.make_weights(shape, 73, 1, device="cuda")
+    below = dataclasses.replace(w, shape=dataclasses.replace(shape, vocab=20464), embed=w.embed[:20464].contiguous(), lm_head=w.lm_head[:20464].contiguous())
+    (a, ka, va), (b, kb, vb) = call(w, n), call(below, n)
+    assert torch.equal(a[:, :20464], b) and torch.equal(ka, kb) and torch.equal(va, vb)
+
+
+def test_the_order_of_sums_of_a_layer_is_the_same_on_both_kernels():
+    """A down projection that k_gemm_rows takes at 8 rows and the ring at 9 (ring_layer): the second layer's K and V and the logits are the same bits."""
+    shape = ModelShape("order_layer", 2, 3584, 28, 4, 128, 16896, 1000, tied_lm_head=False)
+    w = W.make_weights(shape, 79, 1, device="cuda")
+    (a, ka, va), (b, kb, vb) = call(w, 8), call(w, 9)
+    assert torch.equal(a, b[:8]) and torch.equal(ka, kb[:, :8]) and torch.equal(va, vb[:, :8])
 
 
 @pytest.mark.parametrize("vocab", [65, 8196, 8197])

@@ -124,11 +124,11 @@ TILE_CASES = [("one_span_17", [17]), ("one_span_24", [24]), ("two_spans_31", [11
 
 @pytest.mark.parametrize("name,spans", TILE_CASES, ids=[c[0] for c in TILE_CASES])
 def test_calls_of_17_to_128_rows_on_a_2048_wide_shape_match_the_oracle(name, spans):
-    """Calls of more than 16 rows take the kernel in which one workgroup holds all rows of the call against a block of
-    output columns (up to 32 rows: two waves per 16-row block, each with half of the column tiles; up to 64: four waves of 16
-    rows; above: eight; K split over workgroups for QKV / O-proj / down) for every matrix whose workgroups fill the machine: here QKV (192 tiles), gate/up (640 tiles in
-    groups of three: a ragged last group) and down (128 tiles, 160 k windows split over eight workgroups); the O projection
-    (128 tiles, 32 windows) stays on the 32-row-block kernel, so both activation formats are in play in one call."""
+    """Calls of more than 16 rows take the kernel in which one workgroup holds all rows of the call against a block of output columns (up to 32
+    rows two waves per 16-row block, each with half of the column tiles, up to 64 four waves of 16 rows, above eight of them; K split over
+    workgroups for QKV / O-proj / down) for every matrix whose workgroups fill the machine: here QKV (192 tiles), gate/up (1280 tiles of 8 + 8
+    columns in 256 groups of five) and down (128 tiles, 160 k windows split over eight workgroups); the O projection (128 tiles, 32 windows) stays
+    on the 32-row-block kernel, so both are in play in one call."""
     import paper_2507_17307_amd as P
     from workloads.shapes import ModelShape
     shape = ModelShape("wide_2layers", 2, 2048, 16, 4, 128, 10240, 8192, tied_lm_head=False)

@@ -1,8 +1,8 @@
 """Calls of 3 .. 128 rows on the matrix-core kernels: the activation buffers between them hold blocks of 1, 2, 4, 8 or 16 rows in
 operand order (frag_index), so every row count around those block sizes, as a span and as decode rows, against the oracle.
 The first shape's projections have too few columns for k_gemm_ring (ring_layer) and stay on k_gemm_rows, whatever the row count;
-those of the second take it from 17 rows on (gate/up from 3), with two waves per row block up to 32 rows, one up to 64, and two
-row blocks per wave above."""
+those of the second take it from 17 rows on (gate/up from 3), with two waves per row block up to 32 rows, one up to 64, and above 64
+two row blocks per wave or, in narrow groups, eight waves of one."""
 import pytest
 import torch
 
@@ -39,9 +39,10 @@ def test_row_counts_around_the_block_sizes(rows, weights):
         check_invocation(got[i], lg[i], want, 0.6, router.SLM, where=f"{rows} sequences, {i}")
 
 
-@pytest.mark.parametrize("n", [65, 128])
+@pytest.mark.parametrize("n", [18, 40, 65, 128])
 def test_lm_head_of_many_sequences_with_thirteen_column_tiles(n):
-    """A vocabulary of 3328 column tiles (the last one ragged) on 256 CUs: workgroups of 13 tiles."""
+    """A vocabulary of 3328 column tiles (the last one ragged) on 256 CUs: workgroups of 13 tiles, split between two waves up to 32
+    sequences, on four waves up to 64 and on eight above (which row counts take 13 is checked in test_gemm_plan.py)."""
     import paper_2507_17307_amd as P
     shape = ModelShape("wide_vocab", 1, 128, 4, 2, 32, 128, 53233, tied_lm_head=False)
     w = W.make_weights(shape, 43, 1)
