@@ -55,21 +55,22 @@ inline bool ring_eight_waves(bool lm_head, int M, int ct) { return M > 64 && (lm
 
 // Column tiles per workgroup of a product of M rows with n_tiles tiles (gate/up 8 + 8 columns each, else 16) over n_win windows, K split
 // ks ways: the least estimated time.  A window of a workgroup takes the longest of
-//   its matrix instructions   60.5 ns for each 16 x 16 tile of a wave (96 of them at 128 rows: 1.16 us at the 1.8 GHz that this load leaves)
-//   its loads                 45 bytes/ns into one CU, W at 24.5 of them (6.3 TB/s over 256 CUs)
+//   its matrix instructions   60.5 ns for each column tile and row block of a SIMD (six of 16 cycles and what lies between them, at the 1.8 GHz that this
+//                             load leaves; ten tiles at 128 rows are 20 of them, 1.21 us)
+//   its loads                 45 bytes/ns into one CU, W at 24.5 of them (6.3 TB/s over 256 CUs); the kernels that fetch as much X as W (24 .. 61 rows)
+//                             were seen at 31 .. 35
 //   its dependent steps       0.45 us; above 64 rows 0.6, or 1.0 where X is requested only one window ahead
 inline int plan_ring(bool lm_head, int M, int n_tiles, int n_win, int ks, int n_cu) {
     static const int ct_layer[] = {14, 13, 10, 9, 8, 7, 6, 5, 4, 3, 0}, ct_lm[] = {13, 10, 8, 6, 4, 2, 1, 0};
-    const int rbw = M > 64 ? 2 : 1, cs = ring_column_splits(M), blocks = (M + 15) / 16;
-    const double row_tiles = M > 64 && blocks <= 4 ? 1 : rbw;
+    const int simd_blocks = M > 64 ? 2 : 1, cs = ring_column_splits(M), blocks = (M + 15) / 16;
     int best = 0;
     double least = 1e30;
     for (const int *c = lm_head ? ct_lm : ct_layer; *c; ++c) {
         const int ct = *c, groups = (n_tiles + ct - 1) / ct;
         if (ct == 3 && M <= 64) continue;
         const int units = groups * ks, rounds = (units + n_cu - 1) / n_cu;
-        const double kb = 2.048 * ct, mfma = 0.0605 * ((ct + cs - 1) / cs) * row_tiles, load = (kb + 4.096 * blocks) / 45, w = kb / 24.5;
-        double win = rbw == 2 ? (ct > 10 ? 1.0 : 0.6) : 0.45;
+        const double kb = 2.048 * ct, mfma = 0.0605 * ((ct + cs - 1) / cs) * simd_blocks, load = (kb + 4.096 * blocks) / 45, w = kb / 24.5;
+        double win = M > 64 ? (ct > 10 ? 1.0 : 0.6) : 0.45;
         for (double t : {mfma, load, w}) win = t > win ? t : win;
         const double us = rounds * ((n_win + ks - 1) / ks) * win;
         if (us < least + 1e-9) { least = us; best = ct; }                               // (equal: the smaller groups)

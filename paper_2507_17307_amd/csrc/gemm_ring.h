@@ -13,16 +13,21 @@
 //   matrix instructions to hide behind, two vector instructions between two of them (a third would cost issue slots).
 // Rows: a multiplying wave takes RBW blocks of 16 rows (two above 64 rows, so that a tile of W read from LDS serves 32 rows), or
 // up to 32 / 16 rows two / four waves share a block and split the columns (CS).  A wave whose second block lies past the
-// call's rows leaves its products out.  Above 64 rows narrow groups (ring_eight_waves) and the LM head have eight waves of one block: beside the softmax state the sums
-// of two blocks and 13 tiles do not fit the registers (57 spilled), and twice the waves share the softmax of a group.  With two blocks
-// and ten tiles at most a vocabulary of 50257 took two rounds of 8 tiles in place of one of 13.  Columns: CT tiles of 16; for gate/up a tile is 8 gate and the 8 matching up columns, which come
-// closer to equal shares of the CUs than 16 + 16 (14B: 247 workgroups of 7 instead of 216 of 4; 32B one round of 247 instead of 432).
+// call's rows leaves its products out.  Above 64 rows narrow groups (ring_eight_waves) and the LM head have eight waves of one
+// block: beside the softmax state the sums of two blocks and 13 tiles do not fit the registers (57 spilled), and twice the
+// waves share the softmax of a group.  With two blocks and ten tiles at most a vocabulary of 50257 took two rounds of 8 tiles
+// in place of one of 13.
+// Columns: CT tiles of 16; for gate/up a tile is 8 gate and the 8 matching up columns, which come closer to equal shares of the
+// CUs than 16 + 16 (14B: 247 workgroups of 7 instead of 216 of 4; 32B at 33 .. 64 and from 81 rows on one round of 247 of 14 instead of 432 of 4; at other
+// row counts the estimates of 14 and of 7 tie and it takes 494 of 7 in two rounds).
 //
 // What bounds it: up to 64 rows W, streamed at 5.3 .. 6.1 TB/s; at 128 rows the matrix cores, which run at 1.7 .. 1.8 GHz under this
-// load (2330 cycles a window of 120 instructions, 2230 of them matrix-core time).  Kernel times before -> now, us:
-//   7B gate/up (272 MB)   5 / 16 / 24 / 48 / 72 / 128 rows   51 / 53 / 63 / 72 / 86 / 108 -> 45 / 45 / 46 / 53 / 75 / 90
-//   14B gate/up (283 MB)  8 / 61 / 128 rows  55 / 90 / 112 -> 48 / 69 / 101;   32B gate/up (566 MB)  16 / 29 rows  108 / 128 -> 90 / 94
-//   14B down + O (194 MB) 61 rows 65 -> 53;  7B QKV (33 MB) 48 / 128 rows 15.4 / 22.0 -> 13.3 / 21.5
+// load (2330 cycles a window of 120 instructions, 2230 of them matrix-core time: 73 of the 88 us of 7B gate/up; the rest has not been taken
+// apart).  Kernel times in decode calls, us, k_gemm_rows or the kernel of 17 rows and more before this one (k_gemm_tile) -> now:
+//   7B gate/up (272 MB)   5 / 16 / 24 / 48 / 72 / 128 rows   52 / 53 / 59 / 64 / 80 / 98 -> 46 / 44 / 45 / 50 / 72 / 88
+//   14B gate/up (283 MB)  8 / 61 / 128 rows  56 / 85 / 108 -> 47 / 68 / 99
+//   32B gate/up (566 MB)  16 / 29 / 61 / 128 rows  110 / 123 / 141 / 220 -> 95 / 104 / 107 / 170
+//   14B, 61 rows  down (142 MB) 41 -> 34, O (52 MB) 21 -> 18;  7B QKV (33 MB) 48 / 128 rows 13.6 / 20.7 -> 13.3 / 20.9
 //   LM head of the 7B shape (1090 MB)  5 / 16 / 24 / 65 / 128 sequences  179 / 202 / 213 / 378 / 428 -> 170 / 175 / 193 / 304 / 348
 //   LM head of more than 64 sequences, before / two blocks a wave / eight waves: 50257 entries, 65 / 128 sequences, 1.5B width 71 / 80 / 55 and
 //   76 / 89 / 65, 7B 127 / 146 / 105 and 147 / 165 / 130, 14B 178 / 196 / 148 and 203 / 222 / 177; 8192 entries, 7B 47 / 43 / 39 and 55 / 52 / 50

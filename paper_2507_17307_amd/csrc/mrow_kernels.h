@@ -213,7 +213,6 @@ __global__ void __launch_bounds__(GEMM_NW * 64) k_gemm_rows(GemmArgs a) {
         unit_first = (slot / Y) * 8 + xcd;
         unit_step = (int)(gridDim.x / (8 * Y)) * 8;
     }
-    const int part_id = Y == 1 ? (int)blockIdx.x : unit_first;            // LM head: this workgroup's place among its rows' partial states
     const int m_base = yb * 16 * NB;
 
     // token side: rows past M (inside the padding of the buffer) hold anything; their products fill matrix-core columns
@@ -222,7 +221,7 @@ __global__ void __launch_bounds__(GEMM_NW * 64) k_gemm_rows(GemmArgs a) {
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) xp[nb] = a.X32 + (size_t)(m_base + nb * 16) * K + ((g << a.rsh) + min(i16, (1 << a.rsh) - 1)) * 4;
     SoftState st; st.init();
-    const int lm_row = m_base + i16;                      // LM head (NB = 1): the output row this lane's state follows
+    const int lm_row = i16;                               // LM head (one block of rows): the output row this lane's state follows
     const float lm_scale = (MODE == G_LMHEAD && lm_row < a.M) ? a.seq_scale[lm_row] : 1.f;
     unsigned long long noise_base = 0;                    // sampling: (position of the token being predicted) * V
     if (MODE == G_LMHEAD && a.sample_on && lm_row < a.M) noise_base = (unsigned long long)(a.row_pos[a.out_row[lm_row]] + 1) * (unsigned long long)a.N;
@@ -396,7 +395,7 @@ __global__ void __launch_bounds__(GEMM_NW * 64) k_gemm_rows(GemmArgs a) {
         if (wave == 0 && g == 0 && lm_row < a.M) {
             SoftState s0 = from_partial(sp[i16]);
             for (int w = 1; w < GEMM_NW; ++w) s0.merge(from_partial(sp[w * 16 + i16]));
-            a.parts[(size_t)lm_row * a.n_parts + part_id] = to_partial(s0);
+            a.parts[(size_t)lm_row * a.n_parts + blockIdx.x] = to_partial(s0);
         }
     }
 }

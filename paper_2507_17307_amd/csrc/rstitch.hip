@@ -400,7 +400,8 @@ template <int MODE, int RBW, int CS, int NCW>
 rs_status launch_gemm_ring_waves(int ct, const GemmArgs &a, dim3 blocks, hipStream_t st, const char *name) {
 #define RS_CT(ct) case ct: return launch_gemm_ring_ct<MODE, ct, RBW, CS, NCW>(a, blocks, st, name);
     if constexpr (MODE == G_LMHEAD) {
-        switch (ct) { RS_CT(13) RS_CT(10) RS_CT(8) RS_CT(6) RS_CT(4) RS_CT(2) RS_CT(1) }
+        switch (ct) { RS_CT(13) RS_CT(10) RS_CT(8) RS_CT(6) }
+        if constexpr (CS < 4) { switch (ct) { RS_CT(4) RS_CT(2) RS_CT(1) } }       // (up to 16 sequences: six at least, ring_lm_head)
     } else {
         if constexpr (NCW == 4) { switch (ct) { RS_CT(14) RS_CT(13) RS_CT(10) RS_CT(9) RS_CT(8) RS_CT(7) RS_CT(6) } }
         if constexpr (RBW == 1) { switch (ct) { RS_CT(5) RS_CT(4) } }
