@@ -83,7 +83,8 @@ inline int plan_ring(bool lm_head, int M, int n_tiles, int n_win, int ks, int n_
 // Up to 16 rows: matrices from 64 MB on, because a workgroup that fills a CU starts and ends more slowly than the small ones of k_gemm_rows, and of
 // these the ones that k_gemm_rows does not spread evenly.  It has all of two or three workgroups a CU resident at once, so where every CU gets nearly
 // as many it streams as well as the ring and starts sooner; where some get one more than others they are what the rest waits for.
-// Above 8 rows its workgroups pull twice the X, and K split over ring workgroups of six tiles and 33 windows or more wins all the same.
+// Above 4 rows its workgroups pull X in blocks of 8 and 16, and K split over ring workgroups of six tiles and 33 windows or more is as good or better
+// all the same (7B calls, six layers, spans of 3 / 4 / 5 / 8 rows, down on k_gemm_rows 885.8 914.5 926.5 937.3 us, on the ring 886.1 915.6 925.2 935.9).
 // Measured, us at 3 / 8 / 16 rows, k_gemm_rows (workgroups a CU) and k_gemm_ring:
 //   even    14B QKV  73 MB (1.75)  15.8 17.0 19.6 and 19.8 19.9 20.6;  7B down 136 MB (1.75)  25.5 26.4 26.9 and 26.0 26.3 26.1;
 //           width 3072 gate/up 101 MB (2)  19.2 19.6 21.6 and 22.6 22.7 23.2;  width 8192 O 134 MB (2)  31.9 32.0 32.8 and 36.3 36.0 37.0;
@@ -98,7 +99,7 @@ inline bool ring_layer(int n_cu, int rows, bool gateup, int n_out, int K) {
     const int r = gateup ? rows_tiles_whole(n_tiles, n_cu) : rows_tiles(true, n_win), ks = gateup ? 1 : split_few(true, n_tiles, n_win, n_cu);
     const int units = (n_tiles + r - 1) / r * ks, most = (units + n_cu - 1) / n_cu;
     const bool even = (most == 2 || most == 3) && 8 * units >= 7 * n_cu * most;
-    return !even || (rows > 8 && !gateup && n_win / ks > 32 && n_tiles * ks >= 6 * n_cu);
+    return !even || (rows > 4 && !gateup && n_win / ks > 32 && n_tiles * ks >= 6 * n_cu);
 }
 // LM head: from five column tiles per CU on (a window of fewer costs its dependent steps: vocabulary 8192, one row of the 1.5B shape 12.7 us
 // on k_gemm_rows, 16.0 here; 32 000 entries 22.6 and 21.7, 152 064 81.6 and 77.5) and for more than 16 sequences.

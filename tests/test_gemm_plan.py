@@ -82,18 +82,18 @@ def test_narrow_groups_of_many_rows_fill_the_machine(lib, rows):
 
 
 @pytest.mark.parametrize("shape,name,gateup,takes", [
-    # rows at which the matrix takes k_gemm_ring, of 3, 8, 9 and 16 (the measurements beside ring_layer)
-    ("s15", "gu", 1, ()), ("s15", "down", 0, ()), ("m7", "qkv", 0, ()), ("m7", "o", 0, ()), ("m7", "gu", 1, (3, 8, 9, 16)),
-    ("m7", "down", 0, (9, 16)), ("m14", "qkv", 0, ()), ("m14", "o", 0, ()), ("m14", "gu", 1, (3, 8, 9, 16)), ("m14", "down", 0, (3, 8, 9, 16)),
-    ("m32", "qkv", 0, ()), ("m32", "gu", 1, (3, 8, 9, 16)), ("m32", "down", 0, (3, 8, 9, 16))])
+    # rows at which the matrix takes k_gemm_ring, of 4, 5, 8 and 16 (the measurements beside ring_layer)
+    ("s15", "gu", 1, ()), ("s15", "down", 0, ()), ("m7", "qkv", 0, ()), ("m7", "o", 0, ()), ("m7", "gu", 1, (4, 5, 8, 16)),
+    ("m7", "down", 0, (5, 8, 16)), ("m14", "qkv", 0, ()), ("m14", "o", 0, ()), ("m14", "gu", 1, (4, 5, 8, 16)), ("m14", "down", 0, (4, 5, 8, 16)),
+    ("m32", "qkv", 0, ()), ("m32", "gu", 1, (4, 5, 8, 16)), ("m32", "down", 0, (4, 5, 8, 16))])
 def test_which_products_of_few_rows_take_the_ring(lib, shape, name, gateup, takes):
     """Not those that k_gemm_rows spreads evenly over the CUs."""
     d, _, _, ffn = SHAPES[shape]
     n, k = (ffn, d) if gateup else products(shape)[name]
-    assert tuple(r for r in (3, 8, 9, 16) if lib.ring_layer(CU, r, gateup, n, k)) == takes
+    assert tuple(r for r in (4, 5, 8, 16) if lib.ring_layer(CU, r, gateup, n, k)) == takes
 
 
-def test_the_layer_that_changes_kernels_between_8_and_9_rows(lib):
+def test_the_layer_that_changes_kernels_between_4_and_5_rows(lib):
     """The shape of test_gpu_gemm_ring.py that compares the two kernels' sums, and its LM head on either side of the rule."""
-    assert not lib.ring_layer(CU, 8, 0, 3584, 16896) and lib.ring_layer(CU, 9, 0, 3584, 16896)
+    assert not lib.ring_layer(CU, 4, 0, 3584, 16896) and lib.ring_layer(CU, 5, 0, 3584, 16896)
     assert not lib.ring_lm_head(CU, 3, 20464) and lib.ring_lm_head(CU, 3, 20480)

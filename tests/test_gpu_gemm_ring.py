@@ -87,11 +87,11 @@ def test_the_order_of_sums_of_an_lm_head_is_the_same_on_both_kernels(n):
 
 
 def test_the_order_of_sums_of_a_layer_is_the_same_on_both_kernels():
-    """A down projection that k_gemm_rows takes at 8 rows and the ring at 9 (ring_layer): the second layer's K and V and the logits are the same bits."""
+    """A down projection that k_gemm_rows takes at 4 rows and the ring at 5 (ring_layer): the second layer's K and V and the logits are the same bits."""
     shape = ModelShape("order_layer", 2, 3584, 28, 4, 128, 16896, 1000, tied_lm_head=False)
     w = W.make_weights(shape, 79, 1, device="cuda")
-    (a, ka, va), (b, kb, vb) = call(w, 8), call(w, 9)
-    assert torch.equal(a, b[:8]) and torch.equal(ka, kb[:, :8]) and torch.equal(va, vb[:, :8])
+    (a, ka, va), (b, kb, vb) = call(w, 4), call(w, 5)
+    assert torch.equal(a, b[:4]) and torch.equal(ka, kb[:, :4]) and torch.equal(va, vb[:, :4])
 
 
 @pytest.mark.parametrize("vocab", [65, 8196, 8197])
