@@ -26,7 +26,8 @@
 // apart).  Kernel times in decode calls, us, k_gemm_rows or the kernel of 17 rows and more before this one (k_gemm_tile) -> now:
 //   7B gate/up (272 MB)   5 / 16 / 24 / 48 / 72 / 128 rows   52 / 53 / 59 / 64 / 80 / 98 -> 46 / 44 / 45 / 50 / 72 / 88
 //   14B gate/up (283 MB)  8 / 61 / 128 rows  56 / 85 / 108 -> 47 / 68 / 99
-//   32B gate/up (566 MB)  16 / 29 / 61 / 128 rows  110 / 123 / 141 / 220 -> 95 / 104 / 107 / 170
+//   32B gate/up (566 MB)  16 / 29 / 61 / 128 rows  110 / 123 / 141 / 220 -> 95 / 104 / 107 / 170 (29 rows of ragged spans on
+//                         long contexts 128 -> 112 .. 115)
 //   14B, 61 rows  down (142 MB) 41 -> 34, O (52 MB) 21 -> 18;  7B QKV (33 MB) 48 / 128 rows 13.6 / 20.7 -> 13.3 / 20.9
 //   LM head of the 7B shape (1090 MB)  5 / 16 / 24 / 65 / 128 sequences  179 / 202 / 213 / 378 / 428 -> 170 / 175 / 193 / 304 / 348
 //   LM head of more than 64 sequences, before / two blocks a wave / eight waves: 50257 entries, 65 / 128 sequences, 1.5B width 71 / 80 / 55 and
