@@ -49,7 +49,7 @@ inline int ring_column_splits(int M) { return M <= 16 ? 4 : M <= 32 ? 2 : 1; }
 // More than 64 rows: whether eight waves of one block multiply and not four of two.  A wave splits its X into planes by itself, some 110
 // vector instructions a block and window, which the matrix instructions of a few tiles do not hide; two waves of a SIMD hide each other's.
 // 1.5B down (24 groups of 4 tiles, K split 8 ways), 65 / 128 rows: four waves 19.4 / 22.5 us, eight 18.1 / 20.3, with three tiles and X fetched
-// four windows ahead 17.8 / 20.4 (k_gemm_tile 17.2 / 20.5).  Wider groups are better off with every W tile read once for 32 rows: 7B gate/up,
+// four windows ahead 17.8 / 20.4 (the kernel before the ring 17.2 / 20.5).  Wider groups are better off with every W tile read once for 32 rows: 7B gate/up,
 // ten tiles, 77.6 / 84.6 and 81.1 / 87.5.
 inline bool ring_eight_waves(bool lm_head, int M, int ct) { return M > 64 && (lm_head || ct <= 5); }
 
