@@ -62,18 +62,6 @@ __device__ __forceinline__ SoftState row_state(const float *__restrict__ x, int 
     return st;
 }
 
-// Partial states of caller-provided fp32 logits: grid (n_parts, n_rows), block 256.
-// Each workgroup strides over its row; partial p of row r lands in parts[r*n_parts + p].
-__global__ void __launch_bounds__(256)
-k_route_partials(const float *__restrict__ logits, int vocab, const float *__restrict__ scale,
-                 SoftPartial *__restrict__ parts) {
-    __shared__ SoftPartial sh[4];
-    const int row = blockIdx.y, n_parts = gridDim.x;
-    const SoftState st = row_state(logits + (size_t)row * vocab, vocab, scale ? scale[row] : 1.f, blockIdx.x * 256 + threadIdx.x, n_parts * 256);
-    const SoftState a = block_merge<4>(st, sh, false);
-    if (threadIdx.x == 0) parts[(size_t)row * n_parts + blockIdx.x] = to_partial(a);
-}
-
 // The record of a row from its merged state (one thread).
 __device__ __forceinline__ rs_route_out route_record(const SoftState &st, int vocab, float tau, int active, bool bad, int sample) {
     rs_route_out r;
@@ -97,9 +85,30 @@ __device__ __forceinline__ rs_route_out route_record(const SoftState &st, int vo
     return r;
 }
 
+// The states that workgroups of one launch leave for each other: three words of eight bytes, past the L2s of the XCDs (which
+// are not coherent with each other; a fence would write back and invalidate all of an L2).  The last eight bytes of a SoftPartial, the sampled entry, are
+// not among them.
+__device__ __forceinline__ void store_partial(SoftPartial *p, const SoftPartial &v) {
+    unsigned long long w[4];
+    __builtin_memcpy(w, &v, sizeof(v));
+#pragma unroll
+    for (int i = 0; i < 3; ++i) __hip_atomic_store(reinterpret_cast<unsigned long long *>(p) + i, w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ SoftPartial load_partial(const SoftPartial *p) {
+    unsigned long long w[4];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) w[i] = __hip_atomic_load(reinterpret_cast<const unsigned long long *>(p) + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    w[3] = 0x7fffffffff800000ull;                             // (nothing sampled: -inf, no index)
+    SoftPartial v;
+    __builtin_memcpy(&v, w, sizeof(v));
+    return v;
+}
+
 // Final merge and routing decision for one row by one 256-thread workgroup.
 // row_bad: optional per-row flag (nonzero = the row's inputs were out of range); sh: 4 SoftPartial of LDS.
+// HERE: the states were stored by other workgroups of this launch (k_route_wide): loaded past the L2s, without the sampled entry.
 // sample: the record's token is the arg max of logit + Gumbel noise (a draw from the distribution) instead of the arg max
+template <bool HERE = false>
 __device__ __forceinline__ void route_merge_row(const SoftPartial *__restrict__ parts, int n_parts, int vocab, float tau,
                                                 int active, const int *__restrict__ row_bad, rs_route_out *__restrict__ out,
                                                 int row, SoftPartial *sh, int sample = 0) {
@@ -112,7 +121,7 @@ __device__ __forceinline__ void route_merge_row(const SoftPartial *__restrict__ 
     for (int p0 = tid; p0 < n_parts; p0 += 1024) {
         SoftPartial q[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) q[k] = pr[min(p0 + 256 * k, n_parts - 1)];
+        for (int k = 0; k < 4; ++k) q[k] = HERE ? load_partial(pr + min(p0 + 256 * k, n_parts - 1)) : pr[min(p0 + 256 * k, n_parts - 1)];
         float m = st.m;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -140,6 +149,36 @@ k_route_merge(const SoftPartial *__restrict__ parts, int n_parts, int vocab, flo
               const int *__restrict__ row_bad, rs_route_out *__restrict__ out, int sample) {
     __shared__ SoftPartial sh[4];
     route_merge_row(parts, n_parts, vocab, tau, active, row_bad, out, blockIdx.x, sh, sample);
+}
+
+// The whole of rs_route for long rows: grid (n_parts, n_rows), block 256.  Each workgroup strides over its row and leaves its state; the one that
+// finds all others of the row arrived merges them.  Arrivals are counted in the word behind the row's first state, {tag, count}: nobody has cleared
+// the caller's scratch, so a word without this call's 56-bit tag counts as zero, and the last workgroup leaves zero (a captured call is replayed with
+// its tag).  Nothing waits for another workgroup.
+// What bounds it: up to some ten rows the host's call (one of 50257 or 152064 entries: 11.0 us with a second kernel for the merge, 8.8 now; 8 of 152064
+// 10.8 -> 8.7), for many the exponentials (64 of 152064 15.0 -> 14.1, 128 22.8 -> 21.7).  The word is read before the logits and set while they
+// are added up, so that a workgroup's last act is one addition: a loop of compare and exchange in its place took 102 us for 128 workgroups of a row.
+__global__ void __launch_bounds__(256)
+k_route_wide(const float *__restrict__ logits, int vocab, const float *__restrict__ scale, SoftPartial *parts, unsigned long long tag, float tau, int active,
+             rs_route_out *__restrict__ out) {
+    __shared__ SoftPartial sh[4];
+    __shared__ int sh_last;
+    const int row = blockIdx.y, n_parts = gridDim.x;
+    SoftPartial *pr = parts + (size_t)row * n_parts;
+    unsigned long long *word = reinterpret_cast<unsigned long long *>(pr) + 3, seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const SoftState st = row_state(logits + (size_t)row * vocab, vocab, scale ? scale[row] : 1.f, blockIdx.x * 256 + threadIdx.x, n_parts * 256);
+    if (threadIdx.x == 0 && (seen >> 8) != tag)                // this call's first: no arrivals yet (fails where another workgroup was faster)
+        __hip_atomic_compare_exchange_strong(word, &seen, tag << 8, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const SoftState a = block_merge<4>(st, sh, false);
+    if (threadIdx.x == 0) {
+        store_partial(pr + blockIdx.x, to_partial(a));
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // acknowledged where the other XCDs read it, before it counts as arrived
+        const bool last = (__hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 255) + 1 == n_parts;
+        if (last) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sh_last = last;
+    }
+    __syncthreads();
+    if (sh_last) route_merge_row<true>(parts, n_parts, vocab, tau, active, nullptr, out, row, sh);
 }
 
 // The whole of rs_route for a short row: grid n_rows, block 1024, no partial states in memory and no second launch.

@@ -4,6 +4,8 @@
 // cos/sin table, which is input-independent and built once per model.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -1105,16 +1107,23 @@ rs_status rs_set_phase_timer(rs_model *m, int32_t phase, int32_t layer, void *st
     return RS_OK;
 }
 
+constexpr int ROUTE_PARTS_MAX = 128;
 static int route_parts(int vocab) {
     int p = (vocab / 4 + 255) / 256;      // one float4 per thread and pass
     if (p < 1) p = 1;
-    return p > 128 ? 128 : p;
+    return p > ROUTE_PARTS_MAX ? ROUTE_PARTS_MAX : p;
+}
+
+// 56 bits that tell the arrivals of one call from what its scratch held before: counted from a start of the process's own.
+static unsigned long long route_tag() {
+    static std::atomic<unsigned long long> next{(unsigned long long)std::chrono::system_clock::now().time_since_epoch().count() * 0x9E3779B97F4A7C15ull};
+    return next.fetch_add(1, std::memory_order_relaxed) & 0x00ffffffffffffffull;
 }
 
 // A short row takes one workgroup from its logits to its record (64 rows of 32768: 11.1 us a call against 14.2; one row of
-// 50257: 14.8 against 14.2); longer ones leave partial states, at most route_parts of them per row, that a second kernel merges, and
-// with many rows fewer (ROUTE_WGS workgroups in all: a workgroup's merge costs as much as several groups of logits; 64 / 128 rows of
-// 152064: 45.8 / 79.4 us with 128 workgroups each and pairwise merges, now 15.5 / 22.9; 1024 or 4096 workgroups the same or slower).
+// 50257: 14.8 against 14.2, with two launches for the longer rows); longer ones leave partial states, at most route_parts of them per row, that the last
+// workgroup of a row merges, and with many rows fewer (ROUTE_WGS workgroups in all: a workgroup's merge costs as much as several groups of logits; 64 / 128 rows of
+// 152064: 45.8 / 79.4 us with 128 workgroups each and pairwise merges, now 14.1 / 21.7; 1024 or 4096 workgroups the same or slower).
 constexpr int ROUTE_ROW_VOCAB = 32768, ROUTE_WGS = 2048;
 static rs_status launch_route(const float *d_logits, int n, int vocab, const float *d_scale, float tau, int active,
                               rs_route_out *d_out, rs::SoftPartial *scratch, hipStream_t st) {
@@ -1125,12 +1134,9 @@ static rs_status launch_route(const float *d_logits, int n, int vocab, const flo
     }
     int parts = route_parts(vocab);
     if (parts > (ROUTE_WGS + n - 1) / n) parts = (ROUTE_WGS + n - 1) / n;
-    hipLaunchKernelGGL(rs::k_route_partials, dim3(parts, n), dim3(256), 0, st, d_logits, vocab, d_scale, scratch);
-    RS_LAUNCHED("route_partials");
-    // every partial the merge reads is written by the first kernel of the same call: nothing to clear
-    hipLaunchKernelGGL(rs::k_route_merge, dim3(n), dim3(256), 0, st, (const rs::SoftPartial *)scratch, parts, vocab, tau,
-                       active, (const int *)nullptr, d_out, 0);
-    RS_LAUNCHED("route_merge");
+    static_assert(ROUTE_PARTS_MAX < 256, "arrivals are counted in eight bits");
+    hipLaunchKernelGGL(rs::k_route_wide, dim3(parts, n), dim3(256), 0, st, d_logits, vocab, d_scale, scratch, route_tag(), tau, active, d_out);
+    RS_LAUNCHED("route_wide");
     return RS_OK;
 }
 
