@@ -111,6 +111,15 @@ __device__ __forceinline__ float gumbel_noise(unsigned long long key, unsigned l
     return -logf(-logf(u));
 }
 
+// exp(d) for -200 <= d <= 0: 2^t of the rounded product t = d log2(e), corrected by what the rounding left out.  Six instructions in the place of
+// expf's dozen and more: no reduction to a fraction and back, because v_exp_f32 takes any t (below 2^-126 it gives zero), and nothing to guard
+// at the ends.  Against 64 bits 3.6e-8 rms, expf 2.6e-8; entropies and ln Z of rows of 300 to 200000 entries are as far off with either (8.2e-8 .. 1.1e-7 and
+// 2.5e-8 .. 3.3e-8).
+__device__ __forceinline__ float exp_small(float d) {
+    const float t = d * 1.44269504088896341f, rest = fmaf(d, 1.925963033500e-08f, fmaf(d, 1.44269504088896341f, -t)), e = __builtin_amdgcn_exp2f(t);
+    return fmaf(e, rest * 0.693147180559945f, e);
+}
+
 struct SoftState {
     float m, z, s, best;
     int idx, bad;
@@ -153,8 +162,9 @@ struct SoftState {
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const float d = ok[k] ? v[k] - m : 0.f, e = ok[k] ? expf(d) : 0.f;
-            z += e; s = fmaf(e > 0.f ? d : 0.f, e, s);
+            // (from -104 on the exponential is zero, so that a masked value of the largest negative number takes no part)
+            const float d = ok[k] ? fmaxf(v[k] - m, -200.f) : -200.f, e = exp_small(d);
+            z += e; s = fmaf(d, e, s);
         }
     }
     __device__ __forceinline__ void merge(const SoftState &o) {
