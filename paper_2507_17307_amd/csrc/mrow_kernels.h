@@ -33,12 +33,16 @@ __device__ __forceinline__ float4 sum_splits4(const float *base, size_t i, int k
     return first;
 }
 
-// RMSNorm of whole rows: grid n_out, block ROWK_THREADS; d a multiple of 4, at most 12 * ROWK_THREADS.
+// RMSNorm of whole rows: grid n_out, block ROWK_THREADS; d a multiple of 4, at most 4 * NV * ROWK_THREADS.
 // src row = gather ? gather[blockIdx.x] : blockIdx.x; the normalised row goes to out32[blockIdx.x] as fp32 (the
 // matrix-core kernels split it into bf16 planes themselves), in operand order (frag_index).
 // part != null: the projection before this norm left its result as `ksplit` partial sums
 // part[ks][row][d] (split over K across workgroups); they are added to the residual row here, in a
 // fixed order, and the row is written back before it is normalised.
+// All of a thread's NV quads are requested before the first sum is written back: with a store between them the second quad of a row of 5120
+// values was requested a round trip later (14B width, 61 rows 7.3 -> 7.0 us, 32B, 29 rows 7.5 -> 7.0; with one quad the partial sums no longer wait
+// for the residual: 7B, 128 rows 7.6 -> 6.9).  A row's partial sums, 115 KB of eight splits, come through one CU: that is most of what is left.
+template <int NV>
 __global__ void __launch_bounds__(ROWK_THREADS)
 k_rmsnorm_rows(float *__restrict__ h, const uint16_t *__restrict__ gain, float eps, int d,
                const int *__restrict__ gather, float *__restrict__ out32, int rsh,
@@ -48,8 +52,7 @@ k_rmsnorm_rows(float *__restrict__ h, const uint16_t *__restrict__ gain, float e
     float *hr = h + (size_t)src * d;
     __shared__ float red_ss[ROWK_THREADS / 64];
     const int n4 = d >> 2;
-    constexpr int NV = 3;
-    float4 v[NV];
+    float4 v[NV], p[NV][KSPLIT_MAX];
     uint2 gv[NV];
     float ss = 0.f;
 #pragma unroll
@@ -60,11 +63,22 @@ k_rmsnorm_rows(float *__restrict__ h, const uint16_t *__restrict__ gain, float e
             v[k] = *reinterpret_cast<const float4 *>(hr + 4 * i4);
             gv[k] = *reinterpret_cast<const uint2 *>(gain + 4 * i4);
             if (part) {
-                const float4 p0 = *reinterpret_cast<const float4 *>(part + (size_t)src * d + 4 * i4);
-                float4 t = sum_splits4(part, (size_t)src * d + 4 * i4, ksplit, part_stride, p0);
-                v[k].x += t.x; v[k].y += t.y; v[k].z += t.z; v[k].w += t.w;
-                *reinterpret_cast<float4 *>(hr + 4 * i4) = v[k];
+#pragma unroll
+                for (int ks = 0; ks < KSPLIT_MAX; ++ks) p[k][ks] = *reinterpret_cast<const float4 *>(part + (size_t)min(ks, ksplit - 1) * part_stride + (size_t)src * d + 4 * i4);
             }
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        const int i4 = tid + k * ROWK_THREADS;
+        if (part && i4 < n4) {
+            float4 t = p[k][0];
+#pragma unroll
+            for (int ks = 1; ks < KSPLIT_MAX; ++ks)
+                if (ks < ksplit) { t.x += p[k][ks].x; t.y += p[k][ks].y; t.z += p[k][ks].z; t.w += p[k][ks].w; }
+            v[k].x += t.x; v[k].y += t.y; v[k].z += t.z; v[k].w += t.w;
+            *reinterpret_cast<float4 *>(hr + 4 * i4) = v[k];
         }
         ss = fmaf(v[k].x, v[k].x, ss); ss = fmaf(v[k].y, v[k].y, ss); ss = fmaf(v[k].z, v[k].z, ss); ss = fmaf(v[k].w, v[k].w, ss);
     }

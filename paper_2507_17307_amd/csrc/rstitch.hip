@@ -336,6 +336,17 @@ rs_status launch_attn(AttnArgs &a, const WalkPlan &walk, int n_splits, int n_kv,
     return RS_OK;
 }
 
+// n_out rows of d values, see k_rmsnorm_rows
+rs_status launch_rmsnorm(int n_out, float *h, const uint16_t *gain, float eps, int d, const int *gather, float *out32, int rsh, const float *part, int ksplit,
+                         size_t part_stride, hipStream_t st) {
+    const dim3 grid(n_out), block(ROWK_THREADS);
+    if (d <= 4 * ROWK_THREADS) hipLaunchKernelGGL((k_rmsnorm_rows<1>), grid, block, 0, st, h, gain, eps, d, gather, out32, rsh, part, ksplit, part_stride);
+    else if (d <= 8 * ROWK_THREADS) hipLaunchKernelGGL((k_rmsnorm_rows<2>), grid, block, 0, st, h, gain, eps, d, gather, out32, rsh, part, ksplit, part_stride);
+    else hipLaunchKernelGGL((k_rmsnorm_rows<3>), grid, block, 0, st, h, gain, eps, d, gather, out32, rsh, part, ksplit, part_stride);
+    RS_LAUNCHED("rmsnorm_rows");
+    return RS_OK;
+}
+
 template <int MODE, int NB, int R, int NW>
 rs_status launch_gemm_r(GemmArgs &a, int blocks, hipStream_t st, const char *name) {
     constexpr size_t lds = gemm_lds_bytes<MODE, NB, R, NW>();
@@ -725,9 +736,7 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
             float *xn32 = m->at<float>(L.xn32);
             g.act32 = m->at<float>(L.act);
             // the down projection of the layer before may have left its result as partial sums (pend_*)
-            hipLaunchKernelGGL(k_rmsnorm_rows, dim3(n_rows), dim3(ROWK_THREADS), 0, st, h, m->attn_norm[l], c.rms_eps,
-                               c.d_model, (const int *)nullptr, xn32, rsh, (const float *)pend_part, pend_ks, pend_stride);
-            RS_LAUNCHED("rmsnorm_rows");
+            if ((rc = launch_rmsnorm(n_rows, h, m->attn_norm[l], c.rms_eps, c.d_model, nullptr, xn32, rsh, pend_part, pend_ks, pend_stride, st))) return rc;
             pend_part = nullptr; pend_ks = 0; pend_stride = 0;
             g.W = m->w_qkv[l]; g.N = qkv_rows; g.K = c.d_model; g.X32 = xn32;
             g.out_f32 = m->at<float>(L.qkv_raw); g.ld_out = qkv_rows;
@@ -758,9 +767,7 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
             tic(RS_PHASE_OPROJ, l);
             if ((rc = launch_gemm<G_OPROJ>(m, g, (c.d_model + 15) / 16, st, "gemm_oproj", t_o))) return rc;
             toc(RS_PHASE_OPROJ, l);
-            hipLaunchKernelGGL(k_rmsnorm_rows, dim3(n_rows), dim3(ROWK_THREADS), 0, st, h, m->mlp_norm[l], c.rms_eps,
-                               c.d_model, (const int *)nullptr, xn32, rsh, (const float *)g.part, g.ksplit, g.part_stride);
-            RS_LAUNCHED("rmsnorm_rows");
+            if ((rc = launch_rmsnorm(n_rows, h, m->mlp_norm[l], c.rms_eps, c.d_model, nullptr, xn32, rsh, g.part, g.ksplit, g.part_stride, st))) return rc;
             g.W = m->w_gate_up[l]; g.N = 2 * c.d_ffn; g.K = c.d_model; g.X32 = xn32;
             tic(RS_PHASE_GATEUP, l);
             if ((rc = launch_gemm<G_GATEUP>(m, g, (c.d_ffn + 15) / 16, st, "gemm_gateup", t_gu))) return rc;
@@ -793,10 +800,7 @@ rs_status forward_kernels(rs_model *m, int n_seqs, int n_rows, const int *d_seq_
         if (rc) return rc;
     } else {
         const int lm_rsh = ring_lm_head(m->n_cu, n_seqs, c.vocab) && n_seqs < 4 ? 2 : frag_shift(n_seqs);         // (k_gemm_ring: blocks of four rows at least)
-        hipLaunchKernelGGL(k_rmsnorm_rows, dim3(n_seqs), dim3(ROWK_THREADS), 0, st, h, m->final_norm, c.rms_eps,
-                           c.d_model, (const int *)m->at<int>(L.out_row), m->at<float>(L.lm32), lm_rsh, (const float *)pend_part, pend_ks,
-                           pend_stride);
-        RS_LAUNCHED("rmsnorm_rows");
+        if ((rc = launch_rmsnorm(n_seqs, h, m->final_norm, c.rms_eps, c.d_model, m->at<int>(L.out_row), m->at<float>(L.lm32), lm_rsh, pend_part, pend_ks, pend_stride, st))) return rc;
         GemmArgs g{};
         g.M = n_seqs; g.rsh = lm_rsh; g.W = m->lm_head; g.N = c.vocab; g.K = c.d_model; g.X32 = m->at<float>(L.lm32);
         g.seq_scale = m->at<float>(L.seq_scale); g.parts = parts; g.logits = d_logits;
