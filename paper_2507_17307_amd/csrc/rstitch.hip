@@ -1131,7 +1131,8 @@ static unsigned long long route_tag() {
 // A short row takes one workgroup from its logits to its record (64 rows of 32768: 11.1 us a call against 14.2; one row of
 // 50257: 14.8 against 14.2, with two launches for the longer rows); longer ones leave partial states, at most route_parts of them per row, that the last
 // workgroup of a row merges, and with many rows fewer (ROUTE_WGS workgroups in all: a workgroup's merge costs as much as several groups of logits; 64 / 128 rows of
-// 152064: 45.8 / 79.4 us with 128 workgroups each and pairwise merges, now 12.3 / 18.4; with 1024 workgroups 12.4 / 18.9, 2048 12.9 / 18.7, 4096 14.5 / 20.7).
+// 152064: 45.8 / 79.4 us with 128 workgroups each and pairwise merges, now 12.8 / 19.8; the number was chosen with an exponential of six instructions, 1536 workgroups 12.3 / 18.4,
+// 1024 12.4 / 18.9, 2048 12.9 / 18.7, 4096 14.5 / 20.7).
 constexpr int ROUTE_ROW_VOCAB = 32768, ROUTE_WGS = 1536;
 static rs_status launch_route(const float *d_logits, int n, int vocab, const float *d_scale, float tau, int active,
                               rs_route_out *d_out, rs::SoftPartial *scratch, hipStream_t st) {
