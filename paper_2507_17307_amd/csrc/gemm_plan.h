@@ -1,5 +1,5 @@
 // Arithmetic of the launches of the matrix-core products (k_gemm_rows, k_gemm_ring): which kernel takes a matrix, how K is split and how many
-// column tiles a workgroup gets.  Plain C++ without HIP types, so that it can also be compiled and checked on a CPU.
+// column tiles a workgroup gets; and of the down projection of few rows (k_down_direct).  Plain C++ without HIP types, so that it can also be compiled and checked on a CPU.
 #pragma once
 
 #include <cstddef>
@@ -104,5 +104,16 @@ inline bool ring_layer(int n_cu, int rows, bool gateup, int n_out, int K) {
 // LM head: from five column tiles per CU on (a window of fewer costs its dependent steps: vocabulary 8192, one row of the 1.5B shape 12.7 us
 // on k_gemm_rows, 16.0 here; 32 000 entries 22.6 and 21.7, 152 064 81.6 and 77.5) and for more than 16 sequences.
 inline bool ring_lm_head(int n_cu, int n_seqs, int vocab) { return n_seqs > 16 || (vocab + 15) / 16 >= 5 * n_cu; }
+
+// k_down_direct, rows of W per tile for two to four token rows (mp = 2 or 4 slots) on models up to 2048 wide.  A tile of r rows pulls r rows of W (2 bytes a
+// value) and every row of x (4 bytes), r + 2 mp shares; tiles of three read x less often, tiles of two spread better over the CUs where one or two a CU are
+// all there are.  So: three where the CU with the most tiles pulls less that way.  us a layer (24 layers, K four times the width), two / three-row tiles:
+//   two better    896  2 rows 37.9 and 38.2, 4 rows 45.9 and 47.0;  1024  36.1 and 36.8, 44.6 and 45.2;  256  30.6 and 30.6, 37.6 and 38.3;  512, 3 rows 37.2 and 37.8
+//   three better  640, 3 rows 42.6 and 42.2;  768  43.4 and 43.0;  1152, 2 rows 44.9 and 44.4, 4 rows 57.3 and 55.9;  1536  40.4 and 40.0, 50.9 and 49.1;
+//                 1920  61.9 and 58.9, 77.5 and 72.8;  2048  56.5 and 55.1, 70.5 and 69.2
+inline int down_tile_rows(int d_model, int mp, int n_cu) {
+    const auto most = [&](int r) { return ((d_model + r - 1) / r + n_cu - 1) / n_cu * (r + 2 * mp); };
+    return most(3) < most(2) ? 3 : 2;
+}
 
 }  // namespace rs

@@ -634,15 +634,15 @@ rs_status fma_layer(rs_model *m, int l, GemvArgs &g, AttnArgs &aa, const WalkPla
     // from same-process A/B runs of whole decode steps: two-row tiles at three workgroups per CU up to
     // d_model 2048 (1.5B step 1.153 -> 1.082 ms against the LDS-staged kernel), seven-row tiles for 3584
     // (7B: 2.994 -> 2.850 ms), five-row tiles at four workgroups per CU above (14B: 6.08 -> 5.86 ms,
-    // 32B: 13.16 -> 11.80 ms).  Several token rows of a narrow model: three-row tiles, because every tile reads all rows of x, which with
-    // two rows of weights a tile are twice (four times) the weights' bytes (1.5B shape, 2 rows 8.9 -> 8.1 us a layer, 3 and 4 rows 12.9 ->
-    // 12.2; tiles of four 9.0 and 12.8; one row 7.2 with either)
+    // 32B: 13.16 -> 11.80 ms).  Several token rows of a narrow model: tiles of two or three rows, whichever leaves the busiest CU less to pull
+    // (down_tile_rows), because every tile reads all rows of x, which with two rows of weights a tile are twice (four times) the weights' bytes
+    // (1.5B shape, tiles of three in the place of two: 2 rows 8.9 -> 8.1 us a layer, 3 and 4 rows 12.9 -> 12.2; of four 9.0 and 12.8; one row 7.2 with either)
     {
-        const int rt = MP > 1 && pl.down_rt == 2 ? 3 : pl.down_rt;
+        const int rt = MP > 1 && pl.down_rt == 2 ? down_tile_rows(c.d_model, MP, m->n_cu) : pl.down_rt;
         const int tiles = (c.d_model + rt - 1) / rt;
         const int blocks = pl.down_blocks < tiles ? pl.down_blocks : tiles;
         switch (rt) {
-            case 2: if constexpr (MP == 1) hipLaunchKernelGGL((k_down_direct<2, 4, 1>), dim3(blocks), dim3(256), 0, st, g); break;
+            case 2: hipLaunchKernelGGL((k_down_direct<2, 4, MP>), dim3(blocks), dim3(256), 0, st, g); break;
             case 3: if constexpr (MP > 1) hipLaunchKernelGGL((k_down_direct<3, 1, MP>), dim3(blocks), dim3(256), 0, st, g); break;
             case 7: hipLaunchKernelGGL((k_down_direct<7, (MP > 1 ? 1 : 2), MP>), dim3(blocks), dim3(256), 0, st, g); break;
             default: hipLaunchKernelGGL((k_down_direct<5, (MP > 1 ? 1 : 2), MP>), dim3(blocks), dim3(256), 0, st, g); break;
