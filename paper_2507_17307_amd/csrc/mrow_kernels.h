@@ -40,8 +40,8 @@ __device__ __forceinline__ float4 sum_splits4(const float *base, size_t i, int k
 // part[ks][row][d] (split over K across workgroups); they are added to the residual row here, in a
 // fixed order, and the row is written back before it is normalised.
 // All of a thread's NV quads are requested before the first sum is written back: with a store between them the second quad of a row of 5120
-// values was requested a round trip later (14B width, 61 rows 7.3 -> 7.0 us, 32B, 29 rows 7.5 -> 7.0; with one quad the partial sums no longer wait
-// for the residual: 7B, 128 rows 7.6 -> 6.9).  A row's partial sums, 115 KB of eight splits, come through one CU: that is most of what is left.
+// values was requested a round trip later (kernel times of both builds in turn: width 5120, 61 rows 6.9 -> 6.7 us, 29 rows 6.7 -> 6.4; with one quad the partial
+// sums no longer wait for the residual: width 3584, 128 rows 7.2 -> 6.5; three quads, width 12288, 128 rows 14.8 and 15.0, width 8320, 61 rows 9.6 and 9.5).  A row's partial sums, 115 KB of eight splits, come through one CU: that is most of what is left.
 template <int NV>
 __global__ void __launch_bounds__(ROWK_THREADS)
 k_rmsnorm_rows(float *__restrict__ h, const uint16_t *__restrict__ gain, float eps, int d,
