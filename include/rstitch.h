@@ -203,7 +203,14 @@ rs_status rs_catchup_prefill(rs_model *model, int32_t n_seqs, int32_t n_rows,
  * entropy of softmax(scale * logits), its normalised value, the argmax and the
  * routing flags.  Same reduction code as the epilogue fused behind the LM head.
  *   d_scratch / scratch_bytes  DEVICE scratch of at least
- *                              rs_route_scratch_bytes(n, vocab), 256-byte aligned
+ *                              rs_route_scratch_bytes(n, vocab), 256-byte aligned;
+ *                              any content
+ * While a call runs, d_scratch holds the softmax states of its workgroups and
+ * how many of them have arrived.  Calls and graph replays that overlap must not
+ * share it: besides wrong numbers, an overlap can leave records unwritten and
+ * arrivals uncounted, and a count that is left behind makes the next replay of
+ * the same captured call merge too early.  Clearing d_scratch, or an ordinary
+ * call of the same shape on it, sets that right.
  * Errors: RS_EINVAL (n < 1, vocab < 2, null pointer, scratch too small). */
 size_t    rs_route_scratch_bytes(int32_t n, int32_t vocab);
 rs_status rs_route(const float *d_logits, int32_t n, int32_t vocab,
@@ -338,10 +345,10 @@ rs_status rs_stitch_generate(rs_model *slm, rs_model *llm, int32_t seq_slot,
  * address up once (make that first call outside a graph capture).
  *   n             1..64 rows; n * ceil(vocab / 1024, at most 128) partial
  *                 states of 32 bytes must fit the array
- * All calls on one GPU share the array: calls that overlap on one GPU (two
- * streams, two threads) race; calls on one stream are ordered.  Nothing has to
- * be cleared between calls (every state the merge reads is written by the same
- * call).
+ * All calls on one GPU share the array: calls and graph replays that overlap on
+ * one GPU (two streams, two threads) race, with what rs_route says of a shared
+ * d_scratch; calls on one stream are ordered, and nothing has to be cleared
+ * between them.
  * Errors: RS_EINVAL as rs_route; RS_ECAPACITY (n > 64, state count beyond the
  * array, device ordinal >= 64); RS_EHIP. */
 rs_status rs_route_static(const float *d_logits, int32_t n, int32_t vocab,
