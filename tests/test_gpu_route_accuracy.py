@@ -80,3 +80,26 @@ def test_one_exponential_of_a_row_behind_the_lm_head():
         ds += [-float(lg[k, 1]) for k in keep]
     assert len(hs) > 1500 and math.isfinite(sum(hs))
     check(hs, torch.tensor(ds))
+
+
+@pytest.mark.parametrize("n,vocab", [(64, 1000), (64, 1001), (64, 32768), (32, 50257), (32, 152064)])
+@pytest.mark.parametrize("spread", [0.3, 10.0])
+def test_entropy_and_ln_z_of_whole_rows(n, vocab, spread):
+    import paper_2507_17307_amd as P
+    g = torch.Generator(device="cuda").manual_seed(vocab)
+    x = torch.empty(n, vocab, device="cuda").normal_(0, spread, generator=g)
+    out = P.binding.new_route_out(n)
+    P.rs_route(x, n, vocab, None, 0.5, P.RS_SLM, out, torch.empty(P.rs_route_scratch_bytes(n, vocab), dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    h, lz = (out.view(torch.float32)[:, k].double().cpu() for k in (2, 5))
+    x = x.double().cpu()
+    want = torch.logsumexp(x, 1)
+    p = torch.exp(x - want[:, None])
+    mean = (p * x).sum(1)
+    # ln Z is the largest logit + ln z, the entropy ln z + the mean distance from the largest logit.  z is within a few roundings of 2^-24 of its value (a
+    # thread's sums of up to 150 terms, the workgroups'), which is an absolute error of ln z; logarithm, mean and sum add as much of their own values.
+    # A distance d is rounded by 2^-24 of it, within a thread and again between threads: so much of its exponential, d times as much of the mean
+    top = x.max(1).values
+    second = (p * (x - top[:, None]).square()).sum(1)
+    assert ((lz - want).abs() <= 2.0 ** -22 * (1 + top.abs() + (want - top))).all()
+    assert ((h - (want - mean)).abs() <= 2.0 ** -22 * (1 + (want - top) + (top - mean)) + 2.0 ** -23 * second).all()

@@ -1,6 +1,6 @@
 """rs_route_static (the entry point that allocates nothing) against rs_route, through the C ABI.
 
-Both run the same two kernels; only where the partial softmax states live differs (a device array
+Both run the same kernel; only where the partial softmax states live differs (a device array
 inside the library instead of a caller buffer), so the records must be identical bit for bit.  Two
 calls in a row on the same stream, the second with a smaller input: the shared array keeps the first
 call's states and none of them may leak into the second result.
