@@ -22,8 +22,8 @@
 // row counts the estimates of 14 and of 7 tie and it takes 494 of 7 in two rounds).
 //
 // What bounds it: up to 64 rows W, streamed at 5.3 .. 6.1 TB/s; at 128 rows the matrix cores, which run at 1.7 .. 1.8 GHz under this
-// load (2330 cycles a window of 120 instructions, 2230 of them matrix-core time: 73 of the 88 us of 7B gate/up; with activations of zeros, the
-// same instructions at less power, it takes 80 in place of 93).  Kernel times in decode calls, us, k_gemm_rows or the kernel of 17 rows and more before this one (k_gemm_tile) -> now:
+// load (2330 cycles a window of 120 instructions, 2230 of them matrix-core time: 73 of the 88 us of 7B gate/up on that card, 93 and 102
+// on others; where it took 93, activations of zeros, the same instructions at less power, took 80).  Kernel times in decode calls, us, k_gemm_rows or the kernel of 17 rows and more before this one (k_gemm_tile) -> now:
 //   7B gate/up (272 MB)   5 / 16 / 24 / 48 / 72 / 128 rows   52 / 53 / 59 / 64 / 80 / 98 -> 46 / 44 / 45 / 50 / 72 / 88
 //   14B gate/up (283 MB)  8 / 61 / 128 rows  56 / 85 / 108 -> 47 / 68 / 99
 //   32B gate/up (566 MB)  16 / 29 / 61 / 128 rows  110 / 123 / 141 / 220 -> 95 / 104 / 107 / 170 (29 rows of ragged spans on

@@ -200,8 +200,9 @@ k_route_row(const float *__restrict__ logits, int vocab, const float *__restrict
 // accumulation fp32.  The record of the sequence is updated in place: a small-model step above tau
 // whose router output prefers "stay" keeps its token and stays (RS_FLAG_ROUTER_STAY); every other
 // record is left as the entropy rule made it.
-// What bounds it: twelve dependent phases, each a round trip for its weights.  The weights do not depend on x, so each phase
-// requests those of the next one before it starts on its own (one call, d 1536, r 8: 25.4 -> 10.1 us; 5120, 8: 65 -> 22).
+// What bounds it: one workgroup's chain of twelve phases, each a read of x or t from LDS, its sums and a barrier.  The weights do not depend on x,
+// so each phase requests those of the next one before it starts on its own (one call, d 1536, r 8: 25.4 -> 10.1 us; 5120, 8: 65 -> 22; all six
+// blocks' weights requested up front 10.8).
 // With a wide bottleneck it is the megabytes that one CU draws (5120, 64: 562 -> 191 us for 7.9 MB).
 // ------------------------------------------------------------------------------------------------
 constexpr int ROUTER_BLOCKS = 6;

@@ -1128,11 +1128,15 @@ static unsigned long long route_tag() {
     return next.fetch_add(1, std::memory_order_relaxed) & 0x00ffffffffffffffull;
 }
 
-// A short row takes one workgroup from its logits to its record (64 rows of 32768: 11.1 us a call against 14.2; one row of
-// 50257: 14.8 against 14.2, with two launches for the longer rows); longer ones leave partial states, at most route_parts of them per row, that the last
-// workgroup of a row merges, and with many rows fewer (ROUTE_WGS workgroups in all: a workgroup's merge costs as much as several groups of logits; 64 / 128 rows of
-// 152064: 45.8 / 79.4 us with 128 workgroups each and pairwise merges, now 12.8 / 19.8; the number was chosen with an exponential of six instructions, 1536 workgroups 12.3 / 18.4,
-// 1024 12.4 / 18.9, 2048 12.9 / 18.7, 4096 14.5 / 20.7).
+// A short row takes one workgroup from its logits to its record; a longer one leaves partial states, at most route_parts of them, that the last
+// workgroup of the row merges, and with many rows fewer (ROUTE_WGS workgroups in all: a workgroup's merge costs as much as several groups of logits; 64 / 128
+// rows of 152064: 45.8 / 79.4 us with 128 workgroups each and pairwise merges, now 12.8 / 19.8; the number was chosen with an exponential of six
+// instructions, 1536 workgroups 12.3 / 18.4, 1024 12.4 / 18.9, 2048 12.9 / 18.7, 4096 14.5 / 20.7).
+// The line between them dates from when the longer rows took two launches (64 rows of 32768: one workgroup each 11.1 us a call, two launches 14.2; one row of
+// 50257 14.8 and 14.2).  With one launch, us on the device for 1 / 64 / 128 / 512 rows, k_route_row and k_route_wide:
+//   1024    3.7  4.0  4.1  5.6 and 4.4  5.2  5.2  5.6        16384   6.1  6.6  6.9 11.4 and 5.1  6.3  7.2 12.5
+//   8192    4.8  5.1  5.2  8.4 and 5.1  5.5  6.3  9.6        32768   8.8  9.9 10.4 17.4 and 5.2  7.2  9.2 18.8
+// so that it is right below 8192 entries and for hundreds of rows, and too high for fewer than a hundred rows of 16384 to 32768.
 constexpr int ROUTE_ROW_VOCAB = 32768, ROUTE_WGS = 1536;
 static rs_status launch_route(const float *d_logits, int n, int vocab, const float *d_scale, float tau, int active,
                               rs_route_out *d_out, rs::SoftPartial *scratch, hipStream_t st) {
