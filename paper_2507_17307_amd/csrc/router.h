@@ -56,7 +56,11 @@ __device__ __forceinline__ SoftState row_state(const float *__restrict__ x, int 
         for (int i = first; i < vocab; i += 4 * step) {
             const int j[4] = {i, i + step, i + 2 * step, i + 3 * step};
             const bool ok[4] = {true, j[1] < vocab, j[2] < vocab, j[3] < vocab};
-            st.push4({x[j[0]] * sc, x[ok[1] ? j[1] : i] * sc, x[ok[2] ? j[2] : i] * sc, x[ok[3] ? j[3] : i] * sc}, j, ok);
+            // all four requested before the first is looked at: left to itself the compiler of k_route_wide waits for the first one (3000 rows of
+            // 40001 entries 124 -> 107 us, 32769 105 -> 89)
+            const float q[4] = {x[i], x[ok[1] ? j[1] : i], x[ok[2] ? j[2] : i], x[ok[3] ? j[3] : i]};
+            __builtin_amdgcn_sched_barrier(0);
+            st.push4({q[0] * sc, q[1] * sc, q[2] * sc, q[3] * sc}, j, ok);
         }
     }
     return st;
