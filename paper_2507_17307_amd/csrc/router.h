@@ -159,8 +159,8 @@ k_route_merge(const SoftPartial *__restrict__ parts, int n_parts, int vocab, flo
 // finds all others of the row arrived merges them.  Arrivals are counted in the word behind the row's first state, {tag, count}: nobody has cleared
 // the caller's scratch, so a word without this call's 56-bit tag counts as zero, and the last workgroup leaves zero (a captured call is replayed with
 // its tag).  Nothing waits for another workgroup.
-// What bounds it: a few rows the launch and the round trips (calls back to back, one row of 50257 / 152064 entries: 8.7 / 8.7 us with a second kernel for the
-// merge, 5.7 / 7.0 now; 8 of 152064 8.9 -> 8.0), many the exponentials (64 of 152064 15.1 -> 12.8, 128 22.8 -> 19.8, both with exp_small and 1536 workgroups in the place of 2048).  The word is read before the logits and set while they
+// What bounds it: a few rows the launch and the round trips (calls back to back, one row of 50257 / 152064 entries: 8.5 / 8.6 us with a second kernel for the
+// merge, 5.6 / 6.2 now; 8 of 152064 8.9 -> 6.7), many the exponentials (64 of 152064 15.1 -> 12.8, 128 22.8 -> 19.8, both with exp_small and 1536 workgroups in the place of 2048).  The word is read before the logits and set while they
 // are added up, so that a workgroup's last act is one addition: a loop of compare and exchange in its place took 102 us for 128 workgroups of a row.
 __global__ void __launch_bounds__(256)
 k_route_wide(const float *__restrict__ logits, int vocab, const float *__restrict__ scale, SoftPartial *parts, unsigned long long tag, float tau, int active,

@@ -1137,7 +1137,10 @@ static unsigned long long route_tag() {
 //   1024    3.7  4.0  4.1  5.6 and 4.4  5.2  5.2  5.6        16384   6.1  6.6  6.9 11.4 and 5.1  6.3  7.2 12.5
 //   8192    4.8  5.1  5.2  8.4 and 5.1  5.5  6.3  9.6        32768   8.8  9.9 10.4 17.4 and 5.2  7.2  9.2 18.8
 // so that it is right below 8192 entries and for hundreds of rows, and too high for fewer than a hundred rows of 16384 to 32768.
-constexpr int ROUTE_ROW_VOCAB = 32768, ROUTE_WGS = 1536;
+// A few rows of more than 65536 entries: at most 64 workgroups a row, because all of them count themselves in one word, some 10 ns each beyond the XCDs'
+// L2s (one row of 131072 / 152064 entries 7.1 / 7.2 us on the device with 128, 6.1 / 6.1 with 64, 6.2 / 6.2 with 48, two launches 6.0 / 6.3; 8 rows 7.8 / 8.0, 6.3 /
+// 6.7, 6.4 / 7.0, two launches 6.9 / 7.9).
+constexpr int ROUTE_ROW_VOCAB = 32768, ROUTE_WGS = 1536, ROUTE_ROW_WGS = 64;
 static rs_status launch_route(const float *d_logits, int n, int vocab, const float *d_scale, float tau, int active,
                               rs_route_out *d_out, rs::SoftPartial *scratch, hipStream_t st) {
     if (vocab <= ROUTE_ROW_VOCAB) {
@@ -1146,8 +1149,9 @@ static rs_status launch_route(const float *d_logits, int n, int vocab, const flo
         return RS_OK;
     }
     int parts = route_parts(vocab);
+    if (parts > ROUTE_ROW_WGS) parts = ROUTE_ROW_WGS;
     if (parts > (ROUTE_WGS + n - 1) / n) parts = (ROUTE_WGS + n - 1) / n;
-    static_assert(ROUTE_PARTS_MAX < 256, "arrivals are counted in eight bits");
+    static_assert(ROUTE_ROW_WGS < 256 && ROUTE_ROW_WGS <= ROUTE_PARTS_MAX, "arrivals are counted in eight bits");
     hipLaunchKernelGGL(rs::k_route_wide, dim3(parts, n), dim3(256), 0, st, d_logits, vocab, d_scale, scratch, route_tag(), tau, active, d_out);
     RS_LAUNCHED("route_wide");
     return RS_OK;
